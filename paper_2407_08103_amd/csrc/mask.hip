@@ -228,6 +228,16 @@ __device__ __forceinline__ int32_t table_entry(const MaskArgs& a, int q, int tok
     return packed_entry(a, packed_block(a, q, token >> 7), token);
 }
 
+// How many tokens row q of the table allows: a count the library keeps beside a table it has written, or the
+// edges of a packed row; kUnknown where neither is there.
+constexpr uint32_t kUnknown = 0xFFFFFFFFu;
+__device__ __forceinline__ uint32_t allowed_count(const MaskArgs& a, int q)
+{
+    if (a.row_allowed) return a.row_allowed[q];
+    if (a.row_begin) return (uint32_t)(a.row_begin[q + 1] - a.row_begin[q]);
+    return kUnknown;
+}
+
 __device__ __forceinline__ void write_result(const MaskArgs& a, int b, int q, bool valid, unsigned long long cand)
 {
     int32_t token = TDFA_NO_TOKEN, next = valid ? q : TDFA_DEAD;
@@ -308,6 +318,102 @@ __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t w)
 constexpr int kListCap = 256;          // groups a wavefront may fetch one by one instead of reading its stretch
 constexpr int kEarlyWaves = 8;         // wavefronts of a workgroup that request their first group of logits before the state is known
 
+// A state known to allow less than this part of the vocabulary (one in ...) is gathered by the workgroup instead of
+// each wavefront finding out about its own stretch.  1,024 rows of 128,256 tokens whose states allow few tokens:
+// 20.0 -> 16.5 us (50 signatures), 18.2 -> 14.0 us (16 schemas); states anywhere in the texts of 16 schemas 30.6 -> 29.2
+// us.  With 8 instead of 32 the states that allow 4 to 12 % are gathered too, and streaming them is faster (the
+// same signatures 36 -> 51 us); 64 is as good as 32.
+constexpr uint32_t kSparseShare = 32;
+
+constexpr int kGatherQueue = 128;      // groups a wavefront's ring holds (a power of two; 64 are fetched at a time)
+
+// Greedy choice over groups [g_lo, g_hi) of a row that allows few tokens, by the whole workgroup: this thread's
+// best candidate.  A thread reads the allowed bits of four groups per load, four loads in flight; a wavefront
+// whose 256 groups allow nothing is done with them after one ballot, and the groups that hold an allowed token
+// wait in its ring in LDS (`ring`, kGatherQueue entries of (group, bits)) until 64 of them are fetched at once,
+// one per lane, a batch ahead of the one that is compared.  Bound by instructions where several such rows share a
+// compute unit and by latency where they do not; logits of groups without an allowed token are never read.
+template <int DTYPE>
+__device__ __forceinline__ unsigned long long gather_scan(const typename ElemOf<DTYPE>::type* row, const uint8_t* bits, int V,
+                                                          int g_lo, int g_hi, uint2* ring)
+{
+    using Elem = typename ElemOf<DTYPE>::type;
+    const uint32_t lane = threadIdx.x & 63u;
+    auto wave_sync = []() {                                    // LDS written by some lanes, read by others
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    uint32_t best_key = 0, best_idx = 0xFFFFFFFFu;             // key 0: no candidate yet
+    uint32_t head = 0, tail = 0;                               // ring positions, the same in all lanes
+    uint32_t m = 0;                                            // allowed bits of this lane's group; 0: none
+    int t = 0;                                                 // its first token
+    Elem e[8] = {};
+    auto compare = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t x = (uint32_t)e[j], key = key_f32(DTYPE == TDFA_F32 ? x : x << 16), tok = (uint32_t)(t + j);
+            if (((m >> j) & 1u) && (key > best_key || (key == best_key && tok < best_idx))) {
+                best_key = key;
+                best_idx = tok;
+            }
+        }
+    };
+    auto fetch = [&](uint32_t n) __attribute__((always_inline)) {        // n <= 64 waiting groups: request them, compare the batch before
+        wave_sync();
+        uint32_t m_next = 0;
+        int t_next = 0;
+        Elem e_next[8] = {};
+        if (lane < n) {
+            const uint2 en = ring[(head + lane) & (kGatherQueue - 1)];
+            t_next = (int)en.x << 3;
+            m_next = en.y;
+            load_group<DTYPE>(row, t_next, V, e_next);
+        }
+        head += n;
+        wave_sync();
+        compare();
+        m = m_next;
+        t = t_next;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) e[j] = e_next[j];
+    };
+    const uint32_t* words = reinterpret_cast<const uint32_t*>(bits);
+    const int w_lo = g_lo >> 2, w_hi = (g_hi + 3) >> 2;                    // (g_lo is a multiple of four groups)
+    const int NT = (int)blockDim.x;
+    auto load_word = [&](int wi) { return wi < w_hi ? words[wi] : 0u; };
+    int wi = w_lo + (int)threadIdx.x;
+    uint32_t w0 = load_word(wi), w1 = load_word(wi + NT), w2 = load_word(wi + 2 * NT), w3 = load_word(wi + 3 * NT);
+    for (int base = w_lo; base < w_hi; base += NT, wi += NT) {               // trip count uniform in the workgroup
+        const uint32_t w = w0;
+        w0 = w1;
+        w1 = w2;
+        w2 = w3;
+        w3 = load_word(wi + 4 * NT);
+        const int left = g_hi - (wi << 2);                                   // groups of this word inside the part
+        const uint32_t wm = left >= 4 ? w : (left > 0 ? w & ((1u << (8 * left)) - 1u) : 0u);
+        if (__builtin_amdgcn_ballot_w64(wm != 0) == 0) continue;
+        // 64 consecutive groups at a time (lane L takes byte L mod 4 of the word of lane 16 i + L / 4), so that
+        // neighbouring lanes fetch neighbouring logits
+#pragma unroll 1
+        for (int i = 0; i < 4; ++i) {
+            const int src = 16 * i + (int)(lane >> 2);
+            const uint32_t ws = (uint32_t)__shfl((int)wm, src, 64);
+            const uint32_t mg = (ws >> (8 * (lane & 3u))) & 0xFFu;
+            const unsigned long long bal = __builtin_amdgcn_ballot_w64(mg != 0);
+            if (bal == 0) continue;
+            const uint32_t at = tail + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+            const int g = ((wi - (int)lane + src) << 2) + (int)(lane & 3u);
+            if (mg != 0) ring[at & (kGatherQueue - 1)] = make_uint2((uint32_t)g, mg);
+            tail += (uint32_t)__popcll(bal);
+            if (tail - head >= 64u) fetch(64u);
+        }
+    }
+    if (tail != head) fetch(tail - head);
+    compare();
+    return best_key ? ((unsigned long long)best_key << 32) | (0xFFFFFFFFu - best_idx) : 0ull;
+}
+
 // One step on 16-bit logits.  The groups [g_lo, g_hi) of a workgroup are cut into one stretch of
 // `stretch` groups (a multiple of 16) per wavefront, read 64 consecutive groups per load.
 //
@@ -328,7 +434,8 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
 {
     static_assert(!PDA || (SKIP && !WRITE), "the push-down step reads its bits into LDS");
     extern __shared__ uint4 s_pieces[];
-    __shared__ uint32_t s_list[SKIP ? kMaxWaves * kListCap : 1];
+    __shared__ __attribute__((aligned(8))) uint32_t s_list[SKIP ? kMaxWaves * kListCap : 1];
+    static_assert(kListCap >= 2 * kGatherQueue, "the rings of a sparse row share the lists' room");
     __shared__ unsigned long long wave_best[kMaxWaves], wave_best_exact[kMaxWaves];
     __shared__ int s_exact;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -387,8 +494,8 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
     bool valid = q >= 0 && (int64_t)q < a.n_rows;
     bool surely_wide = false;                         // the state allows so many tokens that the row is streamed whatever the bits say
     if constexpr (!WRITE && !PDA) {
-        if (a.row_allowed != nullptr && valid) {
-            const uint32_t n_allowed = a.row_allowed[q];
+        const uint32_t n_allowed = valid ? allowed_count(a, q) : kUnknown;
+        if (n_allowed != kUnknown) {
             // A state that allows no token (a sequence whose text is complete): no token, the state stays.
             if (n_allowed == 0u) {
                 if (threadIdx.x == 0) {
@@ -396,6 +503,16 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
                     if (combine_parts(a, b, parts, none)) write_result(a, b, q, valid, none);
                 }
                 return;
+            }
+            if constexpr (SKIP) {
+                // A state known to allow few tokens.
+                if (n_allowed < (uint32_t)V / kSparseShare) {
+                    unsigned long long c = gather_scan<TDFA_BF16>(row, reinterpret_cast<const uint8_t*>(a.allow + (int64_t)q * a.row_words),
+                                                                  V, g_lo, g_hi, reinterpret_cast<uint2*>(s_list) + wave * kGatherQueue);
+                    c = block_max_u64(c, wave_best);
+                    if (threadIdx.x == 0 && combine_parts(a, b, parts, c)) write_result(a, b, q, valid, c);
+                    return;
+                }
             }
             surely_wide = n_allowed >= (uint32_t)V / 4u;
         }
@@ -1490,11 +1607,22 @@ void stream_shape(const MaskArgs& a, int* parts_out, int* threads_out, int* gpp_
 }
 }  // namespace
 
+namespace {
+// A packed table takes the step kernel of the dense ones on 16-bit logits without a penalised row (512 rows of a
+// constraint's states at 128,256 tokens: 29.8 us by the gathering scan alone, whose wide rows are compared element
+// by element, 17 us by the step kernel); fp32 logits, where that scan reads wide rows as fast and sparse ones faster
+// (1,024 rows: 67 against 87 us), and penalised rows stay with it, as do rows beyond the step kernel's 32-bit offsets.
+bool packed_takes_gather(const MaskArgs& a)
+{
+    return !a.delta && a.targets && (a.dtype == TDFA_F32 || a.masked_out || a.n_tokens > (1 << 27));
+}
+}  // namespace
+
 bool mask_step_uses_scratch(const MaskArgs& a)
 {
     if (a.batch <= 0) return false;
     int parts, threads, gpp;
-    if (!a.delta && a.targets) gather_shape(a, &parts, &threads, &gpp);
+    if (packed_takes_gather(a)) gather_shape(a, &parts, &threads, &gpp);
     else stream_shape(a, &parts, &threads, &gpp);
     return parts > 1;
 }
@@ -1539,7 +1667,7 @@ int launch_mask_step(const MaskArgs& a, hipStream_t stream)
 {
     if (a.batch <= 0) return TDFA_OK;
     if (a.pda.class_first && !mask_step_takes_pda(a)) return fail(TDFA_E_UNSUPPORTED, "this step wants one row of allowed bits per sequence");
-    if (!a.delta && a.targets) {
+    if (packed_takes_gather(a)) {
         // a packed table: the scan that reads only the groups with allowed tokens
         int g_parts, g_threads, g_gpp;
         gather_shape(a, &g_parts, &g_threads, &g_gpp);

@@ -121,6 +121,32 @@ def test_random_tables(T, oracle, n_rows, n_tokens, p_live):
     assert np.array_equal(hist.cpu().numpy(), want_hist) and np.array_equal(nv.cpu().numpy(), want_nv)
 
 
+@pytest.mark.parametrize("n_tokens,batch", [(4001, 7), (33001, 3), (40007, 200), (131077, 193)])
+def test_rows_around_the_gathering_switch(T, oracle, n_tokens, batch):
+    """Tables that know how many tokens a state allows, with states on both sides of the count below which a row
+    is gathered (one token in 32), packed and dense: exact integers, so no tolerance."""
+    rng = np.random.default_rng(n_tokens)
+    counts = [0, 1, n_tokens // 32 - 1, n_tokens // 32, n_tokens // 32 + 1, n_tokens // 4, n_tokens]
+    tab = np.full((len(counts) + 1, n_tokens), DEAD, dtype=np.int32)
+    for q, c in enumerate(counts):
+        tab[q, rng.choice(n_tokens, size=c, replace=False)] = rng.integers(0, len(tab), size=c)
+    tab[-1, n_tokens - 9:] = 2                                # the last groups only, the partial one among them
+    states = (np.arange(batch) % (len(tab) + 2) - 1).astype(np.int32)
+    stride = (n_tokens + 7) // 8 * 8
+    x = np.round(rng.normal(0, 2, size=(batch, stride)) * 4).astype(np.float32) / 4       # many ties
+    dense, _ = T.table_concat([_upload_table(T, tab)])        # written by the library: its rows are counted
+    for table in (dense, T.table_pack(dense)):
+        for dtype in (F32, BF16):
+            lg_np = x if dtype == F32 else LG.f32_to_bf16_bits(x)
+            lg = torch.from_numpy(lg_np).cuda() if dtype == F32 else torch.from_numpy(lg_np.view(np.int16)).cuda().view(torch.bfloat16)
+            tok = torch.full((batch,), -9, dtype=torch.int32, device="cuda")
+            new = torch.full((batch,), -9, dtype=torch.int32, device="cuda")
+            T.mask_step(table, lg, torch.from_numpy(states).cuda(), tok, new)
+            torch.cuda.synchronize()
+            want_tok, want_new = oracle.mask_step(tab, lg_np, dtype, states, row_stride=stride)
+            assert np.array_equal(tok.cpu().numpy(), want_tok) and np.array_equal(new.cpu().numpy(), want_new)
+
+
 @pytest.mark.parametrize("dtype", [F32, BF16])
 def test_special_values_on_packed(T, oracle, dtype):
     """NaN, infinities, ties and signed zeros through the scan that packed tables use: a sparse
