@@ -337,7 +337,7 @@ int count_rows(tdfa_table* t, hipStream_t s);
 // until the process ends.
 struct DeviceScratch {
     unsigned long long* best = nullptr;
-    unsigned int* count = nullptr;      // [2 * cap]: arrival counters, then scratch words that need not be zero
+    unsigned int* count = nullptr;      // [cap]: arrival counters
     int32_t cap = 0;
 };
 constexpr int kMaxDevices = 64;
@@ -368,14 +368,14 @@ int ensure_scratch(int32_t batch, hipStream_t stream, DeviceScratch* out)
     DeviceScratch grown;
     int rc = device_alloc(&grown.best, (size_t)cap);
     if (rc != TDFA_OK) return rc;
-    rc = device_alloc(&grown.count, 2 * (size_t)cap);      // second half: the top-k cuts of a sampling step
+    rc = device_alloc(&grown.count, (size_t)cap);
     if (rc != TDFA_OK) {
         (void)hipFree(grown.best);
         return rc;
     }
     // cleared before the call returns, so a step on any stream finds zeros
     TDFA_HIP(hipMemset(grown.best, 0, sizeof(unsigned long long) * (size_t)cap));
-    TDFA_HIP(hipMemset(grown.count, 0, sizeof(unsigned int) * 2 * (size_t)cap));
+    TDFA_HIP(hipMemset(grown.count, 0, sizeof(unsigned int) * (size_t)cap));
     grown.cap = cap;
     *sc = grown;                                             // the old block, if any, stays allocated
     *out = grown;
@@ -1304,7 +1304,7 @@ void fill_table_args(const tdfa_table* table, tdfa::MaskArgs* a)
 // Argument checks and kernel arguments shared by the greedy and the sampling step.
 int prepare_step(const tdfa_table* table, const void* logits_dev, int dtype, int32_t batch, int64_t row_stride,
                  const int32_t* states_dev, int32_t* tokens_dev, int32_t* new_states_dev, void* masked_out_dev,
-                 hipStream_t s, tdfa::MaskArgs* a, uint32_t** words_scratch = nullptr, bool use_static = false)
+                 hipStream_t s, tdfa::MaskArgs* a, bool use_static = false)
 {
     if (!table) return fail(TDFA_E_INVALID_ARG, "table is NULL");
     if (dtype != TDFA_F32 && dtype != TDFA_BF16) return fail(TDFA_E_INVALID_ARG, "unknown dtype %d", dtype);
@@ -1343,7 +1343,6 @@ int prepare_step(const tdfa_table* table, const void* logits_dev, int dtype, int
     a->masked_out = masked_out_dev;
     a->scratch_best = sc.best;
     a->scratch_count = sc.count;
-    if (words_scratch) *words_scratch = use_static ? nullptr : sc.count + sc.cap;
     return TDFA_OK;
 }
 
@@ -1372,7 +1371,7 @@ int tdfa_mask_step_noalloc(const tdfa_table* table, const void* logits_dev, int 
     MaskArgs a = {};
     a.batch = 0;
     int rc = prepare_step(table, logits_dev, dtype, batch, row_stride, states_dev, tokens_dev, new_states_dev,
-                          masked_out_dev, s, &a, nullptr, true);
+                          masked_out_dev, s, &a, true);
     if (rc != TDFA_OK || batch == 0) return rc;
     // The array is shared by every call on this GPU and keeps what the last one left: the words this
     // call's workgroups meet through are cleared first, by a kernel (a recorded graph may hold this).
@@ -1399,11 +1398,10 @@ int sample_step_impl(const tdfa_table* table, const void* logits_dev, int dtype,
     hipStream_t s = static_cast<hipStream_t>(stream);
     MaskArgs a = {};
     a.batch = 0;
-    uint32_t* cut = nullptr;
     int rc = prepare_step(table, logits_dev, dtype, batch, row_stride, states_dev, tokens_dev, new_states_dev,
-                          masked_out_dev, s, &a, &cut);
+                          masked_out_dev, s, &a);
     if (rc != TDFA_OK || batch == 0) return rc;
-    return launch_sample_step(a, inv_t, top_k, cut, seed, offset, offset_dev, s);
+    return launch_sample_step(a, inv_t, top_k, seed, offset, offset_dev, s);
 }
 
 }  // namespace

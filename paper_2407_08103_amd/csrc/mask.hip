@@ -951,7 +951,6 @@ struct SampleParams {
     float inv_t;
     uint32_t seed_lo, seed_hi, off_lo, off_hi;
     const unsigned long long* off_dev;   // if not NULL: the offset is read from here by the kernel (off_lo / off_hi unused)
-    const uint32_t* cut;      // top-k: per sequence, the order key of the smallest logit still drawn from; or NULL
 };
 
 // counter (c0, c1, c2, c3), key (k0, k1) -> four words, ten rounds
@@ -1002,6 +1001,18 @@ __device__ __forceinline__ float gumbel_of(uint32_t x)
     return -ln32(-ln32(u));
 }
 
+constexpr float kNoiseMax = 16.64f;    // above every noise value: -ln(-ln(1 - 2^-24)) = 16.6355...
+
+// Not below the noise that generator word x makes: with n = 2^23 - (x >> 9), u = 1 - (n - 1/2) 2^-23 and
+// g = -ln(-ln u) <= -ln(1 - u) <= (clz(n) - 7) ln 2; the slack added covers the rounding of the noise as
+// computed.  fma is monotonic in its addend, so a token whose bound stays below a score already reached
+// scores below it as well.
+__device__ __forceinline__ float noise_bound(uint32_t x)
+{
+    const uint32_t n = 0x800000u - (x >> 9);
+    return __builtin_fmaf((float)(__clz((int)n) - 7), 0.693147180559945309f, 1.0e-3f);
+}
+
 // The noise alone: out[b][t] = g_t of sequence b, for callers that want to reproduce a draw.
 __global__ void __launch_bounds__(256)
 sample_noise_kernel(SampleParams sp, int32_t n_tokens, int64_t n_quads_total, int32_t quads_per_row, float* __restrict__ out)
@@ -1016,210 +1027,476 @@ sample_noise_kernel(SampleParams sp, int32_t n_tokens, int64_t n_quads_total, in
         if (4 * k + j < n_tokens) out[(int64_t)b * n_tokens + 4 * k + j] = gumbel_of(w[j]);
 }
 
-// Top-k: the order key of the k-th largest allowed logit of each sequence (0 if the state allows
-// fewer than k tokens: nothing is cut).  One workgroup per sequence.
+// Draw under a top-k cut: one workgroup per sequence finds the order key of the k-th largest allowed logit and draws
+// among the tokens that reach it (fewer than k allowed tokens: among all).
 //
-// The selection itself is a radix selection over 32-bit order keys, most significant digit first
-// (11 + 11 + 10 bits): a pass counts, in an LDS histogram, the keys whose higher digits equal those
-// already fixed, and the digit is the bin in which the count from the top reaches what is still
-// wanted.  Run over a whole wildcard-like row that would send a hundred thousand atomic adds
-// through one LDS, so the row is thinned out first:
-//   1. every thread takes the largest key among a few groups of the row, an eighth of a large
-//      vocabulary in all (no atomics);
-//   2. the k-th largest of these thread maxima, L, is selected in LDS: at least k allowed logits
-//      reach L, so the k-th largest of the row does too;
-//   3. a second pass over the row collects the keys that reach L (about k of them) in LDS, and the
-//      k-th largest of the collected keys is selected there.
-// If k exceeds the number of threads, or the collected keys do not fit (masses of equal logits),
-// the selection runs over the row itself, restricted to the keys that reach L.
-constexpr int kCutBins = 2048;
-constexpr int kCutKeep = 2048;         // collected keys that fit in LDS
+// The row is read once.  Every thread keeps 16 groups of eight tokens (kRowGroups; 1,024 threads: 131,072 tokens) in
+// registers as 16-bit order keys, a token that is not allowed as key 0, all loads in flight at once:
+//   1. the k-th largest of the threads' maxima, L, is selected from two 256-bin histograms in LDS: at least k allowed
+//      logits reach L, so the k-th largest of the row does too;
+//   2. the tokens that reach L (little more than k of them) are collected in LDS from the registers, and the k-th
+//      largest of the collected keys is the cut;
+//   3. the collected tokens at or above the cut, one per thread, get their noise and compete.
+// A state that allows at most kKeep tokens is collected whole, reading only its groups.  Where the shortcut does not
+// hold (k above the number of threads that saw a token, masses of equal logits, NaN or -inf at the cut) the cut is
+// selected over the row, most significant digit first, and a scan of the row draws (`slow` below).
+//
+// What bounds it: a compute unit streams its 256 KB row at what one unit gets from memory (9 to 10 us), then five
+// barriers and two dependent reads follow.  k = 50, T = 0.7, 256 sequences, 128,256 tokens in bf16: states anywhere in
+// their texts 73.6 -> 17.6 us, all in states that allow most tokens 75.7 -> 19.3 us, all in states that allow few
+// 22.6 -> 9.1 us (fp32: 78.5 -> 31.5 us where most are allowed), against a kernel that made the cut, which read the row
+// one and an eighth times, and the gathering scan for the draw, which read it again.
+constexpr int kKeep = 2048;            // collected tokens that fit in LDS
+constexpr int kRowGroups = 16;         // groups of eight tokens that a thread holds in registers
 
-template <int DTYPE>
+template <int DTYPE, bool WRITE, bool RESIDENT>
 __global__ void __launch_bounds__(kMaxThreads)
-topk_cut_kernel(MaskArgs a, int32_t top_k, uint32_t* __restrict__ cut)
+topk_step_kernel(MaskArgs a, SampleParams sp, int32_t top_k)
 {
     using Elem = typename ElemOf<DTYPE>::type;
-    __shared__ uint32_t hist[kCutBins];
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __shared__ __attribute__((aligned(16))) uint32_t s_keys[kKeep];
+    __shared__ __attribute__((aligned(16))) uint32_t hist[4 * 256];        // a histogram of 256 bins per digit of a key
+    __shared__ uint2 s_cand[kKeep];                                        // (token, logit as binary32)
+    __shared__ uint2 s_list[kKeep];                                        // few: (group << 8 | bits, place of its first token)
+    __shared__ unsigned long long wave_best[kMaxWaves];
     __shared__ uint32_t s_scan[kMaxWaves];
-    __shared__ __attribute__((aligned(16))) uint32_t s_keys[kCutKeep];
-    __shared__ uint32_t s_bin, s_want, s_found, s_n;
+    __shared__ uint32_t s_bin, s_n, s_groups, s_special;
     const int b = blockIdx.x;
     const int V = a.n_tokens;
     const int q = a.states[b];
     const bool valid = q >= 0 && (int64_t)q < a.n_rows;
     const uint8_t* bits = reinterpret_cast<const uint8_t*>(a.allow + (valid ? (int64_t)q * a.row_words : 0));
     const Elem* row = static_cast<const Elem*>(a.logits) + (int64_t)b * a.row_stride;
-    const int n_groups = (V + 7) >> 3;
-    const int T = (int)blockDim.x, per = kCutBins / T;          // T is 256 or 1024
+    Elem* orow = WRITE ? static_cast<Elem*>(a.masked_out) + (int64_t)b * a.row_stride : nullptr;
+    const int n_groups = (V + 7) >> 3, n_full = V >> 3;
+    const int T = (int)blockDim.x, tid = (int)threadIdx.x, lane = tid & 63;     // T is 256 or 1024
+    const uint32_t k = (uint32_t)top_k;
+    if (sp.off_dev) {                                              // the same word for every thread
+        const unsigned long long o = *sp.off_dev;
+        sp.off_lo = (uint32_t)o;
+        sp.off_hi = (uint32_t)(o >> 32);
+    }
+    if (tid == 0) {
+        s_n = 0;
+        s_groups = 0;
+        s_special = 0;
+    }
+    for (int i = tid; i < 512; i += T) hist[i] = 0;
 
-    // f(key) for every allowed logit of the row (NaN ranks as -inf).  Eight groups per thread are in
-    // flight: their allowed bits first, then the logits of those that have an allowed token.
-    auto for_groups = [&](int g_begin, int g_end, auto&& f) {
-        constexpr int kU = 8;
-        for (int base = g_begin; base < g_end; base += T * kU) {
-            uint32_t m[kU];
-            Elem e[kU][8];
+    // how many tokens the state allows
+    uint32_t n_allowed = valid ? allowed_count(a, q) : 0u;
+    __syncthreads();
+    if (n_allowed == kUnknown) {                                   // the bit row tells
+        const uint32_t* words = reinterpret_cast<const uint32_t*>(bits);
+        const int n_words = (V + 31) >> 5;
+        uint32_t c = 0;
+        for (int i = tid; i < n_words; i += T) c += __popc(words[i]);
+        c = wave_sum_u32(c);
+        if (lane == 0) s_scan[tid >> 6] = c;
+        __syncthreads();
+        n_allowed = 0;
+        for (int w = 0; w < (T >> 6); ++w) n_allowed += s_scan[w];
+    }
+    if (!WRITE && n_allowed == 0) {
+        if (tid == 0) write_result(a, b, q, valid, 0ull);
+        return;
+    }
+    const bool few = n_allowed <= (uint32_t)kKeep;
+    // rows beyond the reach of 32-bit byte offsets are scanned through pointers
+    const bool huge = V > (1 << 26);
+
+    // f(u, group, its eight logits, the words they came in, its allowed bits) for the thread's whole groups of chunk c:
+    // kRowGroups loads in flight (fp32: four groups, eight loads).  The tokens of the row's last, partial group are
+    // for the first threads: for_tail.
+    constexpr int kAhead = DTYPE == TDFA_F32 ? (WRITE ? 2 : 4) : kRowGroups;
+    auto for_chunk = [&](int c, auto&& f) __attribute__((always_inline)) {
+        const int g0 = c * kRowGroups * T + tid;
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int g = base + u * T + (int)threadIdx.x;
-                m[u] = (valid && g < g_end) ? bits[g] : 0u;
+        for (int u0 = 0; u0 < kRowGroups; u0 += kAhead) {
+            if (DTYPE == TDFA_F32) __builtin_amdgcn_sched_barrier(0);      // (loads of later batches moved up here would spill)
+            u32x4 lo[kAhead], hi[DTYPE == TDFA_F32 ? kAhead : 1];
+            uint32_t m[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                // a descriptor of its own per pass over the threads, made of scalars: the lane's offsets are the same in
+                // all of them.  (A group past the end reads zeros, without a memory access.)
+                const int gs = (c * kRowGroups + u0 + u) * T;
+                const __amdgpu_buffer_rsrc_t r_x = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<Elem*>(row) + (int64_t)gs * 8, 0, max(n_full - gs, 0) * 8 * (int)sizeof(Elem), kRawBuffer);
+                const __amdgpu_buffer_rsrc_t r_m =
+                    __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(bits) + gs, 0, valid ? max(n_full - gs, 0) : 0, kRawBuffer);
+                lo[u] = __builtin_amdgcn_raw_buffer_load_b128(r_x, tid * 8 * (int)sizeof(Elem), 0, kReadOnce);
+                if constexpr (DTYPE == TDFA_F32) hi[u] = __builtin_amdgcn_raw_buffer_load_b128(r_x, tid * 32 + 16, 0, kReadOnce);
+                m[u] = __builtin_amdgcn_raw_buffer_load_b8(r_m, tid, 0, 0);
             }
 #pragma unroll
-            for (int u = 0; u < kU; ++u)
-                if (m[u]) load_group<DTYPE>(row, (base + u * T + (int)threadIdx.x) << 3, V, e[u]);
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const uint32_t x = (uint32_t)e[u][j];
-                    if ((m[u] >> j) & 1u) f(key_f32(DTYPE == TDFA_F32 ? x : x << 16));
+            for (int u = 0; u < kAhead; ++u) {
+                const int g = g0 + (u0 + u) * T;
+                Elem e[8];
+                if constexpr (DTYPE == TDFA_F32) {
+                    e[0] = lo[u].x; e[1] = lo[u].y; e[2] = lo[u].z; e[3] = lo[u].w;
+                    e[4] = hi[u].x; e[5] = hi[u].y; e[6] = hi[u].z; e[7] = hi[u].w;
+                } else {
+                    e[0] = (Elem)lo[u].x; e[1] = (Elem)(lo[u].x >> 16); e[2] = (Elem)lo[u].y; e[3] = (Elem)(lo[u].y >> 16);
+                    e[4] = (Elem)lo[u].z; e[5] = (Elem)(lo[u].z >> 16); e[6] = (Elem)lo[u].w; e[7] = (Elem)(lo[u].w >> 16);
                 }
+                f(u0 + u, g, e, lo[u], m[u]);
             }
         }
     };
-    auto for_row = [&](auto&& f) { for_groups(0, n_groups, f); };
-    // f(key) for the first n keys held in s_keys, zeros skipped
-    auto for_kept = [&](uint32_t n, auto&& f) {
-        for (uint32_t i = threadIdx.x; i < n; i += (uint32_t)T) {
-            const uint32_t key = s_keys[i];
-            if (key) f(key);
+    const int n_chunks = RESIDENT ? 1 : (n_full + kRowGroups * T - 1) / (kRowGroups * T);
+    auto as_f32 = [](uint32_t x) {                                 // NaN counts as -inf
+        uint32_t lb = DTYPE == TDFA_F32 ? x : x << 16;
+        if ((lb & 0x7FFFFFFFu) > 0x7F800000u) lb = 0xFF800000u;
+        return lb;
+    };
+    auto push = [&](int t, uint32_t lb) {
+        const uint32_t i = atomicAdd(&s_n, 1u);
+        if (i < (uint32_t)kKeep) {
+            s_cand[i] = make_uint2((uint32_t)t, lb);
+            s_keys[i] = key_f32(lb);
         }
     };
-    // The want-th largest of the keys >= floor that `each` enumerates; false if there are fewer.
-    // Called by all threads; ends with a barrier.
-    auto select = [&](auto&& each, uint32_t want, uint32_t floor_key, uint32_t* result) -> bool {
-        constexpr int kShift[3] = {21, 10, 0};
-        constexpr int kWidth[3] = {11, 11, 10};
+    // the penalised logits of group gs + tid (gs: scalar); nothing past the whole groups
+    auto store_masked = [&](int gs, const Elem (&e)[8], uint32_t mg) {
+        if constexpr (WRITE) {
+            constexpr Elem NEG_INF = DTYPE == TDFA_F32 ? (Elem)0xFF800000u : (Elem)0xFF80u;
+            uint32_t o[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) o[j] = (mg >> j) & 1u ? e[j] : NEG_INF;
+            const __amdgpu_buffer_rsrc_t r_o = __builtin_amdgcn_make_buffer_rsrc(
+                orow + (int64_t)gs * 8, 0, max(n_full - gs, 0) * 8 * (int)sizeof(Elem), kRawBuffer);
+            if constexpr (DTYPE == TDFA_F32) {
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{o[0], o[1], o[2], o[3]}, r_o, tid * 32, 0, kReadOnce);
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{o[4], o[5], o[6], o[7]}, r_o, tid * 32 + 16, 0, kReadOnce);
+            } else {
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{o[0] | o[1] << 16, o[2] | o[3] << 16, o[4] | o[5] << 16, o[6] | o[7] << 16}, r_o,
+                                                       tid * 16, 0, kReadOnce);
+            }
+        }
+    };
+    // f(token, its logit, whether it is allowed) for the tokens of the partial group
+    auto for_tail = [&](auto&& f) {
+        const int t = (n_full << 3) + tid;
+        if (t < V) f(t, row[t], valid && ((bits[n_full] >> tid) & 1u));
+    };
+    auto store_tail = [&]() {
+        if constexpr (WRITE) {
+            constexpr Elem NEG_INF = DTYPE == TDFA_F32 ? (Elem)0xFF800000u : (Elem)0xFF80u;
+            for_tail([&](int t, Elem x, bool ok) { orow[t] = ok ? x : NEG_INF; });
+        }
+    };
+
+    // The bin of a 256-bin histogram that holds the want-th entry from the top, and which entry of the bin it is; false
+    // if there are fewer.  Every wavefront reads the histogram for itself, four bins per lane.
+    auto find_bin = [&](const uint32_t* h, uint32_t want, uint32_t* bin, uint32_t* left) -> bool {
+        const uint4 v = *reinterpret_cast<const uint4*>(h + 4 * lane);
+        const uint32_t mine = v.x + v.y + v.z + v.w;
+        uint32_t incl = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t other = __shfl_down(incl, d, 64);
+            if (lane + d < 64) incl += other;
+        }
+        const uint32_t a3 = incl - mine, a2 = a3 + v.w, a1 = a2 + v.z, a0 = a1 + v.y;        // counts above the lane's bins
+        const uint32_t sub = want <= a2 ? 3u : want <= a1 ? 2u : want <= a0 ? 1u : 0u;
+        const uint32_t above = want <= a2 ? a3 : want <= a1 ? a2 : want <= a0 ? a1 : a0;
+        const unsigned long long at = __builtin_amdgcn_ballot_w64(a3 < want && want <= incl);
+        if (at == 0) return false;
+        const int src = __builtin_ctzll(at);
+        *bin = 4u * (uint32_t)src + (uint32_t)__builtin_amdgcn_readlane((int)sub, src);
+        *left = want - (uint32_t)__builtin_amdgcn_readlane((int)above, src);
+        return true;
+    };
+    // The want-th largest of the keys that `each` enumerates, or a number between it and the next smaller key; false if
+    // there are fewer keys.  Eight bits per pass from the top; the upper half of a bf16 logit's key tells all of it.
+    auto select = [&](auto&& each, uint32_t want, uint32_t* result) -> bool {
+        __syncthreads();
+        for (int i = tid; i < 4 * 256; i += T) hist[i] = 0;
+        __syncthreads();
         uint32_t prefix = 0, fixed_mask = 0;
-        for (int pass = 0; pass < 3; ++pass) {
-            for (int i = threadIdx.x; i < kCutBins; i += T) hist[i] = 0;
-            if (threadIdx.x == 0) s_found = 0;
-            __syncthreads();
-            const int shift = kShift[pass];
-            const uint32_t digit_mask = (1u << kWidth[pass]) - 1u;
+        for (int pass = 0; pass < (DTYPE == TDFA_F32 ? 4 : 2); ++pass) {
+            const int shift = 24 - 8 * pass;
             each([&](uint32_t key) {
-                if (key >= floor_key && (key & fixed_mask) == prefix) atomicAdd(&hist[(key >> shift) & digit_mask], 1u);
+                if ((key & fixed_mask) == prefix) atomicAdd(&hist[256 * pass + ((key >> shift) & 255u)], 1u);
             });
             __syncthreads();
-            // thread i owns bins [i * per, (i + 1) * per); `above` = count in the bins of the threads above
-            // i: a suffix scan inside each wavefront by shuffles, then the totals of the wavefronts above
-            uint32_t mine = 0;
-            for (int i = 0; i < per; ++i) mine += hist[threadIdx.x * per + i];
-            uint32_t incl = mine;
-            const int ln = (int)(threadIdx.x & 63u);
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const uint32_t other = __shfl_down(incl, d, 64);
-                if (ln + d < 64) incl += other;
-            }
-            if (ln == 0) s_scan[threadIdx.x >> 6] = incl;       // total of this wavefront
-            __syncthreads();
-            uint32_t higher = 0;
-            for (int w = (int)(threadIdx.x >> 6) + 1; w < (T >> 6); ++w) higher += s_scan[w];
-            uint32_t above = higher + incl - mine;
-            for (int i = per - 1; i >= 0; --i) {
-                const uint32_t c = hist[threadIdx.x * per + i];
-                if (above < want && want <= above + c) {          // true in exactly one bin, if there are enough keys
-                    s_bin = (uint32_t)(threadIdx.x * per + i);
-                    s_want = want - above;
-                    s_found = 1;
-                }
-                above += c;
-            }
-            __syncthreads();
-            const bool found = s_found != 0;
-            const uint32_t bin = s_bin, next_want = s_want;
-            __syncthreads();
-            if (!found) return false;
+            uint32_t bin = 0;
+            if (!find_bin(hist + 256 * pass, want, &bin, &want)) return false;
             prefix |= bin << shift;
-            fixed_mask |= digit_mask << shift;
-            want = next_want;
+            fixed_mask |= 255u << shift;
         }
         *result = prefix;
         return true;
     };
 
-    // The want-th largest of the first n <= 512 keys in s_keys, by counting: a key is the answer if
-    // fewer than `want` keys are greater and at least `want` are greater or equal.
-    auto select_few = [&](uint32_t n, uint32_t want, uint32_t* result) -> bool {
-        if (threadIdx.x == 0) s_found = 0;
-        for (uint32_t i = n + threadIdx.x; i < ((n + 3u) & ~3u); i += (uint32_t)T) s_keys[i] = 0;   // pad to whole uint4
-        __syncthreads();
-        for (uint32_t i = threadIdx.x; i < n; i += (uint32_t)T) {
-            const uint32_t mine = s_keys[i];
-            uint32_t gt = 0, ge = 0;
-            for (uint32_t j = 0; j < n; j += 4) {
-                const uint4 o = *reinterpret_cast<const uint4*>(&s_keys[j]);
-                gt += (o.x > mine) + (o.y > mine) + (o.z > mine) + (o.w > mine);
-                ge += (o.x >= mine) + (o.y >= mine) + (o.z >= mine) + (o.w >= mine);
-            }
-            if (mine != 0 && gt < want && want <= ge) {        // equal keys all write the same value
-                s_bin = mine;
-                s_found = 1;
-            }
+    uint32_t best_key = 0, best_idx = 0xFFFFFFFFu;                 // key 0: no candidate yet
+    auto consider = [&](uint32_t tok, uint32_t lb, uint32_t word) {
+        const uint32_t key = key_f32(__float_as_uint(__builtin_fmaf(__uint_as_float(lb), sp.inv_t, gumbel_of(word))));
+        if (key > best_key || (key == best_key && tok < best_idx)) {
+            best_key = key;
+            best_idx = tok;
         }
-        __syncthreads();
-        const bool found = s_found != 0;
-        *result = s_bin;
-        __syncthreads();
-        return found;
     };
 
-    const uint32_t k = (uint32_t)top_k;
-    // how many tokens the state allows: the bit row alone tells
-    uint32_t n_allowed = 0;
-    {
-        const uint32_t* words = reinterpret_cast<const uint32_t*>(bits);
-        const int n_words = (V + 31) >> 5;
-        uint32_t c = 0;
-        for (int i = threadIdx.x; valid && i < n_words; i += T) c += __popc(words[i]);
+    bool slow = huge;
+    if (few && !huge) {
+        // The groups with an allowed token, and where their tokens go among the collected ones: 16 groups per thread
+        // and pass, a prefix over the lanes, one addition per wavefront to the two counts.  Then a group per thread.
+        const uint4* pieces = reinterpret_cast<const uint4*>(bits);
+        const int n_pieces = (n_groups + 15) >> 4;
+        for (int i0 = 0; i0 < n_pieces; i0 += T) {                 // (uniform trip count)
+            const int i = i0 + tid;
+            uint4 pc = make_uint4(0, 0, 0, 0);
+            if (valid && i < n_pieces) pc = pieces[i];
+            uint32_t w[4] = {pc.x, pc.y, pc.z, pc.w};
+            uint32_t n_here = 0, g_here = 0;
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
-        if ((threadIdx.x & 63u) == 0) s_scan[threadIdx.x >> 6] = c;
-        __syncthreads();
-        for (int w = 0; w < (T >> 6); ++w) n_allowed += s_scan[w];
-        __syncthreads();
-    }
-    uint32_t floor_key = 0, result = 0;
-    bool found = false;
-    if (n_allowed >= k) {                                         // else nothing is cut, and no logit is read
-        if (n_allowed > (uint32_t)kCutKeep && k <= (uint32_t)T) {
-            // a part of the row is enough for a bound: two stretches of T groups, at the start and in the middle
-            uint32_t top = 0;
-            auto take_max = [&](uint32_t key) { top = max(top, key); };
-            if (n_groups <= 4 * T) {
-                for_row(take_max);
-            } else {
-                for_groups(0, T, take_max);
-                for_groups(n_groups / 2, n_groups / 2 + T, take_max);
+            for (int d = 0; d < 4; ++d) {
+                const int rem = V - (i * 16 + d * 4) * 8;          // tokens from this word on
+                if (rem < 32) w[d] = rem <= 0 ? 0u : w[d] & ((1u << rem) - 1u);
+                n_here += __popc(w[d]);
+                g_here += nonzero_bytes(w[d]);
             }
-            s_keys[threadIdx.x] = top;                            // 0: this thread saw no allowed token
-            __syncthreads();
-            if (!select([&](auto&& f) { for_kept((uint32_t)T, f); }, k, 0u, &floor_key)) floor_key = 0;
+            // both counts in one word: at most 128 tokens and 16 groups a lane
+            const uint32_t both = n_here | (g_here << 16);
+            uint32_t incl = both;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t other = __shfl_up(incl, d, 64);
+                if (lane >= d) incl += other;
+            }
+            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            if (total == 0) continue;                              // (uniform in the wavefront)
+            uint32_t n_base = 0, g_base = 0;
+            if (lane == 0) {
+                n_base = atomicAdd(&s_n, total & 0xFFFFu);
+                g_base = atomicAdd(&s_groups, total >> 16);
+            }
+            n_base = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_base) + ((incl - both) & 0xFFFFu);
+            g_base = (uint32_t)__builtin_amdgcn_readfirstlane((int)g_base) + ((incl - both) >> 16);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                uint32_t rest = w[d];
+                while (rest) {
+                    const int at = __builtin_ctz(rest) & 24;
+                    const uint32_t m = (rest >> at) & 0xFFu;
+                    if (g_base < (uint32_t)kKeep) s_list[g_base] = make_uint2((uint32_t)(i * 16 + d * 4 + (at >> 3)) << 8 | m, n_base);
+                    ++g_base;
+                    n_base += __popc(m);
+                    rest &= ~(0xFFu << at);
+                }
+            }
         }
-        if (threadIdx.x == 0) s_n = 0;
         __syncthreads();
-        for_row([&](uint32_t key) {
-            if (key >= floor_key) {
-                const uint32_t i = atomicAdd(&s_n, 1u);
-                if (i < (uint32_t)kCutKeep) s_keys[i] = key;
+        if (s_n <= (uint32_t)kKeep) {                              // (always, unless the count beside the table is not the row's)
+            for (uint32_t i = tid; i < s_groups; i += (uint32_t)T) {
+                const uint2 en = s_list[i];
+                const int t = (int)(en.x >> 8) << 3;
+                Elem e[8];
+                load_group<DTYPE>(row, t, V, e);
+                uint32_t at = en.y;
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if ((en.x >> j) & 1u) {
+                        const uint32_t lb = as_f32((uint32_t)e[j]);
+                        s_cand[at] = make_uint2((uint32_t)(t + j), lb);
+                        s_keys[at] = key_f32(lb);
+                        ++at;
+                    }
             }
-        });
+        }
+        if constexpr (WRITE) {
+            __syncthreads();                                       // (the rows may be the same memory)
+            for (int c = 0; c < n_chunks; ++c)
+                for_chunk(c, [&](int u, int, const Elem (&e)[8], const u32x4&, uint32_t mg) {
+                    store_masked((c * kRowGroups + u) * T, e, mg);
+                });
+            store_tail();
+        }
+    } else if (!huge) {
+        // 16-bit order keys, two per word, 0 for a token that is not allowed: of a bf16 logit the whole key, of an fp32
+        // logit its upper half (NaN and -0 as their patterns)
+        uint32_t kk[RESIDENT ? kRowGroups : 1][4];
+        auto keys_of = [&](const Elem (&e)[8], const u32x4& raw, uint32_t mg, uint32_t (&o)[4]) {
+            const uint32_t d[4] = {raw.x, raw.y, raw.z, raw.w};
+            const uint32_t y = mg | (mg << 15);                    // allowed bit 2j at bit 2j, bit 2j + 1 at bit 16 + 2j
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint32_t two;
+                if constexpr (DTYPE == TDFA_F32) {
+                    const uint32_t x0 = (uint32_t)e[2 * i], x1 = (uint32_t)e[2 * i + 1];
+                    const uint32_t k0 = x0 ^ ((uint32_t)((int32_t)x0 >> 31) | 0x80000000u), k1 = x1 ^ ((uint32_t)((int32_t)x1 >> 31) | 0x80000000u);
+                    two = __builtin_amdgcn_perm(k1, k0, 0x07060302u);          // the upper halves
+                } else {
+                    two = keys2(d[i]);
+                }
+                const uint32_t pj = (y >> (2 * i)) & 0x00010001u;
+                o[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, two) * __builtin_bit_cast(u16x2, pj));
+            }
+        };
+        u16x2 acc = {0, 0};
+        for (int c = 0; c < n_chunks; ++c)
+            for_chunk(c, [&](int u, int g, const Elem (&e)[8], const u32x4& raw, uint32_t mg) {
+                uint32_t o[4];
+                keys_of(e, raw, mg, o);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    acc = __builtin_elementwise_max(acc, __builtin_bit_cast(u16x2, o[i]));
+                    if constexpr (RESIDENT) kk[u][i] = o[i];
+                }
+                store_masked((c * kRowGroups + u) * T, e, mg);
+            });
+        store_tail();
+        const uint32_t a2 = __builtin_bit_cast(uint32_t, acc);
+        const uint32_t top = max(a2 & 0xFFFFu, a2 >> 16);
+        // the k-th largest of the threads' maxima
+        if (top != 0) atomicAdd(&hist[top >> 8], 1u);
+        if (top > KU_POS_INF || (DTYPE == TDFA_F32 && top == KU_POS_INF)) s_special = 1;         // perhaps NaN
         __syncthreads();
-        const uint32_t n = s_n;
-        if (n <= 512u)
-            found = select_few(n, k, &result);
-        else if (n <= (uint32_t)kCutKeep)
-            found = select([&](auto&& f) { for_kept(n, f); }, k, 0u, &result);
-        else
-            found = select(for_row, k, floor_key, &result);
+        uint32_t hi8 = 0, lo8 = 0, left = 0;
+        bool found = find_bin(hist, k, &hi8, &left);
+        if (found && top != 0 && (top >> 8) == hi8) atomicAdd(&hist[256 + (top & 255u)], 1u);
+        __syncthreads();
+        found = found && find_bin(hist + 256, left, &lo8, &left);
+        uint32_t L = (hi8 << 8) | lo8;
+        if (!found || s_special || L <= KU_NEG_INF) {
+            slow = true;                                           // the same in every thread
+        } else {
+            if (L == KU_POS_ZERO) L = KU_NEG_ZERO;                 // -0 equals +0
+            for_tail([&](int t, Elem x, bool ok) {
+                if (ok && key_f32(as_f32((uint32_t)x)) >> 16 >= L) push(t, as_f32((uint32_t)x));
+            });
+            if constexpr (RESIDENT) {
+                if (__builtin_amdgcn_ballot_w64(top >= L) != 0) {
+#pragma unroll
+                    for (int u = 0; u < kRowGroups; ++u) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const uint32_t k0 = kk[u][i] & 0xFFFFu, k1 = kk[u][i] >> 16;
+                            if (k0 >= L || k1 >= L) {
+                                const int t = ((u * T + tid) << 3) + 2 * i;
+                                auto put = [&](uint32_t key, int tok) {
+                                    if (key < L) return;
+                                    if constexpr (DTYPE == TDFA_F32) push(tok, as_f32((uint32_t)row[tok]));
+                                    else push(tok, as_f32(key & 0x8000u ? key ^ 0x8000u : ~key & 0xFFFFu));
+                                };
+                                put(k0, t);
+                                put(k1, t + 1);
+                            }
+                        }
+                    }
+                }
+            } else {
+                for (int c = 0; c < n_chunks; ++c)
+                    for_chunk(c, [&](int, int g, const Elem (&e)[8], const u32x4& raw, uint32_t mg) {
+                        uint32_t o[4];
+                        keys_of(e, raw, mg, o);
+                        u16x2 ga = {0, 0};
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) ga = __builtin_elementwise_max(ga, __builtin_bit_cast(u16x2, o[i]));
+                        const uint32_t g2 = __builtin_bit_cast(uint32_t, ga);
+                        if (__builtin_amdgcn_ballot_w64(max(g2 & 0xFFFFu, g2 >> 16) >= L) == 0) return;
+#pragma unroll
+                        for (int j = 0; j < 8; ++j)
+                            if ((o[j >> 1] >> (16 * (j & 1)) & 0xFFFFu) >= L) push((g << 3) + j, as_f32((uint32_t)e[j]));
+                    });
+            }
+        }
     }
-    if (threadIdx.x == 0) cut[b] = found ? result : 0u;
+    __syncthreads();
+    const uint32_t n = s_n;
+    slow = slow || n > (uint32_t)kKeep;
+    uint32_t cut = 0;
+    if (!slow) {
+        // the k-th largest of the collected keys (fewer than k allowed tokens: no cut)
+        if (n_allowed >= k) {
+            if (n <= 128u) {
+                // by counting: a key is the answer if fewer than k keys are greater and at least k are greater or equal
+                for (uint32_t i = n + tid; i < ((n + 3u) & ~3u); i += (uint32_t)T) s_keys[i] = 0;   // pad to whole uint4
+                if (tid == 0) s_bin = 0;
+                __syncthreads();
+                for (uint32_t i = tid; i < n; i += (uint32_t)T) {
+                    const uint32_t mine = s_keys[i];
+                    uint32_t gt = 0, ge = 0;
+                    for (uint32_t j = 0; j < n; j += 4) {
+                        const uint4 o = *reinterpret_cast<const uint4*>(&s_keys[j]);
+                        gt += (o.x > mine) + (o.y > mine) + (o.z > mine) + (o.w > mine);
+                        ge += (o.x >= mine) + (o.y >= mine) + (o.z >= mine) + (o.w >= mine);
+                    }
+                    if (gt < k && k <= ge) s_bin = mine;            // equal keys all write the same value
+                }
+                __syncthreads();
+                cut = s_bin;
+            } else if (!select([&](auto&& f) { for (uint32_t i = tid; i < n; i += (uint32_t)T) f(s_keys[i]); }, k, &cut)) {
+                cut = 0;
+            }
+        }
+        for (uint32_t i = tid; i < n; i += (uint32_t)T) {
+            if (s_keys[i] < cut) continue;
+            const uint2 en = s_cand[i];
+            uint32_t w[4];
+            philox4x32_10(en.x >> 2, (uint32_t)b, sp.off_lo, sp.off_hi, sp.seed_lo, sp.seed_hi, w);
+            const uint32_t lo = (en.x & 1u) ? w[1] : w[0], hi = (en.x & 1u) ? w[3] : w[2];
+            consider(en.x, en.y, (en.x & 2u) ? hi : lo);
+        }
+    } else {
+        auto for_row = [&](auto&& f) {                             // f(key) for every allowed logit of the row
+            for (int g = tid; g < n_groups; g += T) {
+                const uint32_t mg = valid ? bits[g] : 0u;
+                if (mg == 0) continue;
+                Elem e[8];
+                load_group<DTYPE>(row, g << 3, V, e);
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if ((mg >> j) & 1u) f(key_f32(as_f32((uint32_t)e[j])));
+            }
+        };
+        if (n_allowed >= k && !select(for_row, k, &cut)) cut = 0;
+        float reached = -__builtin_inff();                         // a score some token of this wavefront has reached
+        for (int base = 0; base < n_groups; base += T) {
+            const int g = base + tid;
+            const uint32_t mg = valid && g < n_groups ? bits[g] : 0u;
+            uint32_t take = 0;
+            Elem e[8] = {};
+            if (mg != 0 || (WRITE && huge && g < n_groups)) load_group<DTYPE>(row, g << 3, V, e);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t lb = as_f32((uint32_t)e[j]);
+                // no noise value exceeds kNoiseMax: a token that cannot reach the best score is not drawn for
+                const bool may = __builtin_fmaf(__uint_as_float(lb), sp.inv_t, kNoiseMax) >= reached;
+                take |= (uint32_t)(((mg >> j) & 1u) && key_f32(lb) >= cut && may) << j;
+            }
+            if (WRITE && huge && g < n_groups) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int64_t t = (int64_t)g * 8 + j;
+                    if (t < V) orow[t] = (mg >> j) & 1u ? e[j] : (Elem)(DTYPE == TDFA_F32 ? 0xFF800000u : 0xFF80u);
+                }
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (((take >> (4 * h)) & 15u) == 0) continue;
+                uint32_t w[4];
+                philox4x32_10(((uint32_t)g << 1) + h, (uint32_t)b, sp.off_lo, sp.off_hi, sp.seed_lo, sp.seed_hi, w);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (!((take >> (4 * h + j)) & 1u)) continue;
+                    const uint32_t lb = as_f32((uint32_t)e[4 * h + j]);
+                    if (__builtin_fmaf(__uint_as_float(lb), sp.inv_t, noise_bound(w[j])) >= reached) consider((uint32_t)((g << 3) + 4 * h + j), lb, w[j]);
+                }
+            }
+            const uint32_t wave_top = wave_max_u32(best_key);      // 0: nothing scored yet
+            if (wave_top != 0) reached = __uint_as_float((wave_top & 0x80000000u) ? wave_top & 0x7FFFFFFFu : ~wave_top);
+        }
+    }
+    unsigned long long cand = best_key ? ((unsigned long long)best_key << 32) | (0xFFFFFFFFu - best_idx) : 0ull;
+    cand = block_max_u64(cand, wave_best);
+    if (tid == 0) write_result(a, b, q, valid, cand);
 }
 
 constexpr int kQueue = 128;            // entries of a wavefront's queues (rings, a power of two)
-constexpr float kNoiseMax = 16.64f;    // above every noise value: -ln(-ln(1 - 2^-24)) = 16.6355...
 constexpr int kWordsAhead = 4;         // 32-bit words of allowed bits (four groups each) a thread has in flight
 
 // One workgroup scans groups [g_lo, g_hi) of a row.  Only allowed tokens cost arithmetic (a
@@ -1298,7 +1575,6 @@ gather_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
         }
     }
 
-    const uint32_t cut_key = (SAMPLE && sp.cut) ? sp.cut[b] : 0u;
     if (SAMPLE && sp.off_dev) {                                // the same word for every thread
         const unsigned long long o = *sp.off_dev;
         sp.off_lo = (uint32_t)o;
@@ -1307,7 +1583,6 @@ gather_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
     uint32_t best_key = 0, best_idx = 0xFFFFFFFFu;           // key 0: no candidate yet
     auto consider = [&](uint32_t tok, uint32_t lb, uint32_t word) {
         if ((lb & 0x7FFFFFFFu) > 0x7F800000u) lb = 0xFF800000u;             // NaN counts as -inf
-        if (SAMPLE && key_f32(lb) < cut_key) return;                         // below the k-th largest allowed logit
         const uint32_t key = SAMPLE ? key_f32(__float_as_uint(__builtin_fmaf(__uint_as_float(lb), sp.inv_t, gumbel_of(word))))
                                     : key_f32(lb);
         if (key > best_key || (key == best_key && tok < best_idx)) {
@@ -1364,15 +1639,6 @@ gather_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
             }
         } else if (__ballot(m != 0) != 0) {
             uint32_t take = m;                                 // tokens to queue for scoring
-            if (cut_key != 0) {                                // top-k: nothing below the cut is drawn (uniform branch)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const uint32_t x = (uint32_t)e[j];
-                    uint32_t lb = DTYPE == TDFA_F32 ? x : x << 16;
-                    if ((lb & 0x7FFFFFFFu) > 0x7F800000u) lb = 0xFF800000u;
-                    if (key_f32(lb) < cut_key) take &= ~(1u << j);
-                }
-            }
             float lv[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -1411,10 +1677,7 @@ gather_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
             const uint32_t live = take;
             if (__popcll(__ballot(__popc(live) >= 2)) >= 32) {
                 // Still many: one generator block per four tokens, and a token is queued only if its
-                // own noise lets it win.  With n = 2^23 - (x >> 9), u = 1 - (n - 1/2) 2^-23 and
-                // g = -ln(-ln u) <= -ln(1 - u) <= (clz(n) - 7) ln 2; the slack added covers the
-                // rounding of the noise as computed.  fma is monotonic in its addend, so a token
-                // whose bound stays below a score already reached scores below it as well.
+                // own noise lets it win (noise_bound).
                 take = 0;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
@@ -1424,9 +1687,7 @@ gather_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
                     philox4x32_10((uint32_t)(t >> 2) + h, (uint32_t)b, sp.off_lo, sp.off_hi, sp.seed_lo, sp.seed_hi, w);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        const uint32_t n = 0x800000u - (w[j] >> 9);
-                        const float ub = __builtin_fmaf((float)(__clz((int)n) - 7), 0.693147180559945309f, 1.0e-3f);
-                        const float bound = __builtin_fmaf(lv[4 * h + j], sp.inv_t, ub);
+                        const float bound = __builtin_fmaf(lv[4 * h + j], sp.inv_t, noise_bound(w[j]));
                         take |= (uint32_t)(bound >= reached) << (4 * h + j);
                     }
                 }
@@ -1724,31 +1985,41 @@ int launch_mask_step(const MaskArgs& a, hipStream_t stream)
     return TDFA_OK;
 }
 
-int launch_sample_step(const MaskArgs& a, float inv_t, int32_t top_k, uint32_t* cut_scratch, uint64_t seed,
-                       uint64_t offset, const uint64_t* offset_dev, hipStream_t stream)
+int launch_sample_step(const MaskArgs& a, float inv_t, int32_t top_k, uint64_t seed, uint64_t offset, const uint64_t* offset_dev,
+                       hipStream_t stream)
 {
     if (a.batch <= 0) return TDFA_OK;
-    if (top_k > 0) {
-        const unsigned t = a.n_tokens >= 32768 ? 1024u : 256u;
-        if (a.dtype == TDFA_F32)
-            topk_cut_kernel<TDFA_F32><<<(unsigned)a.batch, t, 0, stream>>>(a, top_k, cut_scratch);
-        else
-            topk_cut_kernel<TDFA_BF16><<<(unsigned)a.batch, t, 0, stream>>>(a, top_k, cut_scratch);
-        TDFA_HIP(hipGetLastError());
-    }
-    int parts, threads, gpp;
-    gather_shape(a, &parts, &threads, &gpp);
-    if ((int64_t)a.batch * parts > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
-    const dim3 grid((unsigned)(a.batch * parts));
     SampleParams sp;
     sp.inv_t = inv_t;
     sp.seed_lo = (uint32_t)seed;
     sp.seed_hi = (uint32_t)(seed >> 32);
     sp.off_lo = (uint32_t)offset;
     sp.off_hi = (uint32_t)(offset >> 32);
-    sp.cut = top_k > 0 ? cut_scratch : nullptr;
     sp.off_dev = reinterpret_cast<const unsigned long long*>(offset_dev);
-    launch_gather<true>(a, sp, grid, (unsigned)threads, parts, gpp, stream);
+    if (top_k > 0) {
+        // a workgroup per sequence: as many threads as hold the row in registers, 1,024 at most
+        const unsigned t = a.n_tokens > kRowGroups * 8 * 256 ? 1024u : 256u;
+        const bool resident = a.n_tokens <= (int32_t)t * kRowGroups * 8;
+        auto launch = [&](auto dtype, auto write) {
+            constexpr int kType = decltype(dtype)::value;
+            constexpr bool kWrite = decltype(write)::value;
+            // (with the penalised row written, keys and stores together would not fit the registers: the row is read twice)
+            if (resident && !kWrite) topk_step_kernel<kType, kWrite, !kWrite><<<(unsigned)a.batch, t, 0, stream>>>(a, sp, top_k);
+            else topk_step_kernel<kType, kWrite, false><<<(unsigned)a.batch, t, 0, stream>>>(a, sp, top_k);
+        };
+        using F32 = std::integral_constant<int, TDFA_F32>;
+        using Bf16 = std::integral_constant<int, TDFA_BF16>;
+        if (a.dtype == TDFA_F32 && a.masked_out) launch(F32{}, std::true_type{});
+        else if (a.dtype == TDFA_F32) launch(F32{}, std::false_type{});
+        else if (a.masked_out) launch(Bf16{}, std::true_type{});
+        else launch(Bf16{}, std::false_type{});
+        TDFA_HIP(hipGetLastError());
+        return TDFA_OK;
+    }
+    int parts, threads, gpp;
+    gather_shape(a, &parts, &threads, &gpp);
+    if ((int64_t)a.batch * parts > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
+    launch_gather<true>(a, sp, dim3((unsigned)(a.batch * parts)), (unsigned)threads, parts, gpp, stream);
     TDFA_HIP(hipGetLastError());
     return TDFA_OK;
 }
@@ -1761,7 +2032,6 @@ int launch_sample_noise(int32_t batch, int32_t n_tokens, uint64_t seed, uint64_t
     if ((total + 255) / 256 > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch * n_tokens too large for one launch");
     SampleParams sp;
     sp.inv_t = 1.0f;
-    sp.cut = nullptr;
     sp.off_dev = nullptr;
     sp.seed_lo = (uint32_t)seed;
     sp.seed_hi = (uint32_t)(seed >> 32);

@@ -963,7 +963,7 @@ int pda_step_impl(const tdfa_ptable* table, const void* logits_dev, int dtype, i
         table->step_cap = 0;
         int rc = dev_alloc(&table->step_allow, (size_t)batch * (size_t)table->row_words);
         if (rc == TDFA_OK) rc = dev_alloc(&table->step_rows, (size_t)batch);
-        if (rc == TDFA_OK) rc = dev_alloc(&table->step_unused, 2 * (size_t)batch);     // (the second half: a word per sequence for the cut of a drawn step)
+        if (rc == TDFA_OK) rc = dev_alloc(&table->step_unused, (size_t)batch);
         if (rc != TDFA_OK) return rc;
         table->step_cap = batch;
     }
@@ -1012,8 +1012,7 @@ int pda_step_impl(const tdfa_ptable* table, const void* logits_dev, int dtype, i
                                                                    table->edge_first, table->token, table->n_pops, table->pops,
                                                                    table->row_words, table->step_allow, table->step_rows);
         TDFA_HIP(hipGetLastError());
-        const int rc = tdfa::launch_sample_step(m, draw->inv_t, draw->top_k, reinterpret_cast<uint32_t*>(table->step_unused + table->step_cap),
-                                                draw->seed, draw->offset, nullptr, s);
+        const int rc = tdfa::launch_sample_step(m, draw->inv_t, draw->top_k, draw->seed, draw->offset, nullptr, s);
         if (rc != TDFA_OK) return rc;
     } else if (tdfa::mask_step_takes_pda(fused)) {
         const int rc = tdfa::launch_mask_step(fused, s);

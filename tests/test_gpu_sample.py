@@ -152,6 +152,51 @@ def test_top_k(T, oracle, dtype, p_live, n_tokens, batch):
 
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("n_tokens", [2051, 32768, 32771, 131072, 131077])
+def test_top_k_edges(T, oracle, dtype, n_tokens):
+    """Around the sizes where the cut changes its way: rows that do and do not fit the threads' registers, states on
+    both sides of the 2,048 tokens that are collected whole, k beyond the number of threads, ties across the cut,
+    zeros of both signs at the cut, NaN at the top; the masked row in place every other time.  Exact integers."""
+    rng = np.random.default_rng(n_tokens + dtype)
+    counts = [0, 1, 60, 2047, 2048, 2049, n_tokens // 2, n_tokens]
+    tab = np.full((len(counts) + 1, n_tokens), DEAD, dtype=np.int32)
+    for q, c in enumerate(counts):
+        tab[q, rng.choice(n_tokens, size=c, replace=False)] = q
+    tab[-1, n_tokens - 11:] = 3                               # the last groups only, the partial one among them
+    table, _ = T.table_concat([_upload_table(T, tab)])
+    states = np.arange(-1, len(tab) + 1).astype(np.int32)
+    batch, stride = len(states), (n_tokens + 7) // 8 * 8
+    for trial, k in enumerate((1, 50, 129, 700, 1025, 3000)):
+        x = np.zeros((batch, stride), dtype=np.float32)
+        x[:, :n_tokens] = rng.normal(0, 2, size=(batch, n_tokens))
+        if trial % 3 == 1:
+            x = np.minimum(np.round(x), 2.0)                  # thousands of equal logits at the top
+        if trial == 2:
+            x = -np.abs(x)
+            x[:, rng.integers(0, n_tokens, 40)] = 0.0
+            x[:, rng.integers(0, n_tokens, 400)] = -0.0
+        if trial == 5:
+            x[::2, rng.integers(0, n_tokens, 30)] = np.nan
+            x[1::2] = -np.inf
+        lg = x if dtype == F32 else LG.f32_to_bf16_bits(x)
+        if dtype == BF16 and trial == 5:
+            lg[np.isnan(x)] = 0x7FC1
+            lg[0, :9] = 0xFFFF
+        dev = _to_dev(lg, dtype)
+        st = torch.from_numpy(states).cuda()
+        tok = torch.full((batch,), -9, dtype=torch.int32, device="cuda")
+        new = torch.full((batch,), -9, dtype=torch.int32, device="cuda")
+        out = dev if trial % 2 else None
+        T.sample_step(table, dev, st, 0.8, 21, trial, tok, new, out, top_k=k)
+        torch.cuda.synchronize()
+        want = oracle.sample_step(tab, lg, dtype, states, 0.8, 21, trial, row_stride=stride, want_masked=True, top_k=k, n_threads=16)
+        assert np.array_equal(tok.cpu().numpy(), want[0]), (trial, k, tok.cpu().numpy(), want[0])
+        assert np.array_equal(new.cpu().numpy(), want[1])
+        if out is not None:
+            assert np.array_equal(_bits(out)[:, :n_tokens], want[2].view(_bits(out).dtype)[:, :n_tokens])
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
 def test_special_values(T, oracle, dtype):
     n_tokens = 4096 + 64
     tab = _rand_table(5, n_tokens, 0.3, 1)
