@@ -953,7 +953,9 @@ struct SampleParams {
     const unsigned long long* off_dev;   // if not NULL: the offset is read from here by the kernel (off_lo / off_hi unused)
 };
 
-// counter (c0, c1, c2, c3), key (k0, k1) -> four words, ten rounds
+// counter (c0, c1, c2, c3), key (k0, k1) -> four words, ten rounds.  Where c1, c2, c3 and the key are the same in all
+// lanes, half of the first three rounds is scalar: their exclusive-ors are grouped for that, the later ones take one
+// three-input instruction.
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                               uint32_t k1, uint32_t (&w)[4])
 {
@@ -961,11 +963,11 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
     for (int r = 0; r < 10; ++r) {
         const unsigned long long p0 = (unsigned long long)0xD2511F53u * c0;
         const unsigned long long p1 = (unsigned long long)0xCD9E8D57u * c2;
-        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0, n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+        const uint32_t h0 = (uint32_t)(p0 >> 32), h1 = (uint32_t)(p1 >> 32);
+        c0 = r < 2 ? h1 ^ (c1 ^ k0) : __builtin_amdgcn_bitop3_b32(h1, c1, k0, 0x96);
+        c2 = r == 1 ? c3 ^ (h0 ^ k1) : r < 3 ? h0 ^ (c3 ^ k1) : __builtin_amdgcn_bitop3_b32(h0, c3, k1, 0x96);
         c1 = (uint32_t)p1;
         c3 = (uint32_t)p0;
-        c0 = n0;
-        c2 = n2;
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
@@ -1003,14 +1005,15 @@ __device__ __forceinline__ float gumbel_of(uint32_t x)
 
 constexpr float kNoiseMax = 16.64f;    // above every noise value: -ln(-ln(1 - 2^-24)) = 16.6355...
 
-// Not below the noise that generator word x makes: with n = 2^23 - (x >> 9), u = 1 - (n - 1/2) 2^-23 and
-// g = -ln(-ln u) <= -ln(1 - u) <= (clz(n) - 7) ln 2; the slack added covers the rounding of the noise as
-// computed.  fma is monotonic in its addend, so a token whose bound stays below a score already reached
+// Not below the noise that generator word x makes.  With v = 2^32 (1 - u), a multiple of 256 below 2^32 and so exact in
+// binary32, g = -ln(-ln u) <= -ln(1 - u) = (32 - log2 v) ln 2, and the bits of v's binary32 pattern, as an integer
+// divided by 2^23, less 127, are its logarithm with straight lines between the powers of two: never above log2 v,
+// and at most 0.0861 below.  The slack added covers the rounding of the noise as computed and of this bound.  fma is monotonic in its addend, so a token whose bound stays below a score already reached
 // scores below it as well.
 __device__ __forceinline__ float noise_bound(uint32_t x)
 {
-    const uint32_t n = 0x800000u - (x >> 9);
-    return __builtin_fmaf((float)(__clz((int)n) - 7), 0.693147180559945309f, 1.0e-3f);
+    const uint32_t v = (~x & 0xFFFFFE00u) | 0x100u;
+    return __builtin_fmaf((float)(int32_t)__float_as_uint((float)v), -0.693147180559945309f * 0x1p-23f, 159.0f * 0.693147180559945309f + 1.0e-3f);
 }
 
 // The noise alone: out[b][t] = g_t of sequence b, for callers that want to reproduce a draw.
@@ -1496,42 +1499,74 @@ topk_step_kernel(MaskArgs a, SampleParams sp, int32_t top_k)
     if (tid == 0) write_result(a, b, q, valid, cand);
 }
 
+// Greedy step on a packed table whose logits are fp32 (or whose rows the step kernel cannot address): the
+// gathering scan of sparse rows, and an element by element comparison of the rows that allow an eighth of the
+// vocabulary or more.
+template <int DTYPE>
+__global__ void __launch_bounds__(kMaxThreads)
+packed_step_kernel(MaskArgs a, int parts, int groups_per_part)
+{
+    using Elem = typename ElemOf<DTYPE>::type;
+    __shared__ unsigned long long wave_best[kMaxWaves];
+    __shared__ uint2 s_ring[kMaxWaves][kGatherQueue];
+    const int b = blockIdx.x / parts, p = blockIdx.x % parts;
+    const int V = a.n_tokens;
+    const int q = a.states[b];
+    const bool valid = q >= 0 && (int64_t)q < a.n_rows;
+    const uint8_t* bits = reinterpret_cast<const uint8_t*>(a.allow + (valid ? (int64_t)q * a.row_words : 0));
+    const Elem* row = static_cast<const Elem*>(a.logits) + (int64_t)b * a.row_stride;
+    const int g_lo = p * groups_per_part;
+    const int g_hi = min((V + 7) >> 3, g_lo + groups_per_part);
+    const uint32_t n_allowed = valid ? allowed_count(a, q) : 0u;
+    unsigned long long cand = 0ull;
+    if (n_allowed != 0u) {                                     // uniform in the workgroup
+        if ((uint64_t)n_allowed * 8u >= (uint64_t)V) cand = exact_scan<DTYPE>(row, nullptr, bits, true, V, g_lo, g_hi);
+        else cand = gather_scan<DTYPE>(row, bits, V, g_lo, g_hi, s_ring[threadIdx.x >> 6]);
+        cand = block_max_u64(cand, wave_best);
+    }
+    if (threadIdx.x == 0 && combine_parts(a, b, parts, cand)) write_result(a, b, q, valid, cand);
+}
+
 constexpr int kQueue = 128;            // entries of a wavefront's queues (rings, a power of two)
 constexpr int kWordsAhead = 4;         // 32-bit words of allowed bits (four groups each) a thread has in flight
+constexpr int kDrawThreads = 256;      // workgroup of the draw
+constexpr int kDrawGroups = 2048;      // workgroups that a draw of a smaller batch is split into
+constexpr int kDenseQuads = 48;        // lanes with a quad to draw for from which on a wavefront draws in place
 
-// One workgroup scans groups [g_lo, g_hi) of a row.  Only allowed tokens cost arithmetic (a
-// generator block, two logarithms), and in the automata of constrained decoding most states
-// allow few tokens, scattered over the row.  Two queues per wavefront, in LDS, keep the lanes
-// busy all the same:
-//   groups : the groups of eight tokens with an allowed token among them.  A thread reads the
-//            allowed bits of 4 * kWordsAhead groups at once; the groups that need their logits are
-//            queued and fetched 64 at a time, one per lane, so the logits of groups without an
-//            allowed token are never read (unless the masked row is wanted: then all are queued).
-//   tokens : the allowed tokens (id, logit) of the fetched groups, scored 64 at a time, one per
-//            lane.  Where most lanes hold groups that are at least half allowed (a wildcard-like
-//            state) the lanes score their own eight tokens in place instead, which shares a
-//            generator block among four neighbouring tokens.
-// A queue belongs to one wavefront, so the loop needs no workgroup barrier; the maximum does not
-// depend on the order of scoring because candidates are compared as (score, lowest id).
+// The draw from the whole allowed set.  `parts` workgroups scan a row; one takes groups [g_lo, g_hi).  Only tokens that
+// may win cost arithmetic, and what they cost is their generator block, made for four neighbouring tokens (a quad) at
+// a time.  Two queues per wavefront, in LDS, keep the lanes busy:
+//   groups : the groups of eight tokens with an allowed token among them.  A thread reads the allowed bits of
+//            4 * kWordsAhead groups at once; the groups that need their logits are queued and fetched 64 at a time, one
+//            per lane, a batch ahead (with the masked row wanted all groups are).
+//   quads  : the quads of the fetched groups with an allowed token that could still win whatever its noise: no noise
+//            value exceeds kNoiseMax, so a logit too far below the best score of the workgroup so far cannot.  They
+//            wait until there are 64, one per lane; where most lanes hold one they are drawn in place.
+// A quad's generator block gives every token's noise but for two logarithms; a bound on it that takes a few
+// instructions (noise_bound) lets all but about one token in 10^4 go without them.
 //
-// With SAMPLE off the same scan is the greedy step for packed tables, whose states mostly allow
-// few tokens: the score of a token is its logit, fetched groups are compared in place (no token
-// queue), and a state that allows at least an eighth of the vocabulary (its edge count is in the
-// packed table) is scanned by the streaming loop instead, which reads every logit.
-template <int DTYPE, bool WRITE, bool SAMPLE>
-__global__ void __launch_bounds__(kMaxThreads)
-gather_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
+// Bound by the instructions issued: a generator block is 18 multiplications (64-bit products, at the full rate)
+// and as many three-input exclusive-ors, the bounds six instructions per token.  A workgroup of 1,024 threads per row (a compute unit with a
+// row that allows most tokens works for 45 us while those with sparse rows idle) and a queue of single tokens, each with
+// a generator block and two logarithms of its own, took longer: T = 1, 128,256 tokens, bf16, 256 sequences anywhere in
+// the texts of 50 signatures 42.6 -> 30 us, all in states that allow most tokens 45.9 -> 36.3 us (1,024 sequences: 139
+// -> 89 and 166 -> 105 us), all in states that allow few 9.3 -> 9.9 us.
+// A queue belongs to one wavefront, so the loop needs no workgroup barrier; the maximum does not depend on the
+// order because candidates are compared as (score, lowest id).
+template <int DTYPE, bool WRITE>
+__global__ void __launch_bounds__(kDrawThreads)
+draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
 {
     using Elem = typename ElemOf<DTYPE>::type;
     constexpr Elem NEG_INF = DTYPE == TDFA_F32 ? (Elem)0xFF800000u : (Elem)0xFF80u;
+    constexpr int kWaves = kDrawThreads / 64;
     __shared__ unsigned long long wave_best[kMaxWaves];
-    __shared__ uint2 s_groups[kMaxWaves][kQueue];
-    __shared__ uint2 s_tokens[kMaxWaves][kQueue];
+    __shared__ uint2 s_groups[kWaves][kQueue];
+    __shared__ __attribute__((aligned(16))) float4 s_logits[kWaves][kQueue];   // a waiting quad's logits, -inf where not allowed
+    __shared__ uint32_t s_quads[kWaves][kQueue];                               // its number << 4 | allowed bits
     __shared__ uint32_t s_reached;                             // order key of the best score any wavefront has reached
-    if (SAMPLE) {
-        if (threadIdx.x == 0) s_reached = 0;
-        __syncthreads();
-    }
+    if (threadIdx.x == 0) s_reached = 0;
+    __syncthreads();
     const int b = blockIdx.x / parts, p = blockIdx.x % parts;
     const int V = a.n_tokens;
     const int q = a.states[b];
@@ -1544,7 +1579,8 @@ gather_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
     const int g_hi = min(n_groups, g_lo + groups_per_part);
     const uint32_t lane = threadIdx.x & 63u;
     uint2* group_q = s_groups[threadIdx.x >> 6];
-    uint2* token_q = s_tokens[threadIdx.x >> 6];
+    float4* logit_q = s_logits[threadIdx.x >> 6];
+    uint32_t* quad_q = s_quads[threadIdx.x >> 6];
     auto below = [](unsigned long long bal) {                  // lanes below this one that are set in bal
         return __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
     };
@@ -1555,10 +1591,8 @@ gather_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
     };
 
     if constexpr (!WRITE) {
-        // A state that allows no token (its count, or in a packed table its edges): no token, the state stays.
-        const bool none = valid && (a.delta ? (a.row_allowed != nullptr && a.row_allowed[q] == 0u)
-                                            : (a.targets != nullptr && a.row_begin[q + 1] == a.row_begin[q]));
-        if (none) {                                                                           // uniform in the workgroup
+        // A state that allows no token: no token, the state stays.
+        if (valid && allowed_count(a, q) == 0u) {              // uniform in the workgroup
             if (threadIdx.x == 0) {
                 unsigned long long nothing = 0ull;
                 if (combine_parts(a, b, parts, nothing)) write_result(a, b, q, valid, nothing);
@@ -1566,49 +1600,59 @@ gather_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
             return;
         }
     }
-    if constexpr (!SAMPLE) {
-        if (valid && !a.delta && (a.row_begin[q + 1] - a.row_begin[q]) * 8 >= (int64_t)V) {   // uniform in the workgroup
-            unsigned long long c = exact_scan<DTYPE>(row, orow, bits, valid, V, g_lo, g_hi);
-            c = block_max_u64(c, wave_best);
-            if (threadIdx.x == 0 && combine_parts(a, b, parts, c)) write_result(a, b, q, valid, c);
-            return;
-        }
-    }
-
-    if (SAMPLE && sp.off_dev) {                                // the same word for every thread
+    if (sp.off_dev) {                                          // the same word for every thread
         const unsigned long long o = *sp.off_dev;
         sp.off_lo = (uint32_t)o;
         sp.off_hi = (uint32_t)(o >> 32);
     }
-    uint32_t best_key = 0, best_idx = 0xFFFFFFFFu;           // key 0: no candidate yet
-    auto consider = [&](uint32_t tok, uint32_t lb, uint32_t word) {
-        if ((lb & 0x7FFFFFFFu) > 0x7F800000u) lb = 0xFF800000u;             // NaN counts as -inf
-        const uint32_t key = SAMPLE ? key_f32(__float_as_uint(__builtin_fmaf(__uint_as_float(lb), sp.inv_t, gumbel_of(word))))
-                                    : key_f32(lb);
-        if (key > best_key || (key == best_key && tok < best_idx)) {
-            best_key = key;
-            best_idx = tok;
+    uint32_t best_key = 0, best_idx = 0xFFFFFFFFu;             // key 0: no candidate yet
+    float reached = -__builtin_inff();                         // a score that some token of the workgroup has reached
+    auto reach = [&](uint32_t key) {                           // (key 0: nothing scored yet)
+        if (key != 0) reached = fmaxf(reached, __uint_as_float((key & 0x80000000u) ? key & 0x7FFFFFFFu : ~key));
+    };
+    // One quad per lane (all lanes active; mask 0: none): its allowed tokens compete.
+    auto draw_quads = [&](uint32_t quad, uint32_t mask, const float (&l)[4]) __attribute__((always_inline)) {
+        uint32_t w[4];
+        philox4x32_10(quad, (uint32_t)b, sp.off_lo, sp.off_hi, sp.seed_lo, sp.seed_hi, w);
+        float bd[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bd[j] = __builtin_fmaf(l[j], sp.inv_t, noise_bound(w[j]));
+        const float top = fmaxf(fmaxf(bd[0], bd[1]), fmaxf(bd[2], bd[3]));
+        if (__builtin_amdgcn_ballot_w64(!(top < reached)) == 0) return;         // (a NaN logit does not hide the others)
+        uint32_t take = mask;
+        for (;;) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (bd[j] < reached) take &= ~(1u << j);
+            if (__builtin_amdgcn_ballot_w64(take != 0) == 0) break;
+            if (take != 0) {
+                const int j = __builtin_ctz(take);
+                take &= take - 1u;
+                uint32_t lb = __float_as_uint(j == 0 ? l[0] : j == 1 ? l[1] : j == 2 ? l[2] : l[3]);
+                const uint32_t word = j == 0 ? w[0] : j == 1 ? w[1] : j == 2 ? w[2] : w[3];
+                if ((lb & 0x7FFFFFFFu) > 0x7F800000u) lb = 0xFF800000u;         // NaN counts as -inf
+                const uint32_t key = key_f32(__float_as_uint(__builtin_fmaf(__uint_as_float(lb), sp.inv_t, gumbel_of(word))));
+                const uint32_t tok = quad * 4u + (uint32_t)j;
+                if (key > best_key || (key == best_key && tok < best_idx)) {
+                    best_key = key;
+                    best_idx = tok;
+                }
+            }
+            const uint32_t top_key = wave_max_u32(best_key);
+            if (lane == 0) atomicMax(&s_reached, top_key);       // the other wavefronts prune by it too
+            reach(top_key);
         }
     };
-
-    uint32_t t_head = 0, t_tail = 0, g_head = 0, g_tail = 0;   // ring positions, the same in all lanes
-    float reached = -__builtin_inff();                         // a score some token of this wavefront has reached
-    auto score_tokens = [&](uint32_t n) __attribute__((always_inline)) {   // n <= 64 queued tokens, one per lane
+    uint32_t q_head = 0, q_tail = 0, g_head = 0, g_tail = 0;   // ring positions, the same in all lanes
+    auto draw_waiting = [&](uint32_t n) __attribute__((always_inline)) {       // n <= 64 waiting quads, one per lane
         wave_sync();
-        if (lane < n) {
-            const uint2 en = token_q[(t_head + lane) & (kQueue - 1)];
-            uint32_t w[4];
-            philox4x32_10(en.x >> 2, (uint32_t)b, sp.off_lo, sp.off_hi, sp.seed_lo, sp.seed_hi, w);
-            const uint32_t lo = (en.x & 1u) ? w[1] : w[0], hi = (en.x & 1u) ? w[3] : w[2];
-            consider(en.x, en.y, (en.x & 2u) ? hi : lo);
-        }
-        t_head += n;
+        const uint32_t at = (q_head + lane) & (kQueue - 1);
+        const uint32_t en = lane < n ? quad_q[at] : 0u;
+        const float4 l4 = logit_q[at];
+        const float l[4] = {l4.x, l4.y, l4.z, l4.w};
+        q_head += n;
         wave_sync();
-        const uint32_t top = wave_max_u32(best_key);           // 0: nothing scored yet
-        if (top != 0) {
-            if (lane == 0) atomicMax(&s_reached, top);           // the other wavefronts of the row prune by it too
-            reached = fmaxf(reached, __uint_as_float((top & 0x80000000u) ? top & 0x7FFFFFFFu : ~top));
-        }
+        draw_quads(en >> 4, en & 15u, l);
     };
     // Fetched groups are worked on one batch late: the logits of a batch are requested when it is
     // taken from the queue and used when the next batch is taken (or at the end), so that a
@@ -1631,82 +1675,34 @@ gather_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
         wave_sync();
     };
     auto work_batch = [&]() __attribute__((always_inline)) {   // the batch whose logits were requested before
-        if constexpr (!SAMPLE) {
+        if (__builtin_amdgcn_ballot_w64(m != 0) != 0) {
+            const uint32_t rk = __hip_atomic_load(&s_reached, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            reach((uint32_t)__builtin_amdgcn_readfirstlane((int)rk));
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const uint32_t x = (uint32_t)e[j];
-                if ((m >> j) & 1u) consider((uint32_t)(t + j), DTYPE == TDFA_F32 ? x : x << 16, 0u);
-            }
-        } else if (__ballot(m != 0) != 0) {
-            uint32_t take = m;                                 // tokens to queue for scoring
-            float lv[8];
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t mask = (m >> (4 * h)) & 15u;
+                float l[4], most[4];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const uint32_t x = (uint32_t)e[j];
-                uint32_t lb = DTYPE == TDFA_F32 ? x : x << 16;
-                if ((lb & 0x7FFFFFFFu) > 0x7F800000u) lb = 0xFF800000u;
-                lv[j] = __uint_as_float(lb);
-            }
-            {
-                const uint32_t rk = __hip_atomic_load(&s_reached, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                const uint32_t top = (uint32_t)__builtin_amdgcn_readfirstlane((int)rk);
-                if (top != 0) reached = fmaxf(reached, __uint_as_float((top & 0x80000000u) ? top & 0x7FFFFFFFu : ~top));
-            }
-            if (reached == -__builtin_inff() && __ballot(take != 0) != 0) {
-                // Nothing scored in this row yet: one token per lane is scored right away, so that the
-                // rest of the group already has a score to be measured against.
-                const unsigned long long first = __ballot(take != 0);
-                if (take != 0) {
-                    const int j = __builtin_ctz(take);
-                    take &= take - 1u;
-                    float l = lv[0];
-#pragma unroll
-                    for (int i = 1; i < 8; ++i) l = j == i ? lv[i] : l;
-                    token_q[(t_tail + below(first)) & (kQueue - 1)] = make_uint2((uint32_t)(t + j), __float_as_uint(l));
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t x = (uint32_t)e[4 * h + j];
+                    l[j] = (mask >> j) & 1u ? __uint_as_float(DTYPE == TDFA_F32 ? x : x << 16) : -__builtin_inff();
+                    most[j] = __builtin_fmaf(l[j], sp.inv_t, kNoiseMax);
                 }
-                t_tail += (uint32_t)__popcll(first);
-                if (t_tail - t_head > 64u) score_tokens(64u);    // fewer than 64 waited, at most 64 came
-                score_tokens(t_tail - t_head);
-            }
-            // No noise value exceeds kNoiseMax, so a logit too far below a score already reached cannot
-            // win whatever its noise: dropped before any generator block is made.  With peaked
-            // logits (a language model's, or a low temperature) that is nearly all of the row.
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (!(__builtin_fmaf(lv[j], sp.inv_t, kNoiseMax) >= reached)) take &= ~(1u << j);
-            const uint32_t live = take;
-            if (__popcll(__ballot(__popc(live) >= 2)) >= 32) {
-                // Still many: one generator block per four tokens, and a token is queued only if its
-                // own noise lets it win (noise_bound).
-                take = 0;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const uint32_t mh = (live >> (4 * h)) & 15u;
-                    if (mh == 0) continue;
-                    uint32_t w[4];
-                    philox4x32_10((uint32_t)(t >> 2) + h, (uint32_t)b, sp.off_lo, sp.off_hi, sp.seed_lo, sp.seed_hi, w);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float bound = __builtin_fmaf(lv[4 * h + j], sp.inv_t, noise_bound(w[j]));
-                        take |= (uint32_t)(bound >= reached) << (4 * h + j);
+                const bool live = mask != 0 && !(fmaxf(fmaxf(most[0], most[1]), fmaxf(most[2], most[3])) < reached);
+                const unsigned long long bal = __builtin_amdgcn_ballot_w64(live);
+                if (bal == 0) continue;
+                const uint32_t quad = (uint32_t)(t >> 2) + (uint32_t)h, n = (uint32_t)__popcll(bal);
+                if (n >= (uint32_t)kDenseQuads) {
+                    draw_quads(quad, live ? mask : 0u, l);
+                } else {
+                    if (live) {
+                        const uint32_t at = (q_tail + below(bal)) & (kQueue - 1);
+                        quad_q[at] = quad << 4 | mask;
+                        logit_q[at] = make_float4(l[0], l[1], l[2], l[3]);
                     }
+                    q_tail += n;
+                    if (q_tail - q_head >= 64u) draw_waiting(64u);   // fewer than 64 waited, fewer than 64 came
                 }
-                take &= live;
-            }
-            // each lane hands over its next token per round; a round adds at most 64
-            unsigned long long bal = __ballot(take != 0);
-            while (bal != 0) {
-                if (take != 0) {
-                    const int j = __builtin_ctz(take);
-                    take &= take - 1u;
-                    float l = lv[0];
-#pragma unroll
-                    for (int i = 1; i < 8; ++i) l = j == i ? lv[i] : l;
-                    token_q[(t_tail + below(bal)) & (kQueue - 1)] = make_uint2((uint32_t)(t + j), __float_as_uint(l));
-                }
-                t_tail += (uint32_t)__popcll(bal);
-                if (t_tail - t_head >= 64u) score_tokens(64u);       // fewer than 64 waited, at most 64 came
-                bal = __ballot(take != 0);
             }
         }
         if (WRITE && own) {
@@ -1745,7 +1741,7 @@ gather_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
         w3 = load_word(wi + 4 * NT);
         const int left = g_hi - (wi << 2);                                   // groups of this word inside the part
         const uint32_t wm = left >= 4 ? w : (left > 0 ? w & ((1u << (8 * left)) - 1u) : 0u);
-        if (!WRITE && __ballot(wm != 0) == 0) continue;
+        if (!WRITE && __builtin_amdgcn_ballot_w64(wm != 0) == 0) continue;
         // The 64 words of the wavefront cover 256 consecutive groups.  They are handed over 64
         // consecutive groups at a time (lane L takes byte L mod 4 of the word of lane 16 i + L / 4), so
         // that neighbouring lanes fetch neighbouring logits.
@@ -1756,7 +1752,7 @@ gather_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
             const int g = ((wi - (int)lane + src) << 2) + (int)(lane & 3u);
             const uint32_t mg = (ws >> (8 * (lane & 3u))) & 0xFFu;
             const bool has = WRITE ? g < g_hi : mg != 0;                     // the masked row needs every group
-            const unsigned long long bal = __ballot(has);
+            const unsigned long long bal = __builtin_amdgcn_ballot_w64(has);
             if (bal == 0) continue;
             if (has) group_q[(g_tail + below(bal)) & (kQueue - 1)] = make_uint2((uint32_t)g, mg);
             g_tail += (uint32_t)__popcll(bal);
@@ -1765,7 +1761,7 @@ gather_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
     }
     if (g_tail != g_head) fetch_groups(g_tail - g_head);
     if (pending_batch) work_batch();
-    if (t_tail != t_head) score_tokens(t_tail - t_head);
+    if (q_tail != q_head) draw_waiting(q_tail - q_head);
     unsigned long long cand = best_key ? ((unsigned long long)best_key << 32) | (0xFFFFFFFFu - best_idx) : 0ull;
     cand = block_max_u64(cand, wave_best);
     if (threadIdx.x != 0) return;
@@ -1807,20 +1803,7 @@ clear_scratch_kernel(unsigned long long* __restrict__ best, unsigned int* __rest
     }
 }
 
-template <bool SAMPLE>
-void launch_gather(const MaskArgs& a, const SampleParams& sp, dim3 grid, unsigned threads, int parts, int gpp, hipStream_t stream)
-{
-    if (a.dtype == TDFA_F32 && a.masked_out)
-        gather_step_kernel<TDFA_F32, true, SAMPLE><<<grid, threads, 0, stream>>>(a, sp, parts, gpp);
-    else if (a.dtype == TDFA_F32)
-        gather_step_kernel<TDFA_F32, false, SAMPLE><<<grid, threads, 0, stream>>>(a, sp, parts, gpp);
-    else if (a.masked_out)
-        gather_step_kernel<TDFA_BF16, true, SAMPLE><<<grid, threads, 0, stream>>>(a, sp, parts, gpp);
-    else
-        gather_step_kernel<TDFA_BF16, false, SAMPLE><<<grid, threads, 0, stream>>>(a, sp, parts, gpp);
-}
-
-// Launch shape of the gather kernel: a row per workgroup of 1024 threads when the batch fills the
+// Launch shape of the packed step kernel: a row per workgroup of 1024 threads when the batch fills the
 // chip, else rows split over `parts` workgroups of 256, each part a whole number of 32-bit words
 // of allowed bits.
 void gather_shape(const MaskArgs& a, int* parts_out, int* threads_out, int* gpp_out)
@@ -1875,7 +1858,7 @@ namespace {
 // (1,024 rows: 67 against 87 us), and penalised rows stay with it, as do rows beyond the step kernel's 32-bit offsets.
 bool packed_takes_gather(const MaskArgs& a)
 {
-    return !a.delta && a.targets && (a.dtype == TDFA_F32 || a.masked_out || a.n_tokens > (1 << 27));
+    return !a.delta && a.targets && !a.masked_out && (a.dtype == TDFA_F32 || a.n_tokens > (1 << 27));
 }
 }  // namespace
 
@@ -1933,7 +1916,9 @@ int launch_mask_step(const MaskArgs& a, hipStream_t stream)
         int g_parts, g_threads, g_gpp;
         gather_shape(a, &g_parts, &g_threads, &g_gpp);
         if ((int64_t)a.batch * g_parts > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
-        launch_gather<false>(a, SampleParams{}, dim3((unsigned)(a.batch * g_parts)), (unsigned)g_threads, g_parts, g_gpp, stream);
+        const dim3 grid((unsigned)(a.batch * g_parts));
+        if (a.dtype == TDFA_F32) packed_step_kernel<TDFA_F32><<<grid, (unsigned)g_threads, 0, stream>>>(a, g_parts, g_gpp);
+        else packed_step_kernel<TDFA_BF16><<<grid, (unsigned)g_threads, 0, stream>>>(a, g_parts, g_gpp);
         TDFA_HIP(hipGetLastError());
         return TDFA_OK;
     }
@@ -1943,9 +1928,14 @@ int launch_mask_step(const MaskArgs& a, hipStream_t stream)
     const bool skip = sh.fits;
     if ((int64_t)a.batch * parts > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
     // the 16-bit kernel addresses a row through 32-bit byte offsets
-    if (a.dtype != TDFA_F32 && a.n_tokens > (1 << 27)) return fail(TDFA_E_UNSUPPORTED, "more than 2^27 tokens in a 16-bit row");
     const dim3 grid((unsigned)(a.batch * parts));
     const unsigned kThreads = (unsigned)threads;
+    if (a.dtype != TDFA_F32 && a.n_tokens > (1 << 27)) {
+        if (a.delta || !a.targets) return fail(TDFA_E_UNSUPPORTED, "more than 2^27 tokens in a 16-bit row");
+        mask_step_exact_kernel<TDFA_BF16><<<grid, kThreads, 0, stream>>>(a, parts, gpp);     // (packed rows have no such limit)
+        TDFA_HIP(hipGetLastError());
+        return TDFA_OK;
+    }
     const int n_waves = threads / 64;
     if (skip && a.dtype != TDFA_F32 && lds > (size_t)kPlainLdsBytes) {
         // once per device: let the kernels that keep the bits in LDS take more than the default 64 KB
@@ -2016,10 +2006,20 @@ int launch_sample_step(const MaskArgs& a, float inv_t, int32_t top_k, uint64_t s
         TDFA_HIP(hipGetLastError());
         return TDFA_OK;
     }
-    int parts, threads, gpp;
-    gather_shape(a, &parts, &threads, &gpp);
+    // workgroups of 256 threads, kDrawGroups or more of them (rows in parts of at least 1,024 groups)
+    const int n_groups = (a.n_tokens + 7) >> 3;
+    int parts = (kDrawGroups + a.batch - 1) / a.batch;
+    const int max_parts = (n_groups + 1023) / 1024;
+    if (parts > max_parts) parts = max_parts;
+    if (parts < 1) parts = 1;
+    int gpp = ((n_groups + parts - 1) / parts + 3) / 4 * 4;
+    if (gpp < 4) gpp = 4;
     if ((int64_t)a.batch * parts > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
-    launch_gather<true>(a, sp, dim3((unsigned)(a.batch * parts)), (unsigned)threads, parts, gpp, stream);
+    const dim3 grid((unsigned)(a.batch * parts));
+    if (a.dtype == TDFA_F32 && a.masked_out) draw_step_kernel<TDFA_F32, true><<<grid, kDrawThreads, 0, stream>>>(a, sp, parts, gpp);
+    else if (a.dtype == TDFA_F32) draw_step_kernel<TDFA_F32, false><<<grid, kDrawThreads, 0, stream>>>(a, sp, parts, gpp);
+    else if (a.masked_out) draw_step_kernel<TDFA_BF16, true><<<grid, kDrawThreads, 0, stream>>>(a, sp, parts, gpp);
+    else draw_step_kernel<TDFA_BF16, false><<<grid, kDrawThreads, 0, stream>>>(a, sp, parts, gpp);
     TDFA_HIP(hipGetLastError());
     return TDFA_OK;
 }

@@ -203,6 +203,26 @@ def test_noise_is_monotonic_and_bounded_by_leading_zeros(oracle):
     assert np.abs(g[ks] - want).max() < 4e-6
 
 
+def test_noise_bound_from_the_bits_of_the_tail(oracle):
+    """The bound that the drawing kernels measure a token by before they make its noise: with v = 2^32 (1 - u), exact
+    in binary32, and B its bit pattern, fma(B, -ln 2 2^-23, 159 ln 2 + 0.001), all in binary32, is above the noise for
+    every one of the 2^23 values, and by at most 0.0861 ln 2 + 0.001 (the chord of the logarithm) plus the
+    difference between -ln(1 - u) and the noise."""
+    k = np.arange(2 ** 23, dtype=np.uint32)
+    for low in (0, 0x1FF):
+        x = (k << np.uint32(9)) | np.uint32(low)
+        v = (~x & np.uint32(0xFFFFFE00)) | np.uint32(0x100)
+        f = v.astype(np.float32)
+        assert (f.astype(np.float64) == v.astype(np.float64)).all()
+        b = f.view(np.int32).astype(np.float32)                       # rounded, as the conversion on the device
+        c0, c1 = np.float32(-0.693147180559945309) * np.float32(2.0 ** -23), np.float32(159.0) * np.float32(0.693147180559945309) + np.float32(1.0e-3)
+        ub = (b.astype(np.float64) * float(c0) + float(c1)).astype(np.float32)          # one rounding: the fused operation
+        g = oracle.gumbel_of_words(x)
+        assert (ub.astype(np.float64) >= g.astype(np.float64) + 5e-4).all()             # half the slack is still unused
+        tail = -np.log(v.astype(np.float64) * 2.0 ** -32)
+        assert (ub.astype(np.float64) - tail).max() < 0.0861 * np.log(2.0) + 1.1e-3
+
+
 def test_top_k(oracle):
     """k = 1 is the greedy step; k at least the size of the allowed set changes nothing; the drawn
     tokens never fall below the cut, tokens tied with the k-th are kept, and among the kept tokens
