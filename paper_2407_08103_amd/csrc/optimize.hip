@@ -119,22 +119,57 @@ verify_classes_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, const
 
 // New row c = row first_row[c] of the old table with its entries renamed by `map` (-1 for a state
 // that was dropped); allowed words from the new entries.
-__global__ void __launch_bounds__(kThreads)
-compact_rows_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, int64_t row_words,
+//
+// A workgroup of a grid that fills the chip takes rows in turn and keeps the map in LDS where it fits (LDS_MAP; 16,384
+// states: 64 KB): looked up in memory, the 64 lanes' scattered entries cost a compute unit more than two cycles each.
+// A wavefront renames kRenameChunks * 64 tokens at a time, so that as many loads are in flight, and writes their allowed
+// words side by side.
+//
+// Bound by the memory: 4,245 rows of 128,256 tokens are 2.2 GB read and 2.2 GB written: 1,570 us with a workgroup per 256
+// entries and the map in memory (2.1 million workgroups, whose launch alone takes a millisecond), 890 us so.
+constexpr int kRenameThreads = 512;
+constexpr int kRenameChunks = 8;
+constexpr size_t kMapLdsBytes = 64 * 1024;
+
+template <bool LDS_MAP>
+__global__ void __launch_bounds__(kRenameThreads)
+compact_rows_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, int64_t row_words, int64_t n_new, int32_t n_old,
                     const int32_t* __restrict__ first_row, const int32_t* __restrict__ map,
                     int32_t* __restrict__ out_delta, uint32_t* __restrict__ out_allow)
 {
-    const int t = blockIdx.x * kThreads + threadIdx.x;
-    int v = TDFA_DEAD;
-    if (t < n_tokens) {
-        const int32_t old = delta[(size_t)first_row[blockIdx.y] * n_tokens + t];
-        v = old >= 0 ? map[old] : TDFA_DEAD;
-        out_delta[(size_t)blockIdx.y * n_tokens + t] = v;
+    extern __shared__ int32_t s_map[];
+    if constexpr (LDS_MAP) {
+        for (int i = threadIdx.x; i < n_old; i += kRenameThreads) s_map[i] = map[i];
+        __syncthreads();
     }
-    const uint64_t m = __builtin_amdgcn_ballot_w64(v != TDFA_DEAD);
     const int lane = threadIdx.x & 63;
-    const int64_t word = (int64_t)((t - lane) >> 5) + lane;
-    if (lane < 2 && word < row_words) out_allow[(size_t)blockIdx.y * row_words + word] = lane ? (uint32_t)(m >> 32) : (uint32_t)m;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    constexpr int kSpan = kRenameChunks * 64;
+    for (int64_t c = blockIdx.x; c < n_new; c += gridDim.x) {
+        const int32_t* row = delta + (size_t)first_row[c] * n_tokens;
+        int32_t* out = out_delta + (size_t)c * n_tokens;
+        for (int64_t t0 = (int64_t)wave * kSpan; t0 < row_words * 32; t0 += kRenameThreads / 64 * kSpan) {
+            int32_t v[kRenameChunks];
+#pragma unroll
+            for (int u = 0; u < kRenameChunks; ++u) {
+                const int64_t t = t0 + u * 64 + lane;
+                v[u] = t < n_tokens ? __builtin_nontemporal_load(row + t) : TDFA_DEAD;
+            }
+            uint32_t word = 0;                                     // lanes 2 u, 2 u + 1: the allowed words of chunk u
+#pragma unroll
+            for (int u = 0; u < kRenameChunks; ++u) {
+                const int64_t t = t0 + u * 64 + lane;
+                if (v[u] >= 0) v[u] = LDS_MAP ? s_map[v[u]] : map[v[u]];
+                else v[u] = TDFA_DEAD;
+                if (t < n_tokens) __builtin_nontemporal_store(v[u], out + t);
+                const uint64_t m = __builtin_amdgcn_ballot_w64(v[u] != TDFA_DEAD);
+                if (lane == 2 * u) word = (uint32_t)m;
+                if (lane == 2 * u + 1) word = (uint32_t)(m >> 32);
+            }
+            const int64_t wi = (t0 >> 5) + lane;
+            if (lane < 2 * kRenameChunks && wi < row_words) out_allow[(size_t)c * row_words + wi] = word;
+        }
+    }
 }
 
 struct DeviceBuffers {
@@ -165,9 +200,14 @@ constexpr int kSlots = 4096;           // its table of targets in LDS (open addr
 constexpr int kMaxTargets = 3072;      // more distinct targets in one row: the dense path
 constexpr int kLoadsAhead = 8;
 
+// w(t), odd: three products of 32 bits, each half of the one before folded into the next (a dozen instructions; the
+// pass below is bound by them, and mix64 takes three times as many).
 __device__ __forceinline__ unsigned long long token_weight(unsigned long long seed, int t)
 {
-    return mix64(seed + (unsigned long long)t * 0x9E3779B97F4A7C15ull) | 1ull;
+    const unsigned long long p = (unsigned long long)((uint32_t)t ^ (uint32_t)seed) * 0x9E3779B1u + seed;
+    const unsigned long long r = (unsigned long long)((uint32_t)p ^ (uint32_t)(p >> 32)) * 0x85EBCA77u + p;
+    const unsigned long long u = (unsigned long long)((uint32_t)r ^ (uint32_t)(r >> 32)) * 0xC2B2AE3Du;
+    return (((unsigned long long)((uint32_t)(u >> 32) ^ (uint32_t)r) << 32) | ((uint32_t)u ^ (uint32_t)(r >> 32))) | 1ull;
 }
 
 __device__ __forceinline__ void add_target(int32_t* key, unsigned long long* sum, int* n_used, int32_t v, unsigned long long w)
@@ -226,6 +266,7 @@ row_targets_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, unsigned
         }
 #pragma unroll
         for (int u = 0; u < kLoadsAhead; ++u) {
+            if (__builtin_amdgcn_ballot_w64(v[u] >= 0 || last >= 0) == 0) continue;       // no edge here, none waiting
             if (v[u] != last) {             // runs of one target (a state that mostly loops) cost one update
                 if (last >= 0) add_target(key, sum, &n_used, last, acc);
                 last = v[u];
@@ -693,12 +734,17 @@ int launch_compact_rows(const int32_t* delta, int32_t n_tokens, int64_t row_word
     TDFA_HIP(hipMalloc(&d.aux, map.size() * 4));
     TDFA_HIP(hipMemcpyAsync(d.rows, first_rows.data(), first_rows.size() * 4, hipMemcpyHostToDevice, s));
     TDFA_HIP(hipMemcpyAsync(d.aux, map.data(), map.size() * 4, hipMemcpyHostToDevice, s));
-    const unsigned bx = (unsigned)((row_words * 32 + kThreads - 1) / kThreads);
-    for (size_t lo = 0; lo < first_rows.size(); lo += kMaxGridY) {
-        compact_rows_kernel<<<dim3(bx, (unsigned)std::min(kMaxGridY, first_rows.size() - lo)), kThreads, 0, s>>>(
-            delta, n_tokens, row_words, d.rows + lo, d.aux, out_delta + lo * (size_t)n_tokens, out_allow + lo * (size_t)row_words);
-        TDFA_HIP(hipGetLastError());
-    }
+    // four workgroups of eight wavefronts per compute unit (two where the map is at its largest)
+    const int64_t n_new = (int64_t)first_rows.size();
+    const size_t lds = map.size() * 4;
+    const unsigned grid = (unsigned)std::min<int64_t>(n_new, 256 * 4);
+    if (lds <= kMapLdsBytes)
+        compact_rows_kernel<true><<<grid, kRenameThreads, lds, s>>>(delta, n_tokens, row_words, n_new, (int32_t)map.size(), d.rows, d.aux,
+                                                                    out_delta, out_allow);
+    else
+        compact_rows_kernel<false><<<grid, kRenameThreads, 0, s>>>(delta, n_tokens, row_words, n_new, (int32_t)map.size(), d.rows, d.aux,
+                                                                   out_delta, out_allow);
+    TDFA_HIP(hipGetLastError());
     TDFA_HIP(hipStreamSynchronize(s));
     return TDFA_OK;
 }

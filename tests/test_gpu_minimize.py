@@ -69,6 +69,21 @@ def test_random_tables(T, oracle, seed):
     _check(T, oracle, _upload_table(T, table_np), table_np, accept, starts)
 
 
+@pytest.mark.parametrize("n,v", [(50, 63), (50, 511), (50, 513), (50, 4097), (16384, 67), (16385, 67)])
+def test_edges_of_the_renaming(T, oracle, n, v):
+    """Around the tokens that a wavefront and a workgroup rename at a time, and the number of states up to which the
+    map of names is kept in LDS; half of the states copies of others, so that names change."""
+    rng = np.random.default_rng(n + v)
+    half = n // 2
+    table_np = rng.integers(0, n, size=(n, v), dtype=np.int32)
+    table_np[rng.random((n, v)) < 0.5] = DEAD
+    table_np[half:2 * half] = table_np[:half]
+    accept = (rng.random(n) < 0.3).astype(np.uint8)
+    accept[half:2 * half] = accept[:half]
+    new, want, _ = _check(T, oracle, _upload_table(T, table_np), table_np, accept, [0, n - 1])
+    assert 0 < new.n_rows <= n - half
+
+
 def _most_targets(table_np):
     return max(len(np.unique(r[r >= 0])) for r in table_np)
 

@@ -224,3 +224,16 @@ def test_c3_full_size(T, oracle):
     torch.cuda.synchronize()
     assert torch.equal(hs[0], hs[1]) and torch.equal(ht[0], ht[1])
     assert len(torch.unique(hs[0])) > 50
+
+
+@pytest.mark.parametrize("n_tokens", [1, 63, 64, 65, 1023, 1025, 8191, 8193, 16385])
+def test_edges_of_the_packing_spans(T, oracle, n_tokens):
+    """Around the 1,024 tokens that a wavefront packs at a time and the 8 of them in a workgroup: rows that are full,
+    empty, or have an edge only on the last token or in every other block.  Exact integers."""
+    rng = np.random.default_rng(n_tokens)
+    tab = rng.integers(0, 6, size=(6, n_tokens), dtype=np.int32)
+    tab[1] = DEAD
+    tab[2, :-1] = DEAD
+    tab[3, (np.arange(n_tokens) // 64) % 2 == 0] = DEAD
+    tab[4, rng.random(n_tokens) < 0.97] = DEAD
+    _check_pack(T, oracle, _upload_table(T, tab), tab)
