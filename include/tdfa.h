@@ -139,6 +139,9 @@ TDFA_API int tdfa_dfa_compile_path(tdfa_dfa *dfa, int path);
 /* The four large workspace arrays of TDFA_PATH_PAIRS are kept when their automaton is destroyed (at
  * most eight blocks per process, the oldest freed first) and handed to the next automaton that needs
  * blocks of about their size: allocating them anew costs as much as a tenth of such a compile.
+ * The device memory of destroyed automata and of destroyed tables that tdfa_table_minimize or
+ * tdfa_table_pack made, and the workspace of those two calls, are kept likewise (at most 12 GiB and 256
+ * blocks per process together, the oldest freed first).
  * tdfa_trim() gives the kept blocks back to the device.  Errors: none. */
 TDFA_API int tdfa_trim(void);
 

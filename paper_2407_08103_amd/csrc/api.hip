@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <cstdint>
+#include <initializer_list>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -87,6 +88,9 @@ struct tdfa_table {
     int64_t* row_begin = nullptr;
     uint32_t* dir = nullptr;
     int64_t n_edges = 0;
+    // memory of this table that goes back to the library's cache (tables of tdfa_table_minimize and tdfa_table_pack)
+    std::vector<tdfa::DeviceBlock> blocks;
+    int device = 0;
 };
 
 namespace tdfa {
@@ -144,20 +148,32 @@ int device_alloc(T** p, size_t count)
 
 int static_scratch(void** out);
 
-// Device memory of automaton handles is kept for the next handle instead of going back to the runtime:
-// hipFree waits for all work on the device, and a caller that prepares its next constraint while the GPU
-// still decodes under the last one would stall on every destroyed automaton.  A block carries the event
-// recorded behind the last launches that used it and is handed out again only when that has completed.
+// Device memory of automaton handles, and of the set-up calls that make tables of their own (minimise, pack), is kept
+// for the next one instead of going back to the runtime.  hipFree waits for all work on the device, and a caller that
+// prepares its next constraint while the GPU still decodes under the last one would stall on every destroyed automaton;
+// and memory that goes back to the driver is cleared before it is handed out again, at some 40 GB/s: once a program
+// has passed all of the card's memory through such calls, every gigabyte it allocates takes 25 ms (minimising and
+// packing a table of 5,387 x 128,256: 8 ms the first eighty times, 82 ms from then on).
+//
+// A block is handed out again when the GPU is done with it: when the event recorded behind the last launches that
+// used it has completed, or, where no event can tell (`wait_device`: a table may have been read on any stream), after
+// a wait for the device in the call that takes it.  Only calls that wait for the device anyway take such blocks.
+// Bounded: kCacheMaxBytes and kCacheMaxBlocks, the oldest go first; given back by tdfa_trim and when an allocation
+// of the library fails.
 struct CachedBlock {
     void* ptr;
     size_t bytes;
     int device;
     std::shared_ptr<UseEvent> used;
+    bool wait_device;
+    uint64_t seq;                              // order in which blocks came
 };
 std::mutex g_cache_mutex;
 std::vector<CachedBlock> g_cache;              // free blocks, oldest first
 size_t g_cache_bytes = 0;
-constexpr size_t kCacheMaxBytes = (size_t)4 << 30, kCacheMaxBlocks = 256;
+uint64_t g_cache_seq = 0;
+constexpr size_t kCacheMaxBytes = (size_t)12 << 30, kCacheMaxBlocks = 256;
+constexpr size_t kCacheSmall = (size_t)2 << 30;   // with fewer bytes behind events a call allocates rather than waits for one
 
 bool use_completed(const std::shared_ptr<UseEvent>& used)
 {
@@ -167,40 +183,78 @@ bool use_completed(const std::shared_ptr<UseEvent>& used)
     return e == hipSuccess;
 }
 
-int cache_alloc(void** out, size_t bytes)
+void cache_put(const CachedBlock& block)
+{
+    std::vector<void*> to_free;
+    try {
+        std::lock_guard<std::mutex> lock(g_cache_mutex);
+        to_free.reserve(g_cache.size() + 1);
+        g_cache.push_back(block);
+        g_cache.back().seq = ++g_cache_seq;
+        g_cache_bytes += block.bytes;
+        while (g_cache.size() > kCacheMaxBlocks || g_cache_bytes > kCacheMaxBytes) {
+            to_free.push_back(g_cache.front().ptr);
+            g_cache_bytes -= g_cache.front().bytes;
+            g_cache.erase(g_cache.begin());
+        }
+    } catch (const std::bad_alloc&) {                  // no room to note it: back to the runtime
+        (void)hipFree(block.ptr);
+    }
+    for (void* q : to_free) (void)hipFree(q);          // (waits for the device: whatever used the block is done)
+}
+
+// *bytes: the size wanted, and on return the block's own.  `may_wait`: the call may wait for the device.
+int cache_alloc(void** out, size_t* bytes, bool may_wait)
 {
     *out = nullptr;
-    if (!bytes) bytes = 1;
+    if (!*bytes) *bytes = 1;
+    const size_t want = *bytes;
     int dev = 0;
     TDFA_HIP(hipGetDevice(&dev));
-    std::shared_ptr<UseEvent> wait_for;
+    CachedBlock got{};
+    bool must_wait = false;
+    uint64_t until = 0;
     {
         std::lock_guard<std::mutex> lock(g_cache_mutex);
-        size_t busy = g_cache.size();
+        const size_t none = g_cache.size();
+        size_t best = none, busy = none, with_event = 0;
         for (size_t i = 0; i < g_cache.size(); ++i) {
-            CachedBlock& b = g_cache[i];
-            if (b.device != dev || b.bytes < bytes || b.bytes > 2 * bytes + ((size_t)64 << 10)) continue;
-            if (use_completed(b.used)) {
-                *out = b.ptr;
-                g_cache_bytes -= b.bytes;
-                g_cache.erase(g_cache.begin() + (long)i);
-                return TDFA_OK;
+            const CachedBlock& b = g_cache[i];
+            if (b.used) with_event += b.bytes;
+            if (b.device != dev || b.bytes < want || b.bytes > 2 * want + ((size_t)64 << 10)) continue;
+            if (b.wait_device && !may_wait) continue;
+            if (!use_completed(b.used)) {
+                if (busy == none) busy = i;
+            } else if (best == none || b.bytes < g_cache[best].bytes) {
+                best = i;
             }
-            if (busy == g_cache.size()) busy = i;
         }
-        // every fitting block is still in use: a new one while the cache is small, else wait for the oldest
-        if (busy != g_cache.size() && g_cache_bytes > kCacheMaxBytes / 2) {
-            *out = g_cache[busy].ptr;
-            wait_for = g_cache[busy].used;
-            g_cache_bytes -= g_cache[busy].bytes;
-            g_cache.erase(g_cache.begin() + (long)busy);
+        // every fitting block is still in use: a new one while there are few such, else wait for the oldest
+        if (best == none && busy != none && with_event > kCacheSmall) best = busy;
+        if (best != none) {
+            got = g_cache[best];
+            must_wait = got.wait_device;
+            until = g_cache_seq;
+            g_cache_bytes -= got.bytes;
+            g_cache.erase(g_cache.begin() + (long)best);
         }
     }
-    if (*out) {
-        TDFA_HIP(hipEventSynchronize(wait_for->ev));
-        return TDFA_OK;
+    if (!got.ptr) return device_malloc(out, want);
+    hipError_t e = hipSuccess;
+    if (must_wait) e = hipDeviceSynchronize();
+    else if (got.used && got.used->ev) e = hipEventSynchronize(got.used->ev);
+    if (e != hipSuccess) {                             // (a capture is under way, say): the block stays where it was
+        cache_put(got);
+        return fail(TDFA_E_DEVICE, "waiting for a block of device memory: %s", hipGetErrorString(e));
     }
-    return device_malloc(out, bytes);
+    if (must_wait) {                                   // what was in the cache before the wait is idle now
+        std::lock_guard<std::mutex> lock(g_cache_mutex);
+        for (CachedBlock& b : g_cache)
+            if (b.device == dev && b.seq <= until) b.wait_device = false;
+    }
+    *out = got.ptr;
+    *bytes = got.bytes;
+    return TDFA_OK;
 }
 
 // The block goes to the cache; `used` (may be empty) tells when the GPU is done with it.
@@ -209,18 +263,7 @@ void cache_free(void* p, size_t bytes, const std::shared_ptr<UseEvent>& used)
     if (!p) return;
     int dev = 0;
     (void)hipGetDevice(&dev);
-    std::vector<void*> to_free;
-    {
-        std::lock_guard<std::mutex> lock(g_cache_mutex);
-        g_cache.push_back(CachedBlock{p, bytes, dev, used});
-        g_cache_bytes += bytes;
-        while (g_cache.size() > kCacheMaxBlocks || g_cache_bytes > kCacheMaxBytes) {
-            to_free.push_back(g_cache.front().ptr);
-            g_cache_bytes -= g_cache.front().bytes;
-            g_cache.erase(g_cache.begin());
-        }
-    }
-    for (void* q : to_free) (void)hipFree(q);          // (waits for the device: whatever used the block is done)
+    cache_put(CachedBlock{p, bytes, dev, used, false, 0});
 }
 
 void cache_trim()
@@ -240,8 +283,8 @@ template <typename T>
 int dfa_alloc(const tdfa_dfa* d, T** p, size_t count)
 {
     void* v = nullptr;
-    const size_t bytes = (count ? count : 1) * sizeof(T);
-    const int rc = cache_alloc(&v, bytes);
+    size_t bytes = (count ? count : 1) * sizeof(T);
+    const int rc = cache_alloc(&v, &bytes, false);
     *p = static_cast<T*>(v);
     if (rc == TDFA_OK) d->cached.emplace_back(v, bytes);
     return rc;
@@ -388,6 +431,17 @@ int ensure_scratch(int32_t batch, hipStream_t stream, DeviceScratch* out)
 constexpr int32_t kStaticMaxBatch = 4096;
 constexpr size_t kStaticScratchBytes = (size_t)kStaticMaxBatch * (sizeof(unsigned long long) + sizeof(unsigned int));
 }  // namespace
+
+int block_alloc(DeviceBlock* out, size_t bytes)
+{
+    out->bytes = bytes;
+    return cache_alloc(&out->ptr, &out->bytes, true);
+}
+
+void block_free(const DeviceBlock& block, int device)
+{
+    if (block.ptr) cache_put(CachedBlock{block.ptr, block.bytes, device, nullptr, true, 0});
+}
 
 int step_scratch(int32_t batch, hipStream_t stream, unsigned long long** best, unsigned int** count)
 {
@@ -1279,9 +1333,7 @@ int tdfa_table_destroy(tdfa_table* t)
     tdfa::pool_release(t->row_allowed);
     if (t->own_delta && t->delta) (void)hipFree(t->delta);
     if (t->own_allow && t->allow) (void)hipFree(t->allow);
-    if (t->targets) (void)hipFree(t->targets);
-    if (t->row_begin) (void)hipFree(t->row_begin);
-    if (t->dir) (void)hipFree(t->dir);
+    for (const tdfa::DeviceBlock& b : t->blocks) tdfa::block_free(b, t->device);
     delete t;
     return TDFA_OK;
 }
@@ -1500,6 +1552,20 @@ int tdfa_table_apply_terminals(tdfa_table* table, int32_t n_edges, const int32_t
     return rc;
 }
 
+namespace {
+// The table owns the blocks from here on (false: it could not note them, and does not).
+bool keep_blocks(tdfa_table* t, int device, std::initializer_list<DeviceBlock> blocks)
+{
+    try {
+        t->blocks.insert(t->blocks.end(), blocks);
+    } catch (const std::bad_alloc&) {
+        return false;
+    }
+    t->device = device;
+    return true;
+}
+}  // namespace
+
 int tdfa_table_minimize(const tdfa_table* table, const uint8_t* accept_host, const int32_t* start_states_host,
                         int32_t n_starts, void* stream, tdfa_table** out, int32_t* state_map_host, uint8_t* accept_out_host)
 {
@@ -1525,8 +1591,20 @@ int tdfa_table_minimize(const tdfa_table* table, const uint8_t* accept_host, con
     }
     if (rc != TDFA_OK) return rc;
     tdfa_table* t = nullptr;
-    rc = make_table((int64_t)first_rows.size(), table->n_tokens, nullptr, nullptr, &t);
-    if (rc != TDFA_OK) return rc;
+    int dev = 0;
+    TDFA_HIP(hipGetDevice(&dev));
+    DeviceBlock delta, allow;
+    rc = block_alloc(&delta, first_rows.size() * (size_t)table->n_tokens * sizeof(int32_t));
+    if (rc == TDFA_OK) rc = block_alloc(&allow, first_rows.size() * (size_t)table->row_words * sizeof(uint32_t));
+    if (rc == TDFA_OK)
+        rc = make_table((int64_t)first_rows.size(), table->n_tokens, static_cast<int32_t*>(delta.ptr), static_cast<uint32_t*>(allow.ptr), &t);
+    if (rc != TDFA_OK || !keep_blocks(t, dev, {delta, allow})) {
+        block_free(delta, dev);
+        block_free(allow, dev);
+        if (rc != TDFA_OK) return rc;
+        tdfa_table_destroy(t);
+        return fail(TDFA_E_OOM, "host allocation failed");
+    }
     rc = launch_compact_rows(table->delta, table->n_tokens, table->row_words, first_rows, map, t->delta, t->allow, s);
     if (rc == TDFA_OK) rc = count_rows(t, s);
     if (rc != TDFA_OK) {
@@ -1569,16 +1647,27 @@ int tdfa_table_pack(const tdfa_table* table, void* stream, tdfa_table** out)
     t->n_rows = table->n_rows;
     t->n_tokens = table->n_tokens;
     t->row_words = table->row_words;
-    int rc = device_alloc(&t->allow, (size_t)t->n_rows * (size_t)t->row_words);
-    t->own_allow = rc == TDFA_OK;
+    int dev = 0;
+    DeviceBlock allow, dir, row_begin, targets;
+    int rc = hipGetDevice(&dev) == hipSuccess ? TDFA_OK : fail(TDFA_E_DEVICE, "no current device");
+    if (rc == TDFA_OK) rc = block_alloc(&allow, (size_t)t->n_rows * (size_t)t->row_words * sizeof(uint32_t));
+    if (rc == TDFA_OK) t->allow = static_cast<uint32_t*>(allow.ptr);
     if (rc == TDFA_OK && t->n_rows > 0 && t->row_words > 0) {
         hipError_t e = hipMemcpyAsync(t->allow, table->allow, (size_t)t->n_rows * (size_t)t->row_words * sizeof(uint32_t),
                                       hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) rc = fail(TDFA_E_DEVICE, "copy of the allowed bits: %s", hipGetErrorString(e));
     }
     if (rc == TDFA_OK)
-        rc = pack_table(table->delta, table->allow, t->n_rows, t->n_tokens, t->row_words, s, &t->dir, &t->row_begin,
-                        &t->targets, &t->n_edges);
+        rc = pack_table(table->delta, table->allow, t->n_rows, t->n_tokens, t->row_words, s, &dir, &row_begin, &targets, &t->n_edges);
+    if (rc == TDFA_OK && !keep_blocks(t, dev, {allow, dir, row_begin, targets})) rc = fail(TDFA_E_OOM, "host allocation failed");
+    if (rc == TDFA_OK) {
+        t->dir = static_cast<uint32_t*>(dir.ptr);
+        t->row_begin = static_cast<int64_t*>(row_begin.ptr);
+        t->targets = static_cast<int32_t*>(targets.ptr);
+    } else {
+        for (const DeviceBlock& b : {allow, dir, row_begin, targets}) block_free(b, dev);
+        t->allow = nullptr;
+    }
     if (rc != TDFA_OK) {
         (void)hipStreamSynchronize(s);
         tdfa_table_destroy(t);

@@ -174,18 +174,41 @@ compact_rows_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, int64_t
 
 struct DeviceBuffers {
     int32_t* rows = nullptr;
-    int32_t* aux = nullptr;       // first_of / map
+    int32_t* aux = nullptr;       // first_of
     int32_t* cls = nullptr;
     uint8_t* mark = nullptr;
     uint8_t* good = nullptr;
     unsigned long long* hash = nullptr;
     int32_t* flag = nullptr;
-    ~DeviceBuffers()
+};
+
+// Device memory of one call, given back to the library's cache when it ends.
+struct Arena {
+    std::vector<DeviceBlock> blocks;
+    template <class T>
+    int get(T** p, size_t n)
     {
-        for (void* p : {(void*)rows, (void*)aux, (void*)cls, (void*)mark, (void*)good, (void*)hash, (void*)flag})
-            if (p) (void)hipFree(p);
+        try {
+            blocks.emplace_back();
+        } catch (const std::bad_alloc&) {
+            return fail(TDFA_E_OOM, "host allocation failed");
+        }
+        const int rc = block_alloc(&blocks.back(), std::max<size_t>(n, 1) * sizeof(T));
+        *p = static_cast<T*>(blocks.back().ptr);
+        return rc;
+    }
+    ~Arena()
+    {
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        for (const DeviceBlock& b : blocks) block_free(b, dev);
     }
 };
+#define TDFA_GET(expr)                                                                            \
+    do {                                                                                          \
+        const int rc_ = (expr);                                                                   \
+        if (rc_ != TDFA_OK) return rc_;                                                           \
+    } while (0)
 
 constexpr size_t kMaxGridY = 65535;
 
@@ -422,13 +445,14 @@ int minimize_dense(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
                    int32_t n_starts, hipStream_t s, std::vector<int32_t>* first_rows, std::vector<int32_t>* map_out)
 {
     DeviceBuffers d;
-    TDFA_HIP(hipMalloc(&d.rows, (size_t)n_rows * 4));
-    TDFA_HIP(hipMalloc(&d.aux, (size_t)n_rows * 4));
-    TDFA_HIP(hipMalloc(&d.cls, (size_t)n_rows * 4));
-    TDFA_HIP(hipMalloc(&d.mark, (size_t)n_rows));
-    TDFA_HIP(hipMalloc(&d.good, (size_t)n_rows));
-    TDFA_HIP(hipMalloc(&d.hash, (size_t)n_rows * 8));
-    TDFA_HIP(hipMalloc(&d.flag, 4));
+    Arena mem;
+    TDFA_GET(mem.get(&d.rows, (size_t)n_rows));
+    TDFA_GET(mem.get(&d.aux, (size_t)n_rows));
+    TDFA_GET(mem.get(&d.cls, (size_t)n_rows));
+    TDFA_GET(mem.get(&d.mark, (size_t)n_rows));
+    TDFA_GET(mem.get(&d.good, (size_t)n_rows));
+    TDFA_GET(mem.get(&d.hash, (size_t)n_rows));
+    TDFA_GET(mem.get(&d.flag, 1));
     std::vector<uint8_t> mark((size_t)n_rows, 0), good((size_t)n_rows, 0), seen((size_t)n_rows, 0);
     std::vector<int32_t> rows;
     const unsigned gx = grid_x(n_tokens);
@@ -558,24 +582,6 @@ int minimize_dense(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
     return TDFA_OK;
 }
 
-// Device memory of one call, freed when it ends.
-struct Arena {
-    std::vector<void*> blocks;
-    template <class T>
-    hipError_t get(T** p, size_t n)
-    {
-        void* v = nullptr;
-        const hipError_t e = hipMalloc(&v, std::max<size_t>(n, 1) * sizeof(T));
-        if (e == hipSuccess) blocks.push_back(v);
-        *p = static_cast<T*>(v);
-        return e;
-    }
-    ~Arena()
-    {
-        for (void* b : blocks) (void)hipFree(b);
-    }
-};
-
 constexpr int kNotSparse = -1000;       // minimize_lists: take the dense path
 
 // The sparse path.  Returns kNotSparse when a row has too many distinct targets or the final
@@ -591,27 +597,27 @@ int minimize_lists(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
     uint8_t *mark, *aux, *good, *accept_dev;
     uint32_t ht_size = 1024;
     while (ht_size < 2u * (uint32_t)n_rows && ht_size < 0x80000000u) ht_size <<= 1;
-    TDFA_HIP(mem.get(&counter, 1));
-    TDFA_HIP(mem.get(&row_begin, n_rows));
-    TDFA_HIP(mem.get(&row_n, n_rows));
-    TDFA_HIP(mem.get(&flags, 2));                  // [0] too many targets / changed / mismatch, [1] classes
-    TDFA_HIP(mem.get(&key, n_rows));
-    TDFA_HIP(mem.get(&ht_key, ht_size));
-    TDFA_HIP(mem.get(&ht_min, ht_size));
-    TDFA_HIP(mem.get(&slot_of, n_rows));
-    TDFA_HIP(mem.get(&cls_a, n_rows));
-    TDFA_HIP(mem.get(&cls_b, n_rows));
-    TDFA_HIP(mem.get(&mark, n_rows));
-    TDFA_HIP(mem.get(&aux, n_rows));
-    TDFA_HIP(mem.get(&good, n_rows));
-    TDFA_HIP(mem.get(&accept_dev, n_rows));
+    TDFA_GET(mem.get(&counter, 1));
+    TDFA_GET(mem.get(&row_begin, n_rows));
+    TDFA_GET(mem.get(&row_n, n_rows));
+    TDFA_GET(mem.get(&flags, 2));                  // [0] too many targets / changed / mismatch, [1] classes
+    TDFA_GET(mem.get(&key, n_rows));
+    TDFA_GET(mem.get(&ht_key, ht_size));
+    TDFA_GET(mem.get(&ht_min, ht_size));
+    TDFA_GET(mem.get(&slot_of, n_rows));
+    TDFA_GET(mem.get(&cls_a, n_rows));
+    TDFA_GET(mem.get(&cls_b, n_rows));
+    TDFA_GET(mem.get(&mark, n_rows));
+    TDFA_GET(mem.get(&aux, n_rows));
+    TDFA_GET(mem.get(&good, n_rows));
+    TDFA_GET(mem.get(&accept_dev, n_rows));
     int32_t flag = 0;
 
     // ---- the lists: one pass over the table (a second one when they need more room than guessed)
     unsigned long long e_cap = std::max<unsigned long long>(1u << 20, std::min<unsigned long long>((unsigned long long)n_rows * 512, 1ull << 26));
     for (int attempt = 0;; ++attempt) {
-        TDFA_HIP(mem.get(&e_target, e_cap));
-        TDFA_HIP(mem.get(&e_weight, e_cap));
+        TDFA_GET(mem.get(&e_target, e_cap));
+        TDFA_GET(mem.get(&e_weight, e_cap));
         TDFA_HIP(hipMemsetAsync(counter, 0, 8, s));
         TDFA_HIP(hipMemsetAsync(flags, 0, 8, s));
         row_targets_kernel<<<(unsigned)n_rows, kListThreads, 0, s>>>(delta, n_tokens, seed, e_cap, counter, row_begin, row_n, e_target,
@@ -685,8 +691,8 @@ int minimize_lists(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
         with.push_back(c);
     }
     if (!joined.empty() && n_tokens > 0) {
-        TDFA_HIP(mem.get(&rows_dev, joined.size()));
-        TDFA_HIP(mem.get(&first_dev, joined.size()));
+        TDFA_GET(mem.get(&rows_dev, joined.size()));
+        TDFA_GET(mem.get(&first_dev, joined.size()));
         TDFA_HIP(hipMemcpyAsync(rows_dev, joined.data(), joined.size() * 4, hipMemcpyHostToDevice, s));
         TDFA_HIP(hipMemcpyAsync(first_dev, with.data(), with.size() * 4, hipMemcpyHostToDevice, s));
         TDFA_HIP(hipMemsetAsync(flags, 0, 4, s));
@@ -729,20 +735,21 @@ int launch_compact_rows(const int32_t* delta, int32_t n_tokens, int64_t row_word
                         const std::vector<int32_t>& map, int32_t* out_delta, uint32_t* out_allow, hipStream_t s)
 {
     if (first_rows.empty()) return TDFA_OK;
-    DeviceBuffers d;
-    TDFA_HIP(hipMalloc(&d.rows, first_rows.size() * 4));
-    TDFA_HIP(hipMalloc(&d.aux, map.size() * 4));
-    TDFA_HIP(hipMemcpyAsync(d.rows, first_rows.data(), first_rows.size() * 4, hipMemcpyHostToDevice, s));
-    TDFA_HIP(hipMemcpyAsync(d.aux, map.data(), map.size() * 4, hipMemcpyHostToDevice, s));
+    Arena mem;
+    int32_t *rows = nullptr, *map_dev = nullptr;
+    TDFA_GET(mem.get(&rows, first_rows.size()));
+    TDFA_GET(mem.get(&map_dev, map.size()));
+    TDFA_HIP(hipMemcpyAsync(rows, first_rows.data(), first_rows.size() * 4, hipMemcpyHostToDevice, s));
+    TDFA_HIP(hipMemcpyAsync(map_dev, map.data(), map.size() * 4, hipMemcpyHostToDevice, s));
     // four workgroups of eight wavefronts per compute unit (two where the map is at its largest)
     const int64_t n_new = (int64_t)first_rows.size();
     const size_t lds = map.size() * 4;
     const unsigned grid = (unsigned)std::min<int64_t>(n_new, 256 * 4);
     if (lds <= kMapLdsBytes)
-        compact_rows_kernel<true><<<grid, kRenameThreads, lds, s>>>(delta, n_tokens, row_words, n_new, (int32_t)map.size(), d.rows, d.aux,
+        compact_rows_kernel<true><<<grid, kRenameThreads, lds, s>>>(delta, n_tokens, row_words, n_new, (int32_t)map.size(), rows, map_dev,
                                                                     out_delta, out_allow);
     else
-        compact_rows_kernel<false><<<grid, kRenameThreads, 0, s>>>(delta, n_tokens, row_words, n_new, (int32_t)map.size(), d.rows, d.aux,
+        compact_rows_kernel<false><<<grid, kRenameThreads, 0, s>>>(delta, n_tokens, row_words, n_new, (int32_t)map.size(), rows, map_dev,
                                                                    out_delta, out_allow);
     TDFA_HIP(hipGetLastError());
     TDFA_HIP(hipStreamSynchronize(s));

@@ -143,66 +143,48 @@ int launch_row_allowed(const uint32_t* allow, int64_t n_rows, int32_t n_tokens, 
 }
 
 int pack_table(const int32_t* delta, const uint32_t* allow, int64_t n_rows, int32_t n_tokens, int64_t row_words,
-               hipStream_t stream, uint32_t** dir_out, int64_t** row_begin_out, int32_t** targets_out, int64_t* n_edges_out)
+               hipStream_t stream, DeviceBlock* dir_block, DeviceBlock* begin_block, DeviceBlock* targets_block, int64_t* n_edges_out)
 {
     const int32_t n_blocks = (int32_t)(row_words / 4);
-    uint32_t* dir = nullptr;
-    uint32_t* counts = nullptr;
-    int64_t* row_begin = nullptr;
-    int32_t* targets = nullptr;
-    auto cleanup = [&]() {
-        (void)hipFree(dir);
-        (void)hipFree(counts);
-        (void)hipFree(row_begin);
-        (void)hipFree(targets);
-    };
-#define PACK_HIP(expr)                                                                          \
-    do {                                                                                        \
-        hipError_t e_ = (expr);                                                                 \
-        if (e_ != hipSuccess) {                                                                 \
-            cleanup();                                                                          \
-            return fail(e_ == hipErrorOutOfMemory ? TDFA_E_OOM : TDFA_E_DEVICE, "%s: %s", #expr, hipGetErrorString(e_)); \
-        }                                                                                       \
-    } while (0)
     const size_t rows = (size_t)(n_rows > 0 ? n_rows : 1);
-    PACK_HIP(hipMalloc(reinterpret_cast<void**>(&dir), rows * (size_t)(n_blocks > 0 ? n_blocks : 1) * sizeof(uint32_t)));
-    PACK_HIP(hipMalloc(reinterpret_cast<void**>(&counts), rows * sizeof(uint32_t)));
-    PACK_HIP(hipMalloc(reinterpret_cast<void**>(&row_begin), (rows + 1) * sizeof(int64_t)));
+    int rc = block_alloc(dir_block, rows * (size_t)(n_blocks > 0 ? n_blocks : 1) * sizeof(uint32_t));
+    if (rc == TDFA_OK) rc = block_alloc(begin_block, (rows + 1) * sizeof(int64_t));
+    // the counts of the states share the block of row_begin until that is known: they are read before it is written
+    if (rc != TDFA_OK) return rc;
+    uint32_t* dir = static_cast<uint32_t*>(dir_block->ptr);
+    int64_t* row_begin = static_cast<int64_t*>(begin_block->ptr);
+    uint32_t* counts = static_cast<uint32_t*>(begin_block->ptr);
     std::vector<uint32_t> h_counts;
     std::vector<int64_t> h_begin;
     try {
         h_counts.resize((size_t)n_rows);
         h_begin.resize((size_t)n_rows + 1);
     } catch (const std::bad_alloc&) {
-        cleanup();
         return fail(TDFA_E_OOM, "host allocation failed");
     }
     // grids of at most 2^31 - 1 workgroups: one per state
     if (n_rows > 0) {
         pack_count_kernel<<<(unsigned)n_rows, kThreads, 0, stream>>>(allow, n_tokens, row_words, n_blocks, dir, counts);
-        PACK_HIP(hipGetLastError());
-        PACK_HIP(hipMemcpyAsync(h_counts.data(), counts, (size_t)n_rows * sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
+        TDFA_HIP(hipGetLastError());
+        TDFA_HIP(hipMemcpyAsync(h_counts.data(), counts, (size_t)n_rows * sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
     }
-    PACK_HIP(hipStreamSynchronize(stream));
+    TDFA_HIP(hipStreamSynchronize(stream));
     int64_t n_edges = 0;
     for (int64_t q = 0; q < n_rows; ++q) {
         h_begin[(size_t)q] = n_edges;
         n_edges += h_counts[(size_t)q];
     }
     h_begin[(size_t)n_rows] = n_edges;
-    PACK_HIP(hipMalloc(reinterpret_cast<void**>(&targets), (size_t)(n_edges > 0 ? n_edges : 1) * sizeof(int32_t)));
-    PACK_HIP(hipMemcpyAsync(row_begin, h_begin.data(), ((size_t)n_rows + 1) * sizeof(int64_t), hipMemcpyHostToDevice, stream));
-    if (n_rows > 0 && n_edges > 0) {
-        pack_targets_kernel<<<(unsigned)n_rows, kPackThreads, 0, stream>>>(delta, allow, n_tokens, row_words, n_blocks, dir,
-                                                                     row_begin, targets);
-        PACK_HIP(hipGetLastError());
-    }
-    PACK_HIP(hipStreamSynchronize(stream));                // h_begin is read by the copy until here
-#undef PACK_HIP
-    (void)hipFree(counts);
-    *dir_out = dir;
-    *row_begin_out = row_begin;
-    *targets_out = targets;
+    rc = block_alloc(targets_block, (size_t)(n_edges > 0 ? n_edges : 1) * sizeof(int32_t));
+    if (rc != TDFA_OK) return rc;
+    TDFA_HIP(hipMemcpyAsync(row_begin, h_begin.data(), ((size_t)n_rows + 1) * sizeof(int64_t), hipMemcpyHostToDevice, stream));
+    if (n_rows > 0 && n_edges > 0)
+        pack_targets_kernel<<<(unsigned)n_rows, kPackThreads, 0, stream>>>(delta, allow, n_tokens, row_words, n_blocks, dir, row_begin,
+                                                                         static_cast<int32_t*>(targets_block->ptr));
+    const hipError_t launched = hipGetLastError();
+    const hipError_t done = hipStreamSynchronize(stream);  // h_begin is read by the copy until here
+    TDFA_HIP(launched);
+    TDFA_HIP(done);
     *n_edges_out = n_edges;
     return TDFA_OK;
 }

@@ -59,6 +59,15 @@ __host__ __device__ inline size_t plan_jump_offset(int32_t n_order)
     return plan_live_offset(n_order) + ((size_t)(n_order + 63) / 64 * 32 + 255) / 256 * 256;
 }
 
+// Device memory of the set-up calls, from the library's cache (api.hip).  block_alloc may wait for the device;
+// block_free does not: a freed block is handed out again only after such a wait.
+struct DeviceBlock {
+    void* ptr = nullptr;
+    size_t bytes = 0;
+};
+int block_alloc(DeviceBlock* out, size_t bytes);
+void block_free(const DeviceBlock& block, int device);
+
 // The device arrays of a vocabulary handle that other translation units read (api.hip owns the handle).
 struct VocabView {
     const uint32_t* words;   // token bytes, each token padded to a multiple of 4 bytes
@@ -159,9 +168,9 @@ int launch_compact_rows(const int32_t* delta, int32_t n_tokens, int64_t row_word
 // out[q] = the tokens row q of `allow` allows (pack.hip).
 int launch_row_allowed(const uint32_t* allow, int64_t n_rows, int32_t n_tokens, int64_t row_words, uint32_t* out, hipStream_t stream);
 
-// Edge-list form of a table (pack.hip): the device arrays are allocated here and owned by the caller.
+// Edge-list form of a table (pack.hip): the device arrays are allocated here and owned by the caller, on failure too.
 int pack_table(const int32_t* delta, const uint32_t* allow, int64_t n_rows, int32_t n_tokens, int64_t row_words,
-               hipStream_t stream, uint32_t** dir_out, int64_t** row_begin_out, int32_t** targets_out, int64_t* n_edges_out);
+               hipStream_t stream, DeviceBlock* dir, DeviceBlock* row_begin, DeviceBlock* targets, int64_t* n_edges_out);
 
 struct MaskArgs {
     const int32_t* delta;               // dense rows, or NULL for a packed table: then the three arrays below.

@@ -179,6 +179,49 @@ def test_stacked_with_several_starts(T, oracle):
     _check(T, oracle, _upload_table(T, ref), ref, accept, starts)
 
 
+def test_blocks_of_a_destroyed_table_in_use_on_another_stream(T, oracle):
+    """A minimised table is destroyed while steps on another stream still read it; the next minimisations and packings
+    take blocks of its size.  The steps see the table as it was (they are enqueued before, and the block is handed
+    out only after a wait), and tdfa_trim gives the memory back."""
+    rng = np.random.default_rng(5)
+    n, v, steps, batch = 400, 40000, 24, 64
+    a_np = rng.integers(0, n, size=(n, v), dtype=np.int32)
+    b_np = rng.integers(0, n, size=(n, v), dtype=np.int32)
+    accept = np.ones(n, dtype=np.uint8)
+    accept[::2] = 0
+    a, b = _upload_table(T, a_np), _upload_table(T, b_np)
+    x = rng.normal(0, 2, size=(batch, v)).astype(np.float32)
+    lg = torch.from_numpy(x).cuda()
+    states = rng.integers(0, n, size=batch).astype(np.int32)
+    want = states.copy()
+    for _ in range(steps):
+        _, want = oracle.mask_step(a_np, x, 0, want)
+    side = torch.cuda.Stream()
+    st = torch.from_numpy(states).cuda()
+    tok = torch.empty_like(st)
+    T.trim()
+    for _ in range(3):
+        small, _, mp = T.table_minimize(a, accept, [0])
+        assert small.n_rows == n and (mp == np.arange(n)).all()       # nothing merges: the same rows under the same names
+        q = st.clone()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            for _ in range(steps):
+                T.mask_step(small, lg, q, tok, q)
+        small.close()
+        other, _, _ = T.table_minimize(b, accept, [0])
+        packed = T.table_pack(other)
+        torch.cuda.synchronize()
+        assert np.array_equal(q.cpu().numpy(), want)
+        G.check_rows(_as_torch(T, other), b_np, np.arange(n))
+        packed.close()
+        other.close()
+    torch.cuda.synchronize()
+    kept = torch.cuda.mem_get_info()[0]
+    T.trim()
+    assert torch.cuda.mem_get_info()[0] >= kept + n * v * 4
+
+
 def test_bad_arguments(T):
     table = _upload_table(T, np.zeros((2, 3), dtype=np.int32))
     with pytest.raises(T.TdfaError):
