@@ -169,6 +169,34 @@ def test_special_values_and_ties(T, oracle, dtype):
         _step_and_check(T, oracle, table, tab, lg, dtype, states, masked=False)
 
 
+@pytest.mark.parametrize("n_tokens,batch", [(1, 3), (7, 2), (4093, 5), (4096, 5), (8197, 4), (16387, 9), (33001, 200), (32775, 193)])
+def test_penalised_fp32_rows_at_the_edges(T, oracle, n_tokens, batch):
+    """fp32 rows written with the penalty, around the 1,024 and 4,096 logits that a workgroup takes per load and per
+    round, with partial groups, in place and into another buffer whose padding must stay as it was; bit for bit."""
+    tab = _rand_table(6, n_tokens, 0.4, n_tokens)
+    tab[2] = DEAD
+    tab[3] = 1
+    table = _upload_table(T, tab)
+    rng = np.random.default_rng(batch)
+    stride = (n_tokens + 3) // 4 * 4 + 8
+    x = (np.round(rng.normal(0, 2, size=(batch, stride)) * 8) / 8).astype(np.float32)
+    x[:, rng.integers(0, n_tokens, 3)] = np.nan
+    states = (np.arange(batch) % 8 - 1).astype(np.int32)
+    want = oracle.mask_step(tab, x, F32, states, row_stride=stride, want_masked=True)
+    for in_place in (False, True):
+        lg = _to_dev(x, F32)
+        out = lg if in_place else torch.full_like(lg, 7.0)
+        tok = torch.full((batch,), -9, dtype=torch.int32, device="cuda")
+        new = torch.full((batch,), -9, dtype=torch.int32, device="cuda")
+        T.mask_step(table, lg, torch.from_numpy(states).cuda(), tok, new, out)
+        torch.cuda.synchronize()
+        assert np.array_equal(tok.cpu().numpy(), want[0]) and np.array_equal(new.cpu().numpy(), want[1])
+        got = _bits(out)
+        assert np.array_equal(got[:, :n_tokens], want[2].view(np.uint32)[:, :n_tokens])
+        rest = x[:, n_tokens:].view(np.uint32) if in_place else np.full((batch, stride - n_tokens), np.float32(7.0).view(np.uint32))
+        assert np.array_equal(got[:, n_tokens:], rest)
+
+
 def test_stride_inplace_and_alias(T, oracle):
     n_tokens = 3000
     tab = _rand_table(7, n_tokens, 0.2, 2)
