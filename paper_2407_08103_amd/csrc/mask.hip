@@ -22,6 +22,7 @@
 // of eight tokens that holds it.  The packed keys do not treat NaN and -0 specially, so a row
 // whose winning key is NaN-like, not above -inf, or a zero is handed to the exact path, which the
 // last workgroup of the row runs over the whole row.
+#include "pda_device.h"
 #include "tdfa_internal.h"
 
 #include <type_traits>
@@ -499,7 +500,8 @@ __device__ __forceinline__ unsigned long long gather_scan(const typename ElemOf<
 // PDA: the step of a push-down constraint.  The allowed bits of a sequence are not one row but
 // the OR of the rows of its state's classes of edges whose pops its stack ends with; the wavefront
 // finds those classes (one per lane) before it reads its stretch of bits, and ORs the rows as it
-// reads them.  The table lookup at the end is the caller's (the traversal also moves the stack).
+// reads them.  At the end the wavefront that finishes the row traverses the chosen token's edge, which also moves
+// the stack (every workgroup of the row has read it by then).
 template <bool WRITE, int kUnroll, bool SKIP, int kBuf = 2, bool PDA = false>
 __global__ void __launch_bounds__(kMaxThreads)
 mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
@@ -591,8 +593,9 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
     }
     unsigned long long classes = 0;                   // PDA: the classes of q (bit j: row class_row0 + j) the stack matches
     int32_t class_row0 = 0;
+    int32_t depth = 0;                                // PDA: of the sequence's stack
     if constexpr (PDA) {
-        const int32_t depth = a.pda.depths[b];
+        depth = a.pda.depths[b];
         valid = q >= 0 && q < a.pda.n_states && depth >= 0 && depth <= a.pda.stack_cap;
         class_row0 = valid ? a.pda.class_first[q] : 0;
         const int n_classes = valid ? a.pda.class_first[q + 1] - class_row0 : 0;
@@ -860,14 +863,42 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
     if (lane == 0) wave_best[wave] = wmax;
     __syncthreads();
     unsigned long long cand = wave_max_u64(lane < ((int)blockDim.x >> 6) ? wave_best[lane] : 0ull);
+    auto needs_exact = [](unsigned long long c) {
+        const uint32_t ku = (uint32_t)(c >> 32) & 0xFFFFu;
+        return ku > KU_POS_INF || ku <= KU_NEG_INF || ku == KU_POS_ZERO || ku == KU_NEG_ZERO;
+    };
+    // what lane 0 has, in every lane
+    auto from_lane0 = [](unsigned long long c) {
+        return ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(c >> 32)) << 32) |
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)c);
+    };
+    // PDA, by a whole wavefront: the row's token is taken (0: none)
+    auto traverse = [&](unsigned long long c) {
+        if (c == 0) {
+            if (lane == 0) write_result(a, b, q, valid, 0ull);
+        } else {
+            pda_traverse(a.pda.edges, a.pda.stacks + (int64_t)b * a.pda.stack_cap, a.pda.depths + b, depth, a.pda.stack_cap, q,
+                         (int)(0xFFFFFFFFu - (uint32_t)c), a.tokens + b, a.new_states + b);
+        }
+    };
+    if constexpr (PDA) {
+        if (cand == 0 ? wave == 0 : wmax == cand) {            // (one wavefront: candidates differ in their tokens)
+            int last = 0;
+            if (lane == 0) last = combine_parts(a, b, parts, cand) ? 1 : 0;
+            last = __builtin_amdgcn_readfirstlane(last);
+            cand = from_lane0(cand);
+            const bool exact = last && cand != 0 && needs_exact(cand);
+            if (last && !exact) traverse(cand);
+            if (lane == 0) s_exact = exact ? 1 : 0;
+        }
+    } else {
     const bool finisher = lane == 0 && (cand == 0 ? threadIdx.x == 0 : wmax == cand);
     if (finisher) {
         int exact = 0;
         if (combine_parts(a, b, parts, cand)) {
-            const uint32_t ku = (uint32_t)(cand >> 32) & 0xFFFFu;
             if (cand == 0) {
                 write_result(a, b, q, valid, 0ull);
-            } else if (ku > KU_POS_INF || ku <= KU_NEG_INF || ku == KU_POS_ZERO || ku == KU_NEG_ZERO) {
+            } else if (needs_exact(cand)) {
                 exact = 1;
             } else {
                 const uint32_t token = 0xFFFFFFFFu - (uint32_t)cand;
@@ -880,13 +911,18 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
         }
         s_exact = exact;
     }
+    }
     __syncthreads();
     if (!s_exact) return;
     // Rare: NaN, zeros or nothing above -inf at the top of the row.  The masked row is already
     // written, so this pass only chooses the token.
     unsigned long long c = exact_scan_with<TDFA_BF16>(row, nullptr, bits_at, valid, V, 0, n_groups);
     c = block_max_u64(c, wave_best_exact);
-    if (threadIdx.x == 0) write_result(a, b, q, valid, c);
+    if constexpr (PDA) {
+        if (wave == 0) traverse(from_lane0(c));
+    } else {
+        if (threadIdx.x == 0) write_result(a, b, q, valid, c);
+    }
 }
 
 // One step on fp32 logits.  Like the 16-bit kernel, every wavefront first reads the allowed bytes of

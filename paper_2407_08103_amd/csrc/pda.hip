@@ -29,6 +29,7 @@
 #include <new>
 #include <vector>
 
+#include "pda_device.h"
 #include "tdfa_internal.h"
 
 struct tdfa_pda {
@@ -53,6 +54,8 @@ struct tdfa_ptable {
     int32_t* pops = nullptr;        // device [n_edges][TDFA_PDA_STRING], bottom to top, unused places -1
     int32_t* n_push = nullptr;
     int32_t* pushes = nullptr;
+    uint32_t* dir = nullptr;        // device [n_states][dir_stride]: edges of the state on tokens below 64 k
+    int64_t dir_stride = 0;
     // classes of edges by their pops, per state; n_class_rows == 0: none kept
     int32_t n_class_rows = 0;
     int64_t row_words = 0;          // 32-bit words per row of allowed bits
@@ -553,77 +556,33 @@ pda_allow_edges_kernel(const int32_t* __restrict__ states, const int32_t* __rest
     }
 }
 
-// After the step kernel has chosen the tokens: one wavefront per sequence finds the edge of its token
-// that the stack matches and traverses it.  The edges of a state ascend by token; the wavefront
-// narrows the range 64 probes at a time (three rounds for 25,000 edges, where a binary search by one
-// thread would make seventeen dependent reads), then its first lanes test the few edges of the token.
+// After a step that has only chosen the tokens: one wavefront per sequence traverses the edge of its token that the
+// stack matches.
 __global__ void __launch_bounds__(256)
-pda_advance_kernel(PdaStepArgs a, int32_t batch)
+pda_advance_kernel(PdaStepArgs a, PdaEdges edges, int32_t batch)
 {
-    const int lane = (int)threadIdx.x & 63;
-    const int b = (int)(blockIdx.x * 4 + (threadIdx.x >> 6));
+    const int b = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
     if (b >= batch) return;                                     // (whole wavefronts leave)
     const int32_t q = a.states[b], depth = a.depths[b], tok = a.tokens[b];
     const bool valid = q >= 0 && q < a.n_states && depth >= 0 && depth <= a.stack_cap;
     if (tok < 0 || !valid) {
-        if (lane == 0) {
+        if ((threadIdx.x & 63) == 0) {
             a.tokens[b] = TDFA_NO_TOKEN;
             a.new_states[b] = valid ? q : TDFA_DEAD;
         }
         return;
     }
-    int32_t* stack = a.stacks + (int64_t)b * a.stack_cap;
-    // lo: no edge below it has token >= tok is false ... invariant: token[i] < tok for i < lo, token[i] >= tok for i >= hi
-    int64_t lo = a.edge_first[q], hi = a.edge_first[q + 1];
-    const int64_t e_hi = hi;
-    while (hi - lo > 64) {
-        const int64_t span = hi - lo;
-        const int64_t pos = lo + (span * (lane + 1)) / 65;       // 64 probes strictly inside, ascending with the lane
-        const bool ge = a.token[pos] >= tok;
-        const unsigned long long m = __builtin_amdgcn_ballot_w64(ge);
-        const int first = m ? (int)__builtin_ctzll(m) : 64;       // the first probe that is not below tok
-        const int64_t new_hi = first < 64 ? lo + (span * (first + 1)) / 65 : hi;
-        const int64_t new_lo = first > 0 ? lo + (span * first) / 65 + 1 : lo;
-        lo = new_lo;
-        hi = new_hi;
-    }
-    {
-        const int64_t pos = lo + lane;
-        const bool ge = pos < hi && a.token[pos] >= tok;
-        const unsigned long long m = __builtin_amdgcn_ballot_w64(ge);
-        lo = m ? lo + (int64_t)__builtin_ctzll(m) : hi;
-    }
-    // the edges of the token (a few: one per pops string): lane i tests edge lo + i
-    long long e = -1;
-    for (int64_t base = lo; base < e_hi && e < 0; base += 64) {
-        const int64_t c = base + lane;
-        bool mine = c < e_hi && a.token[c] == tok;
-        const bool more = c < e_hi && a.token[c] == tok;         // (uniform exit below: edges of the token are contiguous)
-        if (mine) {
-            const int np = a.n_pops[c];
-            mine = np <= depth;
-            for (int j = 0; mine && j < np; ++j) mine = a.pops[c * kStr + j] == stack[depth - np + j];
-        }
-        const unsigned long long hit = __builtin_amdgcn_ballot_w64(mine);
-        if (hit) e = (long long)(base + (int64_t)__builtin_ctzll(hit));
-        if (__builtin_amdgcn_ballot_w64(more) != ~0ull) break;    // the token's edges end inside this batch
-    }
-    if (lane != 0) return;
-    if (e < 0) {                                                // cannot happen: the token was allowed through such an edge
-        a.tokens[b] = TDFA_NO_TOKEN;
-        a.new_states[b] = TDFA_DEAD;
-        return;
-    }
-    const int np = a.n_pops[e], nu = a.n_push[e];
-    const int m_keep = depth - np;
-    if (m_keep + nu > a.stack_cap) {                            // the stack would outgrow its buffer: the sequence ends
-        a.tokens[b] = TDFA_NO_TOKEN;
-        a.new_states[b] = TDFA_DEAD;
-        return;
-    }
-    for (int j = 0; j < nu; ++j) stack[m_keep + j] = a.pushes[e * kStr + j];
-    a.depths[b] = m_keep + nu;
-    a.new_states[b] = a.dst[e];
+    pda_traverse(edges, a.stacks + (int64_t)b * a.stack_cap, a.depths + b, depth, a.stack_cap, q, tok, a.tokens + b, a.new_states + b);
+}
+
+// dir[q][k] = edges of state q on tokens below 64 k, from the offsets of the tokens within their state.
+__global__ void __launch_bounds__(256)
+pda_dir_kernel(const uint32_t* __restrict__ offsets, const unsigned long long* __restrict__ row_total, int32_t n_tokens,
+               int64_t dir_stride, uint32_t* __restrict__ dir)
+{
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t q = blockIdx.y, t = k << kPdaDirShift;
+    if (k < dir_stride) dir[q * dir_stride + k] = t < n_tokens ? offsets[q * n_tokens + t] : (uint32_t)row_total[q];
 }
 
 template <typename T>
@@ -808,6 +767,13 @@ int tdfa_compile_token_pda(const tdfa_vocab* vocab, const tdfa_pda* pda, void* s
         EdgeOut eo{t->token, t->dst, t->n_pops, t->pops, t->n_push, t->pushes};
         pda_fill_kernel<<<grid, 256, 0, s>>>(a, v.words, v.off, v.len, v.n_tokens, counts, t->edge_first, eo, err);
         check(hipGetLastError(), "pda_fill_kernel");
+        t->dir_stride = ((int64_t)v.n_tokens >> kPdaDirShift) + 2;
+        if (rc == TDFA_OK) rc = dev_alloc(&t->dir, (size_t)pda->n_states * (size_t)t->dir_stride);
+        if (rc == TDFA_OK) {
+            pda_dir_kernel<<<dim3((unsigned)((t->dir_stride + 255) / 256), (unsigned)pda->n_states), 256, 0, s>>>(counts, row_total, v.n_tokens,
+                                                                                                                t->dir_stride, t->dir);
+            check(hipGetLastError(), "pda_dir_kernel");
+        }
         check(hipStreamSynchronize(s), "hipStreamSynchronize");
     }
     if (counts) (void)hipFree(counts);
@@ -890,7 +856,7 @@ int tdfa_ptable_destroy(tdfa_ptable* t)
 {
     if (!t) return TDFA_OK;
     for (void* d : {(void*)t->edge_first, (void*)t->token, (void*)t->dst, (void*)t->n_pops, (void*)t->pops, (void*)t->n_push,
-                    (void*)t->pushes, (void*)t->class_first, (void*)t->class_n_pops, (void*)t->class_pops, (void*)t->class_bits,
+                    (void*)t->pushes, (void*)t->dir, (void*)t->class_first, (void*)t->class_n_pops, (void*)t->class_pops, (void*)t->class_bits,
                     (void*)t->step_allow, (void*)t->step_rows, (void*)t->step_unused})
         if (d) (void)hipFree(d);
     for (void* d : t->retired) (void)hipFree(d);
@@ -1000,6 +966,10 @@ int pda_step_impl(const tdfa_ptable* table, const void* logits_dev, int dtype, i
     fused.pda.depths = depths_dev;
     fused.pda.stack_cap = stack_cap;
     fused.pda.n_states = table->n_states;
+    const PdaEdges edges = {table->edge_first, table->dir, table->dir_stride, table->token, table->dst, table->n_pops, table->pops,
+                            table->n_push, table->pushes};
+    fused.pda.edges = edges;
+    fused.new_states = new_states_dev;
     if (draw) {
         // the rows of the sequences first (from the class rows, or edge by edge where the table has none), then
         // the draw of the sampled step on them (it only chooses tokens)
@@ -1015,8 +985,7 @@ int pda_step_impl(const tdfa_ptable* table, const void* logits_dev, int dtype, i
         const int rc = tdfa::launch_sample_step(m, draw->inv_t, draw->top_k, draw->seed, draw->offset, nullptr, s);
         if (rc != TDFA_OK) return rc;
     } else if (tdfa::mask_step_takes_pda(fused)) {
-        const int rc = tdfa::launch_mask_step(fused, s);
-        if (rc != TDFA_OK) return rc;
+        return tdfa::launch_mask_step(fused, s);                // it traverses the edges as well
     } else {
         pda_allow_kernel<<<(unsigned)batch, 256, 0, s>>>(states_dev, stacks_dev, depths_dev, stack_cap, table->n_states, table->class_first,
                                                          table->class_n_pops, table->class_pops, table->class_bits, table->row_words,
@@ -1025,7 +994,7 @@ int pda_step_impl(const tdfa_ptable* table, const void* logits_dev, int dtype, i
         const int rc = tdfa::launch_mask_step(m, s);
         if (rc != TDFA_OK) return rc;
     }
-    pda_advance_kernel<<<(unsigned)((batch + 3) / 4), 256, 0, s>>>(a, batch);
+    pda_advance_kernel<<<(unsigned)((batch + 3) / 4), 256, 0, s>>>(a, edges, batch);
     TDFA_HIP(hipGetLastError());
     return TDFA_OK;
 }

@@ -172,6 +172,22 @@ int launch_row_allowed(const uint32_t* allow, int64_t n_rows, int32_t n_tokens, 
 int pack_table(const int32_t* delta, const uint32_t* allow, int64_t n_rows, int32_t n_tokens, int64_t row_words,
                hipStream_t stream, DeviceBlock* dir, DeviceBlock* row_begin, DeviceBlock* targets, int64_t* n_edges_out);
 
+constexpr int kPdaPops = 12;            // symbols an edge of a push-down automaton may pop or push
+constexpr int kPdaDirShift = 6;         // the directory of a state's edges has an entry per 64 tokens
+
+// The token edges of a push-down constraint, sorted by (state, token).
+struct PdaEdges {
+    const int64_t* edge_first;          // [n_states + 1]
+    const uint32_t* dir;                // [n_states][dir_stride]: edges of the state on tokens below 64 k, for k = 0 .. dir_stride - 1
+    int64_t dir_stride;                 // n_tokens / 64 + 2
+    const int32_t* token;
+    const int32_t* dst;
+    const int32_t* n_pops;
+    const int32_t* pops;                // [n_edges][kPdaPops], bottom to top
+    const int32_t* n_push;
+    const int32_t* pushes;
+};
+
 struct MaskArgs {
     const int32_t* delta;               // dense rows, or NULL for a packed table: then the three arrays below.
                                         // Both delta and targets NULL: no table; the step chooses tokens only and
@@ -204,13 +220,13 @@ struct MaskArgs {
         const int32_t* class_first;     // [n_states + 1]
         const int32_t* class_n_pops;    // [rows]
         const int32_t* class_pops;      // [rows][kPdaPops], the symbol popped first (the top of the stack) first
-        const int32_t* stacks;          // [batch][stack_cap]
-        const int32_t* depths;          // [batch]
+        int32_t* stacks;                // [batch][stack_cap], updated
+        int32_t* depths;                // [batch], updated
         int32_t stack_cap;
         int32_t n_states;
+        PdaEdges edges;                 // the chosen token's edge is traversed by the step kernel
     } pda;
 };
-constexpr int kPdaPops = 12;            // symbols an edge of a push-down automaton may pop
 int launch_mask_step(const MaskArgs& a, hipStream_t stream);
 // Whether launch_mask_step takes `a` with a.pda set (16-bit logits, no masked row written, a vocabulary whose
 // allowed bits fit the workgroup's LDS); otherwise the caller makes one row per sequence first.
