@@ -369,10 +369,16 @@ list_reach_final_kernel(Lists g, const uint8_t* mark, uint8_t* good, int32_t* ch
     }
 }
 
-__global__ void __launch_bounds__(kThreads) fill_i32_kernel(int32_t* p, size_t n, int32_t v)
+// An empty hash table for a round of the refinement, and its count of classes.
+__global__ void __launch_bounds__(kThreads)
+list_clear_kernel(unsigned long long* __restrict__ ht_key, int32_t* __restrict__ ht_min, size_t n, int32_t* __restrict__ n_classes)
 {
     const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n) p[i] = v;
+    if (i < n) {
+        ht_key[i] = 0ull;
+        ht_min[i] = 0x7FFFFFFF;
+    }
+    if (i == 0) *n_classes = 0;
 }
 
 // The first partition: kept rows by their final flag (cls 0 for every kept row, -1 for the rest).
@@ -416,9 +422,11 @@ list_insert_kernel(int32_t n_rows, const int32_t* __restrict__ cls, const unsign
     const unsigned long long k = key[q];
     uint32_t slot = (uint32_t)(k >> 20) & ht_mask;
     for (uint32_t probe = 0; probe <= ht_mask; ++probe, slot = (slot + 1) & ht_mask) {
-        const unsigned long long was = atomicCAS(&ht_key[slot], 0ull, k);
+        // (a look first: in the early rounds thousands of rows share a slot, and most need not change it)
+        unsigned long long was = __hip_atomic_load(&ht_key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (was == 0ull) was = atomicCAS(&ht_key[slot], 0ull, k);
         if (was == 0ull || was == k) {
-            atomicMin(&ht_min[slot], q);
+            if (__hip_atomic_load(&ht_min[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > q) atomicMin(&ht_min[slot], q);
             slot_of[q] = slot;
             return;
         }
@@ -600,7 +608,7 @@ int minimize_lists(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
     TDFA_GET(mem.get(&counter, 1));
     TDFA_GET(mem.get(&row_begin, n_rows));
     TDFA_GET(mem.get(&row_n, n_rows));
-    TDFA_GET(mem.get(&flags, 2));                  // [0] too many targets / changed / mismatch, [1] classes
+    TDFA_GET(mem.get(&flags, 1 + 3));              // [0] too many targets / changed / mismatch, [1 ..] classes after each round of a look
     TDFA_GET(mem.get(&key, n_rows));
     TDFA_GET(mem.get(&ht_key, ht_size));
     TDFA_GET(mem.get(&ht_min, ht_size));
@@ -635,7 +643,9 @@ int minimize_lists(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
     const Lists g = {row_begin, row_n, e_target, e_weight, n_rows};
     const unsigned by_wave = (unsigned)(((size_t)n_rows + kRowsPerBlock - 1) / kRowsPerBlock);
     const unsigned by_thread = (unsigned)(((size_t)n_rows + kThreads - 1) / kThreads);
-    constexpr int kRoundsPerLook = 4;              // rounds between two looks at the flag
+    // Rounds between two looks of the host: a look costs as much as half a dozen rounds (a copy and a wait, some 25 us),
+    // and a round past the last one changes nothing.
+    constexpr int kRoundsPerLook = 12, kRefinesPerLook = 3;
 
     // ---- states that a token sequence reaches, then of those the ones that reach a final state
     std::vector<uint8_t> mark_h((size_t)n_rows, 0);
@@ -663,19 +673,25 @@ int minimize_lists(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
     // ---- refinement: classes named by their smallest row
     int32_t *cls = cls_a, *cls_next = cls_b;
     list_first_keys_kernel<<<by_thread, kThreads, 0, s>>>(n_rows, mark, good, accept_dev, seed, cls, key);
-    int32_t n_cls = 0;
-    for (int32_t prev = -1;; prev = n_cls) {
-        TDFA_HIP(hipMemsetAsync(ht_key, 0, (size_t)ht_size * 8, s));
-        fill_i32_kernel<<<(ht_size + kThreads - 1) / kThreads, kThreads, 0, s>>>(ht_min, ht_size, 0x7FFFFFFF);
-        TDFA_HIP(hipMemsetAsync(flags + 1, 0, 4, s));
-        list_insert_kernel<<<by_thread, kThreads, 0, s>>>(n_rows, cls, key, ht_key, ht_min, ht_size - 1, slot_of);
-        list_assign_kernel<<<by_thread, kThreads, 0, s>>>(n_rows, cls, slot_of, ht_min, cls_next, flags + 1);
-        std::swap(cls, cls_next);
-        list_keys_kernel<<<by_wave, kThreads, 0, s>>>(g, cls, seed, key);       // for the next round
+    int32_t n_cls[kRefinesPerLook] = {};
+    for (int32_t prev = -1;;) {
+        for (int r = 0; r < kRefinesPerLook; ++r) {
+            list_clear_kernel<<<(ht_size + kThreads - 1) / kThreads, kThreads, 0, s>>>(ht_key, ht_min, ht_size, flags + 1 + r);
+            list_insert_kernel<<<by_thread, kThreads, 0, s>>>(n_rows, cls, key, ht_key, ht_min, ht_size - 1, slot_of);
+            list_assign_kernel<<<by_thread, kThreads, 0, s>>>(n_rows, cls, slot_of, ht_min, cls_next, flags + 1 + r);
+            std::swap(cls, cls_next);
+            list_keys_kernel<<<by_wave, kThreads, 0, s>>>(g, cls, seed, key);   // for the next round
+        }
         TDFA_HIP(hipGetLastError());
-        TDFA_HIP(hipMemcpyAsync(&n_cls, flags + 1, 4, hipMemcpyDeviceToHost, s));
+        TDFA_HIP(hipMemcpyAsync(n_cls, flags + 1, sizeof(n_cls), hipMemcpyDeviceToHost, s));
         TDFA_HIP(hipStreamSynchronize(s));
-        if (n_cls == prev) break;
+        // no class split in some round: none did after it either
+        bool stable = false;
+        for (int r = 0; r < kRefinesPerLook; ++r) {
+            stable = stable || n_cls[r] == prev;
+            prev = n_cls[r];
+        }
+        if (stable) break;
     }
     std::vector<int32_t> cls_h((size_t)n_rows);
     TDFA_HIP(hipMemcpyAsync(cls_h.data(), cls, (size_t)n_rows * 4, hipMemcpyDeviceToHost, s));
