@@ -216,18 +216,27 @@ int cache_alloc(void** out, size_t* bytes, bool may_wait)
     uint64_t until = 0;
     {
         std::lock_guard<std::mutex> lock(g_cache_mutex);
+        // the smallest block that fits, the oldest of that size first, that the GPU is done with (asked one at a time:
+        // a question costs a microsecond or two, and the first block is nearly always free)
         const size_t none = g_cache.size();
         size_t best = none, busy = none, with_event = 0;
-        for (size_t i = 0; i < g_cache.size(); ++i) {
-            const CachedBlock& b = g_cache[i];
+        for (const CachedBlock& b : g_cache)
             if (b.used) with_event += b.bytes;
-            if (b.device != dev || b.bytes < want || b.bytes > 2 * want + ((size_t)64 << 10)) continue;
-            if (b.wait_device && !may_wait) continue;
-            if (!use_completed(b.used)) {
-                if (busy == none) busy = i;
-            } else if (best == none || b.bytes < g_cache[best].bytes) {
-                best = i;
+        for (size_t last = none;;) {
+            size_t next = none;
+            for (size_t i = 0; i < g_cache.size(); ++i) {
+                const CachedBlock& b = g_cache[i];
+                if (b.device != dev || b.bytes < want || b.bytes > 2 * want + ((size_t)64 << 10) || (b.wait_device && !may_wait)) continue;
+                if (last != none && (b.bytes < g_cache[last].bytes || (b.bytes == g_cache[last].bytes && i <= last))) continue;
+                if (next == none || b.bytes < g_cache[next].bytes) next = i;
             }
+            if (next == none) break;
+            if (use_completed(g_cache[next].used)) {
+                best = next;
+                break;
+            }
+            if (busy == none) busy = next;
+            last = next;
         }
         // every fitting block is still in use: a new one while there are few such, else wait for the oldest
         if (best == none && busy != none && with_event > kCacheSmall) best = busy;

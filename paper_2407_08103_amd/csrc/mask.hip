@@ -397,6 +397,9 @@ constexpr int kEarlyWaves = 8;         // wavefronts of a workgroup that request
 // us.  With 8 instead of 32 the states that allow 4 to 12 % are gathered too, and streaming them is faster (the
 // same signatures 36 -> 51 us); 64 is as good as 32.
 constexpr uint32_t kSparseShare = 32;
+// Gathering pays where sparse rows share a compute unit; for fewer rows of a dense table it gains nothing, and the code
+// alone costs the step 0.15 us (380 rows of 69,160 tokens 14.80 -> 14.95 us).  Packed tables take it at any size.
+constexpr int kGatherRows = 512;
 
 constexpr int kGatherQueue = 128;      // groups a wavefront's ring holds (a power of two; 64 are fetched at a time)
 
@@ -502,11 +505,12 @@ __device__ __forceinline__ unsigned long long gather_scan(const typename ElemOf<
 // finds those classes (one per lane) before it reads its stretch of bits, and ORs the rows as it
 // reads them.  At the end the wavefront that finishes the row traverses the chosen token's edge, which also moves
 // the stack (every workgroup of the row has read it by then).
-template <bool WRITE, int kUnroll, bool SKIP, int kBuf = 2, bool PDA = false>
+template <bool WRITE, int kUnroll, bool SKIP, int kBuf = 2, bool PDA = false, bool GATHER = false>
 __global__ void __launch_bounds__(kMaxThreads)
 mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
 {
     static_assert(!PDA || (SKIP && !WRITE), "the push-down step reads its bits into LDS");
+    static_assert(!GATHER || (SKIP && !PDA), "the rings of a gathered row lie in the lists' room");
     extern __shared__ uint4 s_pieces[];
     __shared__ __attribute__((aligned(8))) uint32_t s_list[SKIP ? kMaxWaves * kListCap : 1];
     static_assert(kListCap >= 2 * kGatherQueue, "the rings of a sparse row share the lists' room");
@@ -578,7 +582,7 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
                 }
                 return;
             }
-            if constexpr (SKIP) {
+            if constexpr (GATHER) {
                 // A state known to allow few tokens.
                 if (n_allowed < (uint32_t)V / kSparseShare) {
                     unsigned long long c = gather_scan<TDFA_BF16>(row, reinterpret_cast<const uint8_t*>(a.allow + (int64_t)q * a.row_words),
@@ -2053,6 +2057,8 @@ int launch_mask_step(const MaskArgs& a, hipStream_t stream)
         if (dev >= 0 && dev < 64 && !raised[dev]) {
             for (const void* k : {reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true>),
                                   reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true>),
+                                  reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true, 2, false, true>),
+                                  reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true, 2, false, true>),
                                   reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true, 2, true>),
                                   reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true, 2, true>)})
                 TDFA_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBitRowBytes));
@@ -2073,7 +2079,10 @@ int launch_mask_step(const MaskArgs& a, hipStream_t stream)
         mask_step_exact_kernel<TDFA_F32><<<grid, kThreads, 0, stream>>>(a, parts, gpp);
     else if (a.masked_out)
         mask_step_bf16_kernel<true, 2, false><<<grid, kThreads, 0, stream>>>(a, parts, gpp, stretch);
-    else if (skip && unroll == 1)
+    else if (skip && (a.batch >= kGatherRows || !a.delta)) {
+        if (unroll == 1) mask_step_bf16_kernel<false, 1, true, 2, false, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
+        else mask_step_bf16_kernel<false, 2, true, 2, false, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
+    } else if (skip && unroll == 1)
         mask_step_bf16_kernel<false, 1, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
     else if (skip)
         mask_step_bf16_kernel<false, 2, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
