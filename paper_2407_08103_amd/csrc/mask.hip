@@ -1661,7 +1661,7 @@ constexpr int kDenseQuads = 48;        // lanes with a quad to draw for from whi
 // and as many three-input exclusive-ors, the bounds six instructions per token.  A workgroup of 1,024 threads per row (a compute unit with a
 // row that allows most tokens works for 45 us while those with sparse rows idle) and a queue of single tokens, each with
 // a generator block and two logarithms of its own, took longer: T = 1, 128,256 tokens, bf16, 256 sequences anywhere in
-// the texts of 50 signatures 42.6 -> 30 us, all in states that allow most tokens 45.9 -> 36.3 us (1,024 sequences: 139
+// the texts of 50 signatures 42.4 -> 28.2 us, all in states that allow most tokens 45.9 -> 36.3 us (1,024 sequences: 139
 // -> 89 and 166 -> 105 us), all in states that allow few 9.3 -> 9.9 us.
 // A queue belongs to one wavefront, so the loop needs no workgroup barrier; the maximum does not depend on the
 // order because candidates are compared as (score, lowest id).
