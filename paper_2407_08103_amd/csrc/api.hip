@@ -82,13 +82,14 @@ struct tdfa_table {
     int32_t* delta = nullptr;           // dense rows; NULL in a packed table
     uint32_t* allow = nullptr;
     bool own_delta = false, own_allow = false;
-    uint32_t* row_allowed = nullptr;    // device [n_rows] from the pool, or NULL: tokens each state allows (tables the library wrote)
+    uint32_t* row_allowed = nullptr;    // device [n_rows], one of `blocks`, or NULL: tokens each state allows (tables the library wrote)
     // packed form (tdfa_table_pack), owned by the table
     int32_t* targets = nullptr;
     int64_t* row_begin = nullptr;
     uint32_t* dir = nullptr;
     int64_t n_edges = 0;
-    // memory of this table that goes back to the library's cache (tables of tdfa_table_minimize and tdfa_table_pack)
+    // memory of this table that goes back to the library's cache: the counts of every table that the library wrote, and all
+    // of the tables of tdfa_table_minimize and tdfa_table_pack
     std::vector<tdfa::DeviceBlock> blocks;
     int device = 0;
 };
@@ -148,8 +149,8 @@ int device_alloc(T** p, size_t count)
 
 int static_scratch(void** out);
 
-// Device memory of automaton handles, and of the set-up calls that make tables of their own (minimise, pack), is kept
-// for the next one instead of going back to the runtime.  hipFree waits for all work on the device, and a caller that
+// Device memory of automaton handles, of the counts beside a table, and of the set-up calls that make tables of their own
+// (minimise, pack), is kept for the next one instead of going back to the runtime.  hipFree waits for all work on the device, and a caller that
 // prepares its next constraint while the GPU still decodes under the last one would stall on every destroyed automaton;
 // and memory that goes back to the driver is cleared before it is handed out again, at some 40 GB/s: once a program
 // has passed all of the card's memory through such calls, every gigabyte it allocates takes 25 ms (minimising and
@@ -157,7 +158,10 @@ int static_scratch(void** out);
 //
 // A block is handed out again when the GPU is done with it: when the event recorded behind the last launches that
 // used it has completed, or, where no event can tell (`wait_device`: a table may have been read on any stream), after
-// a wait for the device in the call that takes it.  Only calls that wait for the device anyway take such blocks.
+// a wait for the device: in the call that takes it, if that may wait (set-up calls that wait anyway), or at any time
+// since the block came.  A call that must not wait (a compile, for its counts) takes a block of which that is known, or
+// new memory: as blocks beyond the bounds go back to the runtime behind such a wait, a program that compiles and destroys
+// tables without end waits once in a few hundred of them.
 // Bounded: kCacheMaxBytes and kCacheMaxBlocks, the oldest go first; given back by tdfa_trim and when an allocation
 // of the library fails.
 struct CachedBlock {
@@ -183,9 +187,18 @@ bool use_completed(const std::shared_ptr<UseEvent>& used)
     return e == hipSuccess;
 }
 
+// Behind a wait for device `dev`: the blocks that were in the cache before it (`until`: the number of the last) are idle.
+void cache_idle(int dev, uint64_t until)
+{
+    std::lock_guard<std::mutex> lock(g_cache_mutex);
+    for (CachedBlock& b : g_cache)
+        if (b.device == dev && b.seq <= until) b.wait_device = false;
+}
+
 void cache_put(const CachedBlock& block)
 {
     std::vector<void*> to_free;
+    uint64_t until = 0;
     try {
         std::lock_guard<std::mutex> lock(g_cache_mutex);
         to_free.reserve(g_cache.size() + 1);
@@ -197,10 +210,16 @@ void cache_put(const CachedBlock& block)
             g_cache_bytes -= g_cache.front().bytes;
             g_cache.erase(g_cache.begin());
         }
+        until = g_cache_seq;
     } catch (const std::bad_alloc&) {                  // no room to note it: back to the runtime
         (void)hipFree(block.ptr);
     }
-    for (void* q : to_free) (void)hipFree(q);          // (waits for the device: whatever used the block is done)
+    if (to_free.empty()) return;
+    // (giving memory back waits for the device anyway: whatever used a block is done)
+    int dev = 0;
+    if (hipGetDevice(&dev) == hipSuccess && hipDeviceSynchronize() == hipSuccess) cache_idle(dev, until);
+    else (void)hipGetLastError();
+    for (void* q : to_free) (void)hipFree(q);
 }
 
 // *bytes: the size wanted, and on return the block's own.  `may_wait`: the call may wait for the device.
@@ -256,11 +275,7 @@ int cache_alloc(void** out, size_t* bytes, bool may_wait)
         cache_put(got);
         return fail(TDFA_E_DEVICE, "waiting for a block of device memory: %s", hipGetErrorString(e));
     }
-    if (must_wait) {                                   // what was in the cache before the wait is idle now
-        std::lock_guard<std::mutex> lock(g_cache_mutex);
-        for (CachedBlock& b : g_cache)
-            if (b.device == dev && b.seq <= until) b.wait_device = false;
-    }
+    if (must_wait) cache_idle(dev, until);
     *out = got.ptr;
     *bytes = got.bytes;
     return TDFA_OK;
@@ -441,10 +456,10 @@ constexpr int32_t kStaticMaxBatch = 4096;
 constexpr size_t kStaticScratchBytes = (size_t)kStaticMaxBatch * (sizeof(unsigned long long) + sizeof(unsigned int));
 }  // namespace
 
-int block_alloc(DeviceBlock* out, size_t bytes)
+int block_alloc(DeviceBlock* out, size_t bytes, bool may_wait)
 {
     out->bytes = bytes;
-    return cache_alloc(&out->ptr, &out->bytes, true);
+    return cache_alloc(&out->ptr, &out->bytes, may_wait);
 }
 
 void block_free(const DeviceBlock& block, int device)
@@ -559,12 +574,36 @@ void pool_release(void* p)
     for (void* q : to_free) (void)hipFree(q);
 }
 
+// The table owns the blocks from here on (false: it could not note them, and does not).
+bool keep_blocks(tdfa_table* t, int device, std::initializer_list<DeviceBlock> blocks)
+{
+    try {
+        t->blocks.insert(t->blocks.end(), blocks);
+    } catch (const std::bad_alloc&) {
+        return false;
+    }
+    t->device = device;
+    return true;
+}
+
 int count_rows(tdfa_table* t, hipStream_t s)
 {
     if (t->n_rows <= 0) return TDFA_OK;
     if (!t->row_allowed) {
-        const int rc = pool_alloc(&t->row_allowed, (size_t)t->n_rows);
+        int dev = 0;
+        TDFA_HIP(hipGetDevice(&dev));
+        // (a compile call may be under stream capture, where only the relaxed mode takes an allocation)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        DeviceBlock counts;
+        const int rc = block_alloc(&counts, (size_t)t->n_rows * sizeof(uint32_t), false);
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
         if (rc != TDFA_OK) return rc;
+        if (!keep_blocks(t, dev, {counts})) {
+            block_free(counts, dev);
+            return fail(TDFA_E_OOM, "host allocation failed");
+        }
+        t->row_allowed = static_cast<uint32_t*>(counts.ptr);
     }
     return launch_row_allowed(t->allow, t->n_rows, t->n_tokens, t->row_words, t->row_allowed, s);
 }
@@ -1339,7 +1378,6 @@ int tdfa_table_info(const tdfa_table* t, int64_t* n_rows, int32_t* n_tokens, int
 int tdfa_table_destroy(tdfa_table* t)
 {
     if (!t) return TDFA_OK;
-    tdfa::pool_release(t->row_allowed);
     if (t->own_delta && t->delta) (void)hipFree(t->delta);
     if (t->own_allow && t->allow) (void)hipFree(t->allow);
     for (const tdfa::DeviceBlock& b : t->blocks) tdfa::block_free(b, t->device);
@@ -1560,20 +1598,6 @@ int tdfa_table_apply_terminals(tdfa_table* table, int32_t n_edges, const int32_t
     if (he != hipSuccess) return fail(TDFA_E_DEVICE, "apply_terminals: %s", hipGetErrorString(he));
     return rc;
 }
-
-namespace {
-// The table owns the blocks from here on (false: it could not note them, and does not).
-bool keep_blocks(tdfa_table* t, int device, std::initializer_list<DeviceBlock> blocks)
-{
-    try {
-        t->blocks.insert(t->blocks.end(), blocks);
-    } catch (const std::bad_alloc&) {
-        return false;
-    }
-    t->device = device;
-    return true;
-}
-}  // namespace
 
 int tdfa_table_minimize(const tdfa_table* table, const uint8_t* accept_host, const int32_t* start_states_host,
                         int32_t n_starts, void* stream, tdfa_table** out, int32_t* state_map_host, uint8_t* accept_out_host)

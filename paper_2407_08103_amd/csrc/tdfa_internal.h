@@ -59,13 +59,14 @@ __host__ __device__ inline size_t plan_jump_offset(int32_t n_order)
     return plan_live_offset(n_order) + ((size_t)(n_order + 63) / 64 * 32 + 255) / 256 * 256;
 }
 
-// Device memory of the set-up calls, from the library's cache (api.hip).  block_alloc may wait for the device;
-// block_free does not: a freed block is handed out again only after such a wait.
+// Device memory of tables and of the set-up calls, from the library's cache (api.hip).  block_alloc may wait for the
+// device if may_wait is set; block_free does not wait for work that still uses the block, which is handed out again only
+// after a wait for the device.
 struct DeviceBlock {
     void* ptr = nullptr;
     size_t bytes = 0;
 };
-int block_alloc(DeviceBlock* out, size_t bytes);
+int block_alloc(DeviceBlock* out, size_t bytes, bool may_wait = true);
 void block_free(const DeviceBlock& block, int device);
 
 // The device arrays of a vocabulary handle that other translation units read (api.hip owns the handle).

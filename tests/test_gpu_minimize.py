@@ -222,6 +222,91 @@ def test_blocks_of_a_destroyed_table_in_use_on_another_stream(T, oracle):
     assert torch.cuda.mem_get_info()[0] >= kept + n * v * 4
 
 
+def _hold(stream):
+    """Work on `stream` that lasts some tens of milliseconds: what is enqueued on it next is still waiting while the host
+    goes on.  (Products of 8,192 x 8,192, two floating-point operations for each of 2^39 terms.)"""
+    with torch.cuda.stream(stream):
+        a = torch.ones((8192, 8192), dtype=torch.bfloat16, device="cuda")
+        out = torch.empty_like(a)
+        for _ in range(40):
+            torch.mm(a, a, out=out)
+    return a, out                                             # (kept by the caller until the stream is done)
+
+
+@pytest.mark.parametrize("minimised", [True, False])
+def test_counts_of_a_destroyed_table_in_use_on_another_stream(T, oracle, minimised):
+    """A table whose states are counted (one the library minimised, and one it wrote into the caller's buffers) is
+    destroyed while steps on another stream wait to read it; then tables with as many states, none of which allows a
+    token, are written on the current stream.  Their counts are in place before those steps begin, and must not be
+    where the steps read: a state counted as allowing nothing would end its sequence."""
+    rng = np.random.default_rng(6)
+    n, v, batch, steps = 700, 4001, 64, 6
+    tab = rng.integers(0, n, size=(n, v), dtype=np.int32)
+    accept = np.ones(n, dtype=np.uint8)
+    accept[::2] = 0
+    dense, none = _upload_table(T, tab), _upload_table(T, np.full((n, v), -1, dtype=np.int32))
+    x = rng.normal(0, 2, size=(batch, (v + 3) // 4 * 4)).astype(np.float32)
+    lg = torch.from_numpy(x).cuda()
+    states = rng.integers(0, n, size=batch).astype(np.int32)
+    want = states.copy()
+    for _ in range(steps):
+        _, want = oracle.mask_step(tab, x, 0, want, row_stride=x.shape[1])
+    q, tok = torch.from_numpy(states).cuda(), torch.empty(batch, dtype=torch.int32, device="cuda")
+    outs = [(torch.empty_like(none.delta), torch.empty_like(none.allow)) for _ in range(3)]
+    T.mask_step(dense, lg, q, tok, torch.empty_like(q))                 # (the scratch of the steps is there)
+    T.trim()                                                  # (no block goes back to the runtime, which waits, below)
+    table = T.table_minimize(dense, accept, [0])[0] if minimised else T.table_concat([dense])[0]
+    assert table.n_rows == n
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    held = _hold(side)
+    with torch.cuda.stream(side):
+        for _ in range(steps):
+            T.mask_step(table, lg, q, tok, q)
+    buffers = table._keep                                     # (the caller's buffers live on; the counts are the library's)
+    table.close()
+    made = [T.table_concat([none], out=o)[0] for o in outs]
+    torch.cuda.current_stream().synchronize()
+    assert not side.query()                                   # the steps have not begun or are under way
+    torch.cuda.synchronize()
+    assert np.array_equal(q.cpu().numpy(), want)
+    del held, buffers, made
+
+
+def test_compile_under_capture_after_a_destroyed_table(T, oracle):
+    """A compile call that is being captured finds only counts that a step may still read: it takes other memory."""
+    w = configs.get("c1")
+    want = oracle.compile_walk(w.dfas[0].trans, w.vocab.data, w.vocab.offsets)
+    vocab = T.Vocab(w.vocab.data, w.vocab.offsets)
+    dfa = T.CharDFA(w.dfas[0].trans, w.dfas[0].accept, w.dfas[0].start)
+    rows = dfa.n_states
+    out = (torch.empty((rows, vocab.n_tokens), dtype=torch.int32, device="cuda"),
+           torch.empty((rows, T.allow_row_words(vocab.n_tokens)), dtype=torch.int32, device="cuda"))
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    T.trim()
+    with torch.cuda.stream(side):
+        T.compile_token_dfa(vocab, dfa, out=out).close()
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        table = T.compile_token_dfa(vocab, dfa, out=out)
+    for _ in range(3):
+        out[0].fill_(7)
+        out[1].fill_(0)
+        graph.replay()
+        torch.cuda.synchronize()
+        G.check_rows(table, want, np.arange(rows))
+        lg = torch.zeros((rows, (vocab.n_tokens + 3) // 4 * 4), device="cuda")
+        st = torch.arange(rows, dtype=torch.int32, device="cuda")
+        tok, new = torch.empty_like(st), torch.empty_like(st)
+        T.mask_step(table, lg, st, tok, new)
+        torch.cuda.synchronize()
+        live = want >= 0
+        first = np.where(live.any(axis=1), live.argmax(axis=1), -1)
+        assert np.array_equal(tok.cpu().numpy(), first)       # (equal logits: the lowest allowed token)
+
+
 def test_bad_arguments(T):
     table = _upload_table(T, np.zeros((2, 3), dtype=np.int32))
     with pytest.raises(T.TdfaError):
