@@ -187,6 +187,16 @@ bool use_completed(const std::shared_ptr<UseEvent>& used)
     return e == hipSuccess;
 }
 
+// A wait for all work on the current device: freeing memory is one (256 bytes: 1.5 us on an idle device).
+// hipDeviceSynchronize would end every capture that is under way in the process, also a relaxed one, which allocations
+// and frees leave alone.
+hipError_t device_wait()
+{
+    void* p = nullptr;
+    const hipError_t e = hipMalloc(&p, 256);
+    return e == hipSuccess ? hipFree(p) : e;
+}
+
 // Behind a wait for device `dev`: the blocks that were in the cache before it (`until`: the number of the last) are idle.
 void cache_idle(int dev, uint64_t until)
 {
@@ -197,7 +207,7 @@ void cache_idle(int dev, uint64_t until)
 
 void cache_put(const CachedBlock& block)
 {
-    std::vector<void*> to_free;
+    std::vector<CachedBlock> to_free;
     uint64_t until = 0;
     try {
         std::lock_guard<std::mutex> lock(g_cache_mutex);
@@ -206,7 +216,7 @@ void cache_put(const CachedBlock& block)
         g_cache.back().seq = ++g_cache_seq;
         g_cache_bytes += block.bytes;
         while (g_cache.size() > kCacheMaxBlocks || g_cache_bytes > kCacheMaxBytes) {
-            to_free.push_back(g_cache.front().ptr);
+            to_free.push_back(g_cache.front());
             g_cache_bytes -= g_cache.front().bytes;
             g_cache.erase(g_cache.begin());
         }
@@ -215,11 +225,10 @@ void cache_put(const CachedBlock& block)
         (void)hipFree(block.ptr);
     }
     if (to_free.empty()) return;
-    // (giving memory back waits for the device anyway: whatever used a block is done)
-    int dev = 0;
-    if (hipGetDevice(&dev) == hipSuccess && hipDeviceSynchronize() == hipSuccess) cache_idle(dev, until);
-    else (void)hipGetLastError();
-    for (void* q : to_free) (void)hipFree(q);
+    // (giving memory back waits for its device: whatever used a block there is done)
+    for (const CachedBlock& b : to_free)
+        if (hipFree(b.ptr) == hipSuccess) cache_idle(b.device, until);
+        else (void)hipGetLastError();
 }
 
 // *bytes: the size wanted, and on return the block's own.  `may_wait`: the call may wait for the device.
@@ -269,11 +278,13 @@ int cache_alloc(void** out, size_t* bytes, bool may_wait)
     }
     if (!got.ptr) return device_malloc(out, want);
     hipError_t e = hipSuccess;
-    if (must_wait) e = hipDeviceSynchronize();
+    if (must_wait) e = device_wait();
     else if (got.used && got.used->ev) e = hipEventSynchronize(got.used->ev);
-    if (e != hipSuccess) {                             // (a capture is under way, say): the block stays where it was
+    if (e != hipSuccess) {
+        // it cannot be waited for: the block goes back, and new memory is taken
+        (void)hipGetLastError();
         cache_put(got);
-        return fail(TDFA_E_DEVICE, "waiting for a block of device memory: %s", hipGetErrorString(e));
+        return device_malloc(out, want);
     }
     if (must_wait) cache_idle(dev, until);
     *out = got.ptr;

@@ -307,6 +307,37 @@ def test_compile_under_capture_after_a_destroyed_table(T, oracle):
         assert np.array_equal(tok.cpu().numpy(), first)       # (equal logits: the lowest allowed token)
 
 
+def test_set_up_calls_beside_a_capture(T, oracle):
+    """Minimising and packing on one stream while another is captured (by a program that allows that: relaxed mode),
+    with nothing in the cache and with blocks there that need a wait for the device: both times the same tables."""
+    rng = np.random.default_rng(8)
+    n, v = 300, 5000
+    tab = rng.integers(0, n, size=(n, v), dtype=np.int32)
+    accept = np.ones(n, dtype=np.uint8)
+    accept[::2] = 0
+    table = _upload_table(T, tab)
+    work = torch.cuda.Stream()
+    x = torch.zeros(1000, device="cuda")
+    outs = [(torch.empty_like(table.delta), torch.empty_like(table.allow)) for _ in range(2)]
+    torch.cuda.synchronize()
+    T.trim()
+    for out in outs:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+            x.add_(1.0)
+            small, _, mp = T.table_minimize(table, accept, [0], stream=work)
+            packed = T.table_pack(small, stream=work)
+            x.add_(1.0)
+        before = float(x[0])
+        graph.replay()
+        torch.cuda.synchronize()
+        assert float(x[0]) == before + 2.0 and (mp == np.arange(n)).all()
+        G.check_rows(T.table_concat([small], out=out)[0], tab, np.arange(n))
+        assert packed.n_rows == n
+        packed.close()
+        small.close()
+
+
 def test_bad_arguments(T):
     table = _upload_table(T, np.zeros((2, 3), dtype=np.int32))
     with pytest.raises(T.TdfaError):
