@@ -99,9 +99,9 @@ TDFA_API int tdfa_dfa_create(const int32_t *trans, const uint8_t *accept, int32_
                     void *stream, tdfa_dfa **out);
 /* Does not wait for the GPU: the automaton's device memory goes to a cache inside the library, with
  * an event recorded behind the last compile call that used the handle, and is handed to a later
- * tdfa_dfa_create once that event has completed (tdfa_trim gives the cache back to the device).  A
- * handle that a compile call used under stream capture, or that was compiled by the sweep (whose
- * lists are freed), waits for the device instead. */
+ * tdfa_dfa_create once that event has completed (tdfa_trim gives the cache back to the device).  It
+ * waits for the device where the cache is full (its oldest blocks are freed), where a compile call used
+ * the handle under stream capture, and where the sweep compiled it (whose lists are freed). */
 TDFA_API int tdfa_dfa_destroy(tdfa_dfa *dfa);
 
 /* Caps the device workspace that compile calls may allocate for this automaton beyond its tables
@@ -139,9 +139,14 @@ TDFA_API int tdfa_dfa_compile_path(tdfa_dfa *dfa, int path);
 /* The four large workspace arrays of TDFA_PATH_PAIRS are kept when their automaton is destroyed (at
  * most eight blocks per process, the oldest freed first) and handed to the next automaton that needs
  * blocks of about their size: allocating them anew costs as much as a tenth of such a compile.
- * The device memory of destroyed automata and of destroyed tables that tdfa_table_minimize or
- * tdfa_table_pack made, and the workspace of those two calls, are kept likewise (at most 12 GiB and 256
- * blocks per process together, the oldest freed first).
+ * The device memory of destroyed automata is kept likewise, and so is that of destroyed tables that
+ * tdfa_table_minimize or tdfa_table_pack made and the workspace of those two calls (at most 4 GiB and
+ * 256 blocks per process of either kind, the oldest freed first; a larger block is freed at once).  A kept
+ * block serves a request of at least half its size (of a table: of at least four fifths), or one that is
+ * 64 KiB smaller.  The counts beside a destroyed table (see tdfa_compile_token_dfa) are kept as well,
+ * some thousand arrays of 4 to 128 KiB per size; every 1,024th that comes back waits for the device.
+ * No other allocator of the process can ask for the kept memory: call tdfa_trim before a large allocation
+ * elsewhere.
  * tdfa_trim() gives the kept blocks back to the device.  Errors: none. */
 TDFA_API int tdfa_trim(void);
 

@@ -114,7 +114,7 @@ def allow_row_words(n_tokens: int) -> int:
 
 
 def trim() -> None:
-    """tdfa_trim: gives the workspace blocks kept from destroyed automata back to the device."""
+    """tdfa_trim: gives the memory kept from destroyed automata and tables (up to 8 GiB) back to the device."""
     _check(lib().tdfa_trim())
 
 

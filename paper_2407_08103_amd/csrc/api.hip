@@ -149,21 +149,21 @@ int device_alloc(T** p, size_t count)
 
 int static_scratch(void** out);
 
-// Device memory of automaton handles, of the counts beside a table, and of the set-up calls that make tables of their own
-// (minimise, pack), is kept for the next one instead of going back to the runtime.  hipFree waits for all work on the device, and a caller that
-// prepares its next constraint while the GPU still decodes under the last one would stall on every destroyed automaton;
-// and memory that goes back to the driver is cleared before it is handed out again, at some 40 GB/s: once a program
-// has passed all of the card's memory through such calls, every gigabyte it allocates takes 25 ms (minimising and
-// packing a table of 5,387 x 128,256: 8 ms the first eighty times, 82 ms from then on).
+// Device memory is kept for the next handle instead of going back to the runtime: of automata in one cache, of tables and
+// of the set-up calls that make tables of their own (minimise, pack) in another.  hipFree waits for all work on the
+// device, and a caller that prepares its next constraint while the GPU still decodes under the last one would stall on
+// every destroyed automaton; and memory that goes back to the driver is cleared before it is handed out again, at some
+// 40 GB/s: once a program has passed all of the card's memory through such calls, every gigabyte it allocates takes 25 ms
+// (minimising and packing a table of 5,387 x 128,256: 8 ms the first eighty times, 82 ms from then on).
 //
-// A block is handed out again when the GPU is done with it: when the event recorded behind the last launches that
-// used it has completed, or, where no event can tell (`wait_device`: a table may have been read on any stream), after
-// a wait for the device: in the call that takes it, if that may wait (set-up calls that wait anyway), or at any time
-// since the block came.  A call that must not wait (a compile, for its counts) takes a block of which that is known, or
-// new memory: as blocks beyond the bounds go back to the runtime behind such a wait, a program that compiles and destroys
-// tables without end waits once in a few hundred of them.
-// Bounded: kCacheMaxBytes and kCacheMaxBlocks, the oldest go first; given back by tdfa_trim and when an allocation
-// of the library fails.
+// A block is handed out again when the GPU is done with it.  An automaton's carries the event recorded behind the last
+// launches that used it.  Of a table's no event can tell, since it may have been read on any stream (`wait_device`): it
+// is handed out after a wait for the device, in the call that takes it if that may wait (set-up calls that wait
+// anyway), or at any time since the block came.
+//
+// Each cache is bounded, the oldest blocks go first, and one larger than the cache goes straight back; tdfa_trim and an
+// allocation of the library that fails empty both.  4 GiB of tables are the blocks of one table of 4,245 x 128,256
+// minimised and packed (3.0 GB) and no more, since no other allocator of the process can ask for them.
 struct CachedBlock {
     void* ptr;
     size_t bytes;
@@ -172,12 +172,15 @@ struct CachedBlock {
     bool wait_device;
     uint64_t seq;                              // order in which blocks came
 };
+struct BlockCache {
+    std::vector<CachedBlock> blocks;           // free blocks, oldest first
+    size_t bytes = 0;
+};
 std::mutex g_cache_mutex;
-std::vector<CachedBlock> g_cache;              // free blocks, oldest first
-size_t g_cache_bytes = 0;
+BlockCache& g_dfa_cache = *new BlockCache;     // (never destroyed: the runtime may be gone by the end of the process)
+BlockCache& g_table_cache = *new BlockCache;
 uint64_t g_cache_seq = 0;
-constexpr size_t kCacheMaxBytes = (size_t)12 << 30, kCacheMaxBlocks = 256;
-constexpr size_t kCacheSmall = (size_t)2 << 30;   // with fewer bytes behind events a call allocates rather than waits for one
+constexpr size_t kCacheMaxBytes = (size_t)4 << 30, kCacheMaxBlocks = 256;       // of either
 
 bool use_completed(const std::shared_ptr<UseEvent>& used)
 {
@@ -197,42 +200,56 @@ hipError_t device_wait()
     return e == hipSuccess ? hipFree(p) : e;
 }
 
-// Behind a wait for device `dev`: the blocks that were in the cache before it (`until`: the number of the last) are idle.
+// Behind a wait for device `dev`: the tables' blocks that were there before it (`until`: the number of the last) are idle.
 void cache_idle(int dev, uint64_t until)
 {
     std::lock_guard<std::mutex> lock(g_cache_mutex);
-    for (CachedBlock& b : g_cache)
+    for (CachedBlock& b : g_table_cache.blocks)
         if (b.device == dev && b.seq <= until) b.wait_device = false;
 }
 
-void cache_put(const CachedBlock& block)
+void cache_put(BlockCache& cache, const CachedBlock& block)
 {
     std::vector<CachedBlock> to_free;
     uint64_t until = 0;
     try {
         std::lock_guard<std::mutex> lock(g_cache_mutex);
-        to_free.reserve(g_cache.size() + 1);
-        g_cache.push_back(block);
-        g_cache.back().seq = ++g_cache_seq;
-        g_cache_bytes += block.bytes;
-        while (g_cache.size() > kCacheMaxBlocks || g_cache_bytes > kCacheMaxBytes) {
-            to_free.push_back(g_cache.front());
-            g_cache_bytes -= g_cache.front().bytes;
-            g_cache.erase(g_cache.begin());
+        to_free.reserve(cache.blocks.size() + 1);
+        cache.blocks.reserve(cache.blocks.size() + 1);
+        until = ++g_cache_seq;
+        if (block.bytes > kCacheMaxBytes) {
+            to_free.push_back(block);
+        } else {
+            cache.blocks.push_back(block);
+            cache.blocks.back().seq = until;
+            cache.bytes += block.bytes;
         }
-        until = g_cache_seq;
+        while (cache.blocks.size() > kCacheMaxBlocks || cache.bytes > kCacheMaxBytes) {
+            to_free.push_back(cache.blocks.front());
+            cache.bytes -= cache.blocks.front().bytes;
+            cache.blocks.erase(cache.blocks.begin());
+        }
     } catch (const std::bad_alloc&) {                  // no room to note it: back to the runtime
         (void)hipFree(block.ptr);
+        return;
     }
-    if (to_free.empty()) return;
     // (giving memory back waits for its device: whatever used a block there is done)
     for (const CachedBlock& b : to_free)
         if (hipFree(b.ptr) == hipSuccess) cache_idle(b.device, until);
         else (void)hipGetLastError();
 }
 
-// *bytes: the size wanted, and on return the block's own.  `may_wait`: the call may wait for the device.
-int cache_alloc(void** out, size_t* bytes, bool may_wait)
+// The block at index `at` leaves the cache (the caller holds the lock).
+CachedBlock cache_take(BlockCache& cache, size_t at)
+{
+    const CachedBlock got = cache.blocks[at];
+    cache.bytes -= got.bytes;
+    cache.blocks.erase(cache.blocks.begin() + (long)at);
+    return got;
+}
+
+// Memory for an automaton.  *bytes: the size wanted, and on return the block's own.
+int cache_alloc(void** out, size_t* bytes)
 {
     *out = nullptr;
     if (!*bytes) *bytes = 1;
@@ -240,77 +257,99 @@ int cache_alloc(void** out, size_t* bytes, bool may_wait)
     int dev = 0;
     TDFA_HIP(hipGetDevice(&dev));
     CachedBlock got{};
-    bool must_wait = false;
-    uint64_t until = 0;
     {
         std::lock_guard<std::mutex> lock(g_cache_mutex);
         // the smallest block that fits, the oldest of that size first, that the GPU is done with (asked one at a time:
         // a question costs a microsecond or two, and the first block is nearly always free)
-        const size_t none = g_cache.size();
-        size_t best = none, busy = none, with_event = 0;
-        for (const CachedBlock& b : g_cache)
-            if (b.used) with_event += b.bytes;
+        const std::vector<CachedBlock>& blocks = g_dfa_cache.blocks;
+        const size_t none = blocks.size();
+        size_t best = none, busy = none;
         for (size_t last = none;;) {
             size_t next = none;
-            for (size_t i = 0; i < g_cache.size(); ++i) {
-                const CachedBlock& b = g_cache[i];
-                if (b.device != dev || b.bytes < want || b.bytes > 2 * want + ((size_t)64 << 10) || (b.wait_device && !may_wait)) continue;
-                if (last != none && (b.bytes < g_cache[last].bytes || (b.bytes == g_cache[last].bytes && i <= last))) continue;
-                if (next == none || b.bytes < g_cache[next].bytes) next = i;
+            for (size_t i = 0; i < blocks.size(); ++i) {
+                const CachedBlock& b = blocks[i];
+                if (b.device != dev || b.bytes < want || b.bytes > 2 * want + ((size_t)64 << 10)) continue;
+                if (last != none && (b.bytes < blocks[last].bytes || (b.bytes == blocks[last].bytes && i <= last))) continue;
+                if (next == none || b.bytes < blocks[next].bytes) next = i;
             }
             if (next == none) break;
-            if (use_completed(g_cache[next].used)) {
+            if (use_completed(blocks[next].used)) {
                 best = next;
                 break;
             }
             if (busy == none) busy = next;
             last = next;
         }
-        // every fitting block is still in use: a new one while there are few such, else wait for the oldest
-        if (best == none && busy != none && with_event > kCacheSmall) best = busy;
-        if (best != none) {
-            got = g_cache[best];
-            must_wait = got.wait_device;
-            until = g_cache_seq;
-            g_cache_bytes -= got.bytes;
-            g_cache.erase(g_cache.begin() + (long)best);
-        }
+        // every fitting block is still in use: a new one while the cache is small, else wait for the oldest
+        if (best == none && busy != none && g_dfa_cache.bytes > kCacheMaxBytes / 2) best = busy;
+        if (best != none) got = cache_take(g_dfa_cache, best);
     }
     if (!got.ptr) return device_malloc(out, want);
-    hipError_t e = hipSuccess;
-    if (must_wait) e = device_wait();
-    else if (got.used && got.used->ev) e = hipEventSynchronize(got.used->ev);
-    if (e != hipSuccess) {
-        // it cannot be waited for: the block goes back, and new memory is taken
-        (void)hipGetLastError();
-        cache_put(got);
-        return device_malloc(out, want);
+    if (got.used && got.used->ev) {
+        const hipError_t e = hipEventSynchronize(got.used->ev);
+        if (e != hipSuccess) {
+            cache_put(g_dfa_cache, got);
+            return fail(TDFA_E_DEVICE, "waiting for a block of device memory: %s", hipGetErrorString(e));
+        }
     }
-    if (must_wait) cache_idle(dev, until);
     *out = got.ptr;
     *bytes = got.bytes;
     return TDFA_OK;
 }
 
-// The block goes to the cache; `used` (may be empty) tells when the GPU is done with it.
+// The automaton's block goes to the cache; `used` (may be empty) tells when the GPU is done with it.
 void cache_free(void* p, size_t bytes, const std::shared_ptr<UseEvent>& used)
 {
     if (!p) return;
     int dev = 0;
     (void)hipGetDevice(&dev);
-    cache_put(CachedBlock{p, bytes, dev, used, false, 0});
+    cache_put(g_dfa_cache, CachedBlock{p, bytes, dev, used, false, 0});
 }
 
+// The counts beside a table (how many tokens each state allows), a word per state: parts of allocations of kCountsTogether
+// parts of one size, a power of two.  A part may have been read on any stream when its table goes, and the call that
+// wants the next one, a compile, must not wait: it takes a part that is known to be idle, or new ones.  The kCountsUnknown-th
+// of a size that comes back waits for the device, and then all of them are idle.  A loop that compiles and destroys
+// tables (5,387 x 128,256, 705 us each, the host 100 of them ahead) loses half a millisecond to such a wait, and 5 us to a
+// new mapping; larger counts (kCountsMaxBytes) come from the cache above.
+struct CountsPart {
+    void* ptr;
+    std::shared_ptr<void> owner;
+};
+struct CountsSize {
+    std::vector<CountsPart> idle, unknown;
+};
+constexpr size_t kCountsTogether = 32, kCountsUnknown = 1024;
+constexpr int kCountsSizes = 6, kCountsDevices = 64;
+constexpr size_t kCountsMinBytes = (size_t)4 << 10, kCountsMaxBytes = kCountsMinBytes << (kCountsSizes - 1);
+typedef CountsSize CountsPool[kCountsDevices][kCountsSizes];
+CountsPool& g_counts = *reinterpret_cast<CountsPool*>(new CountsPool);     // (under g_cache_mutex; never destroyed, like the caches)
+
+int counts_size(size_t bytes)
+{
+    int c = 0;
+    while ((kCountsMinBytes << c) < bytes) ++c;
+    return c;
+}
+
+// All that is kept goes back (nothing is allocated on the way; the memory is freed when the lock has been given up).
 void cache_trim()
 {
-    std::vector<void*> to_free;
-    {
-        std::lock_guard<std::mutex> lock(g_cache_mutex);
-        for (const CachedBlock& b : g_cache) to_free.push_back(b.ptr);
-        g_cache.clear();
-        g_cache_bytes = 0;
+    for (BlockCache* c : {&g_dfa_cache, &g_table_cache}) {
+        std::vector<CachedBlock> gone;
+        {
+            std::lock_guard<std::mutex> lock(g_cache_mutex);
+            gone.swap(c->blocks);
+            c->bytes = 0;
+        }
+        for (const CachedBlock& b : gone) (void)hipFree(b.ptr);
     }
-    for (void* q : to_free) (void)hipFree(q);
+    for (auto& sizes : g_counts)
+        for (CountsSize& c : sizes) {
+            CountsSize gone;
+            std::lock_guard<std::mutex> lock(g_cache_mutex);
+            std::swap(gone, c);
+        }
 }
 
 // A block of an automaton handle from the cache, remembered in the handle.
@@ -319,7 +358,7 @@ int dfa_alloc(const tdfa_dfa* d, T** p, size_t count)
 {
     void* v = nullptr;
     size_t bytes = (count ? count : 1) * sizeof(T);
-    const int rc = cache_alloc(&v, &bytes, false);
+    const int rc = cache_alloc(&v, &bytes);
     *p = static_cast<T*>(v);
     if (rc == TDFA_OK) d->cached.emplace_back(v, bytes);
     return rc;
@@ -467,15 +506,119 @@ constexpr int32_t kStaticMaxBatch = 4096;
 constexpr size_t kStaticScratchBytes = (size_t)kStaticMaxBatch * (sizeof(unsigned long long) + sizeof(unsigned int));
 }  // namespace
 
+// Whether a kept block serves a request (not much larger: a table keeps it for as long as it lives).
+static bool fits(const CachedBlock& b, size_t want) { return b.bytes >= want && b.bytes <= want + want / 4 + ((size_t)64 << 10); }
+
 int block_alloc(DeviceBlock* out, size_t bytes, bool may_wait)
 {
-    out->bytes = bytes;
-    return cache_alloc(&out->ptr, &out->bytes, may_wait);
+    const size_t want = bytes ? bytes : 1;
+    out->ptr = nullptr;
+    out->bytes = want;
+    int dev = 0;
+    TDFA_HIP(hipGetDevice(&dev));
+    CachedBlock got{};
+    uint64_t until = 0;
+    {
+        std::lock_guard<std::mutex> lock(g_cache_mutex);
+        // the smallest block that fits, an idle one if there is any
+        const std::vector<CachedBlock>& blocks = g_table_cache.blocks;
+        size_t best = blocks.size();
+        for (size_t i = 0; i < blocks.size(); ++i) {
+            const CachedBlock& b = blocks[i];
+            if (b.device != dev || !fits(b, want) || (b.wait_device && !may_wait)) continue;
+            if (best == blocks.size() || b.wait_device < blocks[best].wait_device ||
+                (b.wait_device == blocks[best].wait_device && b.bytes < blocks[best].bytes))
+                best = i;
+        }
+        if (best != blocks.size()) {
+            until = g_cache_seq;
+            got = cache_take(g_table_cache, best);
+        }
+    }
+    if (got.ptr && got.wait_device) {
+        if (device_wait() == hipSuccess) {
+            cache_idle(dev, until);
+        } else {                                       // it cannot be waited for: the block goes back, and new memory is taken
+            (void)hipGetLastError();
+            cache_put(g_table_cache, got);
+            got.ptr = nullptr;
+        }
+    }
+    if (!got.ptr) return device_malloc(&out->ptr, want);
+    out->ptr = got.ptr;
+    out->bytes = got.bytes;
+    return TDFA_OK;
 }
+
+int counts_alloc(DeviceBlock* out, size_t bytes)
+{
+    int dev = 0;
+    TDFA_HIP(hipGetDevice(&dev));
+    if (bytes > kCountsMaxBytes || dev < 0 || dev >= kCountsDevices) return block_alloc(out, bytes, false);
+    const int c = counts_size(bytes);
+    const size_t part = kCountsMinBytes << c;
+    auto take = [&](const CountsPart& p) {
+        out->ptr = p.ptr;
+        out->bytes = part;
+        out->owner = p.owner;
+    };
+    {
+        std::lock_guard<std::mutex> lock(g_cache_mutex);
+        std::vector<CountsPart>& idle = g_counts[dev][c].idle;
+        if (!idle.empty()) {
+            take(idle.back());
+            idle.pop_back();
+            return TDFA_OK;
+        }
+    }
+    void* p = nullptr;
+    const int rc = device_malloc(&p, part * kCountsTogether);
+    if (rc != TDFA_OK) return rc;
+    try {
+        const std::shared_ptr<void> owner(p, [](void* q) { (void)hipFree(q); });       // (frees p if it throws)
+        std::lock_guard<std::mutex> lock(g_cache_mutex);
+        std::vector<CountsPart>& idle = g_counts[dev][c].idle;
+        idle.reserve(idle.size() + kCountsTogether);
+        for (size_t i = 1; i < kCountsTogether; ++i) idle.push_back({static_cast<char*>(p) + i * part, owner});
+        take({p, owner});
+    } catch (const std::bad_alloc&) {
+        return fail(TDFA_E_OOM, "host allocation failed");
+    }
+    return TDFA_OK;
+}
+
+namespace {
+// A part of counts comes back, from a table that may still be read.
+void counts_free(const DeviceBlock& block, int device)
+{
+    CountsSize& pool = g_counts[device][counts_size(block.bytes)];
+    int dev = 0;
+    const bool here = hipGetDevice(&dev) == hipSuccess && dev == device;
+    std::vector<CountsPart> waited;
+    try {
+        std::lock_guard<std::mutex> lock(g_cache_mutex);
+        pool.unknown.push_back({block.ptr, block.owner});
+        if (here && pool.unknown.size() >= kCountsUnknown) waited.swap(pool.unknown);
+    } catch (const std::bad_alloc&) {                  // the part is given up
+        return;
+    }
+    if (waited.empty()) return;
+    const bool idle = device_wait() == hipSuccess;
+    if (!idle) (void)hipGetLastError();
+    try {
+        std::lock_guard<std::mutex> lock(g_cache_mutex);
+        std::vector<CountsPart>& to = idle ? pool.idle : pool.unknown;
+        to.insert(to.end(), waited.begin(), waited.end());
+    } catch (const std::bad_alloc&) {                  // these are given up
+    }
+}
+}  // namespace
 
 void block_free(const DeviceBlock& block, int device)
 {
-    if (block.ptr) cache_put(CachedBlock{block.ptr, block.bytes, device, nullptr, true, 0});
+    if (!block.ptr) return;
+    if (block.owner) counts_free(block, device);
+    else cache_put(g_table_cache, CachedBlock{block.ptr, block.bytes, device, nullptr, true, 0});
 }
 
 int step_scratch(int32_t batch, hipStream_t stream, unsigned long long** best, unsigned int** count)
@@ -607,7 +750,7 @@ int count_rows(tdfa_table* t, hipStream_t s)
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
         DeviceBlock counts;
-        const int rc = block_alloc(&counts, (size_t)t->n_rows * sizeof(uint32_t), false);
+        const int rc = counts_alloc(&counts, (size_t)t->n_rows * sizeof(uint32_t));
         if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
         if (rc != TDFA_OK) return rc;
         if (!keep_blocks(t, dev, {counts})) {

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <functional>
+#include <memory>
 #include <vector>
 
 #include "tdfa.h"
@@ -65,8 +66,10 @@ __host__ __device__ inline size_t plan_jump_offset(int32_t n_order)
 struct DeviceBlock {
     void* ptr = nullptr;
     size_t bytes = 0;
+    std::shared_ptr<void> owner;        // of counts: the allocation that the block is a part of
 };
 int block_alloc(DeviceBlock* out, size_t bytes, bool may_wait = true);
+int counts_alloc(DeviceBlock* out, size_t bytes);       // does not wait
 void block_free(const DeviceBlock& block, int device);
 
 // The device arrays of a vocabulary handle that other translation units read (api.hip owns the handle).

@@ -307,6 +307,41 @@ def test_compile_under_capture_after_a_destroyed_table(T, oracle):
         assert np.array_equal(tok.cpu().numpy(), first)       # (equal logits: the lowest allowed token)
 
 
+def test_kept_memory_is_bounded(T):
+    """What destroyed tables leave with the library: at most 4 GiB however many there were, no block of more than five
+    quarters of what a table needs, and nothing that pushes an automaton's blocks out.  (2 MiB per block: the runtime's own
+    granularity.)"""
+    mib = 1 << 20
+    n, v = 400, 40000
+    tab = _upload_table(T, np.random.default_rng(9).integers(0, n, size=(n, v), dtype=np.int32))
+    accept = np.ones(n, dtype=np.uint8)
+    accept[::2] = 0
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    T.table_minimize(tab, accept, [0])[0].close()             # (what the first call sets up is there)
+    T.trim()
+    start = free()
+    tables = [T.table_minimize(tab, accept, [0])[0] for _ in range(100)]
+    assert start - free() > 100 * n * v * 4                   # 6.4 GB
+    for t in tables:
+        t.close()
+    assert start - free() <= (4 << 30) + 256 * 2 * mib
+    T.trim()
+    assert start - free() <= 8 * mib
+    # a table of five eighths the size does not take the larger table's block
+    rows = np.arange(n) % (n * 5 // 8)
+    merged = _upload_table(T, tab.delta.cpu().numpy()[rows])
+    start = free()
+    T.table_minimize(tab, accept, [0])[0].close()
+    small, _, _ = T.table_minimize(merged, accept[rows], [0])
+    assert small.n_rows == n * 5 // 8
+    T.trim()
+    assert start - free() <= n * 5 // 8 * v * 4 * 5 // 4 + 4 * mib
+
+
 def test_set_up_calls_beside_a_capture(T, oracle):
     """Minimising and packing on one stream while another is captured (by a program that allows that: relaxed mode),
     with nothing in the cache and with blocks there that need a wait for the device: both times the same tables."""
