@@ -861,12 +861,15 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
             best_x = make_uint4(d[0], d[1], d[2], d[3]);
         }
     }
-    // The wavefront that holds the workgroup's maximum finishes the row (the first one if nothing
-    // is allowed): each reads the wavefronts' candidates one per lane and folds them across lanes.
+    // The first wavefront that holds the workgroup's maximum finishes the row (the first of all if nothing is allowed):
+    // each reads the wavefronts' candidates one per lane and folds them across lanes.  (Candidates differ in their
+    // tokens, but where every allowed logit of a part is the NaN pattern 0xFFFF, whose key is 0, no token has been noted.)
     const unsigned long long wmax = wave_max_u64(candidate());         // the wavefront's final candidate
     if (lane == 0) wave_best[wave] = wmax;
     __syncthreads();
-    unsigned long long cand = wave_max_u64(lane < ((int)blockDim.x >> 6) ? wave_best[lane] : 0ull);
+    const unsigned long long theirs = lane < ((int)blockDim.x >> 6) ? wave_best[lane] : 0ull;
+    unsigned long long cand = wave_max_u64(theirs);
+    const bool finishes = wave == (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(theirs == cand));
     auto needs_exact = [](unsigned long long c) {
         const uint32_t ku = (uint32_t)(c >> 32) & 0xFFFFu;
         return ku > KU_POS_INF || ku <= KU_NEG_INF || ku == KU_POS_ZERO || ku == KU_NEG_ZERO;
@@ -886,7 +889,7 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
         }
     };
     if constexpr (PDA) {
-        if (cand == 0 ? wave == 0 : wmax == cand) {            // (one wavefront: candidates differ in their tokens)
+        if (finishes) {
             int last = 0;
             if (lane == 0) last = combine_parts(a, b, parts, cand) ? 1 : 0;
             last = __builtin_amdgcn_readfirstlane(last);
@@ -896,8 +899,7 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
             if (lane == 0) s_exact = exact ? 1 : 0;
         }
     } else {
-    const bool finisher = lane == 0 && (cand == 0 ? threadIdx.x == 0 : wmax == cand);
-    if (finisher) {
+    if (finishes && lane == 0) {
         int exact = 0;
         if (combine_parts(a, b, parts, cand)) {
             if (cand == 0) {

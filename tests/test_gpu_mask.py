@@ -169,6 +169,36 @@ def test_special_values_and_ties(T, oracle, dtype):
         _step_and_check(T, oracle, table, tab, lg, dtype, states, masked=False)
 
 
+@pytest.mark.parametrize("n_tokens,batch", [(8192, 1), (40000, 3), (16384, 200), (128256, 600)])
+def test_rows_of_the_smallest_key(T, oracle, n_tokens, batch):
+    """bf16 rows whose allowed logits are all the NaN pattern 0xFFFF, the only one whose order key is 0, in one stretch,
+    in one part or in the whole row: every wavefront there has the same candidate, and one of them may speak for the
+    workgroup.  The steps that follow find the words through which workgroups meet as they should be.  Dense and packed."""
+    rng = np.random.default_rng(n_tokens)
+    tab = _rand_table(4, n_tokens, 0.6, 5)
+    dense = _upload_table(T, tab)
+    counted, _ = T.table_concat([dense])
+    tables = (dense, counted, T.table_pack(dense))
+    states = (np.arange(batch) % 4).astype(np.int32)
+    stride = (n_tokens + 7) // 8 * 8
+    plain = LG.f32_to_bf16_bits(rng.normal(0, 2, size=(batch, stride)).astype(np.float32))
+    whole, part = plain.copy(), plain.copy()
+    whole[:, :] = 0xFFFF
+    part[:, :n_tokens // 2] = 0xFFFF
+    one = whole.copy()
+    one[:, n_tokens - 5:] = plain[:, n_tokens - 5:]
+    st = torch.from_numpy(states).cuda()
+    for lg in (whole, plain, part, plain, one, whole, plain):
+        want = oracle.mask_step(tab, lg, BF16, states, row_stride=stride)
+        dev = _to_dev(lg, BF16)
+        for table in tables:
+            tok = torch.full((batch,), -9, dtype=torch.int32, device="cuda")
+            new = torch.full((batch,), -9, dtype=torch.int32, device="cuda")
+            T.mask_step(table, dev, st, tok, new)
+            torch.cuda.synchronize()
+            assert np.array_equal(tok.cpu().numpy(), want[0]) and np.array_equal(new.cpu().numpy(), want[1])
+
+
 @pytest.mark.parametrize("n_tokens,batch", [(1, 3), (7, 2), (4093, 5), (4096, 5), (8197, 4), (16387, 9), (33001, 200), (32775, 193)])
 def test_penalised_fp32_rows_at_the_edges(T, oracle, n_tokens, batch):
     """fp32 rows written with the penalty, around the 1,024 and 4,096 logits that a workgroup takes per load and per

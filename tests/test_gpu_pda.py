@@ -108,7 +108,7 @@ def test_errors(T):
     assert e.value.code == -4 and "12" in str(e.value)
 
 
-def _decode(T, oracle, pda, table, want, n_tokens, dtype, batch, steps, cap, seed, sigma=2.0, masked_every=3, odd_stride=False):
+def _decode(T, oracle, pda, table, want, n_tokens, dtype, batch, steps, cap, seed, sigma=2.0, masked_every=3, odd_stride=False, all_ones_at=()):
     rng = np.random.default_rng(seed)
     states_np = np.full(batch, pda.start, dtype=np.int32)
     stacks_np = np.full((batch, cap), -7, dtype=np.int32)
@@ -126,6 +126,8 @@ def _decode(T, oracle, pda, table, want, n_tokens, dtype, batch, steps, cap, see
         if s == 2:
             x[:, ::3] = np.nan
         lg_np = x if dtype == F32 else LG.f32_to_bf16_bits(x)
+        if s in all_ones_at:
+            lg_np.view(np.uint32 if dtype == F32 else np.uint16)[:] = 0xFFFFFFFF if dtype == F32 else 0xFFFF
         lg = torch.from_numpy(lg_np).cuda() if dtype == F32 else torch.from_numpy(lg_np.view(np.int16)).cuda().view(torch.bfloat16)
         want_masked = s % masked_every == 0
         out = torch.empty_like(lg) if want_masked else None
@@ -175,6 +177,20 @@ def test_traversal_at_the_edges_of_the_directory(T, oracle, dtype, n_tokens, bat
     pda = P.dyck2()
     table, want, n = _compile_both(T, oracle, pda, toks)
     _decode(T, oracle, pda, table, want, len(toks), dtype, batch, 4, 24, 7, masked_every=100)
+
+
+@pytest.mark.parametrize("n_tokens,batch", [(8191, 3), (33000, 4), (33000, 200)])
+def test_rows_of_the_smallest_key(T, oracle, n_tokens, batch):
+    """Steps on rows that are the NaN pattern 0xFFFF throughout, whose order key is 0: all wavefronts of a workgroup
+    then have the same candidate, and one of them may speak for it; the step after finds the words through which
+    workgroups meet as they should be."""
+    rng = np.random.default_rng(n_tokens)
+    ones = [b"(", b")", b"[", b"]"]
+    toks = ones + [t for t in _vocab(rng, b"()[]x", n_tokens, [], 7) if t not in ones][:n_tokens - 4]
+    rng.shuffle(toks)
+    pda = P.dyck2()
+    table, want, _ = _compile_both(T, oracle, pda, toks)
+    _decode(T, oracle, pda, table, want, len(toks), BF16, batch, 5, 24, 7, masked_every=100, all_ones_at=(1, 2, 4))
 
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
