@@ -1645,6 +1645,7 @@ constexpr int kQueue = 128;            // entries of a wavefront's queues (rings
 constexpr int kWordsAhead = 4;         // 32-bit words of allowed bits (four groups each) a thread has in flight
 constexpr int kDrawThreads = 256;      // workgroup of the draw
 constexpr int kDrawGroups = 2048;      // workgroups that a draw of a smaller batch is split into
+constexpr int kDrawPartGroups = 1 << 27;    // groups whose quads' numbers have their upper bits in common, of 28 below; no part crosses such a line
 constexpr int kDenseQuads = 48;        // lanes with a quad to draw for from which on a wavefront draws in place
 
 // The draw from the whole allowed set.  `parts` workgroups scan a row; one takes groups [g_lo, g_hi).  Only tokens that
@@ -1677,7 +1678,7 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
     __shared__ unsigned long long wave_best[kMaxWaves];
     __shared__ uint2 s_groups[kWaves][kQueue];
     __shared__ __attribute__((aligned(16))) float4 s_logits[kWaves][kQueue];   // a waiting quad's logits, -inf where not allowed
-    __shared__ uint32_t s_quads[kWaves][kQueue];                               // its number << 4 | allowed bits
+    __shared__ uint32_t s_quads[kWaves][kQueue];                               // its number << 4 | allowed bits (without the number's upper bits)
     __shared__ uint32_t s_reached;                             // order key of the best score any wavefront has reached
     if (threadIdx.x == 0) s_reached = 0;
     __syncthreads();
@@ -1691,6 +1692,7 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
     const int n_groups = (V + 7) >> 3;
     const int g_lo = p * groups_per_part;
     const int g_hi = min(n_groups, g_lo + groups_per_part);
+    const uint32_t quad_top = (uint32_t)(g_lo / kDrawPartGroups) * (2u * kDrawPartGroups);
     const uint32_t lane = threadIdx.x & 63u;
     uint2* group_q = s_groups[threadIdx.x >> 6];
     float4* logit_q = s_logits[threadIdx.x >> 6];
@@ -1766,7 +1768,7 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
         const float l[4] = {l4.x, l4.y, l4.z, l4.w};
         q_head += n;
         wave_sync();
-        draw_quads(en >> 4, en & 15u, l);
+        draw_quads(quad_top | (en >> 4), en & 15u, l);
     };
     // Fetched groups are worked on one batch late: the logits of a batch are requested when it is
     // taken from the queue and used when the next batch is taken (or at the end), so that a
@@ -2135,6 +2137,12 @@ int launch_sample_step(const MaskArgs& a, float inv_t, int32_t top_k, uint64_t s
     if (parts < 1) parts = 1;
     int gpp = ((n_groups + parts - 1) / parts + 3) / 4 * 4;
     if (gpp < 4) gpp = 4;
+    if (n_groups > kDrawPartGroups) {                          // parts of a power of two, so that none crosses a line
+        int power = 4;
+        while (power < gpp && power < kDrawPartGroups) power *= 2;
+        gpp = power;
+        parts = (n_groups + gpp - 1) / gpp;
+    }
     if ((int64_t)a.batch * parts > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
     const dim3 grid((unsigned)(a.batch * parts));
     if (a.dtype == TDFA_F32 && a.masked_out) draw_step_kernel<TDFA_F32, true><<<grid, kDrawThreads, 0, stream>>>(a, sp, parts, gpp);

@@ -196,6 +196,33 @@ def test_top_k_edges(T, oracle, dtype, n_tokens):
             assert np.array_equal(_bits(out)[:, :n_tokens], want[2].view(_bits(out).dtype)[:, :n_tokens])
 
 
+def test_draw_beyond_2_30_tokens(T):
+    """A row of more than 2^30 tokens, few of them allowed: the numbers of the tokens' generator blocks outgrow 28 bits.  At a
+    temperature of 1 a score is the logit plus the noise, rounded once, and the noise is what sample_noise gives."""
+    v = 2 ** 30 + 2 ** 21 + 5
+    n, rw = 300, T.allow_row_words(v)
+    rng = np.random.default_rng(3)
+    tokens = np.unique(np.concatenate([rng.integers(0, 2 ** 30, n // 4), rng.integers(2 ** 30, v, n), [2 ** 30, v - 1]]))
+    bits = torch.zeros((1, rw), dtype=torch.int32, device="cuda")
+    words, values = tokens >> 5, (np.uint32(1) << (tokens & 31).astype(np.uint32))
+    first = np.flatnonzero(np.r_[True, words[1:] != words[:-1]])
+    bits[0, torch.from_numpy(words[first]).cuda()] = torch.from_numpy(np.bitwise_or.reduceat(values, first).view(np.int32)).cuda()
+    delta = torch.zeros((1, v), dtype=torch.int32, device="cuda")
+    table = T.table_wrap(delta, bits)
+    lg = torch.zeros((1, (v + 7) // 8 * 8), dtype=torch.bfloat16, device="cuda")
+    at = torch.from_numpy(tokens).cuda()
+    lg[0, at] = torch.from_numpy(rng.normal(0, 2, len(tokens)).astype(np.float32)).cuda().bfloat16()
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    tok, new = torch.empty_like(st), torch.empty_like(st)
+    noise = torch.empty((1, v), dtype=torch.float32, device="cuda")
+    for offset in range(6):
+        T.sample_noise(noise, 11, offset)
+        T.sample_step(table, lg, st, 1.0, 11, offset, tok, new)
+        torch.cuda.synchronize()
+        score = (lg[0, at].float() + noise[0, at]).cpu().numpy()
+        assert int(tok[0]) == tokens[int(score.argmax())] and int(new[0]) == 0
+
+
 @pytest.mark.parametrize("dtype", [F32, BF16])
 def test_special_values(T, oracle, dtype):
     n_tokens = 4096 + 64
