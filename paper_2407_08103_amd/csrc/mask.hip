@@ -1527,8 +1527,8 @@ topk_step_kernel(MaskArgs a, SampleParams sp, int32_t top_k)
     slow = slow || n > (uint32_t)kKeep;
     uint32_t cut = 0;
     if (!slow) {
-        // the k-th largest of the collected keys (fewer than k allowed tokens: no cut)
-        if (n_allowed >= k) {
+        // the k-th largest of the collected keys (fewer than k, so fewer than k allowed tokens: no cut)
+        if (n >= k) {
             if (n <= 128u) {
                 // by counting: a key is the answer if fewer than k keys are greater and at least k are greater or equal
                 for (uint32_t i = n + tid; i < ((n + 3u) & ~3u); i += (uint32_t)T) s_keys[i] = 0;   // pad to whole uint4
@@ -1570,7 +1570,7 @@ topk_step_kernel(MaskArgs a, SampleParams sp, int32_t top_k)
                     if ((mg >> j) & 1u) f(key_f32(as_f32((uint32_t)e[j])));
             }
         };
-        if (n_allowed >= k && !select(for_row, k, &cut)) cut = 0;
+        if (!select(for_row, k, &cut)) cut = 0;                    // fewer than k allowed tokens: no cut
         float reached = -__builtin_inff();                         // a score some token of this wavefront has reached
         for (int base = 0; base < n_groups; base += T) {
             const int g = base + tid;

@@ -196,6 +196,35 @@ def test_top_k_edges(T, oracle, dtype, n_tokens):
             assert np.array_equal(_bits(out)[:, :n_tokens], want[2].view(_bits(out).dtype)[:, :n_tokens])
 
 
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_top_k_of_rows_with_more_allowed_tokens_than_counted(T, oracle, dtype):
+    """The caller allows further tokens in rows of its own buffers, which the library has counted before: the cut is
+    made where the row as it is allows k tokens or more, whatever the count says."""
+    rng = np.random.default_rng(4)
+    v, k = 5000, 50
+    tab = np.full((4, v), DEAD, dtype=np.int32)
+    for q, c in enumerate((3, 49, 50, 2000)):
+        tab[q, rng.choice(v, size=c, replace=False)] = q
+    table, _ = T.table_concat([_upload_table(T, tab)])
+    more = tab.copy()
+    for q in range(4):
+        more[q, rng.choice(v, size=1500, replace=False)] = q
+    both = _upload_table(T, more)
+    table.delta.copy_(both.delta)
+    table.allow.copy_(both.allow)
+    states = np.arange(64, dtype=np.int32) % 4
+    lg = rng.normal(0, 2, size=(64, v)).astype(np.float32)
+    lg = lg if dtype == F32 else LG.f32_to_bf16_bits(lg)
+    st, dev = torch.from_numpy(states).cuda(), _to_dev(lg, dtype)
+    tok, new = torch.empty_like(st), torch.empty_like(st)
+    T.sample_step(table, dev, st, 3.0, 2, 1, tok, new, top_k=k)         # (hot: without the cut other tokens are drawn)
+    torch.cuda.synchronize()
+    want = oracle.sample_step(more, lg, dtype, states, 3.0, 2, 1, top_k=k)
+    free = oracle.sample_step(more, lg, dtype, states, 3.0, 2, 1)
+    assert (want[0] != free[0]).sum() > 16
+    assert np.array_equal(tok.cpu().numpy(), want[0]) and np.array_equal(new.cpu().numpy(), want[1])
+
+
 def test_draw_beyond_2_30_tokens(T):
     """A row of more than 2^30 tokens, few of them allowed: the numbers of the tokens' generator blocks outgrow 28 bits.  At a
     temperature of 1 a score is the logit plus the noise, rounded once, and the noise is what sample_noise gives."""
