@@ -1358,6 +1358,7 @@ topk_step_kernel(MaskArgs a, SampleParams sp, int32_t top_k)
     };
 
     bool slow = huge;
+    uint32_t floor_key = 0;                                        // k allowed tokens or more are known to reach it
     if (few && !huge) {
         // The groups with an allowed token, and where their tokens go among the collected ones: 16 groups per thread
         // and pass, a prefix over the lanes, one addition per wavefront to the two counts.  Then a group per thread.
@@ -1482,6 +1483,7 @@ topk_step_kernel(MaskArgs a, SampleParams sp, int32_t top_k)
             slow = true;                                           // the same in every thread
         } else {
             if (L == KU_POS_ZERO) L = KU_NEG_ZERO;                 // -0 equals +0
+            floor_key = L << 16;
             for_tail([&](int t, Elem x, bool ok) {
                 if (ok && key_f32(as_f32((uint32_t)x)) >> 16 >= L) push(t, as_f32((uint32_t)x));
             });
@@ -1559,15 +1561,17 @@ topk_step_kernel(MaskArgs a, SampleParams sp, int32_t top_k)
             consider(en.x, en.y, (en.x & 2u) ? hi : lo);
         }
     } else {
-        auto for_row = [&](auto&& f) {                             // f(key) for every allowed logit of the row
+        auto for_row = [&](auto&& f) {                             // f(key) for every allowed logit of the row that may be at the cut
             for (int g = tid; g < n_groups; g += T) {
                 const uint32_t mg = valid ? bits[g] : 0u;
                 if (mg == 0) continue;
                 Elem e[8];
                 load_group<DTYPE>(row, g << 3, V, e);
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if ((mg >> j) & 1u) f(key_f32(as_f32((uint32_t)e[j])));
+                for (int j = 0; j < 8; ++j) {
+                    const uint32_t key = key_f32(as_f32((uint32_t)e[j]));
+                    if (((mg >> j) & 1u) && key >= floor_key) f(key);
+                }
             }
         };
         if (!select(for_row, k, &cut)) cut = 0;                    // fewer than k allowed tokens: no cut

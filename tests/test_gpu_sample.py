@@ -225,6 +225,26 @@ def test_top_k_of_rows_with_more_allowed_tokens_than_counted(T, oracle, dtype):
     assert np.array_equal(tok.cpu().numpy(), want[0]) and np.array_equal(new.cpu().numpy(), want[1])
 
 
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("n_tokens", [40000, 131077])
+def test_top_k_among_thousands_of_zeros(T, oracle, dtype, n_tokens):
+    """More logits at the cut than are collected, zeros of both signs among small and negative numbers: the selection over
+    the row starts from the bound that the threads' maxima give, and -0 counts as +0 there as well."""
+    rng = np.random.default_rng(n_tokens)
+    tab = _rand_table(3, n_tokens, 0.8, 7)
+    table = _upload_table(T, tab)
+    states = (np.arange(6) % 3).astype(np.int32)
+    x = -np.abs(rng.normal(0, 2, size=(6, (n_tokens + 7) // 8 * 8))).astype(np.float32)
+    kind = rng.random(x.shape)
+    x[kind < 0.2] = 0.0
+    x[(kind >= 0.2) & (kind < 0.4)] = -0.0
+    x[(kind >= 0.4) & (kind < 0.41)] = np.float32(-1e-39)
+    x[4:, ::3] = np.float32(1e-39)
+    lg = x if dtype == F32 else LG.f32_to_bf16_bits(x)
+    for k in (1, 60, 1000, 20000):
+        _sample_strided(T, oracle, table, tab, lg, dtype, states, 0.9, 5, k, masked=k == 60, top_k=k)
+
+
 def test_draw_beyond_2_30_tokens(T):
     """A row of more than 2^30 tokens, few of them allowed: the numbers of the tokens' generator blocks outgrow 28 bits.  At a
     temperature of 1 a score is the logit plus the noise, rounded once, and the noise is what sample_noise gives."""
