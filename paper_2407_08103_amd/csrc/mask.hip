@@ -652,7 +652,9 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
     // A lane remembers its best key and the group of eight in which its maximum rose to it (the
     // lowest such group; the maximum rises a few times per row at most), with the group's logits
     // and allowed bits, so that the token inside the group is found from registers when needed.
-    uint32_t best = 0, best_g = 0, best_m = 0, any = 0;
+    // (No key may rise above 0, that of the NaN pattern 0xFFFF: the group is then the stretch's first, so that the
+    // wavefronts' candidates differ all the same.)
+    uint32_t best = 0, best_g = (uint32_t)w_lo, best_m = 0, any = 0;
     uint4 best_x = make_uint4(0, 0, 0, 0);
     // `ANY_ORDER`: groups may come in any order, so an equal key from a lower group takes over.
     auto fold_one = [&](auto any_order, int g, const uint4& x, uint32_t m) {
@@ -861,15 +863,13 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
             best_x = make_uint4(d[0], d[1], d[2], d[3]);
         }
     }
-    // The first wavefront that holds the workgroup's maximum finishes the row (the first of all if nothing is allowed):
-    // each reads the wavefronts' candidates one per lane and folds them across lanes.  (Candidates differ in their
-    // tokens, but where every allowed logit of a part is the NaN pattern 0xFFFF, whose key is 0, no token has been noted.)
+    // The wavefront that holds the workgroup's maximum finishes the row (the first one if nothing is allowed; one
+    // wavefront, since candidates differ in their tokens): each reads the wavefronts' candidates one per lane and folds
+    // them across lanes.
     const unsigned long long wmax = wave_max_u64(candidate());         // the wavefront's final candidate
     if (lane == 0) wave_best[wave] = wmax;
     __syncthreads();
-    const unsigned long long theirs = lane < ((int)blockDim.x >> 6) ? wave_best[lane] : 0ull;
-    unsigned long long cand = wave_max_u64(theirs);
-    const bool finishes = wave == (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(theirs == cand));
+    unsigned long long cand = wave_max_u64(lane < ((int)blockDim.x >> 6) ? wave_best[lane] : 0ull);
     auto needs_exact = [](unsigned long long c) {
         const uint32_t ku = (uint32_t)(c >> 32) & 0xFFFFu;
         return ku > KU_POS_INF || ku <= KU_NEG_INF || ku == KU_POS_ZERO || ku == KU_NEG_ZERO;
@@ -889,7 +889,7 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
         }
     };
     if constexpr (PDA) {
-        if (finishes) {
+        if (cand == 0 ? wave == 0 : wmax == cand) {
             int last = 0;
             if (lane == 0) last = combine_parts(a, b, parts, cand) ? 1 : 0;
             last = __builtin_amdgcn_readfirstlane(last);
@@ -899,7 +899,8 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
             if (lane == 0) s_exact = exact ? 1 : 0;
         }
     } else {
-    if (finishes && lane == 0) {
+    const bool finisher = lane == 0 && (cand == 0 ? threadIdx.x == 0 : wmax == cand);
+    if (finisher) {
         int exact = 0;
         if (combine_parts(a, b, parts, cand)) {
             if (cand == 0) {
