@@ -507,7 +507,7 @@ __device__ __forceinline__ unsigned long long gather_scan(const typename ElemOf<
 // the stack (every workgroup of the row has read it by then).
 template <bool WRITE, int kUnroll, bool SKIP, int kBuf = 2, bool PDA = false, bool GATHER = false>
 __global__ void __launch_bounds__(kMaxThreads)
-mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
+mask_step_bf16_kernel(std::conditional_t<PDA, PdaMaskArgs, MaskArgs> a, int parts, int groups_per_part, int stretch)
 {
     static_assert(!PDA || (SKIP && !WRITE), "the push-down step reads its bits into LDS");
     static_assert(!GATHER || (SKIP && !PDA), "the rings of a gathered row lie in the lists' room");
@@ -572,7 +572,13 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
     bool valid = q >= 0 && (int64_t)q < a.n_rows;
     bool surely_wide = false;                         // the state allows so many tokens that the row is streamed whatever the bits say
     if constexpr (!WRITE && !PDA) {
-        const uint32_t n_allowed = valid ? allowed_count(a, q) : kUnknown;
+        // (packed tables do not come to the form with SKIP alone, which need not ask for the edges of a packed row)
+        uint32_t n_allowed = kUnknown;
+        if constexpr (GATHER || !SKIP) {
+            if (valid) n_allowed = allowed_count(a, q);
+        } else if (a.row_allowed != nullptr && valid) {
+            n_allowed = a.row_allowed[q];
+        }
         if (n_allowed != kUnknown) {
             // A state that allows no token (a sequence whose text is complete): no token, the state stays.
             if (n_allowed == 0u) {
@@ -883,7 +889,7 @@ mask_step_bf16_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
     auto traverse = [&](unsigned long long c) {
         if (c == 0) {
             if (lane == 0) write_result(a, b, q, valid, 0ull);
-        } else {
+        } else if constexpr (PDA) {
             pda_traverse(a.pda.edges, a.pda.stacks + (int64_t)b * a.pda.stack_cap, a.pda.depths + b, depth, a.pda.stack_cap, q,
                          (int)(0xFFFFFFFFu - (uint32_t)c), a.tokens + b, a.new_states + b);
         }
@@ -2021,9 +2027,29 @@ BitsInLds bits_in_lds(const MaskArgs& a)
     r.fits = !a.masked_out && r.lds <= (size_t)kMaxBitRowBytes;
     return r;
 }
+
+// Lets the kernels that keep the bits in LDS take more than the default 64 KB, once per device.
+int raise_lds_limit(size_t lds)
+{
+    if (lds <= (size_t)kPlainLdsBytes) return TDFA_OK;
+    static bool raised[64] = {};
+    int dev = 0;
+    TDFA_HIP(hipGetDevice(&dev));
+    if (dev >= 0 && dev < 64 && !raised[dev]) {
+        for (const void* k : {reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true>),
+                              reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true>),
+                              reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true, 2, false, true>),
+                              reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true, 2, false, true>),
+                              reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true, 2, true>),
+                              reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true, 2, true>)})
+            TDFA_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBitRowBytes));
+        raised[dev] = true;
+    }
+    return TDFA_OK;
+}
 }  // namespace
 
-bool mask_step_takes_pda(const MaskArgs& a)
+bool mask_step_takes_pda(const PdaMaskArgs& a)
 {
     return a.batch > 0 && a.dtype != TDFA_F32 && !a.delta && !a.targets && a.n_tokens <= (1 << 27) && bits_in_lds(a).fits;
 }
@@ -2031,7 +2057,6 @@ bool mask_step_takes_pda(const MaskArgs& a)
 int launch_mask_step(const MaskArgs& a, hipStream_t stream)
 {
     if (a.batch <= 0) return TDFA_OK;
-    if (a.pda.class_first && !mask_step_takes_pda(a)) return fail(TDFA_E_UNSUPPORTED, "this step wants one row of allowed bits per sequence");
     if (packed_takes_gather(a)) {
         // a packed table: the scan that reads only the groups with allowed tokens
         int g_parts, g_threads, g_gpp;
@@ -2058,27 +2083,9 @@ int launch_mask_step(const MaskArgs& a, hipStream_t stream)
         return TDFA_OK;
     }
     const int n_waves = threads / 64;
-    if (skip && a.dtype != TDFA_F32 && lds > (size_t)kPlainLdsBytes) {
-        // once per device: let the kernels that keep the bits in LDS take more than the default 64 KB
-        static bool raised[64] = {};
-        int dev = 0;
-        TDFA_HIP(hipGetDevice(&dev));
-        if (dev >= 0 && dev < 64 && !raised[dev]) {
-            for (const void* k : {reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true>),
-                                  reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true>),
-                                  reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true, 2, false, true>),
-                                  reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true, 2, false, true>),
-                                  reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true, 2, true>),
-                                  reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true, 2, true>)})
-                TDFA_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBitRowBytes));
-            raised[dev] = true;
-        }
-    }
-    if (a.pda.class_first) {
-        if (unroll == 1) mask_step_bf16_kernel<false, 1, true, 2, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
-        else mask_step_bf16_kernel<false, 2, true, 2, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
-        TDFA_HIP(hipGetLastError());
-        return TDFA_OK;
+    if (skip && a.dtype != TDFA_F32) {
+        const int rc = raise_lds_limit(lds);
+        if (rc != TDFA_OK) return rc;
     }
     if (a.dtype == TDFA_F32 && !a.masked_out && (size_t)n_waves * (size_t)stretch <= (size_t)kPlainLdsBytes)
         mask_step_f32_kernel<<<grid, kThreads, (size_t)n_waves * (size_t)stretch, stream>>>(a, parts, gpp, stretch);
@@ -2099,6 +2106,22 @@ int launch_mask_step(const MaskArgs& a, hipStream_t stream)
         mask_step_bf16_kernel<false, 1, false><<<grid, kThreads, 0, stream>>>(a, parts, gpp, stretch);
     else
         mask_step_bf16_kernel<false, 2, false><<<grid, kThreads, 0, stream>>>(a, parts, gpp, stretch);
+    TDFA_HIP(hipGetLastError());
+    return TDFA_OK;
+}
+
+int launch_pda_mask_step(const PdaMaskArgs& a, hipStream_t stream)
+{
+    if (a.batch <= 0) return TDFA_OK;
+    if (!mask_step_takes_pda(a)) return fail(TDFA_E_UNSUPPORTED, "this step wants one row of allowed bits per sequence");
+    const BitsInLds sh = bits_in_lds(a);
+    if ((int64_t)a.batch * sh.parts > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
+    const int rc = raise_lds_limit(sh.lds);
+    if (rc != TDFA_OK) return rc;
+    const dim3 grid((unsigned)(a.batch * sh.parts));
+    const unsigned threads = (unsigned)sh.threads;
+    if (sh.unroll == 1) mask_step_bf16_kernel<false, 1, true, 2, true><<<grid, threads, sh.lds, stream>>>(a, sh.parts, sh.gpp, sh.stretch);
+    else mask_step_bf16_kernel<false, 2, true, 2, true><<<grid, threads, sh.lds, stream>>>(a, sh.parts, sh.gpp, sh.stretch);
     TDFA_HIP(hipGetLastError());
     return TDFA_OK;
 }

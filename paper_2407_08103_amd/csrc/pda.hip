@@ -955,7 +955,8 @@ int pda_step_impl(const tdfa_ptable* table, const void* logits_dev, int dtype, i
         if (rc != TDFA_OK) return rc;
     }
     // 16-bit logits: the step kernel finds a sequence's classes itself and ORs their rows as it reads them
-    tdfa::MaskArgs fused = m;
+    tdfa::PdaMaskArgs fused{};
+    static_cast<tdfa::MaskArgs&>(fused) = m;
     fused.allow = table->class_bits;
     fused.n_rows = table->n_class_rows;
     fused.states = states_dev;
@@ -985,7 +986,7 @@ int pda_step_impl(const tdfa_ptable* table, const void* logits_dev, int dtype, i
         const int rc = tdfa::launch_sample_step(m, draw->inv_t, draw->top_k, draw->seed, draw->offset, nullptr, s);
         if (rc != TDFA_OK) return rc;
     } else if (tdfa::mask_step_takes_pda(fused)) {
-        return tdfa::launch_mask_step(fused, s);                // it traverses the edges as well
+        return tdfa::launch_pda_mask_step(fused, s);                // it traverses the edges as well
     } else {
         pda_allow_kernel<<<(unsigned)batch, 256, 0, s>>>(states_dev, stacks_dev, depths_dev, stack_cap, table->n_states, table->class_first,
                                                          table->class_n_pops, table->class_pops, table->class_bits, table->row_words,
