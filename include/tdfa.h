@@ -325,9 +325,12 @@ TDFA_API int tdfa_table_pack_info(const tdfa_table *table, int64_t *n_edges, int
  *   masked_out_dev : device, same shape and type as logits, or NULL to skip the write-back; may
  *                    equal logits_dev.
  * Enqueues on `stream`; steps issued on one stream run in order, so states can be chained from
- * step to step without host synchronisation.  All steps on one device share a small reduction
- * scratch owned by the library, so steps must not overlap in time on different streams of one
- * device.  The scratch is allocated by the first call on a device (room for 4096 sequences) and
+ * step to step without host synchronisation.  Steps meet through a small reduction scratch owned by the
+ * library.  Each of the first 32 streams on a device that steps are issued on has its own, for batches
+ * of up to 65,536 sequences; further streams share those, larger batches share a single one, and a
+ * recorded graph keeps that of the stream it was captured on: steps that share a scratch must not overlap
+ * in time.
+ * The scratch is allocated by the first call on a device (room for 4096 sequences) and
  * replaced by a larger one when a larger batch comes; such a call allocates and clears device
  * memory synchronously and therefore fails with UNSUPPORTED inside a stream capture: make one
  * step at the largest batch size before capturing.  Earlier scratch blocks stay allocated, so

@@ -448,17 +448,26 @@ int make_table(int64_t n_rows, int32_t n_tokens, int32_t* delta_dev, uint32_t* a
 // table's allowed bits.  Tables over buffers that the caller filled (tdfa_table_wrap) have no counts.
 int count_rows(tdfa_table* t, hipStream_t s);
 
-// Cross-workgroup reduction scratch of the decode step: one per device, shared by every table
-// on it, all zero between launches.  A block that has been handed to a launch is never freed
-// (a recorded graph may still name it): growing allocates a larger block and keeps the old one
+// Cross-workgroup reduction scratch of the decode step, shared by every table on a device and all zero between launches:
+// one for each of the first kScratchStreams streams that steps come on, so that steps on different streams may overlap (a
+// draw of 192 to 2,047 sequences needed none before its rows were split).  Streams beyond those share
+// theirs, and for batches of more than kScratchApart sequences there is a single one.  A block that has been handed to a
+// launch is never freed (a recorded graph may still name it): growing allocates a larger block and keeps the old one
 // until the process ends.
 struct DeviceScratch {
     unsigned long long* best = nullptr;
     unsigned int* count = nullptr;      // [cap]: arrival counters
     int32_t cap = 0;
 };
-constexpr int kMaxDevices = 64;
-DeviceScratch g_scratch[kMaxDevices];
+constexpr int kMaxDevices = 64, kScratchStreams = 32;
+constexpr int32_t kScratchApart = 65536;                   // 24 MiB in all
+struct ScratchOfDevice {
+    DeviceScratch all;                                     // n_parts arrays of `cap` words behind one another
+    int n_parts = 1;
+    const void* stream[kScratchStreams];                   // the streams seen, in order
+    int n_streams = 0;
+};
+ScratchOfDevice g_scratch[kMaxDevices];
 std::mutex g_scratch_mutex;
 
 int ensure_scratch(int32_t batch, hipStream_t stream, DeviceScratch* out)
@@ -466,36 +475,48 @@ int ensure_scratch(int32_t batch, hipStream_t stream, DeviceScratch* out)
     int dev = 0;
     TDFA_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= kMaxDevices) return fail(TDFA_E_UNSUPPORTED, "device index %d", dev);
+    // (one handle stands for a stream per thread)
+    static thread_local char this_thread;
+    const void* key = stream == hipStreamPerThread ? static_cast<const void*>(&this_thread) : static_cast<const void*>(stream);
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
-    DeviceScratch* sc = &g_scratch[dev];
-    if (batch <= sc->cap) {
-        *out = *sc;
-        return TDFA_OK;
+    ScratchOfDevice* sc = &g_scratch[dev];
+    if (batch > sc->all.cap) {
+        // Growing allocates and clears, which a stream capture must not contain.
+        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &capturing) != hipSuccess) (void)hipGetLastError();
+        if (capturing != hipStreamCaptureStatusNone)
+            return fail(TDFA_E_UNSUPPORTED,
+                        "the reduction scratch must grow for batch %d, which cannot happen inside a stream capture: "
+                        "make one step at this batch size before capturing",
+                        batch);
+        int64_t cap = sc->all.cap ? sc->all.cap : 4096;
+        while (cap < batch) cap *= 2;
+        if (cap > 0x7FFFFFFF) cap = 0x7FFFFFFF;
+        const int n_parts = cap <= kScratchApart ? kScratchStreams : 1;
+        const size_t words = (size_t)cap * (size_t)n_parts;
+        DeviceScratch grown;
+        int rc = device_alloc(&grown.best, words);
+        if (rc != TDFA_OK) return rc;
+        rc = device_alloc(&grown.count, words);
+        if (rc != TDFA_OK) {
+            (void)hipFree(grown.best);
+            return rc;
+        }
+        // cleared before the call returns, so a step on any stream finds zeros
+        TDFA_HIP(hipMemset(grown.best, 0, sizeof(unsigned long long) * words));
+        TDFA_HIP(hipMemset(grown.count, 0, sizeof(unsigned int) * words));
+        grown.cap = (int32_t)cap;
+        sc->all = grown;                                     // the old block, if any, stays allocated
+        sc->n_parts = n_parts;
     }
-    // Growing allocates and clears, which a stream capture must not contain.
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &capturing) != hipSuccess) (void)hipGetLastError();
-    if (capturing != hipStreamCaptureStatusNone)
-        return fail(TDFA_E_UNSUPPORTED,
-                    "the reduction scratch must grow for batch %d, which cannot happen inside a stream capture: "
-                    "make one step at this batch size before capturing",
-                    batch);
-    int32_t cap = sc->cap ? sc->cap : 4096;
-    while (cap < batch) cap *= 2;
-    DeviceScratch grown;
-    int rc = device_alloc(&grown.best, (size_t)cap);
-    if (rc != TDFA_OK) return rc;
-    rc = device_alloc(&grown.count, (size_t)cap);
-    if (rc != TDFA_OK) {
-        (void)hipFree(grown.best);
-        return rc;
-    }
-    // cleared before the call returns, so a step on any stream finds zeros
-    TDFA_HIP(hipMemset(grown.best, 0, sizeof(unsigned long long) * (size_t)cap));
-    TDFA_HIP(hipMemset(grown.count, 0, sizeof(unsigned int) * (size_t)cap));
-    grown.cap = cap;
-    *sc = grown;                                             // the old block, if any, stays allocated
-    *out = grown;
+    int i = 0;
+    while (i < sc->n_streams && sc->stream[i] != key) ++i;
+    if (i == kScratchStreams) i = (int)(reinterpret_cast<uintptr_t>(key) >> 4) & (kScratchStreams - 1);
+    else if (i == sc->n_streams) sc->stream[sc->n_streams++] = key;
+    const size_t first = (size_t)(i % sc->n_parts) * (size_t)sc->all.cap;
+    out->best = sc->all.best + first;
+    out->count = sc->all.count + first;
+    out->cap = sc->all.cap;
     return TDFA_OK;
 }
 

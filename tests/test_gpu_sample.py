@@ -245,6 +245,49 @@ def test_top_k_among_thousands_of_zeros(T, oracle, dtype, n_tokens):
         _sample_strided(T, oracle, table, tab, lg, dtype, states, 0.9, 5, k, masked=k == 60, top_k=k)
 
 
+def test_steps_on_two_streams_at_once(T):
+    """Draws and greedy steps whose rows several workgroups share, on two streams that are held back until both have all
+    of theirs waiting: the same tokens as one after the other, and again afterwards."""
+    rng = np.random.default_rng(12)
+    v, steps = 40000, 40
+    table = _upload_table(T, _rand_table(5, v, 0.7, 3))
+    big, small = 256, 24
+    st = torch.from_numpy((np.arange(big) % 5).astype(np.int32)).cuda()
+    lg = [torch.from_numpy(rng.normal(0, 2, size=(big, v)).astype(np.float32)).cuda().bfloat16() for _ in range(2)]
+
+    def run(which, tok, new):
+        for i in range(steps):
+            T.sample_step(table, lg[which], st, 1.0, 5, i + 100 * which, tok[i], new[i])
+            T.mask_step(table, lg[which][i:i + small], st[:small], tok[steps + i], new[steps + i])
+
+    def empty():
+        return torch.full((2, 2 * steps, big), -9, dtype=torch.int32, device="cuda")
+
+    want, want_new = empty(), empty()
+    for which in range(2):
+        run(which, want[which], want_new[which])
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    a = torch.ones((8192, 8192), dtype=torch.bfloat16, device="cuda")
+    held = [torch.empty_like(a) for _ in streams]
+    for _ in range(2):
+        tok, new = empty(), empty()
+        torch.cuda.synchronize()
+        for s, out in zip(streams, held):
+            with torch.cuda.stream(s):
+                for _ in range(8):
+                    torch.mm(a, a, out=out)
+        for which, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                run(which, tok[which], new[which])
+        torch.cuda.synchronize()
+        assert torch.equal(tok, want) and torch.equal(new, want_new)
+    tok, new = empty(), empty()
+    run(0, tok[0], new[0])
+    torch.cuda.synchronize()
+    assert torch.equal(tok[0], want[0])
+
+
 def test_draw_beyond_2_30_tokens(T):
     """A row of more than 2^30 tokens, few of them allowed: the numbers of the tokens' generator blocks outgrow 28 bits.  At a
     temperature of 1 a score is the logit plus the noise, rounded once, and the noise is what sample_noise gives."""
