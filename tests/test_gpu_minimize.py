@@ -179,10 +179,21 @@ def test_stacked_with_several_starts(T, oracle):
     _check(T, oracle, _upload_table(T, ref), ref, accept, starts)
 
 
+def _hold(stream):
+    """Work on `stream` that lasts some tens of milliseconds: what is enqueued on it next is still waiting while the host
+    goes on.  (Products of 8,192 x 8,192, two floating-point operations for each of 2^39 terms.)"""
+    with torch.cuda.stream(stream):
+        a = torch.ones((8192, 8192), dtype=torch.bfloat16, device="cuda")
+        out = torch.empty_like(a)
+        for _ in range(40):
+            torch.mm(a, a, out=out)
+    return a, out                                             # (kept by the caller until the stream is done)
+
+
 def test_blocks_of_a_destroyed_table_in_use_on_another_stream(T, oracle):
-    """A minimised table is destroyed while steps on another stream still read it; the next minimisations and packings
-    take blocks of its size.  The steps see the table as it was (they are enqueued before, and the block is handed
-    out only after a wait), and tdfa_trim gives the memory back."""
+    """A minimised table is destroyed while steps on another stream wait to read it; the next minimisation finds one
+    block that fits its rows, that table's.  The steps see the table as it was: the block is handed out only after a wait,
+    so they are done when the call returns.  tdfa_trim gives the memory back."""
     rng = np.random.default_rng(5)
     n, v, steps, batch = 400, 40000, 24, 64
     a_np = rng.integers(0, n, size=(n, v), dtype=np.int32)
@@ -205,11 +216,15 @@ def test_blocks_of_a_destroyed_table_in_use_on_another_stream(T, oracle):
         assert small.n_rows == n and (mp == np.arange(n)).all()       # nothing merges: the same rows under the same names
         q = st.clone()
         torch.cuda.synchronize()
+        held = _hold(side)
         with torch.cuda.stream(side):
             for _ in range(steps):
                 T.mask_step(small, lg, q, tok, q)
         small.close()
+        assert not side.query()                               # (destroying the table has not waited for the steps)
         other, _, _ = T.table_minimize(b, accept, [0])
+        assert side.query()
+        del held
         packed = T.table_pack(other)
         torch.cuda.synchronize()
         assert np.array_equal(q.cpu().numpy(), want)
@@ -220,17 +235,6 @@ def test_blocks_of_a_destroyed_table_in_use_on_another_stream(T, oracle):
     kept = torch.cuda.mem_get_info()[0]
     T.trim()
     assert torch.cuda.mem_get_info()[0] >= kept + n * v * 4
-
-
-def _hold(stream):
-    """Work on `stream` that lasts some tens of milliseconds: what is enqueued on it next is still waiting while the host
-    goes on.  (Products of 8,192 x 8,192, two floating-point operations for each of 2^39 terms.)"""
-    with torch.cuda.stream(stream):
-        a = torch.ones((8192, 8192), dtype=torch.bfloat16, device="cuda")
-        out = torch.empty_like(a)
-        for _ in range(40):
-            torch.mm(a, a, out=out)
-    return a, out                                             # (kept by the caller until the stream is done)
 
 
 @pytest.mark.parametrize("minimised", [True, False])
