@@ -185,10 +185,9 @@ def test_rows_of_the_smallest_key(T, oracle, n_tokens, batch):
     then have the same candidate, and one of them may speak for it; the step after finds the words through which
     workgroups meet as they should be."""
     rng = np.random.default_rng(n_tokens)
-    ones = [b"(", b")", b"[", b"]"]
-    toks = ones + [t for t in _vocab(rng, b"()[]x", n_tokens, [], 7) if t not in ones][:n_tokens - 4]
-    rng.shuffle(toks)
-    pda = P.dyck2()
+    toks = [t for t in _vocab(rng, b"abcdefgh()", n_tokens, [], 7) if t][:n_tokens]
+    letters = [(0, chr(c), (), 0, ()) for c in b"abcdefgh"]                # most tokens are letters alone: always allowed
+    pda = P.make_pda(1, 0, [0], letters + [(0, "(", (), 0, (1,)), (0, ")", (1,), 0, ())])
     table, want, _ = _compile_both(T, oracle, pda, toks)
     _decode(T, oracle, pda, table, want, len(toks), BF16, batch, 5, 24, 7, masked_every=100, all_ones_at=(1, 2, 4))
 
