@@ -505,9 +505,9 @@ __device__ __forceinline__ unsigned long long gather_scan(const typename ElemOf<
 // finds those classes (one per lane) before it reads its stretch of bits, and ORs the rows as it
 // reads them.  At the end the wavefront that finishes the row traverses the chosen token's edge, which also moves
 // the stack (every workgroup of the row has read it by then).
-template <bool WRITE, int kUnroll, bool SKIP, int kBuf = 2, bool PDA = false, bool GATHER = false>
-__global__ void __launch_bounds__(kMaxThreads)
-mask_step_bf16_kernel(std::conditional_t<PDA, PdaMaskArgs, MaskArgs> a, int parts, int groups_per_part, int stretch)
+template <bool WRITE, int kUnroll, bool SKIP, int kBuf, bool PDA, bool GATHER>
+__device__ __forceinline__ void mask_step_bf16(const std::conditional_t<PDA, PdaMaskArgs, MaskArgs>& a, int parts, int groups_per_part,
+                                               int stretch)
 {
     static_assert(!PDA || (SKIP && !WRITE), "the push-down step reads its bits into LDS");
     static_assert(!GATHER || (SKIP && !PDA), "the rings of a gathered row lie in the lists' room");
@@ -936,6 +936,26 @@ mask_step_bf16_kernel(std::conditional_t<PDA, PdaMaskArgs, MaskArgs> a, int part
     } else {
         if (threadIdx.x == 0) write_result(a, b, q, valid, c);
     }
+}
+
+template <bool WRITE, int kUnroll, bool SKIP, int kBuf = 2, bool PDA = false>
+__global__ void __launch_bounds__(kMaxThreads)
+mask_step_bf16_kernel(std::conditional_t<PDA, PdaMaskArgs, MaskArgs> a, int parts, int groups_per_part, int stretch)
+{
+    mask_step_bf16<WRITE, kUnroll, SKIP, kBuf, PDA, false>(a, parts, groups_per_part, stretch);
+}
+
+// The same for launches of more workgroups than compute units: at most 80 scalar registers, or eight wavefronts of a
+// SIMD do not find room and a compute unit holds one workgroup of 1,024 threads at a time, not two (the compiler counts up
+// to 100 as room for eight; the counters show half the wavefronts in flight from 94 on).  128,256 tokens, packed
+// tables, every row sparse: 1,024 rows 16.7 -> 13.5 us (50 signatures) and 14.4 -> 11.2 us (16 schemas), 512 rows 11.3 ->
+// 8.5 us; 1,024 rows of 64 schemas' states on a dense table 31.8 -> 26.4 us; push-down step, 512 rows 28.1 -> 24.6 us, 1,024
+// rows 51.6 -> 43.0 us.  The registers that are kept in lanes for that cost launches that fill the chip once 0.2 to 0.5 us.
+template <int kUnroll, bool PDA, bool GATHER>
+__global__ void __launch_bounds__(kMaxThreads) __attribute__((amdgpu_num_sgpr(80)))
+mask_step_bf16_many_kernel(std::conditional_t<PDA, PdaMaskArgs, MaskArgs> a, int parts, int groups_per_part, int stretch)
+{
+    mask_step_bf16<false, kUnroll, true, 2, PDA, GATHER>(a, parts, groups_per_part, stretch);
 }
 
 // One step on fp32 logits.  Like the 16-bit kernel, every wavefront first reads the allowed bytes of
@@ -2038,10 +2058,11 @@ int raise_lds_limit(size_t lds)
     if (dev >= 0 && dev < 64 && !raised[dev]) {
         for (const void* k : {reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true>),
                               reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true>),
-                              reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true, 2, false, true>),
-                              reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true, 2, false, true>),
+                              reinterpret_cast<const void*>(mask_step_bf16_many_kernel<1, false, true>),
+                              reinterpret_cast<const void*>(mask_step_bf16_many_kernel<2, false, true>),
                               reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true, 2, true>),
-                              reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true, 2, true>)})
+                              reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true, 2, true>),
+                              reinterpret_cast<const void*>(mask_step_bf16_many_kernel<2, true, false>)})
             TDFA_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBitRowBytes));
         raised[dev] = true;
     }
@@ -2096,8 +2117,8 @@ int launch_mask_step(const MaskArgs& a, hipStream_t stream)
     else if (a.masked_out)
         mask_step_bf16_kernel<true, 2, false><<<grid, kThreads, 0, stream>>>(a, parts, gpp, stretch);
     else if (skip && (a.batch >= kGatherRows || !a.delta)) {
-        if (unroll == 1) mask_step_bf16_kernel<false, 1, true, 2, false, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
-        else mask_step_bf16_kernel<false, 2, true, 2, false, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
+        if (unroll == 1) mask_step_bf16_many_kernel<1, false, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
+        else mask_step_bf16_many_kernel<2, false, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
     } else if (skip && unroll == 1)
         mask_step_bf16_kernel<false, 1, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
     else if (skip)
@@ -2120,7 +2141,10 @@ int launch_pda_mask_step(const PdaMaskArgs& a, hipStream_t stream)
     if (rc != TDFA_OK) return rc;
     const dim3 grid((unsigned)(a.batch * sh.parts));
     const unsigned threads = (unsigned)sh.threads;
-    if (sh.unroll == 1) mask_step_bf16_kernel<false, 1, true, 2, true><<<grid, threads, sh.lds, stream>>>(a, sh.parts, sh.gpp, sh.stretch);
+    // (a workgroup of 1,024 threads to each of 256 compute units, or smaller ones: all are in flight in either form)
+    if (sh.threads == kMaxThreads && a.batch > 256)
+        mask_step_bf16_many_kernel<2, true, false><<<grid, threads, sh.lds, stream>>>(a, sh.parts, sh.gpp, sh.stretch);
+    else if (sh.unroll == 1) mask_step_bf16_kernel<false, 1, true, 2, true><<<grid, threads, sh.lds, stream>>>(a, sh.parts, sh.gpp, sh.stretch);
     else mask_step_bf16_kernel<false, 2, true, 2, true><<<grid, threads, sh.lds, stream>>>(a, sh.parts, sh.gpp, sh.stretch);
     TDFA_HIP(hipGetLastError());
     return TDFA_OK;
