@@ -397,9 +397,13 @@ constexpr int kEarlyWaves = 8;         // wavefronts of a workgroup that request
 // us.  With 8 instead of 32 the states that allow 4 to 12 % are gathered too, and streaming them is faster (the
 // same signatures 36 -> 51 us); 64 is as good as 32.
 constexpr uint32_t kSparseShare = 32;
-// Gathering pays where sparse rows share a compute unit; for fewer rows of a dense table it gains nothing, and the code
-// alone costs the step 0.15 us (380 rows of 69,160 tokens 14.80 -> 14.95 us).  Packed tables take it at any size.
-constexpr int kGatherRows = 512;
+// Gathering pays where rows share a compute unit, and so does the form of the step kernel that does it, two of whose
+// workgroups a compute unit holds (below): rows of a dense table take it from one and a half per compute unit on.  States
+// anywhere in the texts, rows of states that allow few tokens, and rows of states that allow most of 128,256 tokens,
+// without -> with: 300 rows 17.0 -> 15.8, 9.4 -> 8.7 and 19.1 -> 18.0 us for 50 signatures, but 13.3 -> 14.6 us for the texts
+// of 16 schemas; 257 rows 12.1 -> 14.2 us for those of the signatures; 380 rows 17.5 -> 16.2, 9.8 -> 8.7 and 19.7 -> 18.5 us,
+// 16.6 -> 15.1 us for the schemas; 511 rows 18.6 -> 17.2, 10.8 -> 8.7 and 23.3 -> 21.6 us.  Packed tables take it at any size.
+constexpr int kGatherRows = 384;
 
 constexpr int kGatherQueue = 128;      // groups a wavefront's ring holds (a power of two; 64 are fetched at a time)
 

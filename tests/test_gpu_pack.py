@@ -121,11 +121,11 @@ def test_random_tables(T, oracle, n_rows, n_tokens, p_live):
     assert np.array_equal(hist.cpu().numpy(), want_hist) and np.array_equal(nv.cpu().numpy(), want_nv)
 
 
-@pytest.mark.parametrize("n_tokens,batch", [(4001, 7), (33001, 3), (40007, 200), (131077, 193), (4001, 511), (4001, 512), (33001, 512),
+@pytest.mark.parametrize("n_tokens,batch", [(4001, 7), (33001, 3), (40007, 200), (131077, 193), (4001, 383), (4001, 384), (33001, 384),
                                             (131077, 513)])
 def test_rows_around_the_gathering_switch(T, oracle, n_tokens, batch):
     """Tables that know how many tokens a state allows, with states on both sides of the count below which a row
-    is gathered (one token in 32), packed and dense, below and from the 512 rows on with which rows of a dense table
+    is gathered (one token in 32), packed and dense, below and from the 384 rows on with which rows of a dense table
     are gathered: exact integers, so no tolerance."""
     rng = np.random.default_rng(n_tokens)
     counts = [0, 1, n_tokens // 32 - 1, n_tokens // 32, n_tokens // 32 + 1, n_tokens // 4, n_tokens]
