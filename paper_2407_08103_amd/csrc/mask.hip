@@ -393,8 +393,8 @@ constexpr int kEarlyWaves = 8;         // wavefronts of a workgroup that request
 
 // A state known to allow less than this part of the vocabulary (one in ...) is gathered by the workgroup instead of
 // each wavefront finding out about its own stretch.  1,024 rows of 128,256 tokens whose states allow few tokens:
-// 20.0 -> 16.5 us (50 signatures), 18.2 -> 14.0 us (16 schemas); states anywhere in the texts of 16 schemas 30.6 -> 29.2
-// us.  With 8 instead of 32 the states that allow 4 to 12 % are gathered too, and streaming them is faster (the
+// 19.7 -> 16.4 us (50 signatures), 17.8 -> 14.0 us (16 schemas); states anywhere in the texts of 16 schemas 30.0 -> 28.8
+// us (with two workgroups per compute unit, below: 12.9, 10.6 and 24.7 us).  With 8 instead of 32 the states that allow 4 to 12 % are gathered too, and streaming them is faster (the
 // same signatures 36 -> 51 us); 64 is as good as 32.
 constexpr uint32_t kSparseShare = 32;
 // Gathering pays where rows share a compute unit, and so does the form of the step kernel that does it, two of whose
@@ -1696,11 +1696,13 @@ constexpr int kDenseQuads = 48;        // lanes with a quad to draw for from whi
 // instructions (noise_bound) lets all but about one token in 10^4 go without them.
 //
 // Bound by the instructions issued: a generator block is 18 multiplications (64-bit products, at the full rate)
-// and as many three-input exclusive-ors, the bounds six instructions per token.  A workgroup of 1,024 threads per row (a compute unit with a
+// and as many three-input exclusive-ors, the bounds six instructions per token.  (Counters, the 256 sequences below: 8,800
+// vector instructions per SIMD of four cycles each, 62 % of the launch's cycles on all SIMDs, and 39 MB fetched, which the
+// memory delivers in a quarter of the time.)  A workgroup of 1,024 threads per row (a compute unit with a
 // row that allows most tokens works for 45 us while those with sparse rows idle) and a queue of single tokens, each with
 // a generator block and two logarithms of its own, took longer: T = 1, 128,256 tokens, bf16, 256 sequences anywhere in
 // the texts of 50 signatures 42.4 -> 28.2 us, all in states that allow most tokens 45.9 -> 36.3 us (1,024 sequences: 139
-// -> 89 and 166 -> 105 us), all in states that allow few 9.3 -> 9.9 us.
+// -> 89 and 166 -> 105 us), all in states that allow few 9.8 -> 10.2 us (512 sequences 13.7 -> 11.4 us).
 // A queue belongs to one wavefront, so the loop needs no workgroup barrier; the maximum does not depend on the
 // order because candidates are compared as (score, lowest id).
 template <int DTYPE, bool WRITE>
@@ -2005,7 +2007,7 @@ void stream_shape(const MaskArgs& a, int* parts_out, int* threads_out, int* gpp_
 namespace {
 // A packed table takes the step kernel of the dense ones on 16-bit logits without a penalised row (512 rows of a
 // constraint's states at 128,256 tokens: 29.8 us by the gathering scan alone, whose wide rows are compared element
-// by element, 17 us by the step kernel); fp32 logits, where that scan reads wide rows as fast and sparse ones faster
+// by element, 15.6 us by the step kernel); fp32 logits, where that scan reads wide rows as fast and sparse ones faster
 // (1,024 rows: 67 against 87 us), and penalised rows stay with it, as do rows beyond the step kernel's 32-bit offsets.
 bool packed_takes_gather(const MaskArgs& a)
 {

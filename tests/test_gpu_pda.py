@@ -165,7 +165,7 @@ def test_decode_steps(T, oracle, dtype, name, make, alphabet, n_random, extra):
 
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
-@pytest.mark.parametrize("n_tokens,batch", [(63, 5), (64, 5), (65, 200), (129, 3), (8191, 3), (33000, 4), (33000, 200)])
+@pytest.mark.parametrize("n_tokens,batch", [(63, 5), (64, 5), (65, 200), (129, 3), (8191, 3), (33000, 4), (33000, 200), (33000, 300)])
 def test_traversal_at_the_edges_of_the_directory(T, oracle, dtype, n_tokens, batch):
     """Vocabularies around the 64 tokens of a directory entry, rows that one and that several workgroups share, and the
     row whose token the exact scan decides (step 2: NaN); the step without a penalised row traverses the edge itself."""
@@ -179,7 +179,7 @@ def test_traversal_at_the_edges_of_the_directory(T, oracle, dtype, n_tokens, bat
     _decode(T, oracle, pda, table, want, len(toks), dtype, batch, 4, 24, 7, masked_every=100)
 
 
-@pytest.mark.parametrize("n_tokens,batch", [(8191, 3), (33000, 4), (33000, 200)])
+@pytest.mark.parametrize("n_tokens,batch", [(8191, 3), (33000, 4), (33000, 200), (33000, 300)])
 def test_rows_of_the_smallest_key(T, oracle, n_tokens, batch):
     """Steps on rows that are the NaN pattern 0xFFFF throughout, whose order key is 0: all wavefronts of a workgroup
     then have the same candidate, and one of them may speak for it; the step after finds the words through which
