@@ -1789,10 +1789,12 @@ int tdfa_table_minimize(const tdfa_table* table, const uint8_t* accept_host, con
         if (start_states_host[i] < 0 || start_states_host[i] >= table->n_rows)
             return fail(TDFA_E_INVALID_ARG, "start state %d is not a row of the table", start_states_host[i]);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    // bits of a table the library has written mark its edges; of buffers that a caller wraps only the entries are looked at
+    const uint32_t* bits = table->row_allowed ? table->allow : nullptr;
     std::vector<int32_t> first_rows, map;
     int rc;
     try {
-        rc = minimize_table(table->delta, table->n_rows, table->n_tokens, accept_host, start_states_host, n_starts, s,
+        rc = minimize_table(table->delta, bits, table->row_words, table->n_rows, table->n_tokens, accept_host, start_states_host, n_starts, s,
                             &first_rows, &map);
     } catch (const std::bad_alloc&) {
         return fail(TDFA_E_OOM, "host allocation failed");
@@ -1813,7 +1815,7 @@ int tdfa_table_minimize(const tdfa_table* table, const uint8_t* accept_host, con
         tdfa_table_destroy(t);
         return fail(TDFA_E_OOM, "host allocation failed");
     }
-    rc = launch_compact_rows(table->delta, table->n_tokens, table->row_words, first_rows, map, t->delta, t->allow, s);
+    rc = launch_compact_rows(table->delta, bits, table->n_tokens, table->row_words, first_rows, map, t->delta, t->allow, s);
     if (rc == TDFA_OK) rc = count_rows(t, s);
     if (rc != TDFA_OK) {
         tdfa_table_destroy(t);
@@ -1860,13 +1862,8 @@ int tdfa_table_pack(const tdfa_table* table, void* stream, tdfa_table** out)
     int rc = hipGetDevice(&dev) == hipSuccess ? TDFA_OK : fail(TDFA_E_DEVICE, "no current device");
     if (rc == TDFA_OK) rc = block_alloc(&allow, (size_t)t->n_rows * (size_t)t->row_words * sizeof(uint32_t));
     if (rc == TDFA_OK) t->allow = static_cast<uint32_t*>(allow.ptr);
-    if (rc == TDFA_OK && t->n_rows > 0 && t->row_words > 0) {
-        hipError_t e = hipMemcpyAsync(t->allow, table->allow, (size_t)t->n_rows * (size_t)t->row_words * sizeof(uint32_t),
-                                      hipMemcpyDeviceToDevice, s);
-        if (e != hipSuccess) rc = fail(TDFA_E_DEVICE, "copy of the allowed bits: %s", hipGetErrorString(e));
-    }
     if (rc == TDFA_OK)
-        rc = pack_table(table->delta, table->allow, t->n_rows, t->n_tokens, t->row_words, s, &dir, &row_begin, &targets, &t->n_edges);
+        rc = pack_table(table->delta, table->allow, t->n_rows, t->n_tokens, t->row_words, t->allow, s, &dir, &row_begin, &targets, &t->n_edges);
     if (rc == TDFA_OK && !keep_blocks(t, dev, {allow, dir, row_begin, targets})) rc = fail(TDFA_E_OOM, "host allocation failed");
     if (rc == TDFA_OK) {
         t->dir = static_cast<uint32_t*>(dir.ptr);

@@ -25,6 +25,10 @@
 // A row with more distinct targets than the workgroup's table in LDS holds (a table that is not
 // sparse in this sense), or a failed comparison, sends the whole call down the dense path: the same
 // steps with the host driving rounds of kernels that stream the table's rows.
+//
+// Two entries in three of an ordinary table are DEAD, and most of them lie in long runs (states that allow a few
+// hundred tokens).  Where the library has written the table its allowed bits say where the edges are, so the passes over
+// the rows (lists, comparison, renaming) read the bits, an entry's 32nd part, and then only the entries behind a set bit.
 #include <algorithm>
 #include <cstring>
 #include <new>
@@ -36,6 +40,35 @@ namespace tdfa {
 namespace {
 
 constexpr int kThreads = 256;
+
+// A wavefront takes a row in spans of 64 * CHUNKS tokens: 2 * CHUNKS words of bits, a word in each of the first lanes, that
+// say which entries are read.  BITS: the row's allowed bits; otherwise every token of the row counts as one to read.
+template <bool BITS, int CHUNKS>
+__device__ __forceinline__ uint32_t span_word(const uint32_t* bits, int64_t w0, int lane, int32_t n_tokens)
+{
+    const int64_t wi = w0 + lane;
+    const int64_t rem = (int64_t)n_tokens - 32 * wi;
+    if (lane >= 2 * CHUNKS || rem <= 0) return 0u;
+    const uint32_t w = BITS ? bits[wi] : 0xFFFFFFFFu;
+    return rem >= 32 ? w : w & ((1u << rem) - 1u);
+}
+
+// the bits of the span's chunk c: an execution mask
+__device__ __forceinline__ unsigned long long span_mask(uint32_t w, int c)
+{
+    return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)w, 2 * c + 1) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)w, 2 * c);
+}
+
+// the entries of the span's tokens whose bit is set, a token per lane and chunk, all loads in flight; DEAD for the others
+template <int CHUNKS>
+__device__ __forceinline__ void span_load(const int32_t* row, int64_t w0, int lane, uint32_t w, int32_t (&v)[CHUNKS])
+{
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+        v[c] = TDFA_DEAD;
+        if (__builtin_amdgcn_inverse_ballot_w64(span_mask(w, c))) v[c] = __builtin_nontemporal_load(row + 32 * w0 + 64 * c + lane);
+    }
+}
 
 // rows[i] is scanned: every live entry marks its target in `mark` (bytes; equal stores may race).
 __global__ void __launch_bounds__(kThreads)
@@ -100,19 +133,58 @@ row_hash_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, const int32
     }
 }
 
-// rows[i] and first_of[i] (the first row of its class) must agree, entry by entry, on the class
-// of the target.
-__global__ void __launch_bounds__(kThreads)
-verify_classes_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, const int32_t* __restrict__ rows,
-                      const int32_t* __restrict__ first_of, const int32_t* __restrict__ cls, int32_t* __restrict__ mismatch)
+// rows[i] and first_of[i] (the first row of its class) must agree, entry by entry, on the class of the target: the
+// dense path's comparison of n pairs, and the sparse path's (BITS where the table's allowed bits can be relied on).
+//
+// Workgroups take pairs in turn, with the classes in LDS where they fit (LDS_CLS), and a wavefront has the entries of
+// kVerifyChunks * 64 tokens of both rows in flight.  Pieces of rows and not whole ones, because there are about as many pairs
+// as workgroups.  1,142 pairs of 128,256 tokens: 317 us with every entry read and the classes in memory, 180 us by the bits
+// with a workgroup per pair, 135 us so.
+constexpr int kVerifyThreads = 512;
+constexpr int kVerifyChunks = 8;
+constexpr int kPieceWords = 128;       // words of bits of a piece of a row (4,096 tokens): what a wavefront takes at a time
+constexpr size_t kMapLdsBytes = 64 * 1024;
+
+template <bool BITS, bool LDS_CLS>
+__global__ void __launch_bounds__(kVerifyThreads)
+verify_classes_kernel(const int32_t* __restrict__ delta, const uint32_t* __restrict__ allow, int32_t n_tokens, int64_t row_words, int64_t n,
+                      int32_t n_old, const int32_t* __restrict__ rows, const int32_t* __restrict__ first_of, const int32_t* __restrict__ cls,
+                      int32_t* __restrict__ mismatch)
 {
-    const int32_t* a = delta + (size_t)rows[blockIdx.y] * n_tokens;
-    const int32_t* b = delta + (size_t)first_of[blockIdx.y] * n_tokens;
+    extern __shared__ int32_t s_cls[];
+    if constexpr (LDS_CLS) {
+        for (int i = threadIdx.x; i < n_old; i += kVerifyThreads) s_cls[i] = cls[i];
+        __syncthreads();
+    }
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    constexpr int kSpan = 2 * kVerifyChunks;                       // in words of bits
     bool bad = false;
-    for (int t = blockIdx.x * kThreads + threadIdx.x; t < n_tokens; t += gridDim.x * kThreads) {
-        const int32_t x = a[t], y = b[t];
-        const int32_t cx = x >= 0 ? cls[x] : -1, cy = y >= 0 ? cls[y] : -1;
-        bad |= cx != cy;
+    // a wavefront takes pieces of pairs in turn
+    const int64_t per_row = (row_words + kPieceWords - 1) / kPieceWords, n_waves = (int64_t)gridDim.x * (kVerifyThreads / 64);
+    for (int64_t j = (int64_t)blockIdx.x * (kVerifyThreads / 64) + wave; j < n * per_row; j += n_waves) {
+        const int64_t i = j / per_row, lo = (j - i * per_row) * kPieceWords, hi = min(row_words, lo + kPieceWords);
+        const int32_t *a = delta + (size_t)rows[i] * n_tokens, *b = delta + (size_t)first_of[i] * n_tokens;
+        const uint32_t *a_bits = allow + (size_t)rows[i] * row_words, *b_bits = allow + (size_t)first_of[i] * row_words;
+        auto either = [&](int64_t w0) {
+            const uint32_t w = span_word<BITS, kVerifyChunks>(a_bits, w0, lane, n_tokens);
+            return BITS ? w | span_word<BITS, kVerifyChunks>(b_bits, w0, lane, n_tokens) : w;
+        };
+        uint32_t w_next = either(lo);
+        for (int64_t w0 = lo; w0 < hi; w0 += kSpan) {
+            const uint32_t w = w_next;
+            w_next = either(w0 + kSpan);
+            if (__builtin_amdgcn_ballot_w64(w != 0) == 0) continue;
+            int32_t x[kVerifyChunks], y[kVerifyChunks];
+            span_load<kVerifyChunks>(a, w0, lane, w, x);
+            span_load<kVerifyChunks>(b, w0, lane, w, y);
+#pragma unroll
+            for (int u = 0; u < kVerifyChunks; ++u) {
+                const int32_t cx = x[u] >= 0 ? (LDS_CLS ? s_cls[x[u]] : cls[x[u]]) : -1;
+                const int32_t cy = y[u] >= 0 ? (LDS_CLS ? s_cls[y[u]] : cls[y[u]]) : -1;
+                bad |= cx != cy;
+            }
+        }
     }
     if (bad) *mismatch = 1;
 }
@@ -125,16 +197,17 @@ verify_classes_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, const
 // A wavefront renames kRenameChunks * 64 tokens at a time, so that as many loads are in flight, and writes their allowed
 // words side by side.
 //
-// Bound by the memory: 4,245 rows of 128,256 tokens are 2.2 GB read and 2.2 GB written: 1,570 us with a workgroup per 256
-// entries and the map in memory (2.1 million workgroups, whose launch alone takes a millisecond), 890 us so.
+// Wavefronts take pieces of rows (kPieceWords), so that none waits for another's row, and have the next span's entries
+// in flight while they rename one.  Bound by the memory: 4,245 rows of 128,256 tokens are 2.2 GB written and, without the
+// bits, as much read: 890 us; by the bits, which leave about 40 % of the entries to be read, 750 us (writing rows of which
+// a third are copied takes 565 us on this card, only writing them 395; without the non-temporal stores 800 us).
 constexpr int kRenameThreads = 512;
 constexpr int kRenameChunks = 8;
-constexpr size_t kMapLdsBytes = 64 * 1024;
 
-template <bool LDS_MAP>
+template <bool BITS, bool LDS_MAP>
 __global__ void __launch_bounds__(kRenameThreads)
-compact_rows_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, int64_t row_words, int64_t n_new, int32_t n_old,
-                    const int32_t* __restrict__ first_row, const int32_t* __restrict__ map,
+compact_rows_kernel(const int32_t* __restrict__ delta, const uint32_t* __restrict__ allow, int32_t n_tokens, int64_t row_words, int64_t n_new,
+                    int32_t n_old, const int32_t* __restrict__ first_row, const int32_t* __restrict__ map,
                     int32_t* __restrict__ out_delta, uint32_t* __restrict__ out_allow)
 {
     extern __shared__ int32_t s_map[];
@@ -144,21 +217,30 @@ compact_rows_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, int64_t
     }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    constexpr int kSpan = kRenameChunks * 64;
-    for (int64_t c = blockIdx.x; c < n_new; c += gridDim.x) {
+    constexpr int kSpan = 2 * kRenameChunks;                       // in words of bits
+    // a wavefront takes pieces of rows in turn
+    const int64_t per_row = (row_words + kPieceWords - 1) / kPieceWords, n_waves = (int64_t)gridDim.x * (kRenameThreads / 64);
+    for (int64_t i = (int64_t)blockIdx.x * (kRenameThreads / 64) + wave; i < n_new * per_row; i += n_waves) {
+        const int64_t c = i / per_row, lo = (i - c * per_row) * kPieceWords, hi = min(row_words, lo + kPieceWords);
         const int32_t* row = delta + (size_t)first_row[c] * n_tokens;
+        const uint32_t* bits = allow + (size_t)first_row[c] * row_words;
         int32_t* out = out_delta + (size_t)c * n_tokens;
-        for (int64_t t0 = (int64_t)wave * kSpan; t0 < row_words * 32; t0 += kRenameThreads / 64 * kSpan) {
+        // the next span's entries are requested before this one's are renamed, and the bits of the one after it
+        int32_t v_next[kRenameChunks];
+        span_load<kRenameChunks>(row, lo, lane, span_word<BITS, kRenameChunks>(bits, lo, lane, n_tokens), v_next);
+        uint32_t w_next = span_word<BITS, kRenameChunks>(bits, lo + kSpan, lane, n_tokens);
+        for (int64_t w0 = lo; w0 < hi; w0 += kSpan) {
             int32_t v[kRenameChunks];
 #pragma unroll
-            for (int u = 0; u < kRenameChunks; ++u) {
-                const int64_t t = t0 + u * 64 + lane;
-                v[u] = t < n_tokens ? __builtin_nontemporal_load(row + t) : TDFA_DEAD;
+            for (int u = 0; u < kRenameChunks; ++u) v[u] = v_next[u];
+            if (w0 + kSpan < hi) {
+                span_load<kRenameChunks>(row, w0 + kSpan, lane, w_next, v_next);
+                w_next = span_word<BITS, kRenameChunks>(bits, w0 + 2 * kSpan, lane, n_tokens);
             }
             uint32_t word = 0;                                     // lanes 2 u, 2 u + 1: the allowed words of chunk u
 #pragma unroll
             for (int u = 0; u < kRenameChunks; ++u) {
-                const int64_t t = t0 + u * 64 + lane;
+                const int64_t t = 32 * w0 + u * 64 + lane;
                 if (v[u] >= 0) v[u] = LDS_MAP ? s_map[v[u]] : map[v[u]];
                 else v[u] = TDFA_DEAD;
                 if (t < n_tokens) __builtin_nontemporal_store(v[u], out + t);
@@ -166,8 +248,8 @@ compact_rows_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, int64_t
                 if (lane == 2 * u) word = (uint32_t)m;
                 if (lane == 2 * u + 1) word = (uint32_t)(m >> 32);
             }
-            const int64_t wi = (t0 >> 5) + lane;
-            if (lane < 2 * kRenameChunks && wi < row_words) out_allow[(size_t)c * row_words + wi] = word;
+            const int64_t wi = w0 + lane;
+            if (lane < kSpan && wi < row_words) out_allow[(size_t)c * row_words + wi] = word;
         }
     }
 }
@@ -218,13 +300,12 @@ unsigned grid_x(int32_t n_tokens) { return (unsigned)std::max(1, std::min(64, (n
 // ---------------------------------------------------------------------------------------------
 // The sparse path: rows as lists of distinct targets.
 
-constexpr int kListThreads = 512;      // workgroup of the pass that builds a row's list
+constexpr int kListThreads = 1024;      // workgroup of the pass that builds a row's list
 constexpr int kSlots = 4096;           // its table of targets in LDS (open addressing, 48 KB)
 constexpr int kMaxTargets = 3072;      // more distinct targets in one row: the dense path
-constexpr int kLoadsAhead = 8;
+constexpr int kListChunks = 8;         // 64 entries each that a wavefront has in flight
 
-// w(t), odd: three products of 32 bits, each half of the one before folded into the next (a dozen instructions; the
-// pass below is bound by them, and mix64 takes three times as many).
+// w(t), odd: three products of 32 bits, each half of the one before folded into the next.
 __device__ __forceinline__ unsigned long long token_weight(unsigned long long seed, int t)
 {
     const unsigned long long p = (unsigned long long)((uint32_t)t ^ (uint32_t)seed) * 0x9E3779B1u + seed;
@@ -233,9 +314,21 @@ __device__ __forceinline__ unsigned long long token_weight(unsigned long long se
     return (((unsigned long long)((uint32_t)(u >> 32) ^ (uint32_t)r) << 32) | ((uint32_t)u ^ (uint32_t)(r >> 32))) | 1ull;
 }
 
+__global__ void __launch_bounds__(kThreads)
+token_weights_kernel(unsigned long long seed, int32_t n_tokens, unsigned long long* __restrict__ weight)
+{
+    const int32_t t = blockIdx.x * kThreads + threadIdx.x;
+    if (t < n_tokens) weight[t] = token_weight(seed, t);
+}
+
 __device__ __forceinline__ void add_target(int32_t* key, unsigned long long* sum, int* n_used, int32_t v, unsigned long long w)
 {
     unsigned slot = ((unsigned)v * 0x9E3779B1u) >> 20;
+    // (mostly the target is there already, in its first place)
+    if (key[slot] == v) {
+        atomicAdd(&sum[slot], w);
+        return;
+    }
     for (int probe = 0; probe < kSlots; ++probe, slot = (slot + 1) & (kSlots - 1)) {
         int32_t k = key[slot];
         if (k == -1) {
@@ -256,8 +349,15 @@ __device__ __forceinline__ void add_target(int32_t* key, unsigned long long* sum
 // Row blockIdx.x: its distinct targets and their weights, appended to (e_target, e_weight) at a
 // position taken from `counter` (which keeps counting past e_cap, so that a second attempt knows the
 // size).  *overflow is set when a row has more than kMaxTargets targets.
+//
+// Bound by instructions and by the waits of each update (the target's place in LDS, then the atomic): 5,387 rows of 128,256
+// tokens took 690 us with every entry read and its weight made in place (a dozen instructions), 525 us by the bits and with
+// the weights from memory (1 MB, in every L2).  4 and 16 loads in flight take 627 and 678 us, workgroups of 512 threads 567 us;
+// the places of a span looked up beforehand 620 us, the next span's entries requested beforehand 936 us (fewer wavefronts fit).
+template <bool BITS>
 __global__ void __launch_bounds__(kListThreads)
-row_targets_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, unsigned long long seed, unsigned long long e_cap,
+row_targets_kernel(const int32_t* __restrict__ delta, const uint32_t* __restrict__ allow, int32_t n_tokens, int64_t row_words,
+                   const unsigned long long* __restrict__ weight, unsigned long long e_cap,
                    unsigned long long* __restrict__ counter, unsigned long long* __restrict__ row_begin,
                    int32_t* __restrict__ row_n, int32_t* __restrict__ e_target, unsigned long long* __restrict__ e_weight,
                    int32_t* overflow)
@@ -278,24 +378,32 @@ row_targets_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, unsigned
     __syncthreads();
     if (stop) return;
     const int32_t* row = delta + (size_t)blockIdx.x * n_tokens;
+    const uint32_t* bits = allow + (size_t)blockIdx.x * row_words;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    constexpr int kSpan = 2 * kListChunks, kStep = kListThreads / 64 * kSpan;            // in words of bits
     int32_t last = TDFA_DEAD;
     unsigned long long acc = 0;
-    for (int t0 = threadIdx.x; t0 < n_tokens; t0 += kListThreads * kLoadsAhead) {
-        int32_t v[kLoadsAhead];
+    uint32_t w_next = span_word<BITS, kListChunks>(bits, wave * kSpan, lane, n_tokens);
+    for (int64_t w0 = (int64_t)wave * kSpan; w0 < row_words; w0 += kStep) {
+        const uint32_t w = w_next;
+        w_next = span_word<BITS, kListChunks>(bits, w0 + kStep, lane, n_tokens);
+        if (__builtin_amdgcn_ballot_w64(w != 0) == 0) continue;
+        int32_t v[kListChunks];
+        unsigned long long tw[kListChunks];
+        span_load<kListChunks>(row, w0, lane, w, v);
 #pragma unroll
-        for (int u = 0; u < kLoadsAhead; ++u) {
-            const int t = t0 + u * kListThreads;
-            v[u] = t < n_tokens ? row[t] : TDFA_DEAD;
-        }
+        for (int u = 0; u < kListChunks; ++u)
+            if (__builtin_amdgcn_inverse_ballot_w64(span_mask(w, u))) tw[u] = weight[32 * w0 + 64 * u + lane];
 #pragma unroll
-        for (int u = 0; u < kLoadsAhead; ++u) {
-            if (__builtin_amdgcn_ballot_w64(v[u] >= 0 || last >= 0) == 0) continue;       // no edge here, none waiting
+        for (int u = 0; u < kListChunks; ++u) {
+            if (v[u] < 0) continue;
             if (v[u] != last) {             // runs of one target (a state that mostly loops) cost one update
                 if (last >= 0) add_target(key, sum, &n_used, last, acc);
                 last = v[u];
                 acc = 0;
             }
-            acc += token_weight(seed, t0 + u * kListThreads);
+            acc += tw[u];
         }
         if (*(volatile int*)&n_used > kMaxTargets) break;
     }
@@ -332,17 +440,38 @@ struct Lists {
     int32_t n_rows;
 };
 
+// Marks are bytes that only ever rise from 0 to 1, so a wavefront need not wait for a round of all rows to end: it looks
+// at its row kSweeps times in a launch, and what another wavefront has marked meanwhile counts.  (Loads and stores of the
+// marks at device scope; the wavefronts wait for nothing, and a launch that has marked nothing ends the rounds.)  A look is
+// a trip to the L2 or beyond, a third of a microsecond; a launch per round took 3 us and its gap as much.  5,387 rows, both
+// searches: 96 launches of a round each, 12 between two looks of the host: 270 us of kernels and 380 us of gaps; 32 sweeps 13
+// launches, 192 sweeps 5 launches and 120 us of kernels.
+constexpr int kSweeps = 192;
+
+__device__ __forceinline__ bool marked(const uint8_t* mark, int32_t q)
+{
+    return __hip_atomic_load(mark + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+
+__device__ __forceinline__ void set_mark(uint8_t* mark, int32_t q)
+{
+    __hip_atomic_store(mark + q, (uint8_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __global__ void __launch_bounds__(kThreads)
 list_reach_kernel(Lists g, uint8_t* mark, uint8_t* done, int32_t* changed)
 {
-    const int32_t q = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-    if (q >= g.n_rows || !mark[q] || done[q]) return;
+    const int32_t q = blockIdx.x * kRowsPerBlock + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (q >= g.n_rows || done[q]) return;
     const int lane = threadIdx.x & 63;
+    int sweep = 0;
+    while (sweep < kSweeps && !marked(mark, q)) ++sweep;
+    if (sweep == kSweeps) return;
     if (lane == 0) done[q] = 1;
     const int32_t* e = g.e_target + g.row_begin[q];
     for (int i = lane; i < g.row_n[q]; i += 64)
-        if (!mark[e[i]]) {
-            mark[e[i]] = 1;
+        if (!marked(mark, e[i])) {
+            set_mark(mark, e[i]);
             *changed = 1;
         }
 }
@@ -357,15 +486,21 @@ list_good_start_kernel(int32_t n_rows, const uint8_t* __restrict__ mark, const u
 __global__ void __launch_bounds__(kThreads)
 list_reach_final_kernel(Lists g, const uint8_t* mark, uint8_t* good, int32_t* changed)
 {
-    const int32_t q = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
+    const int32_t q = blockIdx.x * kRowsPerBlock + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (q >= g.n_rows || !mark[q] || good[q]) return;
     const int lane = threadIdx.x & 63;
     const int32_t* e = g.e_target + g.row_begin[q];
-    bool hit = false;
-    for (int i = lane; i < g.row_n[q]; i += 64) hit |= mark[e[i]] && good[e[i]];
-    if (__builtin_amdgcn_ballot_w64(hit) != 0 && lane == 0) {
-        good[q] = 1;
-        *changed = 1;
+    const int32_t n = g.row_n[q];
+    for (int sweep = 0; sweep < kSweeps; ++sweep) {
+        bool hit = false;
+        // (every target of a marked row is marked)
+        for (int i = lane; i < n; i += 64) hit |= marked(good, e[i]);
+        if (__builtin_amdgcn_ballot_w64(hit) == 0) continue;
+        if (lane == 0) {
+            set_mark(good, q);
+            *changed = 1;
+        }
+        return;
     }
 }
 
@@ -412,25 +547,44 @@ list_keys_kernel(Lists g, const int32_t* __restrict__ cls, unsigned long long se
 }
 
 // Rows with equal keys meet in one slot of the table (ht_key 0: free; more slots than rows) and
-// leave their smallest row there.
+// leave their smallest row there.  In the early rounds thousands of rows share a key: the lanes that hold the key of the
+// wavefront's first lanes go to the table as one, their first, which has the smallest row.
 __global__ void __launch_bounds__(kThreads)
 list_insert_kernel(int32_t n_rows, const int32_t* __restrict__ cls, const unsigned long long* __restrict__ key,
                    unsigned long long* ht_key, int32_t* ht_min, uint32_t ht_mask, uint32_t* __restrict__ slot_of)
 {
     const int32_t q = blockIdx.x * kThreads + threadIdx.x;
-    if (q >= n_rows || cls[q] < 0) return;
-    const unsigned long long k = key[q];
-    uint32_t slot = (uint32_t)(k >> 20) & ht_mask;
-    for (uint32_t probe = 0; probe <= ht_mask; ++probe, slot = (slot + 1) & ht_mask) {
-        // (a look first: in the early rounds thousands of rows share a slot, and most need not change it)
-        unsigned long long was = __hip_atomic_load(&ht_key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (was == 0ull) was = atomicCAS(&ht_key[slot], 0ull, k);
-        if (was == 0ull || was == k) {
-            if (__hip_atomic_load(&ht_min[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > q) atomicMin(&ht_min[slot], q);
+    bool waiting = q < n_rows && cls[q] >= 0;
+    const unsigned long long k = waiting ? key[q] : 0ull;
+    auto insert = [&]() -> uint32_t {
+        uint32_t slot = (uint32_t)(k >> 20) & ht_mask;
+        for (uint32_t probe = 0; probe <= ht_mask; ++probe, slot = (slot + 1) & ht_mask) {
+            // (a look first: most rows need not change the slot)
+            unsigned long long was = __hip_atomic_load(&ht_key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (was == 0ull) was = atomicCAS(&ht_key[slot], 0ull, k);
+            if (was == 0ull || was == k) {
+                if (__hip_atomic_load(&ht_min[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > q) atomicMin(&ht_min[slot], q);
+                break;
+            }
+        }
+        return slot;
+    };
+    constexpr int kShared = 4;
+    for (int pass = 0; pass < kShared; ++pass) {
+        const unsigned long long all = __builtin_amdgcn_ballot_w64(waiting);
+        if (all == 0) return;
+        const int first = __builtin_ctzll(all);
+        const unsigned long long k0 = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(k >> 32), first) << 32) |
+                                      (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)k, first);
+        uint32_t slot = 0;
+        if ((int)(threadIdx.x & 63) == first) slot = insert();
+        slot = (uint32_t)__builtin_amdgcn_readlane((int)slot, first);
+        if (waiting && k == k0) {
             slot_of[q] = slot;
-            return;
+            waiting = false;
         }
     }
+    if (waiting) slot_of[q] = insert();
 }
 
 __global__ void __launch_bounds__(kThreads)
@@ -448,8 +602,24 @@ list_assign_kernel(int32_t n_rows, const int32_t* __restrict__ cls, const uint32
     if ((threadIdx.x & 63) == 0 && m != 0) atomicAdd(n_classes, __builtin_popcountll(m));
 }
 
+// The comparison of n pairs of rows (allow: the table's bits, or NULL where only the entries count).
+int launch_verify(const int32_t* delta, const uint32_t* allow, int32_t n_tokens, int64_t row_words, int64_t n, int32_t n_old,
+                  const int32_t* rows, const int32_t* first_of, const int32_t* cls, int32_t* mismatch, hipStream_t s)
+{
+    const int64_t pieces = n * ((row_words + kPieceWords - 1) / kPieceWords);
+    const unsigned grid = (unsigned)std::min<int64_t>((pieces + kVerifyThreads / 64 - 1) / (kVerifyThreads / 64), 256 * 4);
+    const size_t lds = (size_t)n_old * 4;
+    auto launch = [&](auto kernel, size_t bytes) {
+        kernel<<<grid, kVerifyThreads, bytes, s>>>(delta, allow, n_tokens, row_words, n, n_old, rows, first_of, cls, mismatch);
+    };
+    if (lds <= kMapLdsBytes) launch(allow ? verify_classes_kernel<true, true> : verify_classes_kernel<false, true>, lds);
+    else launch(allow ? verify_classes_kernel<true, false> : verify_classes_kernel<false, false>, 0);
+    TDFA_HIP(hipGetLastError());
+    return TDFA_OK;
+}
+
 // The dense path: every round streams rows of the table.
-int minimize_dense(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const uint8_t* accept, const int32_t* starts,
+int minimize_dense(const int32_t* delta, int64_t row_words, int32_t n_rows, int32_t n_tokens, const uint8_t* accept, const int32_t* starts,
                    int32_t n_starts, hipStream_t s, std::vector<int32_t>* first_rows, std::vector<int32_t>* map_out)
 {
     DeviceBuffers d;
@@ -564,11 +734,7 @@ int minimize_dense(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
         TDFA_HIP(hipMemcpyAsync(d.aux, first_of_row.data(), n * 4, hipMemcpyHostToDevice, s));
         TDFA_HIP(hipMemcpyAsync(d.cls, cls.data(), (size_t)n_rows * 4, hipMemcpyHostToDevice, s));
         if (n_tokens > 0) {
-            for (size_t lo = 0; lo < n; lo += kMaxGridY) {
-                verify_classes_kernel<<<dim3(gx, (unsigned)std::min(kMaxGridY, n - lo)), kThreads, 0, s>>>(delta, n_tokens, d.rows + lo,
-                                                                                                      d.aux + lo, d.cls, d.flag);
-                TDFA_HIP(hipGetLastError());
-            }
+            TDFA_GET(launch_verify(delta, nullptr, n_tokens, row_words, (int64_t)n, n_rows, d.rows, d.aux, d.cls, d.flag, s));
         }
         TDFA_HIP(hipMemcpyAsync(&bad, d.flag, 4, hipMemcpyDeviceToHost, s));
         TDFA_HIP(hipStreamSynchronize(s));
@@ -594,12 +760,12 @@ constexpr int kNotSparse = -1000;       // minimize_lists: take the dense path
 
 // The sparse path.  Returns kNotSparse when a row has too many distinct targets or the final
 // comparison fails (two different rows with one signature).
-int minimize_lists(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const uint8_t* accept, const int32_t* starts,
+int minimize_lists(const int32_t* delta, const uint32_t* allow, int64_t row_words, int32_t n_rows, int32_t n_tokens, const uint8_t* accept, const int32_t* starts,
                    int32_t n_starts, hipStream_t s, std::vector<int32_t>* first_rows, std::vector<int32_t>* map_out)
 {
     const unsigned long long seed = 0x243F6A8885A308D3ull;
     Arena mem;
-    unsigned long long *counter, *row_begin, *e_weight = nullptr, *key, *ht_key;
+    unsigned long long *counter, *row_begin, *weight, *e_weight = nullptr, *key, *ht_key;
     int32_t *row_n, *e_target = nullptr, *flags, *cls_a, *cls_b, *ht_min, *rows_dev, *first_dev;
     uint32_t* slot_of;
     uint8_t *mark, *aux, *good, *accept_dev;
@@ -607,6 +773,7 @@ int minimize_lists(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
     while (ht_size < 2u * (uint32_t)n_rows && ht_size < 0x80000000u) ht_size <<= 1;
     TDFA_GET(mem.get(&counter, 1));
     TDFA_GET(mem.get(&row_begin, n_rows));
+    TDFA_GET(mem.get(&weight, n_tokens));
     TDFA_GET(mem.get(&row_n, n_rows));
     TDFA_GET(mem.get(&flags, 1 + 3));              // [0] too many targets / changed / mismatch, [1 ..] classes after each round of a look
     TDFA_GET(mem.get(&key, n_rows));
@@ -623,13 +790,19 @@ int minimize_lists(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
 
     // ---- the lists: one pass over the table (a second one when they need more room than guessed)
     unsigned long long e_cap = std::max<unsigned long long>(1u << 20, std::min<unsigned long long>((unsigned long long)n_rows * 512, 1ull << 26));
+    if (n_tokens > 0) token_weights_kernel<<<(unsigned)((n_tokens + kThreads - 1) / kThreads), kThreads, 0, s>>>(seed, n_tokens, weight);
+    TDFA_HIP(hipGetLastError());
     for (int attempt = 0;; ++attempt) {
         TDFA_GET(mem.get(&e_target, e_cap));
         TDFA_GET(mem.get(&e_weight, e_cap));
         TDFA_HIP(hipMemsetAsync(counter, 0, 8, s));
         TDFA_HIP(hipMemsetAsync(flags, 0, 8, s));
-        row_targets_kernel<<<(unsigned)n_rows, kListThreads, 0, s>>>(delta, n_tokens, seed, e_cap, counter, row_begin, row_n, e_target,
-                                                                      e_weight, flags);
+        if (allow)
+            row_targets_kernel<true><<<(unsigned)n_rows, kListThreads, 0, s>>>(delta, allow, n_tokens, row_words, weight, e_cap, counter, row_begin,
+                                                                               row_n, e_target, e_weight, flags);
+        else
+            row_targets_kernel<false><<<(unsigned)n_rows, kListThreads, 0, s>>>(delta, allow, n_tokens, row_words, weight, e_cap, counter, row_begin,
+                                                                                row_n, e_target, e_weight, flags);
         TDFA_HIP(hipGetLastError());
         unsigned long long total = 0;
         TDFA_HIP(hipMemcpyAsync(&total, counter, 8, hipMemcpyDeviceToHost, s));
@@ -643,9 +816,9 @@ int minimize_lists(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
     const Lists g = {row_begin, row_n, e_target, e_weight, n_rows};
     const unsigned by_wave = (unsigned)(((size_t)n_rows + kRowsPerBlock - 1) / kRowsPerBlock);
     const unsigned by_thread = (unsigned)(((size_t)n_rows + kThreads - 1) / kThreads);
-    // Rounds between two looks of the host: a look costs as much as half a dozen rounds (a copy and a wait, some 25 us),
+    // Rounds between two looks of the host: a look costs as much as half a dozen launches (a copy and a wait, some 25 us),
     // and a round past the last one changes nothing.
-    constexpr int kRoundsPerLook = 12, kRefinesPerLook = 3;
+    constexpr int kRefinesPerLook = 3;
 
     // ---- states that a token sequence reaches, then of those the ones that reach a final state
     std::vector<uint8_t> mark_h((size_t)n_rows, 0);
@@ -656,7 +829,7 @@ int minimize_lists(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
     TDFA_HIP(hipMemsetAsync(slot_of, 0, (size_t)n_rows * 4, s));
     for (flag = 1; flag;) {
         TDFA_HIP(hipMemsetAsync(flags, 0, 4, s));
-        for (int r = 0; r < kRoundsPerLook; ++r) list_reach_kernel<<<by_wave, kThreads, 0, s>>>(g, mark, aux, flags);
+        list_reach_kernel<<<by_wave, kThreads, 0, s>>>(g, mark, aux, flags);
         TDFA_HIP(hipGetLastError());
         TDFA_HIP(hipMemcpyAsync(&flag, flags, 4, hipMemcpyDeviceToHost, s));
         TDFA_HIP(hipStreamSynchronize(s));
@@ -664,7 +837,7 @@ int minimize_lists(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
     list_good_start_kernel<<<by_thread, kThreads, 0, s>>>(n_rows, mark, accept_dev, good);
     for (flag = 1; flag;) {
         TDFA_HIP(hipMemsetAsync(flags, 0, 4, s));
-        for (int r = 0; r < kRoundsPerLook; ++r) list_reach_final_kernel<<<by_wave, kThreads, 0, s>>>(g, mark, good, flags);
+        list_reach_final_kernel<<<by_wave, kThreads, 0, s>>>(g, mark, good, flags);
         TDFA_HIP(hipGetLastError());
         TDFA_HIP(hipMemcpyAsync(&flag, flags, 4, hipMemcpyDeviceToHost, s));
         TDFA_HIP(hipStreamSynchronize(s));
@@ -712,12 +885,7 @@ int minimize_lists(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
         TDFA_HIP(hipMemcpyAsync(rows_dev, joined.data(), joined.size() * 4, hipMemcpyHostToDevice, s));
         TDFA_HIP(hipMemcpyAsync(first_dev, with.data(), with.size() * 4, hipMemcpyHostToDevice, s));
         TDFA_HIP(hipMemsetAsync(flags, 0, 4, s));
-        const unsigned gx = grid_x(n_tokens);
-        for (size_t lo = 0; lo < joined.size(); lo += kMaxGridY) {
-            verify_classes_kernel<<<dim3(gx, (unsigned)std::min(kMaxGridY, joined.size() - lo)), kThreads, 0, s>>>(
-                delta, n_tokens, rows_dev + lo, first_dev + lo, cls, flags);
-            TDFA_HIP(hipGetLastError());
-        }
+        TDFA_GET(launch_verify(delta, allow, n_tokens, row_words, (int64_t)joined.size(), n_rows, rows_dev, first_dev, cls, flags, s));
         TDFA_HIP(hipMemcpyAsync(&flag, flags, 4, hipMemcpyDeviceToHost, s));
         TDFA_HIP(hipStreamSynchronize(s));
         if (flag) return kNotSparse;
@@ -738,16 +906,16 @@ int minimize_lists(const int32_t* delta, int32_t n_rows, int32_t n_tokens, const
 
 }  // namespace
 
-int minimize_table(const int32_t* delta, int64_t n_rows64, int32_t n_tokens, const uint8_t* accept, const int32_t* starts,
+int minimize_table(const int32_t* delta, const uint32_t* allow, int64_t row_words, int64_t n_rows64, int32_t n_tokens, const uint8_t* accept, const int32_t* starts,
                    int32_t n_starts, hipStream_t s, std::vector<int32_t>* first_rows, std::vector<int32_t>* map_out)
 {
     const int32_t n_rows = (int32_t)n_rows64;
-    const int rc = minimize_lists(delta, n_rows, n_tokens, accept, starts, n_starts, s, first_rows, map_out);
+    const int rc = minimize_lists(delta, allow, row_words, n_rows, n_tokens, accept, starts, n_starts, s, first_rows, map_out);
     if (rc != kNotSparse) return rc;
-    return minimize_dense(delta, n_rows, n_tokens, accept, starts, n_starts, s, first_rows, map_out);
+    return minimize_dense(delta, row_words, n_rows, n_tokens, accept, starts, n_starts, s, first_rows, map_out);
 }
 
-int launch_compact_rows(const int32_t* delta, int32_t n_tokens, int64_t row_words, const std::vector<int32_t>& first_rows,
+int launch_compact_rows(const int32_t* delta, const uint32_t* allow, int32_t n_tokens, int64_t row_words, const std::vector<int32_t>& first_rows,
                         const std::vector<int32_t>& map, int32_t* out_delta, uint32_t* out_allow, hipStream_t s)
 {
     if (first_rows.empty()) return TDFA_OK;
@@ -760,13 +928,15 @@ int launch_compact_rows(const int32_t* delta, int32_t n_tokens, int64_t row_word
     // four workgroups of eight wavefronts per compute unit (two where the map is at its largest)
     const int64_t n_new = (int64_t)first_rows.size();
     const size_t lds = map.size() * 4;
-    const unsigned grid = (unsigned)std::min<int64_t>(n_new, 256 * 4);
-    if (lds <= kMapLdsBytes)
-        compact_rows_kernel<true><<<grid, kRenameThreads, lds, s>>>(delta, n_tokens, row_words, n_new, (int32_t)map.size(), rows, map_dev,
-                                                                    out_delta, out_allow);
-    else
-        compact_rows_kernel<false><<<grid, kRenameThreads, 0, s>>>(delta, n_tokens, row_words, n_new, (int32_t)map.size(), rows, map_dev,
-                                                                   out_delta, out_allow);
+    const int64_t pieces = n_new * ((row_words + kPieceWords - 1) / kPieceWords);
+    const unsigned grid = (unsigned)std::min<int64_t>((pieces + kRenameThreads / 64 - 1) / (kRenameThreads / 64), 256 * 4);
+    if (grid == 0) return TDFA_OK;
+    auto launch = [&](auto kernel, size_t bytes) {
+        kernel<<<grid, kRenameThreads, bytes, s>>>(delta, allow, n_tokens, row_words, n_new, (int32_t)map.size(), rows, map_dev, out_delta,
+                                                   out_allow);
+    };
+    if (lds <= kMapLdsBytes) launch(allow ? compact_rows_kernel<true, true> : compact_rows_kernel<false, true>, lds);
+    else launch(allow ? compact_rows_kernel<true, false> : compact_rows_kernel<false, false>, 0);
     TDFA_HIP(hipGetLastError());
     TDFA_HIP(hipStreamSynchronize(s));
     return TDFA_OK;

@@ -163,18 +163,20 @@ int launch_apply_terminals(int32_t* delta, uint32_t* allow, int32_t n_tokens, in
 
 // Token-level optimisation (optimize.hip): which old rows are the first rows of the classes that are
 // kept, in the order of the new states, and the new state of every old state (TDFA_DEAD: dropped).
-int minimize_table(const int32_t* delta, int64_t n_rows, int32_t n_tokens, const uint8_t* accept_host,
-                   const int32_t* starts_host, int32_t n_starts, hipStream_t stream, std::vector<int32_t>* first_rows,
+// allow: the table's allowed bits if they are known to mark its edges, else NULL.
+int minimize_table(const int32_t* delta, const uint32_t* allow, int64_t row_words, int64_t n_rows, int32_t n_tokens,
+                   const uint8_t* accept_host, const int32_t* starts_host, int32_t n_starts, hipStream_t stream, std::vector<int32_t>* first_rows,
                    std::vector<int32_t>* map_out);
-int launch_compact_rows(const int32_t* delta, int32_t n_tokens, int64_t row_words, const std::vector<int32_t>& first_rows,
+int launch_compact_rows(const int32_t* delta, const uint32_t* allow, int32_t n_tokens, int64_t row_words, const std::vector<int32_t>& first_rows,
                         const std::vector<int32_t>& map, int32_t* out_delta, uint32_t* out_allow, hipStream_t stream);
 
 // out[q] = the tokens row q of `allow` allows (pack.hip).
 int launch_row_allowed(const uint32_t* allow, int64_t n_rows, int32_t n_tokens, int64_t row_words, uint32_t* out, hipStream_t stream);
 
-// Edge-list form of a table (pack.hip): the device arrays are allocated here and owned by the caller, on failure too.
+// Edge-list form of a table (pack.hip): allow_out gets a copy of the bits; the other device arrays are allocated here and
+// owned by the caller, on failure too.
 int pack_table(const int32_t* delta, const uint32_t* allow, int64_t n_rows, int32_t n_tokens, int64_t row_words,
-               hipStream_t stream, DeviceBlock* dir, DeviceBlock* row_begin, DeviceBlock* targets, int64_t* n_edges_out);
+               uint32_t* allow_out, hipStream_t stream, DeviceBlock* dir, DeviceBlock* row_begin, DeviceBlock* targets, int64_t* n_edges_out);
 
 constexpr int kPdaPops = 12;            // symbols an edge of a push-down automaton may pop or push
 constexpr int kPdaDirShift = 6;         // the directory of a state's edges has an entry per 64 tokens

@@ -84,6 +84,29 @@ def test_edges_of_the_renaming(T, oracle, n, v):
     assert 0 < new.n_rows <= n - half
 
 
+@pytest.mark.parametrize("n,v", [(50, 1), (50, 63), (50, 129), (50, 511), (50, 513), (50, 4095), (50, 4097), (50, 16385), (16384, 67), (16385, 67)])
+def test_passes_led_by_the_bits(T, oracle, n, v):
+    """A table that the library has written (here by stacking): its passes read only the entries behind a set bit.  Around
+    the words that a wavefront reads at a time, the tokens of a piece of a row and the states whose names fit in LDS; rows
+    from empty to full, with long runs of tokens that no state allows; half of the rows copies of others."""
+    rng = np.random.default_rng(7 * n + v)
+    half = n // 2
+    table_np = rng.integers(0, n, size=(n, v), dtype=np.int32)
+    table_np[rng.random((n, v)) < rng.choice([0.0, 0.5, 0.999], size=n)[:, None]] = DEAD
+    table_np[:, v // 3:v // 2] = DEAD
+    table_np[half:2 * half] = table_np[:half]
+    accept = (rng.random(n) < 0.2).astype(np.uint8)
+    accept[half:2 * half] = accept[:half]
+    table, _ = T.table_concat([_upload_table(T, table_np)])
+    new, want, _ = _check(T, oracle, table, table_np, accept, np.array([0, 1, n // 3], dtype=np.int32))
+    packed = T.table_pack(new)
+    if new.n_rows:
+        targets, begin, _, allow = T.table_pack_arrays(packed)
+        assert np.array_equal(targets.cpu().numpy(), want[want != DEAD])
+        assert np.array_equal(begin.cpu().numpy(), np.concatenate([[0], np.cumsum((want != DEAD).sum(axis=1))]))
+        assert np.array_equal(allow.cpu().numpy().view(np.uint32), G.bits_from_table(want, allow.shape[1]))
+
+
 def _most_targets(table_np):
     return max(len(np.unique(r[r >= 0])) for r in table_np)
 
