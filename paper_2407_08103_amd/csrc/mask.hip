@@ -136,6 +136,28 @@ __device__ __forceinline__ void store_group(typename ElemOf<DTYPE>::type* orow, 
     }
 }
 
+// The same with 16-bit logits left in pairs, as they lie in memory.
+template <int DTYPE> constexpr int kGroupWords = DTYPE == TDFA_F32 ? 8 : 4;
+
+template <int DTYPE>
+__device__ __forceinline__ void load_words(const typename ElemOf<DTYPE>::type* row, int t, int V, uint32_t (&x)[kGroupWords<DTYPE>])
+{
+    if (t + 8 <= V) {
+#pragma unroll
+        for (int i = 0; i < kGroupWords<DTYPE> / 4; ++i) {
+            const uint4 v = reinterpret_cast<const uint4*>(row + t)[i];
+            x[4 * i] = v.x; x[4 * i + 1] = v.y; x[4 * i + 2] = v.z; x[4 * i + 3] = v.w;
+        }
+    } else if constexpr (DTYPE == TDFA_F32) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = t + j < V ? row[t + j] : 0xFF800000u;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            x[j] = (t + 2 * j < V ? row[t + 2 * j] : 0xFF80u) | (t + 2 * j + 1 < V ? (uint32_t)row[t + 2 * j + 1] : 0xFF80u) << 16;
+    }
+}
+
 // Exact scan of groups [g_lo, g_hi) of one row by the whole workgroup: this thread's best
 // candidate (key << 32 | ~token), 0 if it saw nothing allowed.  Writes the masked row if orow.
 // (bits_at(g): the allowed bits of group g.)
@@ -1703,6 +1725,9 @@ constexpr int kDenseQuads = 48;        // lanes with a quad to draw for from whi
 // a generator block and two logarithms of its own, took longer: T = 1, 128,256 tokens, bf16, 256 sequences anywhere in
 // the texts of 50 signatures 42.4 -> 28.2 us, all in states that allow most tokens 45.9 -> 36.3 us (1,024 sequences: 139
 // -> 89 and 166 -> 105 us), all in states that allow few 9.8 -> 10.2 us (512 sequences 13.7 -> 11.4 us).
+// With the quad bounded as a whole before its tokens (above), which takes a quarter of the instructions out of a dense row:
+// 28.9 -> 28.0, all in states that allow most 35.6 -> 33.7 us; 1,024 sequences 87 -> 80 and 103 -> 94 us.  (80 scalar and 64
+// vector registers, so that a compute unit holds eight workgroups instead of six: 27.1 and 33.6, but 1,024 sequences 89.)
 // A queue belongs to one wavefront, so the loop needs no workgroup barrier; the maximum does not depend on the
 // order because candidates are compared as (score, lowest id).
 template <int DTYPE, bool WRITE>
@@ -1711,7 +1736,7 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
 {
     using Elem = typename ElemOf<DTYPE>::type;
     constexpr Elem NEG_INF = DTYPE == TDFA_F32 ? (Elem)0xFF800000u : (Elem)0xFF80u;
-    constexpr int kWaves = kDrawThreads / 64;
+    constexpr int kWaves = kDrawThreads / 64, kWords = kGroupWords<DTYPE>;
     __shared__ unsigned long long wave_best[kMaxWaves];
     __shared__ uint2 s_groups[kWaves][kQueue];
     __shared__ __attribute__((aligned(16))) float4 s_logits[kWaves][kQueue];   // a waiting quad's logits, -inf where not allowed
@@ -1763,15 +1788,17 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
     auto reach = [&](uint32_t key) {                           // (key 0: nothing scored yet)
         if (key != 0) reached = fmaxf(reached, __uint_as_float((key & 0x80000000u) ? key & 0x7FFFFFFFu : ~key));
     };
-    // One quad per lane (all lanes active; mask 0: none): its allowed tokens compete.
-    auto draw_quads = [&](uint32_t quad, uint32_t mask, const float (&l)[4]) __attribute__((always_inline)) {
+    // One quad per lane (all lanes active; mask 0: none): its allowed tokens compete.  `most` is the largest of the logits.
+    // (The bound rises with the generator's word, so the largest logit with the largest word bounds the whole quad; the
+    // tokens' own bounds are made where that is not below what is reached, in one wavefront of twenty or so.)
+    auto draw_quads = [&](uint32_t quad, uint32_t mask, const float (&l)[4], float most) __attribute__((always_inline)) {
         uint32_t w[4];
         philox4x32_10(quad, (uint32_t)b, sp.off_lo, sp.off_hi, sp.seed_lo, sp.seed_hi, w);
+        const float top = __builtin_fmaf(most, sp.inv_t, noise_bound(max(max(w[0], w[1]), max(w[2], w[3]))));
+        if (__builtin_amdgcn_ballot_w64(!(top < reached)) == 0) return;         // (a NaN logit does not hide the others)
         float bd[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) bd[j] = __builtin_fmaf(l[j], sp.inv_t, noise_bound(w[j]));
-        const float top = fmaxf(fmaxf(bd[0], bd[1]), fmaxf(bd[2], bd[3]));
-        if (__builtin_amdgcn_ballot_w64(!(top < reached)) == 0) return;         // (a NaN logit does not hide the others)
         uint32_t take = mask;
         for (;;) {
 #pragma unroll
@@ -1805,14 +1832,14 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
         const float l[4] = {l4.x, l4.y, l4.z, l4.w};
         q_head += n;
         wave_sync();
-        draw_quads(quad_top | (en >> 4), en & 15u, l);
+        draw_quads(quad_top | (en >> 4), en & 15u, l, fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3])));
     };
     // Fetched groups are worked on one batch late: the logits of a batch are requested when it is
     // taken from the queue and used when the next batch is taken (or at the end), so that a
     // wavefront always has a load in flight while it computes.
     uint32_t m = 0, m_next = 0;                                // allowed bits of this lane's group; 0: none
     int t = 0, t_next = 0;                                     // its first token
-    Elem e[8], e_next[8];
+    uint32_t e[kWords], e_next[kWords];                        // its logits
     bool own = false, own_next = false;                        // this lane holds a group (WRITE: also when m is 0)
     auto take_batch = [&](uint32_t n) __attribute__((always_inline)) {   // n <= 64 queued groups: request their logits
         wave_sync();
@@ -1822,7 +1849,7 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
             const uint2 en = group_q[(g_head + lane) & (kQueue - 1)];
             t_next = (int)en.x << 3;
             m_next = en.y;
-            load_group<DTYPE>(row, t_next, V, e_next);
+            load_words<DTYPE>(row, t_next, V, e_next);
         }
         g_head += n;
         wave_sync();
@@ -1834,19 +1861,24 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const uint32_t mask = (m >> (4 * h)) & 15u;
-                float l[4], most[4];
+                float l[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const uint32_t x = (uint32_t)e[4 * h + j];
-                    l[j] = (mask >> j) & 1u ? __uint_as_float(DTYPE == TDFA_F32 ? x : x << 16) : -__builtin_inff();
-                    most[j] = __builtin_fmaf(l[j], sp.inv_t, kNoiseMax);
+                    const int i = 4 * h + j;
+                    uint32_t x;
+                    if constexpr (DTYPE == TDFA_F32) x = e[i];
+                    else x = i & 1 ? e[i >> 1] & 0xFFFF0000u : e[i >> 1] << 16;
+                    const uint32_t ok = (uint32_t)((int32_t)(m << (31 - i)) >> 31);         // all bits: the token is allowed
+                    l[j] = __uint_as_float((x & ok) | (0xFF800000u & ~ok));
                 }
-                const bool live = mask != 0 && !(fmaxf(fmaxf(most[0], most[1]), fmaxf(most[2], most[3])) < reached);
+                // (fma rises with the logit, so the largest one decides)
+                const float most = fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3]));
+                const bool live = mask != 0 && !(__builtin_fmaf(most, sp.inv_t, kNoiseMax) < reached);
                 const unsigned long long bal = __builtin_amdgcn_ballot_w64(live);
                 if (bal == 0) continue;
                 const uint32_t quad = (uint32_t)(t >> 2) + (uint32_t)h, n = (uint32_t)__popcll(bal);
                 if (n >= (uint32_t)kDenseQuads) {
-                    draw_quads(quad, live ? mask : 0u, l);
+                    draw_quads(quad, live ? mask : 0u, l, most);
                 } else {
                     if (live) {
                         const uint32_t at = (q_tail + below(bal)) & (kQueue - 1);
@@ -1859,10 +1891,13 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
             }
         }
         if (WRITE && own) {
+            Elem o[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (!((m >> j) & 1u)) e[j] = NEG_INF;
-            store_group<DTYPE>(orow, t, V, e);
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t x = DTYPE == TDFA_F32 ? e[j % kWords] : e[j / 2] >> (16 * (j & 1));
+                o[j] = (m >> j) & 1u ? (Elem)x : NEG_INF;
+            }
+            store_group<DTYPE>(orow, t, V, o);
         }
     };
     bool pending_batch = false;                                // uniform: a batch has been taken and not worked on
@@ -1873,7 +1908,7 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
         t = t_next;
         own = own_next;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) e[j] = e_next[j];
+        for (int j = 0; j < kWords; ++j) e[j] = e_next[j];
         pending_batch = true;
     };
 
