@@ -380,6 +380,54 @@ int upload_stream(hipStream_t* out)
     return TDFA_OK;
 }
 
+// Pinned host memory through which tdfa_dfa_create sends a small automaton as one copy (four copies from the caller's and the
+// library's own pageable memory take 10 us each).  At most kStagingBlocks blocks of kStagingBytes are kept, each with one
+// call at a time; tdfa_trim frees them.  Larger automata are copied from where they lie, which the runtime does at the
+// link's rate.
+constexpr size_t kStagingBytes = (size_t)1 << 20, kStagingBlocks = 4;
+std::mutex g_staging_mutex;
+std::vector<void*>& g_staging = *new std::vector<void*>;       // blocks that no call holds (never destroyed, like the caches)
+
+void* staging_take()
+{
+    {
+        std::lock_guard<std::mutex> lock(g_staging_mutex);
+        if (!g_staging.empty()) {
+            void* p = g_staging.back();
+            g_staging.pop_back();
+            return p;
+        }
+    }
+    void* p = nullptr;
+    if (hipHostMalloc(&p, kStagingBytes, hipHostMallocPortable) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
+
+void staging_give(void* p)
+{
+    if (!p) return;
+    try {
+        std::lock_guard<std::mutex> lock(g_staging_mutex);
+        if (g_staging.size() < kStagingBlocks) {
+            g_staging.push_back(p);
+            return;
+        }
+    } catch (const std::bad_alloc&) {
+    }
+    (void)hipHostFree(p);
+}
+
+void staging_trim()
+{
+    std::vector<void*> gone;
+    {
+        std::lock_guard<std::mutex> lock(g_staging_mutex);
+        gone.swap(g_staging);
+    }
+    for (void* p : gone) (void)hipHostFree(p);
+}
+
 // Before the launches of a compile call on stream s: an automaton last used on another stream is waited for there.
 int before_use(const tdfa_dfa* d, hipStream_t s)
 {
@@ -1186,7 +1234,7 @@ int tdfa_dfa_create(const int32_t* trans, const uint8_t* accept, int32_t n_state
         memcpy(blob.data() + tdfa::plan_live_offset(d->n_order), plan.group_live.data(), plan.group_live.size() * 4);
         if (plan.n_classes) {
             const uint32_t sink = (uint32_t)(d->q_stride - 1);
-            tdfa::host_tasks((unsigned)tdfa::kJumpDepth, [&](unsigned m) {        // a row of the jump table per task
+            auto convert = [&](unsigned m) {                       // a row of the jump table
                 unsigned char* row = blob.data() + jump_off + (size_t)m * d->q_stride * esz;
                 const int32_t* src = plan.jump.data() + (size_t)m * n_states;
                 if (d->narrow) {
@@ -1198,21 +1246,30 @@ int tdfa_dfa_create(const int32_t* trans, const uint8_t* accept, int32_t n_state
                     for (int32_t q = 0; q < n_states; ++q) out32[q] = (src[q] >= 0 ? (uint32_t)src[q] : sink) * 4;
                     for (int32_t q = n_states; q < d->q_stride; ++q) out32[q] = sink * 4;
                 }
-            });
+            };
+            if (n_states >= 2048) {
+                tdfa::host_tasks((unsigned)tdfa::kJumpDepth, convert);
+            } else {
+                for (unsigned m = 0; m < (unsigned)tdfa::kJumpDepth; ++m) convert(m);
+            }
         }
         plan.jump.clear();
         plan.jump.shrink_to_fit();
     } catch (const std::bad_alloc&) {
         rc = fail(TDFA_E_OOM, "host allocation failed");
     }
-    if (rc == TDFA_OK) rc = dfa_alloc(d, &d->trans, (size_t)n_states * 256);
-    if (rc == TDFA_OK) rc = dfa_alloc(d, &d->accept, (size_t)n_states);
-    if (rc == TDFA_OK) rc = dfa_alloc(d, &d->order, (size_t)d->n_order);
-    if (rc == TDFA_OK) rc = dfa_alloc(d, &d->plan, blob.size());
+    // one block of device memory: what is uploaded, side by side, and the room for the transposed table
+    auto aligned = [](size_t n) { return (n + 255) / 256 * 256; };
+    const size_t at_order = aligned((size_t)n_states * 1024), at_plan = at_order + aligned((size_t)d->n_order * 4);
+    const size_t at_accept = at_plan + aligned(blob.size()), n_upload = at_accept + aligned((size_t)n_states);
+    unsigned char* block = nullptr;
+    if (rc == TDFA_OK) rc = dfa_alloc(d, &block, n_upload + (size_t)256 * d->q_stride * (d->narrow ? 2 : 4));
     if (rc == TDFA_OK) {
-        unsigned char* tt = nullptr;
-        rc = dfa_alloc(d, &tt, (size_t)256 * d->q_stride * (d->narrow ? 2 : 4));
-        d->trans_t = tt;
+        d->trans = reinterpret_cast<int32_t*>(block);
+        d->order = reinterpret_cast<int32_t*>(block + at_order);
+        d->plan = block + at_plan;
+        d->accept = block + at_accept;
+        d->trans_t = block + n_upload;
     }
     // the copies go on a stream of the library's own: the call waits for them, not for the caller's stream
     (void)s;
@@ -1228,11 +1285,22 @@ int tdfa_dfa_create(const int32_t* trans, const uint8_t* accept, int32_t n_state
     if (rc == TDFA_OK) {
         if (accept)
             for (int32_t q = 0; q < n_states; ++q) acc[q] = accept[q] ? 1 : 0;
-        hipError_t e = hipMemcpyAsync(d->trans, trans, (size_t)n_states * 1024, hipMemcpyHostToDevice, up);
-        if (e == hipSuccess) e = hipMemcpyAsync(d->accept, acc.data(), (size_t)n_states, hipMemcpyHostToDevice, up);
-        if (e == hipSuccess) e = hipMemcpyAsync(d->order, plan.order.data(), (size_t)d->n_order * 4, hipMemcpyHostToDevice, up);
-        if (e == hipSuccess) e = hipMemcpyAsync(d->plan, blob.data(), blob.size(), hipMemcpyHostToDevice, up);
+        hipError_t e = hipSuccess;
+        unsigned char* staging = n_upload <= kStagingBytes ? static_cast<unsigned char*>(staging_take()) : nullptr;
+        if (staging) {
+            memcpy(staging, trans, (size_t)n_states * 1024);
+            memcpy(staging + at_order, plan.order.data(), (size_t)d->n_order * 4);
+            memcpy(staging + at_plan, blob.data(), blob.size());
+            memcpy(staging + at_accept, acc.data(), (size_t)n_states);
+            e = hipMemcpyAsync(block, staging, n_upload, hipMemcpyHostToDevice, up);
+        } else {
+            e = hipMemcpyAsync(d->trans, trans, (size_t)n_states * 1024, hipMemcpyHostToDevice, up);
+            if (e == hipSuccess) e = hipMemcpyAsync(d->accept, acc.data(), (size_t)n_states, hipMemcpyHostToDevice, up);
+            if (e == hipSuccess) e = hipMemcpyAsync(d->order, plan.order.data(), (size_t)d->n_order * 4, hipMemcpyHostToDevice, up);
+            if (e == hipSuccess) e = hipMemcpyAsync(d->plan, blob.data(), blob.size(), hipMemcpyHostToDevice, up);
+        }
         if (e == hipSuccess) e = hipStreamSynchronize(up);
+        staging_give(staging);
         if (e != hipSuccess) rc = fail(TDFA_E_DEVICE, "upload: %s", hipGetErrorString(e));
     }
     if (rc != TDFA_OK) {
@@ -1367,6 +1435,7 @@ int tdfa_trim(void)
         tdfa::g_pool.clear();
     }
     for (void* p : to_free) (void)hipFree(p);
+    tdfa::staging_trim();
     tdfa::cache_trim();
     return TDFA_OK;
 }

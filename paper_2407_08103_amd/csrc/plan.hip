@@ -13,6 +13,8 @@
 // depends on its length only.  Counter-like subautomata (a bounded string body, an identifier
 // loop) are exactly of this kind.  The plan lists, for the largest classes, J[m][q] = c_C^m(q)
 // for m = 1 .. kJumpDepth, and keeps only the states for which every J[m][q] exists.
+#include <emmintrin.h>
+
 #include <algorithm>
 #include <array>
 #include <condition_variable>
@@ -34,6 +36,40 @@ struct Candidate {
     std::array<uint32_t, 8> clean;
     std::vector<int32_t> states;
 };
+
+// Sets of bytes as 256 bits, made of a row sixteen entries at a time: the signs of the 32-bit entries (or of the outcomes of a
+// comparison) survive two packings with saturation, and then one instruction collects sixteen of them.
+inline uint32_t signs16(__m128i a, __m128i b, __m128i c, __m128i d)
+{
+    return (uint32_t)_mm_movemask_epi8(_mm_packs_epi16(_mm_packs_epi32(a, b), _mm_packs_epi32(c, d)));
+}
+
+template <class Lanes>                 // lanes(v): negative where the byte belongs to the set
+inline void byte_set(const int32_t* row, Lanes lanes, std::array<uint32_t, 8>& out)
+{
+    for (int w = 0; w < 8; ++w) {
+        uint32_t half[2];
+        for (int h = 0; h < 2; ++h) {
+            const __m128i* p = reinterpret_cast<const __m128i*>(row + w * 32 + h * 16);
+            half[h] = signs16(lanes(_mm_loadu_si128(p)), lanes(_mm_loadu_si128(p + 1)), lanes(_mm_loadu_si128(p + 2)), lanes(_mm_loadu_si128(p + 3)));
+        }
+        out[(size_t)w] = half[0] | half[1] << 16;
+    }
+}
+
+// the bytes that lead to `to`
+inline void bytes_to(const int32_t* row, int32_t to, std::array<uint32_t, 8>& out)
+{
+    const __m128i t = _mm_set1_epi32(to);
+    byte_set(row, [t](__m128i v) { return _mm_cmpeq_epi32(v, t); }, out);
+}
+
+inline int count_bytes(const std::array<uint32_t, 8>& set)
+{
+    int n = 0;
+    for (uint32_t w : set) n += __builtin_popcount(w);
+    return n;
+}
 
 // What the first pass keeps of a state.
 struct StateFacts {
@@ -152,48 +188,59 @@ int build_plan(const int32_t* trans, int32_t n_states, StatePlan* plan)
             const int32_t* row = trans + (int64_t)q * 256;
             StateFacts& f = facts[(size_t)q];
             f.clean.fill(0u);
-            // which bytes have a transition, and the range check, without a branch per byte
-            int32_t lo = 0, hi = -1;
-            for (int w = 0; w < 8; ++w) {
-                uint32_t bits = 0;
-                for (int k = 0; k < 32; ++k) {
-                    const int32_t to = row[w * 32 + k];
-                    bits |= (uint32_t)(to >= 0) << k;
-                    lo = std::min(lo, to);
-                    hi = std::max(hi, to);
-                }
-                f.live[(size_t)w] = bits;
-            }
-            if (lo < TDFA_DEAD || hi >= n_states) {
+            // which bytes have a transition, and the range check: an entry plus one lies in [0, n_states]
+            const __m128i one = _mm_set1_epi32(1), most = _mm_set1_epi32(n_states), all = _mm_set1_epi32(-1);
+            __m128i outside = _mm_setzero_si128();
+            byte_set(row, [&](__m128i v) {
+                const __m128i x = _mm_add_epi32(v, one);
+                outside = _mm_or_si128(outside, _mm_or_si128(x, _mm_cmpgt_epi32(x, most)));
+                return _mm_xor_si128(v, all);                 // (negative where v is not)
+            }, f.live);
+            if (_mm_movemask_ps(_mm_castsi128_ps(outside)) != 0) {
                 for (int b = 0; b < 256; ++b)
                     if (row[b] < TDFA_DEAD || row[b] >= n_states) {
                         bad[t] = Bad{q, b, row[b]};
                         return;
                     }
             }
-            // most frequent live target, lowest id on ties: over the live bytes only
-            int live = 0;
-            int32_t dflt = TDFA_DEAD, best = 0;
-            for (int w = 0; w < 8; ++w)
-                for (uint32_t m = f.live[(size_t)w]; m; m &= m - 1) {
-                    const int32_t to = row[w * 32 + __builtin_ctz(m)];
-                    ++live;
-                    const int32_t c = ++count[(size_t)to];
-                    if (c > best || (c == best && to < dflt)) {      // whoever ends with the highest count passes here last
-                        best = c;
-                        dflt = to;
-                    }
-                }
+            const int live = count_bytes(f.live);
             f.n_live = live;
             n_live[(size_t)q] = live;
+            // Most frequent live target, lowest id on ties.  A target of more than half of the live bytes is the one: those of
+            // the first, the middle and the last word's first live byte are tried.
+            int32_t best = 0;
+            std::array<uint32_t, 8> to_it;
+            int32_t tried = TDFA_DEAD;
+            for (int w0 : {0, 3, 7}) {
+                int w = w0;
+                while (w < 7 && f.live[(size_t)w] == 0) ++w;
+                if (f.live[(size_t)w] == 0) continue;
+                const int32_t to = row[w * 32 + __builtin_ctz(f.live[(size_t)w])];
+                if (to == tried) continue;
+                tried = to;
+                bytes_to(row, to, to_it);
+                const int n = count_bytes(to_it);
+                if (2 * n <= live) continue;
+                best = n;
+                if (best >= 2) f.clean = to_it;
+                break;
+            }
+            if (best == 0 && live != 0) {
+                int32_t dflt = TDFA_DEAD;
+                for (int w = 0; w < 8; ++w)
+                    for (uint32_t m = f.live[(size_t)w]; m; m &= m - 1) {
+                        const int32_t to = row[w * 32 + __builtin_ctz(m)];
+                        const int32_t c = ++count[(size_t)to];
+                        if (c > best || (c == best && to < dflt)) {      // whoever ends with the highest count passes here last
+                            best = c;
+                            dflt = to;
+                        }
+                    }
+                for (int w = 0; w < 8; ++w)
+                    for (uint32_t m = f.live[(size_t)w]; m; m &= m - 1) count[(size_t)row[w * 32 + __builtin_ctz(m)]] = 0;
+                if (best >= 2) bytes_to(row, dflt, f.clean);
+            }
             f.has_clean = best >= 2;                         // a clean set of one byte gains nothing
-            for (int w = 0; w < 8; ++w)
-                for (uint32_t m = f.live[(size_t)w]; m; m &= m - 1) {
-                    const int k = __builtin_ctz(m);
-                    const int32_t to = row[w * 32 + k];
-                    count[(size_t)to] = 0;
-                    if (f.has_clean && to == dflt) f.clean[(size_t)w] |= 1u << k;
-                }
             uint64_t h = 0x9E3779B97F4A7C15ull;
             if (f.has_clean)
                 for (uint32_t w : f.clean) h = (h ^ w) * 0xFF51AFD7ED558CCDull, h ^= h >> 29;
@@ -256,16 +303,13 @@ int build_plan(const int32_t* trans, int32_t n_states, StatePlan* plan)
             if (s < 0) return s;
             int32_t& known = memo[(size_t)s];
             if (known != kUnset) return known;
-            // the target on the first clean byte, then: do all clean bytes agree with it?  (compared over
-            // the whole row without a branch, which the compiler turns into vector compares)
+            // the target on the first clean byte, then: do all clean bytes agree with it?
             const int32_t* row = trans + (int64_t)s * 256;
             const int32_t t0 = row[first_clean];
+            std::array<uint32_t, 8> agree;
+            bytes_to(row, t0, agree);
             bool all = true;
-            for (int w = 0; w < 8; ++w) {
-                uint32_t agree = 0;
-                for (int k = 0; k < 32; ++k) agree |= (uint32_t)(row[w * 32 + k] == t0) << k;
-                all = all && (agree & c.clean[(size_t)w]) == c.clean[(size_t)w];
-            }
+            for (size_t w = 0; w < 8; ++w) all = all && (agree[w] & c.clean[w]) == c.clean[w];
             return known = all ? t0 : kNone;
         };
         ClassJumps& out = found[ci];
@@ -303,8 +347,10 @@ int build_plan(const int32_t* trans, int32_t n_states, StatePlan* plan)
         members.push_back(std::move(f.ok));
     }
 
-    // How many (state, b1, b2) survive two bytes: sizes the lists of the sweep over prefixes.
-    {
+    // How many (state, b1, b2) survive two bytes: sizes the lists of the sweep over prefixes, which automata with classes do
+    // not take.
+    plan->n_pairs = 0;
+    if (plan->n_classes == 0) {
         std::array<int64_t, kMaxHostThreads> part{};
         over_states(n_states, [&](int32_t first, int32_t last, unsigned t) {
             int64_t total = 0;
@@ -315,7 +361,6 @@ int build_plan(const int32_t* trans, int32_t n_states, StatePlan* plan)
             }
             part[t] = total;
         });
-        plan->n_pairs = 0;
         for (int64_t v : part) plan->n_pairs += v;
     }
 

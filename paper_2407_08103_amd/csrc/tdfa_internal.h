@@ -39,12 +39,12 @@ struct StatePlan {
     std::vector<int32_t> jump;         // [kJumpDepth][n_states]: state after m + 1 clean bytes (DEAD = -1);
                                        // empty if n_classes == 0
     int n_classes = 0;
-    int64_t n_pairs = 0;               // (state, b1, b2) triples with delta*(state, b1 b2) defined
+    int64_t n_pairs = 0;               // (state, b1, b2) triples with delta*(state, b1 b2) defined (0 if n_classes != 0)
 };
 // Validates trans (every entry in [-1, n_states)) and fills *plan.
 int make_state_plan(const int32_t* trans, int32_t n_states, StatePlan* plan);
 // Calls task(0) .. task(n_tasks - 1) on the library's few host threads (the caller's among them) and
-// returns when all are done.
+// returns when all are done.  (Waking them takes some 20 us.)
 void host_tasks(unsigned n_tasks, const std::function<void(unsigned)>& task);
 
 // Layout of the plan as uploaded (one device blob per automaton):

@@ -65,6 +65,15 @@ def test_random_dfa_shapes(T, oracle, n_states, n_tokens):
     _full_check(T, oracle, dfa, vocab)
 
 
+@pytest.mark.parametrize("n_states", [1, 1000, 1012, 1018, 1019, 1024])
+def test_upload_in_one_piece_or_several(T, oracle, n_states):
+    """Around the size up to which an automaton is sent as one copy."""
+    dfa = random_dfa(n_states, 0.4, 0.2, np.random.default_rng(n_states))
+    vocab = configs.small(1, n_tokens=130).vocab
+    table, v, d = _compile(T, dfa, vocab)
+    G.check_rows(table, oracle.compile_walk(dfa.trans, vocab.data, vocab.offsets, n_threads=8), np.arange(n_states))
+
+
 def test_empty_duplicate_and_long_tokens(T, oracle):
     d = compile_regex(r"(ab)*c|x{0,300}y")
     toks = [b"ab", b"", b"ab", b"c", b"", b"x" * 299 + b"y", b"x" * 301, b"abc", b"x" * 150]

@@ -104,3 +104,42 @@ def test_plan_random_and_configs(T):
 def test_plan_bad_arguments(T):
     with pytest.raises(T.TdfaError):
         T.plan_describe(np.full((2, 256), 9, dtype=np.int32))
+
+
+@pytest.mark.parametrize("clean", ["first byte apart", "last byte apart", "upper half", "half and one", "half, tied", "plurality", "one word", "two bytes"])
+def test_clean_set_found_any_way(T, clean):
+    """The bytes of the most frequent target (lowest id on ties), where it has more than half of the live bytes, wherever
+    those lie in the row, and where it has not."""
+    n = 64
+    rest = np.arange(256)
+    sets = {"first byte apart": rest[1:], "last byte apart": rest[:-1], "upper half": rest[128:], "half and one": rest[::2].tolist() + [1],
+            "half, tied": rest[::2], "plurality": rest[100:140], "one word": rest[224:], "two bytes": [7, 250]}
+    c = np.array(sets[clean])
+    q = np.arange(n)[:, None]
+    trans = np.full((n, 256), -1, dtype=np.int32)
+    if clean in ("plurality", "half and one", "first byte apart", "last byte apart"):
+        trans[:] = (q + 2 + np.arange(256)[None, :] % 40) % n           # many other targets, each less often
+    elif clean == "half, tied":
+        trans[:, 1::2] = np.maximum(q, (q + 1) % n)                     # as often, but never the lower id
+    lower = np.minimum(q, (q + 1) % n) if clean == "half, tied" else (q + 1) % n
+    trans[:, c] = lower
+    if clean == "half, tied":
+        trans[:] = np.where(trans == lower, lower, np.where(trans < 0, -1, np.maximum(trans, lower + 1)))
+        trans = np.minimum(trans, n - 1)
+        trans[n - 1] = -1
+    _, group_class, found, _ = T.plan_describe(trans)
+    want = np.zeros(8, dtype=np.uint32)
+    for b in c:
+        want[int(b) >> 5] |= np.uint32(1 << (int(b) & 31))
+    assert len(found) == 1 and np.array_equal(found[0], want)
+
+
+@pytest.mark.parametrize("at", [0, 3, 4, 15, 16, 31, 100, 255])
+@pytest.mark.parametrize("value", [-2, -2**31, 5, 2**31 - 1])
+def test_entries_outside_the_automaton(T, at, value):
+    trans = np.full((5, 256), -1, dtype=np.int32)
+    trans[:, ::3] = 4
+    T.plan_describe(trans)
+    trans[3, at] = value
+    with pytest.raises(Exception, match=rf"trans\[3\]\[{at}\] = {value} "):
+        T.plan_describe(trans)
