@@ -25,6 +25,7 @@
 #include "pda_device.h"
 #include "tdfa_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace tdfa {
@@ -2014,26 +2015,57 @@ void gather_shape(const MaskArgs& a, int* parts_out, int* threads_out, int* gpp_
 
 }  // namespace
 
-// Launch shape of the streaming kernels: a row per workgroup of 1024 threads when there are
-// enough rows to fill the 256 compute units: the result then needs no meeting of workgroups.
-// Smaller batches split each row over `parts` workgroups of 256 threads, enough to have about
-// 2048 of them, each with at least one unrolled pass of work.
 namespace {
-void stream_shape(const MaskArgs& a, int* parts_out, int* threads_out, int* gpp_out)
+constexpr int kPieceGroups = 4096;     // groups of a row that a workgroup takes where rows are split
+constexpr int kSmallBatch = 16;        // rows from which on that is the better split (1 to 8 rows: 4.8 to 6.0 us in 16 parts of 256 threads, 5.9 to 6.4 us so)
+
+// Launch shape of the streaming kernels: `parts` workgroups of `threads` threads to a row.
+//
+// What it weighs: a compute unit streams at what one unit gets from memory (a 256 KB row in 6.5 us), so few rows are split;
+// every workgroup costs its launch and its own look at state and bits, and workgroups of a row meet at the end; a workgroup
+// of 512 threads starts and ends a microsecond sooner than one of 1,024, which has more loads in flight.
+void stream_shape(const MaskArgs& a, bool pda, int* parts_out, int* threads_out, int* gpp_out)
 {
     const int n_groups = (a.n_tokens + 7) >> 3;
-    int parts = 1, threads = 1024;
-    if (a.batch < 192 || n_groups < 4096) {
+    const int64_t batch = a.batch, pieces = (n_groups + kPieceGroups - 1) / kPieceGroups;
+    const bool plain = a.dtype != TDFA_F32 && !a.masked_out;             // 16-bit logits that are only read
+    int64_t parts = 1;
+    int threads = 1024;
+    if (plain && !pda && n_groups > 1024 && n_groups < kPieceGroups) {
+        // a short row, 8,193 to 32,767 tokens.  32,000 tokens, 16, 64, 256 and 1,024 rows: in parts of 256 threads 5.2, 6.0, 8.2
+        // and 12.9 us; so 4.9, 5.9, 6.4 and 11.9 us (9,000 tokens 5.1, -, 6.3 and 9.4 -> 4.4, -, 5.1 and 8.8)
+        threads = 512;
+    } else if (plain && !pda && n_groups >= kPieceGroups && n_groups < 2 * kPieceGroups && (a.delta ? batch >= 320 || (batch > 128 && batch < 192) : batch >= 768)) {
+        // rows of middle length, enough to fill the chip.  50,000 tokens, 160, 384, 512 and 1,024 rows: 8.3, 10.5, 11.6 and 20.1 -> 5.9,
+        // 9.5, 10.8 and 16.4 us (200 rows that allow most 7.5 -> 8.1, so not; 384 rows
+        // of a packed table 10.1 -> 10.5; 1,024 rows of 128,256 tokens that allow most 42.4 -> 43.6)
+        threads = 512;
+    } else if (plain && n_groups >= kPieceGroups && batch >= kSmallBatch && batch < 192 && (batch <= 170 || pieces <= 4) &&
+               (a.delta || pda || pieces > 2)) {
+        // as many pieces as the chip holds at once.  128,256 tokens, 16, 64 and 128 rows: in parts of 256 threads 7.3, 10.5 and
+        // 13.2 us, in one piece 8.3, 9.3 and 9.1; so 6.0, 7.4 and 8.3 us.  In fewer than
+        // three pieces one workgroup of 1,024 threads is better: 191 rows 13.6 and 11.6 -> 10.1 us; rows too long for that stay as
+        // they were (250,000 tokens, 180 rows: 15.6, in two pieces 20.3), as do the shorter ones of packed tables (50,000 tokens, 64
+        // rows: 6.9, in two pieces 7.4).
+        // The push-down step matches its stack in every workgroup: two large ones at most (64 and 128 rows: 14.7 and 21.0 ->
+        // 12.9 and 13.7 us).
+        parts = pda ? (2 * batch <= 256 ? 2 : 1) : batch <= 170 ? std::min<int64_t>(pieces, 512 / batch) : 1;
+        threads = pda || batch > 170 ? 1024 : 512;
+    } else if (!plain && pieces > 3 && (a.dtype == TDFA_F32 ? batch >= 48 && (batch < 192 || a.masked_out) : batch >= kSmallBatch && batch <= 64)) {
+        // long rows that are written as well, or of fp32: larger workgroups keep the memory busy with fewer of them.  128,256
+        // tokens: fp32, 64 and 128 rows 11.3 and 15.2 -> 9.7 and 13.6 us; with the penalised row 64, 256 and 1,024 rows 15.3, 50.2
+        // and 208 -> 13.8, 46.8 and 193 us; bf16 with it 16 and 64 rows 7.2 and 11.0 -> 6.3 and 8.5 us (100 rows 13.7 -> 14.0, so
+        // not; 32 rows of fp32 8.9 -> 9.2, 128 rows of 70,000 tokens 10.9 -> 11.4)
+        parts = pieces;
+    } else if (batch < 192 || n_groups < kPieceGroups) {
         threads = 256;
-        parts = (2048 + a.batch - 1) / a.batch;
-        const int max_parts = (n_groups + 1023) / 1024;
-        if (parts > max_parts) parts = max_parts;
+        parts = std::min<int64_t>((2048 + batch - 1) / batch, (n_groups + 1023) / 1024);
     }
     if (parts < 1) parts = 1;
-    int gpp = (n_groups + parts - 1) / parts;
+    int gpp = (int)((n_groups + parts - 1) / parts);
     if (gpp < 1) gpp = 1;
     gpp = (gpp + 15) & ~15;                    // the bits of 16 groups are read at once
-    *parts_out = parts;
+    *parts_out = (int)parts;
     *threads_out = threads;
     *gpp_out = gpp;
 }
@@ -2055,7 +2087,7 @@ bool mask_step_uses_scratch(const MaskArgs& a)
     if (a.batch <= 0) return false;
     int parts, threads, gpp;
     if (packed_takes_gather(a)) gather_shape(a, &parts, &threads, &gpp);
-    else stream_shape(a, &parts, &threads, &gpp);
+    else stream_shape(a, false, &parts, &threads, &gpp);
     return parts > 1;
 }
 
@@ -2074,10 +2106,10 @@ struct BitsInLds {
     size_t lds;
     bool fits;
 };
-BitsInLds bits_in_lds(const MaskArgs& a)
+BitsInLds bits_in_lds(const MaskArgs& a, bool pda = false)
 {
     BitsInLds r;
-    stream_shape(a, &r.parts, &r.threads, &r.gpp);
+    stream_shape(a, pda, &r.parts, &r.threads, &r.gpp);
     // groups per load batch: one for the few small workgroups of a small batch
     r.unroll = r.threads < 1024 && (int64_t)a.batch * r.parts <= 384 ? 1 : 2;
     // A stretch of the row per wavefront, in whole 16-group pieces; the bits of the stretches fit
@@ -2113,7 +2145,7 @@ int raise_lds_limit(size_t lds)
 
 bool mask_step_takes_pda(const PdaMaskArgs& a)
 {
-    return a.batch > 0 && a.dtype != TDFA_F32 && !a.delta && !a.targets && a.n_tokens <= (1 << 27) && bits_in_lds(a).fits;
+    return a.batch > 0 && a.dtype != TDFA_F32 && !a.delta && !a.targets && a.n_tokens <= (1 << 27) && bits_in_lds(a, true).fits;
 }
 
 int launch_mask_step(const MaskArgs& a, hipStream_t stream)
@@ -2176,7 +2208,7 @@ int launch_pda_mask_step(const PdaMaskArgs& a, hipStream_t stream)
 {
     if (a.batch <= 0) return TDFA_OK;
     if (!mask_step_takes_pda(a)) return fail(TDFA_E_UNSUPPORTED, "this step wants one row of allowed bits per sequence");
-    const BitsInLds sh = bits_in_lds(a);
+    const BitsInLds sh = bits_in_lds(a, true);
     if ((int64_t)a.batch * sh.parts > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
     const int rc = raise_lds_limit(sh.lds);
     if (rc != TDFA_OK) return rc;

@@ -65,7 +65,7 @@ def _rand_table(n_rows, n_tokens, p_live, seed):
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
 @pytest.mark.parametrize("n_tokens,batch", [(8, 1), (37 * 8, 3), (1000 * 8 + 8, 5), (40000, 2), (50024, 300),
-                                            (5, 2), (37 * 8 + 3, 3), (1000 * 8 + 1, 5), (50021, 300)])
+                                            (5, 2), (37 * 8 + 3, 3), (1000 * 8 + 1, 5), (50021, 300), (98313, 48), (131075, 64), (131080, 200)])
 def test_random_tables(T, oracle, dtype, n_tokens, batch):
     """Random sparse tables; sizes cover one group, ragged parts, many parts per row, one part per
     row, and rows whose length is not a multiple of the eight tokens a lane reads at once (the row
@@ -94,6 +94,15 @@ def test_random_tables(T, oracle, dtype, n_tokens, batch):
                                             (1200011, 192)])                      # rows too long for the bits to sit in LDS at all
 def test_sparse_and_mixed_rows(T, oracle, n_tokens, batch):
     _sparse_and_mixed_rows(T, oracle, n_tokens, batch, BF16)
+
+
+@pytest.mark.parametrize("dtype,n_tokens,batch", [(BF16, v, b) for v, b in [
+    (8192, 20), (8193, 20), (32760, 200), (32767, 16), (32769, 15), (32769, 16), (33003, 128), (33003, 129), (65528, 191), (65529, 192),
+    (65536, 319), (65536, 320), (65537, 170), (65545, 171), (98307, 64), (131081, 65), (140000, 191), (250003, 100), (250003, 172)]] +
+    [(F32, v, b) for v, b in [(98304, 48), (98312, 47), (98313, 48), (98313, 64), (131075, 191), (131075, 192)]])
+def test_rows_at_the_edges_of_the_launch_shapes(T, oracle, dtype, n_tokens, batch):
+    """Around the row lengths and batches at which rows are split into another number of workgroups, or of another size."""
+    _sparse_and_mixed_rows(T, oracle, n_tokens, batch, dtype)
 
 
 @pytest.mark.parametrize("n_tokens,batch", [(128256, 200), (128256, 7), (300011, 16), (5000, 250), (37 * 8 + 3, 3), (400003, 5)])
