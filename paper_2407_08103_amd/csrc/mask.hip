@@ -976,13 +976,12 @@ mask_step_bf16_kernel(std::conditional_t<PDA, PdaMaskArgs, MaskArgs> a, int part
 // SIMD do not find room and a compute unit holds one workgroup of 1,024 threads at a time, not two (the compiler counts up
 // to 100 as room for eight; the counters show half the wavefronts in flight from 94 on).  128,256 tokens, packed
 // tables, every row sparse: 1,024 rows 16.7 -> 13.5 us (50 signatures) and 14.4 -> 11.2 us (16 schemas), 512 rows 11.3 ->
-// 8.5 us; 1,024 rows of 64 schemas' states on a dense table 31.8 -> 26.4 us; push-down step, 512 rows 28.1 -> 24.6 us, 1,024
-// rows 51.6 -> 43.0 us.  The registers that are kept in lanes for that cost launches that fill the chip once 0.2 to 0.5 us.
-template <int kUnroll, bool PDA, bool GATHER>
+// 8.5 us; 1,024 rows of 64 schemas' states on a dense table 31.8 -> 26.4 us.  The registers that are kept in lanes for that cost launches that fill the chip once 0.2 to 0.5 us.
+template <int kUnroll>
 __global__ void __launch_bounds__(kMaxThreads) __attribute__((amdgpu_num_sgpr(80)))
-mask_step_bf16_many_kernel(std::conditional_t<PDA, PdaMaskArgs, MaskArgs> a, int parts, int groups_per_part, int stretch)
+mask_step_bf16_many_kernel(MaskArgs a, int parts, int groups_per_part, int stretch)
 {
-    mask_step_bf16<false, kUnroll, true, 2, PDA, GATHER>(a, parts, groups_per_part, stretch);
+    mask_step_bf16<false, kUnroll, true, 2, false, true>(a, parts, groups_per_part, stretch);
 }
 
 // One step on fp32 logits.  Like the 16-bit kernel, every wavefront first reads the allowed bytes of
@@ -2019,6 +2018,17 @@ namespace {
 constexpr int kPieceGroups = 4096;     // groups of a row that a workgroup takes where rows are split
 constexpr int kSmallBatch = 16;        // rows from which on that is the better split (1 to 8 rows: 4.8 to 6.0 us in 16 parts of 256 threads, 5.9 to 6.4 us so)
 
+// Rows that one workgroup of 512 threads streams with four groups per lane and buffer, not one of 1,024 with two: as much in
+// flight, and the workgroup starts, matches the stack and ends sooner.  Push-down step, 128,256 tokens, 160, 256 and 512 rows
+// 14.8, 15.1 and 23.4 -> 14.2, 14.4 and 22.8 us; greedy, where some compute units hold two rows, 300 and 383 rows 17.3 and 18.0 -> 15.8 and 16.7 (256 rows 9.8
+// -> 10.0, 257 rows 12.3 -> 13.7, 512 rows 18.3 -> 18.6, 1,024 rows 32.8 -> 33.6, so not).
+bool takes_deep(const MaskArgs& a, bool pda)
+{
+    if (a.dtype == TDFA_F32 || a.masked_out) return false;
+    const int n_groups = (a.n_tokens + 7) >> 3;
+    return pda ? n_groups >= kPieceGroups && a.batch > 128 : n_groups >= 2 * kPieceGroups && a.delta && a.batch >= 288 && a.batch < kGatherRows;
+}
+
 // Launch shape of the streaming kernels: `parts` workgroups of `threads` threads to a row.
 //
 // What it weighs: a compute unit streams at what one unit gets from memory (a 256 KB row in 6.5 us), so few rows are split;
@@ -2040,7 +2050,7 @@ void stream_shape(const MaskArgs& a, bool pda, int* parts_out, int* threads_out,
         // 9.5, 10.8 and 16.4 us (200 rows that allow most 7.5 -> 8.1, so not; 384 rows
         // of a packed table 10.1 -> 10.5; 1,024 rows of 128,256 tokens that allow most 42.4 -> 43.6)
         threads = 512;
-    } else if (plain && n_groups >= kPieceGroups && batch >= kSmallBatch && batch < 192 && (batch <= 170 || pieces <= 4) &&
+    } else if (plain && n_groups >= kPieceGroups && batch >= kSmallBatch && batch < (pda ? 129 : 192) && (batch <= 170 || pieces <= 4) &&
                (a.delta || pda || pieces > 2)) {
         // as many pieces as the chip holds at once.  128,256 tokens, 16, 64 and 128 rows: in parts of 256 threads 7.3, 10.5 and
         // 13.2 us, in one piece 8.3, 9.3 and 9.1; so 6.0, 7.4 and 8.3 us.  In fewer than
@@ -2049,7 +2059,7 @@ void stream_shape(const MaskArgs& a, bool pda, int* parts_out, int* threads_out,
         // rows: 6.9, in two pieces 7.4).
         // The push-down step matches its stack in every workgroup: two large ones at most (64 and 128 rows: 14.7 and 21.0 ->
         // 12.9 and 13.7 us).
-        parts = pda ? (2 * batch <= 256 ? 2 : 1) : batch <= 170 ? std::min<int64_t>(pieces, 512 / batch) : 1;
+        parts = pda ? 2 : batch <= 170 ? std::min<int64_t>(pieces, 512 / batch) : 1;
         threads = pda || batch > 170 ? 1024 : 512;
     } else if (!plain && pieces > 3 && (a.dtype == TDFA_F32 ? batch >= 48 && (batch < 192 || a.masked_out) : batch >= kSmallBatch && batch <= 64)) {
         // long rows that are written as well, or of fp32: larger workgroups keep the memory busy with fewer of them.  128,256
@@ -2057,6 +2067,8 @@ void stream_shape(const MaskArgs& a, bool pda, int* parts_out, int* threads_out,
         // and 208 -> 13.8, 46.8 and 193 us; bf16 with it 16 and 64 rows 7.2 and 11.0 -> 6.3 and 8.5 us (100 rows 13.7 -> 14.0, so
         // not; 32 rows of fp32 8.9 -> 9.2, 128 rows of 70,000 tokens 10.9 -> 11.4)
         parts = pieces;
+    } else if (takes_deep(a, pda)) {
+        threads = 512;
     } else if (batch < 192 || n_groups < kPieceGroups) {
         threads = 256;
         parts = std::min<int64_t>((2048 + batch - 1) / batch, (n_groups + 1023) / 1024);
@@ -2110,8 +2122,8 @@ BitsInLds bits_in_lds(const MaskArgs& a, bool pda = false)
 {
     BitsInLds r;
     stream_shape(a, pda, &r.parts, &r.threads, &r.gpp);
-    // groups per load batch: one for the few small workgroups of a small batch
-    r.unroll = r.threads < 1024 && (int64_t)a.batch * r.parts <= 384 ? 1 : 2;
+    // groups per load batch: one for the few small workgroups of a small batch, four where half as many wavefronts stream a row
+    r.unroll = takes_deep(a, pda) ? 4 : r.threads < 1024 && (int64_t)a.batch * r.parts <= 384 ? 1 : 2;
     // A stretch of the row per wavefront, in whole 16-group pieces; the bits of the stretches fit
     // in LDS for any vocabulary of a few hundred thousand tokens, else every stretch is streamed.
     const int n_waves = r.threads / 64;
@@ -2131,11 +2143,12 @@ int raise_lds_limit(size_t lds)
     if (dev >= 0 && dev < 64 && !raised[dev]) {
         for (const void* k : {reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true>),
                               reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true>),
-                              reinterpret_cast<const void*>(mask_step_bf16_many_kernel<1, false, true>),
-                              reinterpret_cast<const void*>(mask_step_bf16_many_kernel<2, false, true>),
+                              reinterpret_cast<const void*>(mask_step_bf16_many_kernel<1>),
+                              reinterpret_cast<const void*>(mask_step_bf16_many_kernel<2>),
                               reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 1, true, 2, true>),
                               reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 2, true, 2, true>),
-                              reinterpret_cast<const void*>(mask_step_bf16_many_kernel<2, true, false>)})
+                              reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 4, true>),
+                              reinterpret_cast<const void*>(mask_step_bf16_kernel<false, 4, true, 2, true>)})
             TDFA_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBitRowBytes));
         raised[dev] = true;
     }
@@ -2190,9 +2203,11 @@ int launch_mask_step(const MaskArgs& a, hipStream_t stream)
     else if (a.masked_out)
         mask_step_bf16_kernel<true, 2, false><<<grid, kThreads, 0, stream>>>(a, parts, gpp, stretch);
     else if (skip && (a.batch >= kGatherRows || !a.delta)) {
-        if (unroll == 1) mask_step_bf16_many_kernel<1, false, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
-        else mask_step_bf16_many_kernel<2, false, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
-    } else if (skip && unroll == 1)
+        if (unroll == 1) mask_step_bf16_many_kernel<1><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
+        else mask_step_bf16_many_kernel<2><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
+    } else if (skip && unroll == 4)
+        mask_step_bf16_kernel<false, 4, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
+    else if (skip && unroll == 1)
         mask_step_bf16_kernel<false, 1, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
     else if (skip)
         mask_step_bf16_kernel<false, 2, true><<<grid, kThreads, lds, stream>>>(a, parts, gpp, stretch);
@@ -2214,9 +2229,7 @@ int launch_pda_mask_step(const PdaMaskArgs& a, hipStream_t stream)
     if (rc != TDFA_OK) return rc;
     const dim3 grid((unsigned)(a.batch * sh.parts));
     const unsigned threads = (unsigned)sh.threads;
-    // (a workgroup of 1,024 threads to each of 256 compute units, or smaller ones: all are in flight in either form)
-    if (sh.threads == kMaxThreads && a.batch > 256)
-        mask_step_bf16_many_kernel<2, true, false><<<grid, threads, sh.lds, stream>>>(a, sh.parts, sh.gpp, sh.stretch);
+    if (sh.unroll == 4) mask_step_bf16_kernel<false, 4, true, 2, true><<<grid, threads, sh.lds, stream>>>(a, sh.parts, sh.gpp, sh.stretch);
     else if (sh.unroll == 1) mask_step_bf16_kernel<false, 1, true, 2, true><<<grid, threads, sh.lds, stream>>>(a, sh.parts, sh.gpp, sh.stretch);
     else mask_step_bf16_kernel<false, 2, true, 2, true><<<grid, threads, sh.lds, stream>>>(a, sh.parts, sh.gpp, sh.stretch);
     TDFA_HIP(hipGetLastError());
