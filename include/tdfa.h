@@ -145,6 +145,7 @@ TDFA_API int tdfa_dfa_compile_path(tdfa_dfa *dfa, int path);
  * block serves a request of at least half its size (of a table: of at least four fifths), or one that is
  * 64 KiB smaller.  The counts beside a destroyed table (see tdfa_compile_token_dfa) are kept as well,
  * some thousand arrays of 4 to 128 KiB per size; every 1,024th that comes back waits for the device.
+ * tdfa_dfa_create keeps at most four pinned host blocks of 1 MiB, through which it sends small automata.
  * No other allocator of the process can ask for the kept memory: call tdfa_trim before a large allocation
  * elsewhere.
  * tdfa_trim() gives the kept blocks back to the device.  Errors: none. */
@@ -225,8 +226,9 @@ TDFA_API int64_t tdfa_allow_row_words(int32_t n_tokens);
  * A table that the library has written (this call, tdfa_compile_stacked, tdfa_table_concat,
  * tdfa_table_minimize) also carries, in a small device array of its own, how many tokens each state
  * allows; a decode step is done after two reads with a sequence whose state allows none (a text that
- * is complete).  A caller that edits the allowed bits in its own buffers afterwards must wrap them
- * again (tdfa_table_wrap keeps no such counts); tdfa_table_apply_terminals recounts by itself.
+ * is complete), and tdfa_table_minimize reads its rows only where an allowed bit is set.  A caller that
+ * edits the allowed bits, or adds edges, in its own buffers afterwards must wrap them again
+ * (tdfa_table_wrap keeps no such counts); tdfa_table_apply_terminals recounts by itself.
  * Errors: INVALID_ARG, OOM, DEVICE. */
 TDFA_API int tdfa_compile_token_dfa(const tdfa_vocab *vocab, const tdfa_dfa *dfa,
                            int32_t *delta_dev, uint32_t *allow_dev,
@@ -455,8 +457,8 @@ TDFA_API int tdfa_table_apply_terminals(tdfa_table *table, int32_t n_edges, cons
  *   accept_out_host   : host, uint8 [n_rows] or NULL; the first (new number of rows) entries
  *                       are written.
  * A set-up call: it allocates and frees device memory of its own (a few bytes per distinct target
- * of every row), reads the table twice, waits for a counter after every round of refinement, and
- * blocks until the new table is complete; not to be called under stream capture.  A table whose rows
+ * of every row, eight per token), reads the table twice, waits for a counter after every few rounds of
+ * refinement, and blocks until the new table is complete; not to be called under stream capture.  A table whose rows
  * have thousands of distinct targets each takes a slower route that streams the rows in every
  * round.  Errors: INVALID_ARG, OOM, DEVICE. */
 TDFA_API int tdfa_table_minimize(const tdfa_table *table, const uint8_t *accept_host,

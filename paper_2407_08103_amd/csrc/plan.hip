@@ -206,24 +206,26 @@ int build_plan(const int32_t* trans, int32_t n_states, StatePlan* plan)
             const int live = count_bytes(f.live);
             f.n_live = live;
             n_live[(size_t)q] = live;
-            // Most frequent live target, lowest id on ties.  A target of more than half of the live bytes is the one: those of
-            // the first, the middle and the last word's first live byte are tried.
+            // Most frequent live target, lowest id on ties.  A target of more than half of the live bytes is the one: of the
+            // targets of a live byte of the first, the middle and the last word one that two of them agree on is tried (random
+            // automata, whose targets all differ, are not).
             int32_t best = 0;
-            std::array<uint32_t, 8> to_it;
-            int32_t tried = TDFA_DEAD;
-            for (int w0 : {0, 3, 7}) {
-                int w = w0;
+            int32_t probe[3] = {-1, -2, -3};
+            for (int i = 0; i < 3; ++i) {
+                int w = i == 0 ? 0 : i == 1 ? 3 : 7;
                 while (w < 7 && f.live[(size_t)w] == 0) ++w;
-                if (f.live[(size_t)w] == 0) continue;
-                const int32_t to = row[w * 32 + __builtin_ctz(f.live[(size_t)w])];
-                if (to == tried) continue;
-                tried = to;
-                bytes_to(row, to, to_it);
+                while (w > 0 && f.live[(size_t)w] == 0) --w;
+                if (f.live[(size_t)w] != 0) probe[i] = row[w * 32 + (i == 2 ? 31 - __builtin_clz(f.live[(size_t)w]) : __builtin_ctz(f.live[(size_t)w]))];
+            }
+            const int32_t likely = probe[0] == probe[1] || probe[0] == probe[2] ? probe[0] : probe[1] == probe[2] ? probe[1] : TDFA_DEAD;
+            if (likely >= 0) {
+                std::array<uint32_t, 8> to_it;
+                bytes_to(row, likely, to_it);
                 const int n = count_bytes(to_it);
-                if (2 * n <= live) continue;
-                best = n;
-                if (best >= 2) f.clean = to_it;
-                break;
+                if (2 * n > live) {
+                    best = n;
+                    if (best >= 2) f.clean = to_it;
+                }
             }
             if (best == 0 && live != 0) {
                 int32_t dflt = TDFA_DEAD;
