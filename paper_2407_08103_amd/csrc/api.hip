@@ -1858,13 +1858,12 @@ int tdfa_table_minimize(const tdfa_table* table, const uint8_t* accept_host, con
         if (start_states_host[i] < 0 || start_states_host[i] >= table->n_rows)
             return fail(TDFA_E_INVALID_ARG, "start state %d is not a row of the table", start_states_host[i]);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // bits of a table the library has written mark its edges; of buffers that a caller wraps only the entries are looked at
-    const uint32_t* bits = table->row_allowed ? table->allow : nullptr;
+    bool bits_agree = false;
     std::vector<int32_t> first_rows, map;
     int rc;
     try {
-        rc = minimize_table(table->delta, bits, table->row_words, table->n_rows, table->n_tokens, accept_host, start_states_host, n_starts, s,
-                            &first_rows, &map);
+        rc = minimize_table(table->delta, table->allow, table->row_words, table->n_rows, table->n_tokens, accept_host, start_states_host, n_starts, s,
+                            &first_rows, &map, &bits_agree);
     } catch (const std::bad_alloc&) {
         return fail(TDFA_E_OOM, "host allocation failed");
     }
@@ -1884,7 +1883,7 @@ int tdfa_table_minimize(const tdfa_table* table, const uint8_t* accept_host, con
         tdfa_table_destroy(t);
         return fail(TDFA_E_OOM, "host allocation failed");
     }
-    rc = launch_compact_rows(table->delta, bits, table->n_tokens, table->row_words, first_rows, map, t->delta, t->allow, s);
+    rc = launch_compact_rows(table->delta, bits_agree ? table->allow : nullptr, table->n_tokens, table->row_words, first_rows, map, t->delta, t->allow, s);
     if (rc == TDFA_OK) rc = count_rows(t, s);
     if (rc != TDFA_OK) {
         tdfa_table_destroy(t);

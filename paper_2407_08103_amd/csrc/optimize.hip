@@ -27,8 +27,9 @@
 // steps with the host driving rounds of kernels that stream the table's rows.
 //
 // Two entries in three of an ordinary table are DEAD, and most of them lie in long runs (states that allow a few
-// hundred tokens).  Where the library has written the table its allowed bits say where the edges are, so the passes over
-// the rows (lists, comparison, renaming) read the bits, an entry's 32nd part, and then only the entries behind a set bit.
+// hundred tokens).  The first pass over the rows (lists) reads every entry and holds the table's allowed bits against them; if
+// they agree, the passes after it (comparison, renaming) read the bits, an entry's 32nd part, and then only the entries
+// behind a set bit.  If they do not (bits or entries that a caller has edited, which the result follows), every pass reads every entry.
 #include <algorithm>
 #include <cstring>
 #include <new>
@@ -134,7 +135,7 @@ row_hash_kernel(const int32_t* __restrict__ delta, int32_t n_tokens, const int32
 }
 
 // rows[i] and first_of[i] (the first row of its class) must agree, entry by entry, on the class of the target: the
-// dense path's comparison of n pairs, and the sparse path's (BITS where the table's allowed bits can be relied on).
+// dense path's comparison of n pairs, and the sparse path's (BITS where the table's allowed bits agree with its entries).
 //
 // Workgroups take pairs in turn, with the classes in LDS where they fit (LDS_CLS), and a wavefront has the entries of
 // kVerifyChunks * 64 tokens of both rows in flight.  Pieces of rows and not whole ones, because there are about as many pairs
@@ -348,19 +349,21 @@ __device__ __forceinline__ void add_target(int32_t* key, unsigned long long* sum
 
 // Row blockIdx.x: its distinct targets and their weights, appended to (e_target, e_weight) at a
 // position taken from `counter` (which keeps counting past e_cap, so that a second attempt knows the
-// size).  *overflow is set when a row has more than kMaxTargets targets.
+// size).  *overflow is set when a row has more than kMaxTargets targets, *differ where a bit of `allow` and its entry
+// disagree: the bits may be the caller's, and its entries may have changed since, so they lead no pass before this one
+// has held them against every entry.
 //
 // Bound by instructions and by the waits of each update (the target's place in LDS, then the atomic): 5,387 rows of 128,256
-// tokens took 690 us with every entry read and its weight made in place (a dozen instructions), 525 us by the bits and with
-// the weights from memory (1 MB, in every L2).  4 and 16 loads in flight take 627 and 678 us, workgroups of 512 threads 567 us;
-// the places of a span looked up beforehand 620 us, the next span's entries requested beforehand 936 us (fewer wavefronts fit).
-template <bool BITS>
-__global__ void __launch_bounds__(kListThreads)
+// tokens took 690 us with each entry's weight made in place (a dozen instructions), 660 us with the weights from memory (1 MB,
+// in every L2) and the bits compared; led by the bits it would take 525 us, and believe them.  More than 80 scalar registers
+// leave room for one workgroup on a compute unit (870 us); 16 loads in flight take 900 us, 4 with the next span's requested
+// beforehand 745 us, 8 of those 670 us, workgroups of 512 threads 710 us.
+__global__ void __launch_bounds__(kListThreads) __attribute__((amdgpu_num_sgpr(80)))
 row_targets_kernel(const int32_t* __restrict__ delta, const uint32_t* __restrict__ allow, int32_t n_tokens, int64_t row_words,
                    const unsigned long long* __restrict__ weight, unsigned long long e_cap,
                    unsigned long long* __restrict__ counter, unsigned long long* __restrict__ row_begin,
                    int32_t* __restrict__ row_n, int32_t* __restrict__ e_target, unsigned long long* __restrict__ e_weight,
-                   int32_t* overflow)
+                   int32_t* overflow, int32_t* differ)
 {
     __shared__ int32_t key[kSlots];
     __shared__ unsigned long long sum[kSlots];
@@ -384,17 +387,23 @@ row_targets_kernel(const int32_t* __restrict__ delta, const uint32_t* __restrict
     constexpr int kSpan = 2 * kListChunks, kStep = kListThreads / 64 * kSpan;            // in words of bits
     int32_t last = TDFA_DEAD;
     unsigned long long acc = 0;
-    uint32_t w_next = span_word<BITS, kListChunks>(bits, wave * kSpan, lane, n_tokens);
+    bool wrong = false;                             // (the same in every lane)
     for (int64_t w0 = (int64_t)wave * kSpan; w0 < row_words; w0 += kStep) {
-        const uint32_t w = w_next;
-        w_next = span_word<BITS, kListChunks>(bits, w0 + kStep, lane, n_tokens);
-        if (__builtin_amdgcn_ballot_w64(w != 0) == 0) continue;
         int32_t v[kListChunks];
+        span_load<kListChunks>(row, w0, lane, span_word<false, kListChunks>(bits, w0, lane, n_tokens), v);
+        const uint32_t w = span_word<true, kListChunks>(bits, w0, lane, n_tokens);
+        unsigned long long any = 0;
+#pragma unroll
+        for (int u = 0; u < kListChunks; ++u) {
+            const unsigned long long edges = __builtin_amdgcn_ballot_w64(v[u] >= 0);
+            any |= edges;
+            wrong |= edges != span_mask(w, u);
+        }
+        if (any == 0) continue;
         unsigned long long tw[kListChunks];
-        span_load<kListChunks>(row, w0, lane, w, v);
 #pragma unroll
         for (int u = 0; u < kListChunks; ++u)
-            if (__builtin_amdgcn_inverse_ballot_w64(span_mask(w, u))) tw[u] = weight[32 * w0 + 64 * u + lane];
+            if (v[u] >= 0) tw[u] = weight[32 * w0 + 64 * u + lane];
 #pragma unroll
         for (int u = 0; u < kListChunks; ++u) {
             if (v[u] < 0) continue;
@@ -407,6 +416,7 @@ row_targets_kernel(const int32_t* __restrict__ delta, const uint32_t* __restrict
         }
         if (*(volatile int*)&n_used > kMaxTargets) break;
     }
+    if (wrong && lane == 0) *differ = 1;
     if (last >= 0) add_target(key, sum, &n_used, last, acc);
     __syncthreads();
     const int n = n_used;
@@ -759,9 +769,9 @@ int minimize_dense(const int32_t* delta, int64_t row_words, int32_t n_rows, int3
 constexpr int kNotSparse = -1000;       // minimize_lists: take the dense path
 
 // The sparse path.  Returns kNotSparse when a row has too many distinct targets or the final
-// comparison fails (two different rows with one signature).
+// comparison fails (two different rows with one signature).  *bits_agree: every bit has been seen to mark its entry.
 int minimize_lists(const int32_t* delta, const uint32_t* allow, int64_t row_words, int32_t n_rows, int32_t n_tokens, const uint8_t* accept, const int32_t* starts,
-                   int32_t n_starts, hipStream_t s, std::vector<int32_t>* first_rows, std::vector<int32_t>* map_out)
+                   int32_t n_starts, hipStream_t s, std::vector<int32_t>* first_rows, std::vector<int32_t>* map_out, bool* bits_agree)
 {
     const unsigned long long seed = 0x243F6A8885A308D3ull;
     Arena mem;
@@ -775,7 +785,7 @@ int minimize_lists(const int32_t* delta, const uint32_t* allow, int64_t row_word
     TDFA_GET(mem.get(&row_begin, n_rows));
     TDFA_GET(mem.get(&weight, n_tokens));
     TDFA_GET(mem.get(&row_n, n_rows));
-    TDFA_GET(mem.get(&flags, 1 + 3));              // [0] too many targets / changed / mismatch, [1 ..] classes after each round of a look
+    TDFA_GET(mem.get(&flags, 1 + 3));              // [0] too many targets / changed / mismatch, [1 ..] bits that differ, then classes after each round of a look
     TDFA_GET(mem.get(&key, n_rows));
     TDFA_GET(mem.get(&ht_key, ht_size));
     TDFA_GET(mem.get(&ht_min, ht_size));
@@ -797,18 +807,16 @@ int minimize_lists(const int32_t* delta, const uint32_t* allow, int64_t row_word
         TDFA_GET(mem.get(&e_weight, e_cap));
         TDFA_HIP(hipMemsetAsync(counter, 0, 8, s));
         TDFA_HIP(hipMemsetAsync(flags, 0, 8, s));
-        if (allow)
-            row_targets_kernel<true><<<(unsigned)n_rows, kListThreads, 0, s>>>(delta, allow, n_tokens, row_words, weight, e_cap, counter, row_begin,
-                                                                               row_n, e_target, e_weight, flags);
-        else
-            row_targets_kernel<false><<<(unsigned)n_rows, kListThreads, 0, s>>>(delta, allow, n_tokens, row_words, weight, e_cap, counter, row_begin,
-                                                                                row_n, e_target, e_weight, flags);
+        row_targets_kernel<<<(unsigned)n_rows, kListThreads, 0, s>>>(delta, allow, n_tokens, row_words, weight, e_cap, counter, row_begin,
+                                                                     row_n, e_target, e_weight, flags, flags + 1);
         TDFA_HIP(hipGetLastError());
         unsigned long long total = 0;
+        int32_t found[2] = {};
         TDFA_HIP(hipMemcpyAsync(&total, counter, 8, hipMemcpyDeviceToHost, s));
-        TDFA_HIP(hipMemcpyAsync(&flag, flags, 4, hipMemcpyDeviceToHost, s));
+        TDFA_HIP(hipMemcpyAsync(found, flags, 8, hipMemcpyDeviceToHost, s));
         TDFA_HIP(hipStreamSynchronize(s));
-        if (flag) return kNotSparse;
+        if (found[0]) return kNotSparse;
+        *bits_agree = found[1] == 0;
         if (total <= e_cap) break;
         if (attempt == 1) return fail(TDFA_E_DEVICE, "the lists of targets changed size between two passes");
         e_cap = total;
@@ -885,7 +893,7 @@ int minimize_lists(const int32_t* delta, const uint32_t* allow, int64_t row_word
         TDFA_HIP(hipMemcpyAsync(rows_dev, joined.data(), joined.size() * 4, hipMemcpyHostToDevice, s));
         TDFA_HIP(hipMemcpyAsync(first_dev, with.data(), with.size() * 4, hipMemcpyHostToDevice, s));
         TDFA_HIP(hipMemsetAsync(flags, 0, 4, s));
-        TDFA_GET(launch_verify(delta, allow, n_tokens, row_words, (int64_t)joined.size(), n_rows, rows_dev, first_dev, cls, flags, s));
+        TDFA_GET(launch_verify(delta, *bits_agree ? allow : nullptr, n_tokens, row_words, (int64_t)joined.size(), n_rows, rows_dev, first_dev, cls, flags, s));
         TDFA_HIP(hipMemcpyAsync(&flag, flags, 4, hipMemcpyDeviceToHost, s));
         TDFA_HIP(hipStreamSynchronize(s));
         if (flag) return kNotSparse;
@@ -907,10 +915,11 @@ int minimize_lists(const int32_t* delta, const uint32_t* allow, int64_t row_word
 }  // namespace
 
 int minimize_table(const int32_t* delta, const uint32_t* allow, int64_t row_words, int64_t n_rows64, int32_t n_tokens, const uint8_t* accept, const int32_t* starts,
-                   int32_t n_starts, hipStream_t s, std::vector<int32_t>* first_rows, std::vector<int32_t>* map_out)
+                   int32_t n_starts, hipStream_t s, std::vector<int32_t>* first_rows, std::vector<int32_t>* map_out, bool* bits_agree)
 {
     const int32_t n_rows = (int32_t)n_rows64;
-    const int rc = minimize_lists(delta, allow, row_words, n_rows, n_tokens, accept, starts, n_starts, s, first_rows, map_out);
+    *bits_agree = false;
+    const int rc = minimize_lists(delta, allow, row_words, n_rows, n_tokens, accept, starts, n_starts, s, first_rows, map_out, bits_agree);
     if (rc != kNotSparse) return rc;
     return minimize_dense(delta, row_words, n_rows, n_tokens, accept, starts, n_starts, s, first_rows, map_out);
 }

@@ -107,6 +107,32 @@ def test_passes_led_by_the_bits(T, oracle, n, v):
         assert np.array_equal(allow.cpu().numpy().view(np.uint32), G.bits_from_table(want, allow.shape[1]))
 
 
+@pytest.mark.parametrize("v", [63, 4097, 9000])
+@pytest.mark.parametrize("how", ["entries added", "bits cleared, then stacked", "bits set, then stacked", "entries removed"])
+def test_result_follows_the_entries(T, oracle, how, v):
+    """The allowed bits of a table may have parted from its entries: the caller has edited its own buffers, or wrapped
+    ones whose bits forbid more (or less) than the entries before stacking them.  The entries decide, in every pass."""
+    n = 60
+    rng = np.random.default_rng(v)
+    table_np = rng.integers(0, n, size=(n, v), dtype=np.int32)
+    table_np[rng.random((n, v)) < rng.choice([0.5, 0.999], size=n)[:, None]] = DEAD
+    table_np[n // 2:] = table_np[:n // 2]
+    accept = (rng.random(n) < 0.2).astype(np.uint8)
+    accept[n // 2:] = accept[:n // 2]
+    other = table_np.copy()
+    other[rng.random((n, v)) < 0.01] = DEAD                   # with fewer edges, and not the same ones in both halves
+    bits_of, entries = (other, table_np) if how in ("entries added", "bits cleared, then stacked") else (table_np, other)
+    rw = T.allow_row_words(v)
+    bits = torch.from_numpy(G.bits_from_table(bits_of, rw).view(np.int32)).cuda()
+    if "stacked" in how:
+        table, _ = T.table_concat([T.table_wrap(torch.from_numpy(entries).cuda(), bits)])
+    else:
+        table, _ = T.table_concat([T.table_wrap(torch.from_numpy(bits_of).cuda(), bits)])
+        table.delta.copy_(torch.from_numpy(entries))
+        torch.cuda.synchronize()
+    _check(T, oracle, table, entries, accept, np.array([0, 1], dtype=np.int32))
+
+
 def _most_targets(table_np):
     return max(len(np.unique(r[r >= 0])) for r in table_np)
 
@@ -131,7 +157,8 @@ def test_long_chains_merge(T, oracle):
     assert new.n_rows == L + 1 and np.array_equal(mp[1:L + 1], mp[L + 1:])
 
 
-def test_rows_with_many_distinct_targets(T, oracle):
+@pytest.mark.parametrize("written_by", ["caller", "library"])
+def test_rows_with_many_distinct_targets(T, oracle, written_by):
     """A table whose rows have more distinct targets than the list-building pass keeps per row:
     the call streams the dense rows instead, with the same result."""
     rng = np.random.default_rng(77)
@@ -143,7 +170,8 @@ def test_rows_with_many_distinct_targets(T, oracle):
     accept = (rng.random(n) < 0.3).astype(np.uint8)
     accept[n - 40:] = accept[n - 80:n - 40]
     assert _most_targets(table_np) > 3072
-    _check(T, oracle, _upload_table(T, table_np), table_np, accept, [0, 17])
+    table = _upload_table(T, table_np)
+    _check(T, oracle, table if written_by == "caller" else _as_torch(T, table), table_np, accept, [0, 17])
 
 
 def test_lists_longer_than_first_guessed(T, oracle):
