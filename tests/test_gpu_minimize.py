@@ -174,6 +174,31 @@ def test_rows_with_many_distinct_targets(T, oracle, written_by):
     _check(T, oracle, table if written_by == "caller" else _as_torch(T, table), table_np, accept, [0, 17])
 
 
+@pytest.mark.parametrize("useful", ["all", "traps", "none final", "few reached"])
+@pytest.mark.parametrize("n,v", [(700, 64), (700, 65), (8192, 70), (8193, 200), (20001, 40)])
+def test_searches(T, oracle, n, v, useful):
+    """Levels of states in shuffled order, each leading to the next: rows that fit the wavefronts in flight and rows that
+    do not (both sides of the line), lists around a wavefront's width; states that reach no final state, or are not reached."""
+    rng = np.random.default_rng(n + v)
+    depth = 30
+    per = n // depth
+    p = rng.permutation(n).astype(np.int32)
+    table_np = np.full((n, v), DEAD, dtype=np.int32)
+    for lv in range(depth - 1):
+        table_np[p[lv * per:(lv + 1) * per]] = p[(lv + 1) * per + rng.integers(0, per, size=(per, v))]
+    table_np[rng.random((n, v)) < 0.3] = DEAD
+    accept = np.zeros(n, np.uint8)
+    accept[p[(depth - 1) * per:depth * per]] = rng.integers(1, 3, size=per) != 1
+    if useful == "traps":                                      # half of the states lead only to one another
+        trap = np.unique(rng.integers(0, n, size=n // 2)).astype(np.int32)
+        table_np[trap] = trap[rng.integers(0, len(trap), size=(len(trap), v))]
+        accept[trap] = 0
+    elif useful == "none final":
+        accept[:] = 0
+    starts = p[:per] if useful != "few reached" else p[:1]
+    _check(T, oracle, _upload_table(T, table_np), table_np, accept, starts.astype(np.int32))
+
+
 def test_lists_longer_than_first_guessed(T, oracle):
     """Rows with about 700 distinct targets each: more list entries in all than the first pass makes room for, so
     the lists are built a second time at their true size."""
