@@ -381,51 +381,49 @@ int upload_stream(hipStream_t* out)
 }
 
 // Pinned host memory through which tdfa_dfa_create sends a small automaton as one copy (four copies from the caller's and the
-// library's own pageable memory take 10 us each).  At most kStagingBlocks blocks of kStagingBytes are kept, each with one
-// call at a time; tdfa_trim frees them.  Larger automata are copied from where they lie, which the runtime does at the
-// link's rate.
+// library's own pageable memory take 10 us each).  There are at most kStagingBlocks blocks of kStagingBytes, each with one
+// call at a time, and only tdfa_trim frees them (freeing pinned memory waits for the device, which creating an automaton
+// must not): a call that finds none free, like larger automata, copies from where the arrays lie.
 constexpr size_t kStagingBytes = (size_t)1 << 20, kStagingBlocks = 4;
 std::mutex g_staging_mutex;
-std::vector<void*>& g_staging = *new std::vector<void*>;       // blocks that no call holds (never destroyed, like the caches)
+void* g_staging[kStagingBlocks];                               // the first g_staging_idle: blocks that no call holds
+size_t g_staging_idle = 0, g_staging_made = 0;
 
 void* staging_take()
 {
     {
         std::lock_guard<std::mutex> lock(g_staging_mutex);
-        if (!g_staging.empty()) {
-            void* p = g_staging.back();
-            g_staging.pop_back();
-            return p;
-        }
+        if (g_staging_idle > 0) return g_staging[--g_staging_idle];
+        if (g_staging_made == kStagingBlocks) return nullptr;
+        ++g_staging_made;
     }
     void* p = nullptr;
     if (hipHostMalloc(&p, kStagingBytes, hipHostMallocPortable) == hipSuccess) return p;
     (void)hipGetLastError();
+    std::lock_guard<std::mutex> lock(g_staging_mutex);
+    --g_staging_made;
     return nullptr;
 }
 
 void staging_give(void* p)
 {
     if (!p) return;
-    try {
-        std::lock_guard<std::mutex> lock(g_staging_mutex);
-        if (g_staging.size() < kStagingBlocks) {
-            g_staging.push_back(p);
-            return;
-        }
-    } catch (const std::bad_alloc&) {
-    }
-    (void)hipHostFree(p);
+    std::lock_guard<std::mutex> lock(g_staging_mutex);
+    g_staging[g_staging_idle++] = p;
 }
 
 void staging_trim()
 {
-    std::vector<void*> gone;
-    {
-        std::lock_guard<std::mutex> lock(g_staging_mutex);
-        gone.swap(g_staging);
+    for (;;) {
+        void* p;
+        {
+            std::lock_guard<std::mutex> lock(g_staging_mutex);
+            if (g_staging_idle == 0) return;
+            p = g_staging[--g_staging_idle];
+            --g_staging_made;
+        }
+        (void)hipHostFree(p);
     }
-    for (void* p : gone) (void)hipHostFree(p);
 }
 
 // Before the launches of a compile call on stream s: an automaton last used on another stream is waited for there.

@@ -1,4 +1,6 @@
 """GPU parity of the compile stage against the oracle, bit for bit, through the C ABI."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -534,4 +536,46 @@ def test_automata_created_compiled_and_destroyed_back_to_back(T, oracle):
     torch.cuda.synchronize()
     for d, t in zip(dfas, tables):
         G.check_rows(t, oracle.compile_walk(d.trans, vocab.data, vocab.offsets), np.arange(n_states))
+    T.trim()
+
+
+def test_automata_created_by_many_threads_beside_a_busy_device(T, oracle):
+    """More threads than there are pinned blocks to upload through: none of them waits for the device, and each table is
+    its own automaton's.  (The work that keeps the device busy, forty products of 8,192 x 8,192, lasts some tens of ms.)"""
+    n_states, n_threads, each = 1000, 12, 4
+    dfas = [random_dfa(n_states, 0.4, 0.2, np.random.default_rng(i)) for i in range(n_threads)]
+    vocab = configs.small(1, n_tokens=130).vocab
+    v = T.Vocab(vocab.data, vocab.offsets)
+    made = [T.CharDFA(dfas[0].trans, dfas[0].accept, dfas[0].start) for _ in range(n_threads * each)]
+    while made:                                               # their device memory is kept, so that no thread takes new memory
+        made.pop().close()
+    side = torch.cuda.Stream()
+    a = torch.ones((8192, 8192), dtype=torch.bfloat16, device="cuda")
+    out = torch.empty_like(a)
+    torch.mm(a, a, out=out)
+    torch.cuda.synchronize()
+    got = [[] for _ in range(n_threads)]
+    start = threading.Barrier(n_threads + 1)
+
+    def create(i):
+        start.wait()
+        for _ in range(each):
+            got[i].append(T.CharDFA(dfas[i].trans, dfas[i].accept, dfas[i].start, stream=side))
+
+    threads = [threading.Thread(target=create, args=(i,)) for i in range(n_threads)]
+    for t in threads:
+        t.start()
+    with torch.cuda.stream(side):
+        for _ in range(40):
+            torch.mm(a, a, out=out)
+    start.wait()
+    for t in threads:
+        t.join()
+    assert not side.query()
+    torch.cuda.synchronize()
+    for d, handles in zip(dfas, got):
+        want = oracle.compile_walk(d.trans, vocab.data, vocab.offsets, n_threads=8)
+        assert len(handles) == each
+        for h in handles:
+            G.check_rows(T.compile_token_dfa(v, h), want, np.arange(n_states))
     T.trim()
