@@ -2269,9 +2269,7 @@ int launch_sample_step(const MaskArgs& a, float inv_t, int32_t top_k, uint64_t s
     }
     // workgroups of 256 threads, kDrawGroups or more of them (rows in parts of at least 1,024 groups)
     const int n_groups = (a.n_tokens + 7) >> 3;
-    // (half as many for up to 128 rows, which leave compute units free in either case: 128 rows that allow most 24.2 -> 21.3 us,
-    // little 11.7 -> 9.4; 192 rows anywhere in their texts 25.5 -> 27.8)
-    int parts = ((a.batch <= 128 ? kDrawGroups / 2 : kDrawGroups) + a.batch - 1) / a.batch;
+    int parts = (kDrawGroups + a.batch - 1) / a.batch;
     const int max_parts = (n_groups + 1023) / 1024;
     if (parts > max_parts) parts = max_parts;
     if (parts < 1) parts = 1;
