@@ -78,7 +78,7 @@ def test_noise_bit_for_bit(T, oracle, batch, n_tokens, seed, offset):
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
 @pytest.mark.parametrize("p_live", [0.02, 0.9])
-@pytest.mark.parametrize("n_tokens,batch", [(8, 1), (37 * 8 + 3, 3), (1000 * 8 + 8, 5), (40000, 2), (50021, 300)])
+@pytest.mark.parametrize("n_tokens,batch", [(8, 1), (37 * 8 + 3, 3), (1000 * 8 + 8, 5), (40000, 2), (50021, 300), (131075, 112), (131075, 113)])
 def test_random_tables(T, oracle, dtype, p_live, n_tokens, batch):
     """Sparse and dense allowed sets; sizes cover one group, ragged rows, many parts per row and one
     workgroup per row; states include sinks, DEAD and ids that are no row."""
