@@ -2061,11 +2061,17 @@ void stream_shape(const MaskArgs& a, bool pda, int* parts_out, int* threads_out,
         // 12.9 and 13.7 us).
         parts = pda ? 2 : batch <= 170 ? std::min<int64_t>(pieces, 512 / batch) : 1;
         threads = pda || batch > 170 ? 1024 : 512;
-    } else if (!plain && pieces > 3 && (a.dtype == TDFA_F32 ? batch >= 48 && (batch < 192 || a.masked_out) : batch >= kSmallBatch && batch <= 64)) {
-        // long rows that are written as well, or of fp32: larger workgroups keep the memory busy with fewer of them.  128,256
-        // tokens: fp32, 64 and 128 rows 11.3 and 15.2 -> 9.7 and 13.6 us; with the penalised row 64, 256 and 1,024 rows 15.3, 50.2
-        // and 208 -> 13.8, 46.8 and 193 us; bf16 with it 16 and 64 rows 7.2 and 11.0 -> 6.3 and 8.5 us (100 rows 13.7 -> 14.0, so
-        // not; 32 rows of fp32 8.9 -> 9.2, 128 rows of 70,000 tokens 10.9 -> 11.4)
+    } else if (!plain && pieces > 3 &&
+               (a.dtype != TDFA_F32 ? batch >= kSmallBatch && batch <= 64 :
+                a.masked_out ? batch >= 256 || (batch >= 48 && batch * pieces <= 256) : batch >= 48 && batch * pieces <= 512)) {
+        // Long rows that are written as well, or of fp32: larger workgroups keep the memory busy with fewer of them, while all of them
+        // are in flight: one to a compute unit where rows are written, two where they are only read.  fp32, in parts of 256 threads
+        // and so: 128,256 tokens, 64, 96 and 128 rows 11.5, 13.8 and 15.1 -> 9.9, 13.2 and 13.5 us, 160 and 191 rows 16.0 and 18.1 -> 19.8
+        // and 21.1; 250,000 tokens, 64 rows 18.3 -> 14.0, 96 rows 19.1 -> 21.1 (32 rows of 128,256 8.9 -> 9.2).  With the
+        // penalised row 64 rows 15.5 -> 14.1, 65 rows 16.7 -> 18.1, 100,000 tokens, 65 and 160 rows 13.4 and 23.3 -> 15.6 and 25.1.  From
+        // 256 rows on, which otherwise are one workgroup each and leave compute units idle at the end: 256, 320, 512 and 1,024 rows
+        // 48.6, 82.4, 109 and 207 -> 46.9, 63.7, 101 and 192 us.  bf16 with the row 16 and 64 rows 7.2 and 11.0 -> 6.3 and 8.5 us (100
+        // rows 13.7 -> 14.0, so not).
         parts = pieces;
     } else if (takes_deep(a, pda)) {
         threads = 512;

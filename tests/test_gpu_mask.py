@@ -99,7 +99,7 @@ def test_sparse_and_mixed_rows(T, oracle, n_tokens, batch):
 @pytest.mark.parametrize("dtype,n_tokens,batch", [(BF16, v, b) for v, b in [
     (8192, 20), (8193, 20), (32760, 200), (32767, 16), (32769, 15), (32769, 16), (33003, 128), (33003, 129), (65528, 191), (65529, 192),
     (65536, 319), (65536, 320), (65537, 170), (65545, 171), (98307, 64), (131081, 65), (140000, 191), (250003, 100), (250003, 172)]] +
-    [(F32, v, b) for v, b in [(98304, 48), (98312, 47), (98313, 48), (98313, 64), (131075, 191), (131075, 192)]])
+    [(F32, v, b) for v, b in [(98304, 48), (98312, 47), (98313, 48), (98313, 64), (131075, 102), (131075, 103), (131075, 191), (131075, 192)]])
 def test_rows_at_the_edges_of_the_launch_shapes(T, oracle, dtype, n_tokens, batch):
     """Around the row lengths and batches at which rows are split into another number of workgroups, or of another size."""
     _sparse_and_mixed_rows(T, oracle, n_tokens, batch, dtype)
@@ -208,7 +208,8 @@ def test_rows_of_the_smallest_key(T, oracle, n_tokens, batch):
             assert np.array_equal(tok.cpu().numpy(), want[0]) and np.array_equal(new.cpu().numpy(), want[1])
 
 
-@pytest.mark.parametrize("n_tokens,batch", [(1, 3), (7, 2), (4093, 5), (4096, 5), (8197, 4), (16387, 9), (33001, 200), (32775, 193)])
+@pytest.mark.parametrize("n_tokens,batch", [(1, 3), (7, 2), (4093, 5), (4096, 5), (8197, 4), (16387, 9), (33001, 200), (32775, 193),
+                                            (131075, 51), (131075, 52), (98313, 255), (98313, 256)])
 def test_penalised_fp32_rows_at_the_edges(T, oracle, n_tokens, batch):
     """fp32 rows written with the penalty, around the 1,024 and 4,096 logits that a workgroup takes per load and per
     round, with partial groups, in place and into another buffer whose padding must stay as it was; bit for bit."""
