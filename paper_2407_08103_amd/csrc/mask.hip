@@ -2045,10 +2045,12 @@ void stream_shape(const MaskArgs& a, bool pda, int* parts_out, int* threads_out,
         // a short row, 8,193 to 32,767 tokens.  32,000 tokens, 16, 64, 256 and 1,024 rows: in parts of 256 threads 5.2, 6.0, 8.2
         // and 12.9 us; so 4.9, 5.9, 6.4 and 11.9 us (9,000 tokens 5.1, -, 6.3 and 9.4 -> 4.4, -, 5.1 and 8.8)
         threads = 512;
-    } else if (plain && !pda && n_groups >= kPieceGroups && n_groups < 2 * kPieceGroups && (a.delta ? batch >= 320 || (batch > 128 && batch < 192) : batch >= 768)) {
-        // rows of middle length, enough to fill the chip.  50,000 tokens, 160, 384, 512 and 1,024 rows: 8.3, 10.5, 11.6 and 20.1 -> 5.9,
-        // 9.5, 10.8 and 16.4 us (200 rows that allow most 7.5 -> 8.1, so not; 384 rows
-        // of a packed table 10.1 -> 10.5; 1,024 rows of 128,256 tokens that allow most 42.4 -> 43.6)
+    } else if (plain && !pda && n_groups >= kPieceGroups && n_groups < 2 * kPieceGroups && (a.delta ? batch >= 320 || (batch > 128 && batch < 192 && n_groups <= (batch <= 170 ? 7000 : 6000)) : batch >= 768)) {
+        // rows of middle length, enough to fill the chip.  50,000 tokens, 384, 512 and 1,024 rows: 10.5, 11.6 and 20.1 -> 9.5, 10.8 and
+        // 16.4 us (200 rows that allow most 7.5 -> 8.1, so not; 384 rows of a packed table 10.1 -> 10.5; 1,024 rows of 128,256 tokens
+        // that allow most 42.4 -> 43.6).  129 to 191 rows, if they are no longer than what the pieces below take as fast: 40,000
+        // tokens, 160 and 191 rows 7.9 and 7.6 -> 7.3 and 7.2 us, 50,000 tokens, 160 rows 8.6 -> 8.4 (all that allow little 7.4 -> 5.4), but 191
+        // rows 7.7 -> 8.4, 60,000 tokens, 160 and 191 rows 8.6 and 7.8 -> 9.2 and 9.0
         threads = 512;
     } else if (plain && n_groups >= kPieceGroups && batch >= kSmallBatch && batch < (pda ? 129 : 192) && (batch <= 170 || pieces <= 4) &&
                (a.delta || pda || pieces > 2)) {

@@ -98,7 +98,8 @@ def test_sparse_and_mixed_rows(T, oracle, n_tokens, batch):
 
 @pytest.mark.parametrize("dtype,n_tokens,batch", [(BF16, v, b) for v, b in [
     (8192, 20), (8193, 20), (32760, 200), (32767, 16), (32769, 15), (32769, 16), (33003, 128), (33003, 129), (65528, 191), (65529, 192),
-    (65536, 319), (65536, 320), (65537, 170), (65545, 171), (98307, 64), (131081, 65), (140000, 191), (250003, 100), (250003, 172)]] +
+    (65536, 319), (65536, 320), (65537, 170), (65545, 171), (98307, 64), (131081, 65), (140000, 191), (250003, 100), (250003, 172),
+    (48000, 171), (48001, 171), (56000, 170), (56001, 170)]] +
     [(F32, v, b) for v, b in [(98304, 48), (98312, 47), (98313, 48), (98313, 64), (131075, 102), (131075, 103), (131075, 191), (131075, 192)]])
 def test_rows_at_the_edges_of_the_launch_shapes(T, oracle, dtype, n_tokens, batch):
     """Around the row lengths and batches at which rows are split into another number of workgroups, or of another size."""
