@@ -2052,15 +2052,18 @@ void stream_shape(const MaskArgs& a, bool pda, int* parts_out, int* threads_out,
         // tokens, 160 and 191 rows 7.9 and 7.6 -> 7.3 and 7.2 us, 50,000 tokens, 160 rows 8.6 -> 8.4 (all that allow little 7.4 -> 5.4), but 191
         // rows 7.7 -> 8.4, 60,000 tokens, 160 and 191 rows 8.6 and 7.8 -> 9.2 and 9.0
         threads = 512;
-    } else if (plain && n_groups >= kPieceGroups && batch >= kSmallBatch && batch < (pda ? 129 : 192) && (batch <= 170 || pieces <= 4) &&
-               (a.delta || pda || pieces > 2)) {
+    } else if (plain && n_groups >= kPieceGroups && batch >= kSmallBatch &&
+               (pda ? batch <= 128 && batch * (n_groups - kPieceGroups) >= 300000 :
+                      batch < 192 && (batch <= 170 || pieces <= 4) && (a.delta || pieces > 2))) {
         // as many pieces as the chip holds at once.  128,256 tokens, 16, 64 and 128 rows: in parts of 256 threads 7.3, 10.5 and
         // 13.2 us, in one piece 8.3, 9.3 and 9.1; so 6.0, 7.4 and 8.3 us.  In fewer than
         // three pieces one workgroup of 1,024 threads is better: 191 rows 13.6 and 11.6 -> 10.1 us; rows too long for that stay as
         // they were (250,000 tokens, 180 rows: 15.6, in two pieces 20.3), as do the shorter ones of packed tables (50,000 tokens, 64
         // rows: 6.9, in two pieces 7.4).
-        // The push-down step matches its stack in every workgroup: two large ones at most (64 and 128 rows: 14.7 and 21.0 ->
-        // 12.9 and 13.7 us).
+        // The push-down step matches its stack in every workgroup: two large ones at most, where what lies beyond the first piece of
+        // each row is work enough for them.  128,256 tokens, 48, 64 and 128 rows 11.6, 13.2 and 18.3 -> 10.7, 11.0 and 11.7 us, 24 rows 9.9 ->
+        // 10.2; 80,000 tokens, 64 and 128 rows 10.8 and 12.3 -> 10.6 and 10.9, 48 rows 9.5 -> 10.3; 65,600 tokens, 96 rows 11.1 -> 10.9, 48 rows
+        // 9.4 -> 10.5; 45,000 tokens, 32 and 128 rows 8.6 and 10.1 -> 9.6 and 10.5; 33,000 tokens, 16 and 64 rows 8.1 and 8.8 -> 9.4 and 9.7.
         parts = pda ? 2 : batch <= 170 ? std::min<int64_t>(pieces, 512 / batch) : 1;
         threads = pda || batch > 170 ? 1024 : 512;
     } else if (!plain && pieces > 3 &&

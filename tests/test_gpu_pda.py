@@ -165,13 +165,14 @@ def test_decode_steps(T, oracle, dtype, name, make, alphabet, n_random, extra):
 
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
-@pytest.mark.parametrize("n_tokens,batch", [(63, 5), (64, 5), (65, 200), (129, 3), (8191, 3), (33000, 4), (33000, 16), (33000, 128), (33000, 129), (33000, 200), (33000, 300)])
+@pytest.mark.parametrize("n_tokens,batch", [(63, 5), (64, 5), (65, 200), (129, 3), (8191, 3), (33000, 4), (33000, 16), (33000, 128), (33000, 129), (33000, 200), (33000, 300),
+                                            (51512, 128), (51513, 128)])
 def test_traversal_at_the_edges_of_the_directory(T, oracle, dtype, n_tokens, batch):
     """Vocabularies around the 64 tokens of a directory entry, rows that one and that several workgroups share, and the
     row whose token the exact scan decides (step 2: NaN); the step without a penalised row traverses the edge itself."""
     rng = np.random.default_rng(n_tokens + batch)
     ones = [b"(", b")", b"[", b"]"]
-    toks = ones + [t for t in _vocab(rng, b"()[]x", n_tokens, [], 7) if t not in ones][:n_tokens - 4]
+    toks = ones + [t for t in _vocab(rng, b"()[]x", n_tokens, [], 7 if n_tokens < 40000 else 9) if t not in ones][:n_tokens - 4]
     assert len(toks) == n_tokens
     rng.shuffle(toks)
     pda = P.dyck2()
