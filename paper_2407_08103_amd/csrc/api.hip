@@ -504,6 +504,7 @@ struct DeviceScratch {
     unsigned long long* best = nullptr;
     unsigned int* count = nullptr;      // [cap]: arrival counters
     int32_t cap = 0;
+    bool own = false;                   // as handed out: the steps of no other stream meet here
 };
 constexpr int kMaxDevices = 64, kScratchStreams = 32;
 constexpr int32_t kScratchApart = 65536;                   // 24 MiB in all
@@ -557,6 +558,7 @@ int ensure_scratch(int32_t batch, hipStream_t stream, DeviceScratch* out)
     }
     int i = 0;
     while (i < sc->n_streams && sc->stream[i] != key) ++i;
+    out->own = i < kScratchStreams && sc->n_parts == kScratchStreams;
     if (i == kScratchStreams) i = (int)(reinterpret_cast<uintptr_t>(key) >> 4) & (kScratchStreams - 1);
     else if (i == sc->n_streams) sc->stream[sc->n_streams++] = key;
     const size_t first = (size_t)(i % sc->n_parts) * (size_t)sc->all.cap;
@@ -688,13 +690,20 @@ void block_free(const DeviceBlock& block, int device)
     else cache_put(g_table_cache, CachedBlock{block.ptr, block.bytes, device, nullptr, true, 0});
 }
 
-int step_scratch(int32_t batch, hipStream_t stream, unsigned long long** best, unsigned int** count)
+int step_scratch(const MaskArgs& a, hipStream_t stream, unsigned long long** best, unsigned int** count, bool* alone)
 {
     DeviceScratch sc;
-    const int rc = ensure_scratch(batch, stream, &sc);
+    const int rc = ensure_scratch(a.batch, stream, &sc);
     if (rc != TDFA_OK) return rc;
     *best = sc.best;
     *count = sc.count;
+    *alone = false;
+    if (sc.own && mask_step_wants_scratch(a)) {
+        // (a recorded step may be replayed beside another one of its stream)
+        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &capturing) == hipSuccess) *alone = capturing == hipStreamCaptureStatusNone;
+        else (void)hipGetLastError();
+    }
     return TDFA_OK;
 }
 }  // namespace tdfa
@@ -1645,8 +1654,9 @@ void fill_table_args(const tdfa_table* table, tdfa::MaskArgs* a)
 // Argument checks and kernel arguments shared by the greedy and the sampling step.
 int prepare_step(const tdfa_table* table, const void* logits_dev, int dtype, int32_t batch, int64_t row_stride,
                  const int32_t* states_dev, int32_t* tokens_dev, int32_t* new_states_dev, void* masked_out_dev,
-                 hipStream_t s, tdfa::MaskArgs* a, bool use_static = false)
+                 hipStream_t s, tdfa::MaskArgs* a, bool* alone, bool use_static = false)
 {
+    *alone = false;
     if (!table) return fail(TDFA_E_INVALID_ARG, "table is NULL");
     if (dtype != TDFA_F32 && dtype != TDFA_BF16) return fail(TDFA_E_INVALID_ARG, "unknown dtype %d", dtype);
     if (batch < 0) return fail(TDFA_E_INVALID_ARG, "batch %d is negative", batch);
@@ -1658,21 +1668,6 @@ int prepare_step(const tdfa_table* table, const void* logits_dev, int dtype, int
     if ((reinterpret_cast<uintptr_t>(logits_dev) & 15) || ((row_stride * esz) & 15) ||
         (reinterpret_cast<uintptr_t>(masked_out_dev) & 15))
         return fail(TDFA_E_INVALID_ARG, "logits / masked_out rows must be 16-byte aligned");
-    DeviceScratch sc;
-    if (use_static) {
-        // no allocation on this path: the fixed array in the device image, for batches that fit it
-        if (batch > kStaticMaxBatch)
-            return fail(TDFA_E_UNSUPPORTED, "batch %d exceeds the %d sequences the static scratch holds", batch, kStaticMaxBatch);
-        void* ptr = nullptr;
-        const int src = static_scratch(&ptr);
-        if (src != TDFA_OK) return src;
-        sc.best = static_cast<unsigned long long*>(ptr);
-        sc.count = reinterpret_cast<unsigned int*>(static_cast<unsigned char*>(ptr) + (size_t)kStaticMaxBatch * sizeof(unsigned long long));
-        sc.cap = kStaticMaxBatch;
-    } else {
-        const int rc = ensure_scratch(batch, s, &sc);
-        if (rc != TDFA_OK) return rc;
-    }
     fill_table_args(table, a);
     a->logits = logits_dev;
     a->dtype = dtype;
@@ -1682,9 +1677,18 @@ int prepare_step(const tdfa_table* table, const void* logits_dev, int dtype, int
     a->tokens = tokens_dev;
     a->new_states = new_states_dev;
     a->masked_out = masked_out_dev;
-    a->scratch_best = sc.best;
-    a->scratch_count = sc.count;
-    return TDFA_OK;
+    if (use_static) {
+        // no allocation on this path: the fixed array in the device image, for batches that fit it
+        if (batch > kStaticMaxBatch)
+            return fail(TDFA_E_UNSUPPORTED, "batch %d exceeds the %d sequences the static scratch holds", batch, kStaticMaxBatch);
+        void* ptr = nullptr;
+        const int src = static_scratch(&ptr);
+        if (src != TDFA_OK) return src;
+        a->scratch_best = static_cast<unsigned long long*>(ptr);
+        a->scratch_count = reinterpret_cast<unsigned int*>(static_cast<unsigned char*>(ptr) + (size_t)kStaticMaxBatch * sizeof(unsigned long long));
+        return TDFA_OK;
+    }
+    return step_scratch(*a, s, &a->scratch_best, &a->scratch_count, alone);
 }
 
 }  // namespace
@@ -1697,10 +1701,11 @@ int tdfa_mask_step(const tdfa_table* table, const void* logits_dev, int dtype, i
     hipStream_t s = static_cast<hipStream_t>(stream);
     MaskArgs a = {};
     a.batch = 0;
+    bool alone;
     int rc = prepare_step(table, logits_dev, dtype, batch, row_stride, states_dev, tokens_dev, new_states_dev,
-                          masked_out_dev, s, &a);
+                          masked_out_dev, s, &a, &alone);
     if (rc != TDFA_OK || batch == 0) return rc;
-    return launch_mask_step(a, s);
+    return launch_mask_step(a, s, alone);
 }
 
 int tdfa_mask_step_noalloc(const tdfa_table* table, const void* logits_dev, int dtype, int32_t batch, int64_t row_stride,
@@ -1711,8 +1716,9 @@ int tdfa_mask_step_noalloc(const tdfa_table* table, const void* logits_dev, int 
     hipStream_t s = static_cast<hipStream_t>(stream);
     MaskArgs a = {};
     a.batch = 0;
+    bool alone;
     int rc = prepare_step(table, logits_dev, dtype, batch, row_stride, states_dev, tokens_dev, new_states_dev,
-                          masked_out_dev, s, &a, true);
+                          masked_out_dev, s, &a, &alone, true);
     if (rc != TDFA_OK || batch == 0) return rc;
     // The array is shared by every call on this GPU and keeps what the last one left: the words this
     // call's workgroups meet through are cleared first, by a kernel (a recorded graph may hold this).
@@ -1739,8 +1745,9 @@ int sample_step_impl(const tdfa_table* table, const void* logits_dev, int dtype,
     hipStream_t s = static_cast<hipStream_t>(stream);
     MaskArgs a = {};
     a.batch = 0;
+    bool alone;
     int rc = prepare_step(table, logits_dev, dtype, batch, row_stride, states_dev, tokens_dev, new_states_dev,
-                          masked_out_dev, s, &a);
+                          masked_out_dev, s, &a, &alone);
     if (rc != TDFA_OK || batch == 0) return rc;
     return launch_sample_step(a, inv_t, top_k, seed, offset, offset_dev, s);
 }

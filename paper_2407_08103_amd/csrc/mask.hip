@@ -2034,7 +2034,7 @@ bool takes_deep(const MaskArgs& a, bool pda)
 // What it weighs: a compute unit streams at what one unit gets from memory (a 256 KB row in 6.5 us), so few rows are split;
 // every workgroup costs its launch and its own look at state and bits, and workgroups of a row meet at the end; a workgroup
 // of 512 threads starts and ends a microsecond sooner than one of 1,024, which has more loads in flight.
-void stream_shape(const MaskArgs& a, bool pda, int* parts_out, int* threads_out, int* gpp_out)
+void stream_shape(const MaskArgs& a, bool pda, bool alone, int* parts_out, int* threads_out, int* gpp_out)
 {
     const int n_groups = (a.n_tokens + 7) >> 3;
     const int64_t batch = a.batch, pieces = (n_groups + kPieceGroups - 1) / kPieceGroups;
@@ -2068,14 +2068,14 @@ void stream_shape(const MaskArgs& a, bool pda, int* parts_out, int* threads_out,
         threads = pda || batch > 170 ? 1024 : 512;
     } else if (!plain && pieces > 3 &&
                (a.dtype != TDFA_F32 ? batch >= kSmallBatch && batch <= 64 :
-                a.masked_out ? batch >= 256 || (batch >= 48 && batch * pieces <= 256) : batch >= 48 && batch * pieces <= 512)) {
+                a.masked_out ? (alone && mask_step_wants_scratch(a)) || (batch >= 48 && batch * pieces <= 256) : batch >= 48 && batch * pieces <= 512)) {
         // Long rows that are written as well, or of fp32: larger workgroups keep the memory busy with fewer of them, while all of them
         // are in flight: one to a compute unit where rows are written, two where they are only read.  fp32, in parts of 256 threads
         // and so: 128,256 tokens, 64, 96 and 128 rows 11.5, 13.8 and 15.1 -> 9.9, 13.2 and 13.5 us, 160 and 191 rows 16.0 and 18.1 -> 19.8
         // and 21.1; 250,000 tokens, 64 rows 18.3 -> 14.0, 96 rows 19.1 -> 21.1 (32 rows of 128,256 8.9 -> 9.2).  With the
         // penalised row 64 rows 15.5 -> 14.1, 65 rows 16.7 -> 18.1, 100,000 tokens, 65 and 160 rows 13.4 and 23.3 -> 15.6 and 25.1.  From
-        // 256 rows on, which otherwise are one workgroup each and leave compute units idle at the end: 256, 320, 512 and 1,024 rows
-        // 48.6, 82.4, 109 and 207 -> 46.9, 63.7, 101 and 192 us.  bf16 with the row 16 and 64 rows 7.2 and 11.0 -> 6.3 and 8.5 us (100
+        // 256 rows on, which otherwise are one workgroup each, need no scratch and leave compute units idle at the end: 256, 320, 512
+        // and 1,024 rows 48.6, 82.4, 109 and 207 -> 46.9, 63.7, 101 and 192 us, where the scratch is this step's alone.  bf16 with the row 16 and 64 rows 7.2 and 11.0 -> 6.3 and 8.5 us (100
         // rows 13.7 -> 14.0, so not).
         parts = pieces;
     } else if (takes_deep(a, pda)) {
@@ -2110,8 +2110,14 @@ bool mask_step_uses_scratch(const MaskArgs& a)
     if (a.batch <= 0) return false;
     int parts, threads, gpp;
     if (packed_takes_gather(a)) gather_shape(a, &parts, &threads, &gpp);
-    else stream_shape(a, false, &parts, &threads, &gpp);
+    else stream_shape(a, false, false, &parts, &threads, &gpp);
     return parts > 1;
+}
+
+// Written rows of fp32, as many as there are compute units or more.
+bool mask_step_wants_scratch(const MaskArgs& a)
+{
+    return a.dtype == TDFA_F32 && a.masked_out && a.batch >= 256;
 }
 
 int launch_clear_scratch(unsigned long long* best, unsigned int* count, int32_t n, hipStream_t stream)
@@ -2129,10 +2135,10 @@ struct BitsInLds {
     size_t lds;
     bool fits;
 };
-BitsInLds bits_in_lds(const MaskArgs& a, bool pda = false)
+BitsInLds bits_in_lds(const MaskArgs& a, bool pda, bool alone)
 {
     BitsInLds r;
-    stream_shape(a, pda, &r.parts, &r.threads, &r.gpp);
+    stream_shape(a, pda, alone, &r.parts, &r.threads, &r.gpp);
     // groups per load batch: one for the few small workgroups of a small batch, four where half as many wavefronts stream a row
     r.unroll = takes_deep(a, pda) ? 4 : r.threads < 1024 && (int64_t)a.batch * r.parts <= 384 ? 1 : 2;
     // A stretch of the row per wavefront, in whole 16-group pieces; the bits of the stretches fit
@@ -2169,10 +2175,10 @@ int raise_lds_limit(size_t lds)
 
 bool mask_step_takes_pda(const PdaMaskArgs& a)
 {
-    return a.batch > 0 && a.dtype != TDFA_F32 && !a.delta && !a.targets && a.n_tokens <= (1 << 27) && bits_in_lds(a, true).fits;
+    return a.batch > 0 && a.dtype != TDFA_F32 && !a.delta && !a.targets && a.n_tokens <= (1 << 27) && bits_in_lds(a, true, false).fits;
 }
 
-int launch_mask_step(const MaskArgs& a, hipStream_t stream)
+int launch_mask_step(const MaskArgs& a, hipStream_t stream, bool alone)
 {
     if (a.batch <= 0) return TDFA_OK;
     if (packed_takes_gather(a)) {
@@ -2186,7 +2192,7 @@ int launch_mask_step(const MaskArgs& a, hipStream_t stream)
         TDFA_HIP(hipGetLastError());
         return TDFA_OK;
     }
-    const BitsInLds sh = bits_in_lds(a);
+    const BitsInLds sh = bits_in_lds(a, false, alone);
     const int parts = sh.parts, threads = sh.threads, gpp = sh.gpp, unroll = sh.unroll, stretch = sh.stretch;
     const size_t lds = sh.lds;
     const bool skip = sh.fits;
@@ -2234,7 +2240,7 @@ int launch_pda_mask_step(const PdaMaskArgs& a, hipStream_t stream)
 {
     if (a.batch <= 0) return TDFA_OK;
     if (!mask_step_takes_pda(a)) return fail(TDFA_E_UNSUPPORTED, "this step wants one row of allowed bits per sequence");
-    const BitsInLds sh = bits_in_lds(a, true);
+    const BitsInLds sh = bits_in_lds(a, true, false);
     if ((int64_t)a.batch * sh.parts > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
     const int rc = raise_lds_limit(sh.lds);
     if (rc != TDFA_OK) return rc;

@@ -950,8 +950,9 @@ int pda_step_impl(const tdfa_ptable* table, const void* logits_dev, int dtype, i
     m.tokens = tokens_dev;
     m.new_states = table->step_unused;
     m.masked_out = masked_out_dev;
+    bool alone;
     {
-        const int rc = tdfa::step_scratch(batch, s, &m.scratch_best, &m.scratch_count);
+        const int rc = tdfa::step_scratch(m, s, &m.scratch_best, &m.scratch_count, &alone);
         if (rc != TDFA_OK) return rc;
     }
     // 16-bit logits: the step kernel finds a sequence's classes itself and ORs their rows as it reads them
@@ -992,7 +993,7 @@ int pda_step_impl(const tdfa_ptable* table, const void* logits_dev, int dtype, i
                                                          table->class_n_pops, table->class_pops, table->class_bits, table->row_words,
                                                          table->step_allow, table->step_rows);
         TDFA_HIP(hipGetLastError());
-        const int rc = tdfa::launch_mask_step(m, s);
+        const int rc = tdfa::launch_mask_step(m, s, alone);
         if (rc != TDFA_OK) return rc;
     }
     pda_advance_kernel<<<(unsigned)((batch + 3) / 4), 256, 0, s>>>(a, edges, batch);

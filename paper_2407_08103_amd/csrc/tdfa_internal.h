@@ -236,16 +236,20 @@ struct PdaMaskArgs : MaskArgs {
         PdaEdges edges;                 // the chosen token's edge is traversed by the step kernel
     } pda;
 };
-int launch_mask_step(const MaskArgs& a, hipStream_t stream);
+// alone: no other step can be in flight that meets through the same scratch, so that also rows may be split which could do
+// without (mask_step_wants_scratch).
+int launch_mask_step(const MaskArgs& a, hipStream_t stream, bool alone = false);
 int launch_pda_mask_step(const PdaMaskArgs& a, hipStream_t stream);
 // Whether launch_pda_mask_step takes `a` (16-bit logits, no masked row written, a vocabulary whose allowed bits fit
 // the workgroup's LDS); otherwise the caller makes one row per sequence first.
 bool mask_step_takes_pda(const PdaMaskArgs& a);
-// The per-device scratch of the step kernels for `batch` sequences (all zero between launches); grown
-// outside stream capture only.
-int step_scratch(int32_t batch, hipStream_t stream, unsigned long long** best, unsigned int** count);
+// The per-device scratch of the step kernels for the step `a` (all zero between launches); grown outside stream capture
+// only.  *alone: as launch_mask_step takes it.
+int step_scratch(const MaskArgs& a, hipStream_t stream, unsigned long long** best, unsigned int** count, bool* alone);
 // Whether launch_mask_step(a) splits rows over workgroups that meet through scratch_best / scratch_count.
 bool mask_step_uses_scratch(const MaskArgs& a);
+// Whether it would split them if it were alone (dtype, batch, n_tokens and masked_out of `a` are looked at).
+bool mask_step_wants_scratch(const MaskArgs& a);
 // best[0 .. n) <- 0, count[0 .. n) <- 0, by a kernel.
 int launch_clear_scratch(unsigned long long* best, unsigned int* count, int32_t n, hipStream_t stream);
 // offset_dev: if not NULL, the kernel reads the offset from this device word instead of `offset`

@@ -238,6 +238,53 @@ def test_penalised_fp32_rows_at_the_edges(T, oracle, n_tokens, batch):
         assert np.array_equal(got[:, n_tokens:], rest)
 
 
+@pytest.mark.parametrize("how", ["graphs", "noalloc"])
+def test_penalised_fp32_rows_of_two_steps_at_once(T, oracle, how):
+    """256 rows and more, written with the penalty: such rows meet through no scratch, so two recorded steps of one stream,
+    or two steps through the library's static scratch, may run side by side; and eager ones, which do, give the same."""
+    n_tokens, batch = 100003, 300
+    tab = _rand_table(6, n_tokens, 0.4, 5)
+    table = _upload_table(T, tab)
+    rng = np.random.default_rng(6)
+    side = [torch.cuda.Stream() for _ in range(3)]
+    step = {"graphs": T.mask_step, "noalloc": T.mask_step_noalloc}[how]
+    runs = []
+    for i in range(2):
+        x = (np.round(rng.normal(0, 2, size=(batch, n_tokens + 5)) * 8) / 8).astype(np.float32)
+        states = rng.integers(-1, 6, size=batch).astype(np.int32)
+        want = oracle.mask_step(tab, x, F32, states, row_stride=n_tokens + 5, want_masked=True)
+        dev = _to_dev(x, F32)
+        args = [dev, torch.from_numpy(states).cuda()] + [torch.full((batch,), -9, dtype=torch.int32, device="cuda") for _ in range(2)] + [torch.zeros_like(dev)]
+        T.mask_step(table, *args)
+        torch.cuda.synchronize()
+        assert np.array_equal(args[2].cpu().numpy(), want[0]) and np.array_equal(args[3].cpu().numpy(), want[1])
+        graph = None
+        if how == "graphs":
+            with torch.cuda.stream(side[2]):
+                step(table, *args)
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side[2]):
+                step(table, *args)
+        runs.append((args, want, graph))
+    torch.cuda.synchronize()
+    for _ in range(10):
+        for args, _, _ in runs:
+            args[2].fill_(-9)
+            args[4].zero_()
+        torch.cuda.synchronize()
+        for i, (args, _, graph) in enumerate(runs):
+            with torch.cuda.stream(side[i]):
+                if graph is not None:
+                    graph.replay()
+                else:
+                    step(table, *args)
+        torch.cuda.synchronize()
+        for args, want, _ in runs:
+            assert np.array_equal(args[2].cpu().numpy(), want[0]) and np.array_equal(args[3].cpu().numpy(), want[1])
+            assert np.array_equal(_bits(args[4])[:, :n_tokens], want[2].view(np.uint32)[:, :n_tokens])
+
+
 def test_stride_inplace_and_alias(T, oracle):
     n_tokens = 3000
     tab = _rand_table(7, n_tokens, 0.2, 2)
