@@ -2016,6 +2016,7 @@ void gather_shape(const MaskArgs& a, int* parts_out, int* threads_out, int* gpp_
 
 namespace {
 constexpr int kPieceGroups = 4096;     // groups of a row that a workgroup takes where rows are split
+constexpr int kBitsGroups = kMaxBitRowBytes - 8192;     // groups of a workgroup whose allowed bits are sure to fit its LDS, beside the loads in flight
 constexpr int kSmallBatch = 16;        // rows from which on that is the better split (1 to 8 rows: 4.8 to 6.0 us in 16 parts of 256 threads, 5.9 to 6.4 us so)
 
 // Rows that one workgroup of 512 threads streams with four groups per lane and buffer, not one of 1,024 with two: as much in
@@ -2026,10 +2027,14 @@ bool takes_deep(const MaskArgs& a, bool pda)
 {
     if (a.dtype == TDFA_F32 || a.masked_out) return false;
     const int n_groups = (a.n_tokens + 7) >> 3;
+    if (n_groups > kBitsGroups) return false;
     return pda ? n_groups >= kPieceGroups && a.batch > 128 : n_groups >= 2 * kPieceGroups && a.delta && a.batch >= 288 && a.batch < kGatherRows;
 }
 
 // Launch shape of the streaming kernels: `parts` workgroups of `threads` threads to a row.
+//
+// Rows whose bits would not fit the LDS of a few large workgroups are cut as small batches are: in parts of 256 threads, or
+// one of 1,024 (without the bits the push-down step makes a row per sequence first, and the others stream rows they could skip).
 //
 // What it weighs: a compute unit streams at what one unit gets from memory (a 256 KB row in 6.5 us), so few rows are split;
 // every workgroup costs its launch and its own look at state and bits, and workgroups of a row meet at the end; a workgroup
@@ -2053,8 +2058,8 @@ void stream_shape(const MaskArgs& a, bool pda, bool alone, int* parts_out, int* 
         // rows 7.7 -> 8.4, 60,000 tokens, 160 and 191 rows 8.6 and 7.8 -> 9.2 and 9.0
         threads = 512;
     } else if (plain && n_groups >= kPieceGroups && batch >= kSmallBatch &&
-               (pda ? batch <= 128 && batch * (n_groups - kPieceGroups) >= 300000 :
-                      batch < 192 && (batch <= 170 || pieces <= 4) && (a.delta || pieces > 2))) {
+               (pda ? batch <= 128 && batch * (n_groups - kPieceGroups) >= 300000 && n_groups <= 2 * kBitsGroups :
+                      batch < 192 && (batch <= 170 || pieces <= 4) && (a.delta || pieces > 2) && n_groups <= 512 / batch * kBitsGroups)) {
         // as many pieces as the chip holds at once.  128,256 tokens, 16, 64 and 128 rows: in parts of 256 threads 7.3, 10.5 and
         // 13.2 us, in one piece 8.3, 9.3 and 9.1; so 6.0, 7.4 and 8.3 us.  In fewer than
         // three pieces one workgroup of 1,024 threads is better: 191 rows 13.6 and 11.6 -> 10.1 us; rows too long for that stay as
