@@ -99,11 +99,19 @@ def test_sparse_and_mixed_rows(T, oracle, n_tokens, batch):
 @pytest.mark.parametrize("dtype,n_tokens,batch", [(BF16, v, b) for v, b in [
     (8192, 20), (8193, 20), (32760, 200), (32767, 16), (32769, 15), (32769, 16), (33003, 128), (33003, 129), (65528, 191), (65529, 192),
     (65536, 319), (65536, 320), (65537, 170), (65545, 171), (98307, 64), (131081, 65), (140000, 191), (250003, 100), (250003, 172),
-    (48000, 171), (48001, 171), (56000, 170), (56001, 170)]] +
+    (48000, 171), (48001, 171), (56000, 170), (56001, 170),
+    # the kernel with four groups per lane in flight: last groups, passes and wavefronts that are not whole, and more than 64 KB of LDS
+    (65537, 288), (65545, 383), (128256, 300), (131075, 330), (460003, 288),
+    (65528, 319), (65528, 320), (65536, 287), (65537, 287), (65545, 384)]] +
     [(F32, v, b) for v, b in [(98304, 48), (98312, 47), (98313, 48), (98313, 64), (131075, 102), (131075, 103), (131075, 191), (131075, 192)]])
 def test_rows_at_the_edges_of_the_launch_shapes(T, oracle, dtype, n_tokens, batch):
     """Around the row lengths and batches at which rows are split into another number of workgroups, or of another size."""
     _sparse_and_mixed_rows(T, oracle, n_tokens, batch, dtype)
+
+
+@pytest.mark.parametrize("n_tokens,batch", [(33003, 767), (33003, 768), (65521, 767), (65521, 768), (32003, 20), (50001, 64), (65545, 40), (131081, 300)])
+def test_packed_rows_at_the_edges_of_the_launch_shapes(T, oracle, n_tokens, batch):
+    _sparse_and_mixed_rows(T, oracle, n_tokens, batch, BF16, packed=True)
 
 
 @pytest.mark.parametrize("n_tokens,batch", [(128256, 200), (128256, 7), (300011, 16), (5000, 250), (37 * 8 + 3, 3), (400003, 5)])
@@ -111,7 +119,7 @@ def test_sparse_and_mixed_rows_fp32(T, oracle, n_tokens, batch):
     _sparse_and_mixed_rows(T, oracle, n_tokens, batch, F32)
 
 
-def _sparse_and_mixed_rows(T, oracle, n_tokens, batch, dtype):
+def _sparse_and_mixed_rows(T, oracle, n_tokens, batch, dtype, packed=False):
     """Rows from empty to full in one batch, around the density at which a wavefront stops fetching
     single groups and streams its stretch instead, with clustered rows (one stretch dense, the rest
     empty), heavy ties (rounded logits, so equal keys meet in every order) and special values."""
@@ -128,6 +136,8 @@ def _sparse_and_mixed_rows(T, oracle, n_tokens, batch, dtype):
     tab[r + 2, ::997] = 3                                               # a regular sprinkle
     tab[r + 2, n_tokens // 2: n_tokens // 2 + 700] = 4                  # plus a cluster in the middle
     table = _upload_table(T, tab)
+    if packed:
+        table = T.table_pack(table)
     stride = (n_tokens + 7) // 8 * 8
     for trial in range(3):
         states = rng.integers(0, n_rows, size=batch).astype(np.int32)
