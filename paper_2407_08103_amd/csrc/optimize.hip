@@ -948,7 +948,10 @@ int minimize_table(const int32_t* delta, const uint32_t* allow, int64_t row_word
 int launch_compact_rows(const int32_t* delta, const uint32_t* allow, int32_t n_tokens, int64_t row_words, const std::vector<int32_t>& first_rows,
                         const std::vector<int32_t>& map, int32_t* out_delta, uint32_t* out_allow, hipStream_t s)
 {
-    if (first_rows.empty()) return TDFA_OK;
+    // (no row kept, or rows without tokens: nothing to write, and nothing is sent that would have to be waited for)
+    const int64_t n_new = (int64_t)first_rows.size();
+    const int64_t pieces = n_new * ((row_words + kPieceWords - 1) / kPieceWords);
+    if (pieces == 0) return TDFA_OK;
     Arena mem;
     int32_t *rows = nullptr, *map_dev = nullptr;
     TDFA_GET(mem.get(&rows, first_rows.size()));
@@ -956,11 +959,8 @@ int launch_compact_rows(const int32_t* delta, const uint32_t* allow, int32_t n_t
     TDFA_HIP(hipMemcpyAsync(rows, first_rows.data(), first_rows.size() * 4, hipMemcpyHostToDevice, s));
     TDFA_HIP(hipMemcpyAsync(map_dev, map.data(), map.size() * 4, hipMemcpyHostToDevice, s));
     // four workgroups of eight wavefronts per compute unit (two where the map is at its largest)
-    const int64_t n_new = (int64_t)first_rows.size();
     const size_t lds = map.size() * 4;
-    const int64_t pieces = n_new * ((row_words + kPieceWords - 1) / kPieceWords);
     const unsigned grid = (unsigned)std::min<int64_t>((pieces + kRenameThreads / 64 - 1) / (kRenameThreads / 64), 256 * 4);
-    if (grid == 0) return TDFA_OK;
     auto launch = [&](auto kernel, size_t bytes) {
         kernel<<<grid, kRenameThreads, bytes, s>>>(delta, allow, n_tokens, row_words, n_new, (int32_t)map.size(), rows, map_dev, out_delta,
                                                    out_allow);

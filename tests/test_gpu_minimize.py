@@ -221,6 +221,16 @@ def test_nothing_left(T, oracle):
     assert new.n_rows == 0 and mp.tolist() == [DEAD, DEAD]
 
 
+def test_table_without_tokens(T, oracle):
+    vocab, d = T.Vocab(np.zeros(0, np.uint8), np.zeros(1, np.int64)), compile_regex(r"ab")
+    table = T.compile_token_dfa(vocab, T.CharDFA(d.trans, d.accept, d.start))
+    accept = np.ones(d.n_states, np.uint8)
+    new, acc, mp = T.table_minimize(table, accept, [1, 0])
+    want, want_acc, want_mp = oracle.minimize(np.zeros((d.n_states, 0), np.int32), accept, np.array([1, 0], np.int32))
+    assert np.array_equal(mp, want_mp) and np.array_equal(acc, want_acc) and new.n_rows == want.shape[0]
+    assert T.table_pack(new).n_rows == new.n_rows
+
+
 def test_c2_and_decode(T, oracle):
     w = configs.get("c2")
     d = w.dfas[0]
