@@ -2020,9 +2020,12 @@ constexpr int kBitsGroups = kMaxBitRowBytes - 8192;     // groups of a workgroup
 constexpr int kSmallBatch = 16;        // rows from which on that is the better split (1 to 8 rows: 4.8 to 6.0 us in 16 parts of 256 threads, 5.9 to 6.4 us so)
 
 // Rows that one workgroup of 512 threads streams with four groups per lane and buffer, not one of 1,024 with two: as much in
-// flight, and the workgroup starts, matches the stack and ends sooner.  Push-down step, 128,256 tokens, 160, 256 and 512 rows
-// 14.8, 15.1 and 23.4 -> 14.2, 14.4 and 22.8 us; greedy, where some compute units hold two rows, 300 and 383 rows 17.3 and 18.0 -> 15.8 and 16.7 (256 rows 9.8
-// -> 10.0, 257 rows 12.3 -> 13.7, 512 rows 18.3 -> 18.6, 1,024 rows 32.8 -> 33.6, so not).
+// flight, and the workgroup starts, matches the stack and ends sooner.  Push-down step, 128,256 tokens, replayed from a graph, 192, 257,
+// 512, 768, 1,024 and 2,048 rows anywhere in their texts 13.2, 15.1, 20.9, 34.0, 38.6 and 70.1 -> 13.3, 13.6, 20.2, 28.0, 40.4 and 65.3 us,
+// 1,024 rows that allow little 23.5 -> 17.5 (against the form with 1,024 threads held to 80 scalar registers, which only 896 to 1,088
+// rows of 100,000 tokens and more anywhere in their texts would prefer, by 2 to 9 %; this form held to 80: 2 to 4 % slower); greedy,
+// where some compute units hold two rows, 300 and 383 rows 17.6 and 18.0 -> 16.4 and 16.3 (256 rows 9.8 -> 10.0, 257 rows 12.3 -> 13.7,
+// 512 rows 18.3 -> 18.6, 1,024 rows 32.8 -> 33.6, so not).
 bool takes_deep(const MaskArgs& a, bool pda)
 {
     if (a.dtype == TDFA_F32 || a.masked_out) return false;
@@ -2038,7 +2041,8 @@ bool takes_deep(const MaskArgs& a, bool pda)
 //
 // What it weighs: a compute unit streams at what one unit gets from memory (a 256 KB row in 6.5 us), so few rows are split;
 // every workgroup costs its launch and its own look at state and bits, and workgroups of a row meet at the end; a workgroup
-// of 512 threads starts and ends a microsecond sooner than one of 1,024, which has more loads in flight.
+// of 512 threads starts and ends a microsecond sooner than one of 1,024, which has more loads in flight.  The times are of steps
+// replayed from a graph, rows anywhere in their texts where nothing else is said (a call of its own costs the host 8 us).
 void stream_shape(const MaskArgs& a, bool pda, bool alone, int* parts_out, int* threads_out, int* gpp_out)
 {
     const int n_groups = (a.n_tokens + 7) >> 3;
@@ -2060,11 +2064,12 @@ void stream_shape(const MaskArgs& a, bool pda, bool alone, int* parts_out, int* 
     } else if (plain && n_groups >= kPieceGroups && batch >= kSmallBatch &&
                (pda ? batch <= 128 && batch * (n_groups - kPieceGroups) >= 300000 && n_groups <= 2 * kBitsGroups :
                       batch < 192 && (batch <= 170 || pieces <= 4) && (a.delta || pieces > 2) && n_groups <= 512 / batch * kBitsGroups)) {
-        // as many pieces as the chip holds at once.  128,256 tokens, 16, 64 and 128 rows: in parts of 256 threads 7.3, 10.5 and
-        // 13.2 us, in one piece 8.3, 9.3 and 9.1; so 6.0, 7.4 and 8.3 us.  In fewer than
-        // three pieces one workgroup of 1,024 threads is better: 191 rows 13.6 and 11.6 -> 10.1 us; rows too long for that stay as
-        // they were (250,000 tokens, 180 rows: 15.6, in two pieces 20.3), as do the shorter ones of packed tables (50,000 tokens, 64
-        // rows: 6.9, in two pieces 7.4).
+        // as many pieces as the chip holds at once.  128,256 tokens, 16, 64 and 128 rows: in parts of 256 threads 7.5, 10.7 and 13.4
+        // us, in one piece 8.3, 9.3 and 9.1; so 7.2, 7.8 and 8.7 us (16 rows that allow little 6.9 -> 6.0).  In fewer than three pieces one
+        // workgroup of 1,024 threads is better: 191 rows 14.0 in parts of 256 threads, 11.6 in two pieces, 10.2 us so; rows too long
+        // for that stay as they were (250,000 tokens, 180 rows: 15.6, in two pieces 20.3), as do the shorter ones of packed tables
+        // (50,000 tokens, 64 rows: 6.9, in two pieces 7.4).  Rows of two pieces gain from 64 rows on (60,000 tokens, 128 rows 8.5 -> 7.7;
+        // 33,000 tokens, 32 rows 5.8 -> 6.0).
         // The push-down step matches its stack in every workgroup: two large ones at most, where what lies beyond the first piece of
         // each row is work enough for them.  128,256 tokens, 48, 64 and 128 rows 11.6, 13.2 and 18.3 -> 10.7, 11.0 and 11.7 us, 24 rows 9.9 ->
         // 10.2; 80,000 tokens, 64 and 128 rows 10.8 and 12.3 -> 10.6 and 10.9, 48 rows 9.5 -> 10.3; 65,600 tokens, 96 rows 11.1 -> 10.9, 48 rows
