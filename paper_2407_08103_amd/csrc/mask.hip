@@ -137,28 +137,6 @@ __device__ __forceinline__ void store_group(typename ElemOf<DTYPE>::type* orow, 
     }
 }
 
-// The same with 16-bit logits left in pairs, as they lie in memory.
-template <int DTYPE> constexpr int kGroupWords = DTYPE == TDFA_F32 ? 8 : 4;
-
-template <int DTYPE>
-__device__ __forceinline__ void load_words(const typename ElemOf<DTYPE>::type* row, int t, int V, uint32_t (&x)[kGroupWords<DTYPE>])
-{
-    if (t + 8 <= V) {
-#pragma unroll
-        for (int i = 0; i < kGroupWords<DTYPE> / 4; ++i) {
-            const uint4 v = reinterpret_cast<const uint4*>(row + t)[i];
-            x[4 * i] = v.x; x[4 * i + 1] = v.y; x[4 * i + 2] = v.z; x[4 * i + 3] = v.w;
-        }
-    } else if constexpr (DTYPE == TDFA_F32) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = t + j < V ? row[t + j] : 0xFF800000u;
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            x[j] = (t + 2 * j < V ? row[t + 2 * j] : 0xFF80u) | (t + 2 * j + 1 < V ? (uint32_t)row[t + 2 * j + 1] : 0xFF80u) << 16;
-    }
-}
-
 // Exact scan of groups [g_lo, g_hi) of one row by the whole workgroup: this thread's best
 // candidate (key << 32 | ~token), 0 if it saw nothing allowed.  Writes the masked row if orow.
 // (bits_at(g): the allowed bits of group g.)
@@ -396,6 +374,18 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true);    // row_mirror
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 0) + (uint32_t)__builtin_amdgcn_readlane((int)v, 16) +
            (uint32_t)__builtin_amdgcn_readlane((int)v, 32) + (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+}
+
+// Sums over the lanes up to and including this one (all lanes active).
+__device__ __forceinline__ uint32_t wave_prefix_u32(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast:15, rows 1 and 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast:31, rows 2 and 3
+    return v;
 }
 
 // Number of lanes below this one for which `flag` holds (all lanes active).
@@ -1698,262 +1688,471 @@ packed_step_kernel(MaskArgs a, int parts, int groups_per_part)
     if (threadIdx.x == 0 && combine_parts(a, b, parts, cand)) write_result(a, b, q, valid, cand);
 }
 
-constexpr int kQueue = 128;            // entries of a wavefront's queues (rings, a power of two)
-constexpr int kWordsAhead = 4;         // 32-bit words of allowed bits (four groups each) a thread has in flight
-constexpr int kDrawThreads = 256;      // workgroup of the draw
-constexpr int kDrawGroups = 2048;      // workgroups that a draw of a smaller batch is split into
-constexpr int kDrawPartGroups = 1 << 27;    // groups whose quads' numbers have their upper bits in common, of 28 below; no part crosses such a line
-constexpr int kDenseQuads = 48;        // lanes with a quad to draw for from which on a wavefront draws in place
+// Rows of a batch shared out over the workgroups of a launch by what they cost, each workgroup working the same plan out
+// for itself from the states and the counts beside the table.  The cost of a row is in 1,024ths of one whose state allows
+// a tenth of the vocabulary or more, which has every quad drawn: a floor for the scan of its bits, and its tokens (measured:
+// a state that allows 7 % costs three quarters).  Rows above kShareSmall come first and take kShareFull workgroups between
+// them, so that every compute unit gets its three or so of about the same cost; the others take one each, behind them.
+constexpr int kShareRows = 1024;       // rows of a batch at most (a multiple of the workgroup's threads)
+constexpr int kShareFull = 720;
+constexpr int kShareGroups = 1024;     // groups of a part at least
+constexpr float kShareFloor = 60.0f, kShareTokens = 10000.0f;     // cost of a row; of a token, times the size of the vocabulary
+constexpr uint32_t kShareSmall = 100;
 
-// The draw from the whole allowed set.  `parts` workgroups scan a row; one takes groups [g_lo, g_hi).  Only tokens that
-// may win cost arithmetic, and what they cost is their generator block, made for four neighbouring tokens (a quad) at
-// a time.  Two queues per wavefront, in LDS, keep the lanes busy:
-//   groups : the groups of eight tokens with an allowed token among them.  A thread reads the allowed bits of
-//            4 * kWordsAhead groups at once; the groups that need their logits are queued and fetched 64 at a time, one
-//            per lane, a batch ahead (with the masked row wanted all groups are).
-//   quads  : the quads of the fetched groups with an allowed token that could still win whatever its noise: no noise
-//            value exceeds kNoiseMax, so a logit too far below the best score of the workgroup so far cannot.  They
-//            wait until there are 64, one per lane; where most lanes hold one they are drawn in place.
-// A quad's generator block gives every token's noise but for two logarithms; a bound on it that takes a few
-// instructions (noise_bound) lets all but about one token in 10^4 go without them.
+// What of the batch a workgroup takes (parts 0: nothing): part `part` of `parts` of a row, its state and how many tokens that allows.
+struct RowShare {
+    int row, part, parts, state;
+    uint32_t n_allowed;
+};
+
+template <int kThreads>
+__device__ __forceinline__ void share_rows(const MaskArgs& a, int max_parts, uint32_t (*s_sums)[kThreads / 64], RowShare* s_share)
+{
+    constexpr int kMost = kShareRows / kThreads, kWaves = kThreads / 64;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int per = (a.batch + kThreads - 1) / kThreads;           // rows per thread, one behind the other
+    int q[kMost];
+    uint32_t n[kMost], cost[kMost], sum = 0;
+#pragma unroll
+    for (int j = 0; j < kMost; ++j) {
+        q[j] = -1;
+        n[j] = cost[j] = 0;
+        if (j < per && tid * per + j < a.batch) q[j] = a.states[tid * per + j];
+    }
+    const float per_token = kShareTokens / (float)a.n_tokens;
+#pragma unroll
+    for (int j = 0; j < kMost; ++j)
+        if (j < per && q[j] >= 0 && (int64_t)q[j] < a.n_rows) n[j] = allowed_count(a, q[j]);
+#pragma unroll
+    for (int j = 0; j < kMost; ++j)
+        if (j < per) {
+            cost[j] = (uint32_t)fminf(1024.0f, kShareFloor + (float)n[j] * per_token);
+            if (cost[j] < kShareSmall) cost[j] = 0;
+            sum += cost[j] + (cost[j] ? 1u << 21 : 0u);            // (at most 1,024 rows of 1,024)
+        }
+    sum = wave_sum_u32(sum);
+    if (lane == 0) s_sums[0][wave] = sum;
+    if (tid == 0) s_share->parts = 0;
+    __syncthreads();
+    sum = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) sum += s_sums[0][w];
+    // A large row takes one workgroup and its share, rounded down, of kShareFull less what the rounding leaves over: kShareFull
+    // and as many as there are rows are enough for all.
+    const float share = fminf(fmaxf((float)kShareFull - 0.55f * (float)(sum >> 21), 0.0f) / (float)max(sum & 0x1FFFFFu, 1u), (float)(max_parts - 1) / 1024.0f);
+    uint32_t parts[kMost], mine = 0;                               // workgroups of the large rows, and the small rows << 16
+#pragma unroll
+    for (int j = 0; j < kMost; ++j) {
+        parts[j] = 0;
+        if (j < per && tid * per + j < a.batch) parts[j] = cost[j] ? 1u + (uint32_t)((float)cost[j] * share) : 0x10000u;
+        mine += parts[j];
+    }
+    const uint32_t incl = wave_prefix_u32(mine);
+    if (lane == 63) s_sums[1][wave] = incl;
+    __syncthreads();
+    uint32_t at = incl - mine, total = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const uint32_t x = s_sums[1][w];
+        if (w < wave) at += x;
+        total += x;
+    }
+    const uint32_t g = blockIdx.x, n_first = total & 0xFFFFu;
+#pragma unroll
+    for (int j = 0; j < kMost; ++j)
+        if (j < per) {
+            const bool small = (parts[j] & 0xFFFF0000u) != 0u;
+            const uint32_t first = small ? n_first + (at >> 16) : at & 0xFFFFu, n_wg = small ? 1u : parts[j];
+            if (g >= first && g < first + n_wg) *s_share = {tid * per + j, (int)(g - first), (int)n_wg, q[j], n[j]};
+            at += parts[j];
+        }
+    __syncthreads();
+}
+
+constexpr int kDrawThreads = 256;      // workgroup of the draw
+constexpr int kDrawGroups = 1024;      // workgroups that a draw of a smaller batch is split into: four to a compute unit, which their LDS lets it hold
+constexpr int kDrawPartGroups = 1 << 24;    // groups of a part at most: its offsets and its quads' numbers have 32 bits
+// noise_bound is above the noise by at most 0.0861 ln 2 + 0.001 and what -ln(1 - u) exceeds -ln(-ln u) by, which is no more
+// than -ln u: from u = 0.9 on by less than 0.168.  With scores of magnitude kTightScore at most, whose sums are rounded
+// by less than 0.002 each, a score is never below its bound less kBoundSlack.
+constexpr uint32_t kTightWord = 0xE6666800u;    // generator words from here on have u >= 0.9
+constexpr float kBoundSlack = 0.2f, kTightScore = 32768.0f;
+constexpr int kDrawList = 2048;        // quads that a wavefront lists at once
+constexpr int kDrawPieces = 4;         // 16-byte pieces of allowed bits that a lane has in flight
+constexpr uint32_t kDrawLone = 256;    // a state known to allow less than one token in so many is one workgroup's
+constexpr uint32_t kDrawDense = 10;    // a state that allows one token in so many or more has every quad drawn
+
+// The draw from the whole allowed set.  A workgroup takes part of a row: which, it works out from the costs of all rows
+// (max_parts > 0: share_rows), or `parts` workgroups of groups_per_part groups scan each row (max_parts < 0: but a row known to
+// allow few tokens is its first workgroup's).  What a token costs is its generator block, made for four neighbouring tokens
+// (a quad) at a time, one quad per lane.
+//   A state known to allow one token in kDrawDense or more (or a masked row to be written) has every quad drawn, in the
+//     order it lies in: one bound for the quad, from its largest logit, allowed or not, and its largest generator word.
+//   Else the quads with an allowed token are listed from the bits, 64 and more at a time, and drawn from the list.
+// Where a quad's bound reaches the best score so far its tokens are bounded one by one; those that may win are kept, the
+// tightest of them raises the best score by its bound less kBoundSlack, and only what is left at the end (or fills the
+// wavefront's 64 places) gets its two logarithms.  The maximum does not depend on the order: candidates are compared as
+// (score, lowest id).
 //
-// Bound by the instructions issued: a generator block is 18 multiplications (64-bit products, at the full rate)
-// and as many three-input exclusive-ors, the bounds six instructions per token.  (Counters, the 256 sequences below: 8,800
-// vector instructions per SIMD of four cycles each, 62 % of the launch's cycles on all SIMDs, and 39 MB fetched, which the
-// memory delivers in a quarter of the time.)  A workgroup of 1,024 threads per row (a compute unit with a
-// row that allows most tokens works for 45 us while those with sparse rows idle) and a queue of single tokens, each with
-// a generator block and two logarithms of its own, took longer: T = 1, 128,256 tokens, bf16, 256 sequences anywhere in
-// the texts of 50 signatures 42.4 -> 28.2 us, all in states that allow most tokens 45.9 -> 36.3 us (1,024 sequences: 139
-// -> 89 and 166 -> 105 us), all in states that allow few 9.8 -> 10.2 us (512 sequences 13.7 -> 11.4 us).
-// With the quad bounded as a whole before its tokens (above), which takes a quarter of the instructions out of a dense row:
-// 28.9 -> 28.0, all in states that allow most 35.6 -> 33.7 us; 1,024 sequences 87 -> 80 and 103 -> 94 us.  (80 scalar and 64
-// vector registers, so that a compute unit holds eight workgroups instead of six: 27.1 and 33.6, but 1,024 sequences 89.)
-// A queue belongs to one wavefront, so the loop needs no workgroup barrier; the maximum does not depend on the
-// order because candidates are compared as (score, lowest id).
+// Bound by the instructions issued where states allow many tokens: 54 per quad, 18 of them 64-bit products, at 1.9 to 2.4
+// ns per instruction and SIMD with four wavefronts (a wavefront alone gets half of that), so 256 rows of 128,256
+// tokens all drawn take 15 us of every SIMD; and by some 20 dependent steps, 6 us, where states allow few.  The scheduler
+// serves the oldest wavefront first, so that the last one of a SIMD would run alone: a wavefront lowers its priority as it
+// gets on.  T = 1, 128,256 tokens in bf16, rows anywhere in the texts of 50 signatures / all in states that allow most / all that
+// allow few, replayed, against rows in parts of equal length and two queues per wavefront: 16 rows 10.9, 12.0 and 6.7 -> 9.8,
+// 10.0 and 6.6 us, 64 rows 14.2, 16.5 and 10.5 -> 12.9, 14.2 and 7.5, 256 rows 27.6, 34.0 and 10.5 -> 20.9, 23.7 and 7.6, 1,024 rows 79.4, 94.0 and
+// 15.0 -> 48.3, 66.5 and 12.2; 9,000 tokens, 256 rows 11.9, 11.7 and 6.8 -> 9.2, 8.9 and 7.8; the masked row as well, 256 rows of
+// 128,256 in place 38.7 -> 31.7.  Without the priorities 256 rows 22.1 and 26.2, with equal parts instead of shares 24 and 27.
 template <int DTYPE, bool WRITE>
 __global__ void __launch_bounds__(kDrawThreads)
-draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part)
+draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part, int max_parts)
 {
     using Elem = typename ElemOf<DTYPE>::type;
-    constexpr Elem NEG_INF = DTYPE == TDFA_F32 ? (Elem)0xFF800000u : (Elem)0xFF80u;
-    constexpr int kWaves = kDrawThreads / 64, kWords = kGroupWords<DTYPE>;
-    __shared__ unsigned long long wave_best[kMaxWaves];
-    __shared__ uint2 s_groups[kWaves][kQueue];
-    __shared__ __attribute__((aligned(16))) float4 s_logits[kWaves][kQueue];   // a waiting quad's logits, -inf where not allowed
-    __shared__ uint32_t s_quads[kWaves][kQueue];                               // its number << 4 | allowed bits (without the number's upper bits)
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    constexpr int kSize = (int)sizeof(Elem);
+    constexpr uint32_t NEG_INF = DTYPE == TDFA_F32 ? 0xFF800000u : 0xFF80u;
+    constexpr int kWaves = kDrawThreads / 64;
+    __shared__ unsigned long long wave_best[kWaves];
+    __shared__ uint32_t s_list[kWaves][kDrawList];             // a quad's number in the part << 4 | its allowed bits
+    __shared__ uint4 s_cands[kWaves][64];                      // tokens that may win: id, logit, generator word, bound of the score
+    __shared__ uint32_t s_sums[2][kWaves];
+    __shared__ RowShare s_share;
     __shared__ uint32_t s_reached;                             // order key of the best score any wavefront has reached
+    const int V = a.n_tokens, n_groups = (V + 7) >> 3;
+    const int lane = (int)threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (threadIdx.x == 0) s_reached = 0;
-    __syncthreads();
-    const int b = blockIdx.x / parts, p = blockIdx.x % parts;
-    const int V = a.n_tokens;
-    const int q = a.states[b];
-    const bool valid = q >= 0 && (int64_t)q < a.n_rows;
-    const uint8_t* bits = reinterpret_cast<const uint8_t*>(a.allow + (valid ? (int64_t)q * a.row_words : 0));
-    const Elem* row = static_cast<const Elem*>(a.logits) + (int64_t)b * a.row_stride;
-    Elem* orow = WRITE ? static_cast<Elem*>(a.masked_out) + (int64_t)b * a.row_stride : nullptr;
-    const int n_groups = (V + 7) >> 3;
-    const int g_lo = p * groups_per_part;
-    const int g_hi = min(n_groups, g_lo + groups_per_part);
-    const uint32_t quad_top = (uint32_t)(g_lo / kDrawPartGroups) * (2u * kDrawPartGroups);
-    const uint32_t lane = threadIdx.x & 63u;
-    uint2* group_q = s_groups[threadIdx.x >> 6];
-    float4* logit_q = s_logits[threadIdx.x >> 6];
-    uint32_t* quad_q = s_quads[threadIdx.x >> 6];
-    auto below = [](unsigned long long bal) {                  // lanes below this one that are set in bal
-        return __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-    };
-    auto wave_sync = []() {                                    // LDS written by some lanes, read by others
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
-
-    if constexpr (!WRITE) {
-        // A state that allows no token: no token, the state stays.
-        if (valid && allowed_count(a, q) == 0u) {              // uniform in the workgroup
-            if (threadIdx.x == 0) {
-                unsigned long long nothing = 0ull;
-                if (combine_parts(a, b, parts, nothing)) write_result(a, b, q, valid, nothing);
-            }
-            return;
+    int b, p, q;
+    uint32_t n_allowed = kUnknown;
+    if (!WRITE && max_parts > 0) {
+        share_rows<kDrawThreads>(a, max_parts, s_sums, &s_share);
+        parts = __builtin_amdgcn_readfirstlane(s_share.parts);
+        if (parts == 0) return;                                // (uniform: no row is left for this workgroup)
+        b = __builtin_amdgcn_readfirstlane(s_share.row);
+        p = __builtin_amdgcn_readfirstlane(s_share.part);
+        q = __builtin_amdgcn_readfirstlane(s_share.state);
+        n_allowed = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_share.n_allowed);
+        groups_per_part = ((n_groups + parts - 1) / parts + 255) & ~255;
+    } else {
+        b = blockIdx.x / parts;
+        p = blockIdx.x % parts;
+        q = a.states[b];
+        if (!WRITE && q >= 0 && (int64_t)q < a.n_rows) n_allowed = allowed_count(a, q);
+        if (!WRITE && max_parts < 0 && n_allowed < (uint32_t)V / kDrawLone) {       // (uniform; kUnknown is above)
+            if (p != 0) return;
+            parts = 1;
+            groups_per_part = n_groups;
         }
+        __syncthreads();
+    }
+    const bool valid = q >= 0 && (int64_t)q < a.n_rows;
+    if (!WRITE && (!valid || n_allowed == 0u)) {               // no token; (uniform in the workgroup)
+        if (threadIdx.x == 0) {
+            unsigned long long none = 0ull;
+            if (combine_parts(a, b, parts, none)) write_result(a, b, q, valid, none);
+        }
+        return;
     }
     if (sp.off_dev) {                                          // the same word for every thread
         const unsigned long long o = *sp.off_dev;
         sp.off_lo = (uint32_t)o;
         sp.off_hi = (uint32_t)(o >> 32);
     }
+    // the workgroup's part of the row: tokens 8 g_lo .. 8 g_lo + n_tok
+    const int64_t g_lo = min((int64_t)p * groups_per_part, (int64_t)n_groups);
+    const int n_part = (int)min((int64_t)groups_per_part, n_groups - g_lo);
+    const int n_tok = (int)max(min((int64_t)n_part * 8, V - g_lo * 8), (int64_t)0);
+    const int n_full = n_tok >> 3;
+    const uint32_t quad0 = (uint32_t)(g_lo * 2);
+    const Elem* row = static_cast<const Elem*>(a.logits) + (int64_t)b * a.row_stride + g_lo * 8;
+    Elem* orow = WRITE ? static_cast<Elem*>(a.masked_out) + (int64_t)b * a.row_stride + g_lo * 8 : nullptr;
+    const uint8_t* bits = reinterpret_cast<const uint8_t*>(a.allow + (valid ? (int64_t)q * a.row_words : 0)) + g_lo;
+
     uint32_t best_key = 0, best_idx = 0xFFFFFFFFu;             // key 0: no candidate yet
     float reached = -__builtin_inff();                         // a score that some token of the workgroup has reached
     auto reach = [&](uint32_t key) {                           // (key 0: nothing scored yet)
-        if (key != 0) reached = fmaxf(reached, __uint_as_float((key & 0x80000000u) ? key & 0x7FFFFFFFu : ~key));
+        const float r = __uint_as_float((key & 0x80000000u) ? key & 0x7FFFFFFFu : ~key);
+        if (key != 0 && r > reached) reached = r;
     };
-    // One quad per lane (all lanes active; mask 0: none): its allowed tokens compete.  `most` is the largest of the logits.
-    // (The bound rises with the generator's word, so the largest logit with the largest word bounds the whole quad; the
-    // tokens' own bounds are made where that is not below what is reached, in one wavefront of twenty or so.)
-    auto draw_quads = [&](uint32_t quad, uint32_t mask, const float (&l)[4], float most) __attribute__((always_inline)) {
-        uint32_t w[4];
-        philox4x32_10(quad, (uint32_t)b, sp.off_lo, sp.off_hi, sp.seed_lo, sp.seed_hi, w);
-        const float top = __builtin_fmaf(most, sp.inv_t, noise_bound(max(max(w[0], w[1]), max(w[2], w[3]))));
-        if (__builtin_amdgcn_ballot_w64(!(top < reached)) == 0) return;         // (a NaN logit does not hide the others)
-        float bd[4];
+    auto look = [&]() {
+        reach((uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(&s_reached, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)));
+    };
+    // The largest score a token of the quad may have; NaN if one of its logits is.
+    auto quad_bound = [&](const float (&l)[4], const uint32_t (&w)[4]) {
+        const float most = __builtin_elementwise_maximum(__builtin_elementwise_maximum(l[0], l[1]), __builtin_elementwise_maximum(l[2], l[3]));
+        return __builtin_fmaf(most, sp.inv_t, noise_bound(max(max(w[0], w[1]), max(w[2], w[3]))));
+    };
+    auto wave_sync = []() {                                    // LDS written by some lanes, read by others
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto publish = [&](uint32_t key) {
+        if (lane == 0) atomicMax(&s_reached, key);               // the other wavefronts prune by it too
+        reach(key);
+    };
+    // The candidates of this wavefront: those that may still win compete.
+    uint32_t n_cand = 0;
+    uint4* cands = s_cands[wave];
+    auto compete = [&]() __attribute__((always_inline)) {
+        wave_sync();
+        look();
+        const uint4 c = cands[lane];
+        const bool live = (uint32_t)lane < n_cand && !(__uint_as_float(c.w) < reached);
+        n_cand = 0;
+        wave_sync();
+        if (__builtin_amdgcn_ballot_w64(live) == 0) return;
+        if (live) {
+            const uint32_t lb = (c.y & 0x7FFFFFFFu) > 0x7F800000u ? 0xFF800000u : c.y;       // NaN counts as -inf
+            const uint32_t key = key_f32(__float_as_uint(__builtin_fmaf(__uint_as_float(lb), sp.inv_t, gumbel_of(c.z))));
+            if (key > best_key || (key == best_key && c.x < best_idx)) {
+                best_key = key;
+                best_idx = c.x;
+            }
+        }
+        publish(wave_max_u32(best_key));
+    };
+    // One quad per lane (all lanes active; take: its allowed tokens, 0: none): those that may win become candidates.
+    auto settle = [&](uint32_t quad, uint32_t take, const float (&l)[4], const uint32_t (&w)[4]) __attribute__((always_inline)) {
+        float bd[4], low = -__builtin_inff();
 #pragma unroll
-        for (int j = 0; j < 4; ++j) bd[j] = __builtin_fmaf(l[j], sp.inv_t, noise_bound(w[j]));
-        uint32_t take = mask;
-        for (;;) {
+        for (int j = 0; j < 4; ++j) {
+            bd[j] = __builtin_fmaf(l[j], sp.inv_t, noise_bound(w[j]));
+            if (bd[j] < reached) take &= ~(1u << j);
+        }
+        if (__builtin_amdgcn_ballot_w64(take != 0) == 0) return;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if ((take >> j & 1u) && w[j] >= kTightWord && fabsf(bd[j]) <= kTightScore && bd[j] > low) low = bd[j];
+        publish(wave_max_u32(key_f32(__float_as_uint(low - kBoundSlack))));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool may = (take >> j & 1u) && !(bd[j] < reached);
+            const unsigned long long bal = __builtin_amdgcn_ballot_w64(may);
+            if (bal == 0) continue;
+            if (n_cand + (uint32_t)__popcll(bal) > 64u) compete();
+            if (may)
+                cands[n_cand + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u))] =
+                    make_uint4((quad0 + quad) * 4u + (uint32_t)j, __float_as_uint(l[j]), w[j], __float_as_uint(bd[j]));
+            n_cand += (uint32_t)__popcll(bal);
+        }
+    };
+    auto generate = [&](uint32_t quad, uint32_t (&w)[4]) {
+        philox4x32_10(quad0 + quad, (uint32_t)b, sp.off_lo, sp.off_hi, sp.seed_lo, sp.seed_hi, w);
+    };
+    uint32_t* list = s_list[wave];
+    const bool ragged = (n_tok & 3) != 0;
+    const __amdgpu_buffer_rsrc_t r_quads =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<Elem*>(row), 0, (n_tok & ~3) * kSize, kRawBuffer);
+    // The n quads of the wavefront's list, 64 at a time, their logits requested a batch ahead.
+    struct Quad {
+        uint32_t e;
+        float l[4];
+    };
+    auto fetch = [&](uint32_t i, uint32_t n, Quad& k) __attribute__((always_inline)) {
+        k.e = i < n ? list[i] : 0u;
+        const int quad = (int)(k.e >> 4);
+        if constexpr (DTYPE == TDFA_F32) {
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r_quads, k.e ? quad * 16 : 0x7FFFFFF0, 0, 0);
+            k.l[0] = __uint_as_float(v.x); k.l[1] = __uint_as_float(v.y); k.l[2] = __uint_as_float(v.z); k.l[3] = __uint_as_float(v.w);
+        } else {
+            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r_quads, k.e ? quad * 8 : 0x7FFFFFF0, 0, 0);
+            k.l[0] = __uint_as_float(v.x << 16); k.l[1] = __uint_as_float(v.x & 0xFFFF0000u);
+            k.l[2] = __uint_as_float(v.y << 16); k.l[3] = __uint_as_float(v.y & 0xFFFF0000u);
+        }
+        if (ragged && k.e != 0u && quad * 4 + 4 > n_tok) {     // the row's last quad, not whole
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (bd[j] < reached) take &= ~(1u << j);
-            if (__builtin_amdgcn_ballot_w64(take != 0) == 0) break;
-            if (take != 0) {
-                const int j = __builtin_ctz(take);
-                take &= take - 1u;
-                uint32_t lb = __float_as_uint(j == 0 ? l[0] : j == 1 ? l[1] : j == 2 ? l[2] : l[3]);
-                const uint32_t word = j == 0 ? w[0] : j == 1 ? w[1] : j == 2 ? w[2] : w[3];
-                if ((lb & 0x7FFFFFFFu) > 0x7F800000u) lb = 0xFF800000u;         // NaN counts as -inf
-                const uint32_t key = key_f32(__float_as_uint(__builtin_fmaf(__uint_as_float(lb), sp.inv_t, gumbel_of(word))));
-                const uint32_t tok = quad * 4u + (uint32_t)j;
-                if (key > best_key || (key == best_key && tok < best_idx)) {
-                    best_key = key;
-                    best_idx = tok;
-                }
-            }
-            const uint32_t top_key = wave_max_u32(best_key);
-            if (lane == 0) atomicMax(&s_reached, top_key);       // the other wavefronts prune by it too
-            reach(top_key);
+                k.l[j] = quad * 4 + j < n_tok ? __uint_as_float(DTYPE == TDFA_F32 ? (uint32_t)row[quad * 4 + j] : (uint32_t)row[quad * 4 + j] << 16) : 0.0f;
         }
     };
-    uint32_t q_head = 0, q_tail = 0, g_head = 0, g_tail = 0;   // ring positions, the same in all lanes
-    auto draw_waiting = [&](uint32_t n) __attribute__((always_inline)) {       // n <= 64 waiting quads, one per lane
+    auto draw_list = [&](uint32_t n) __attribute__((always_inline)) {
         wave_sync();
-        const uint32_t at = (q_head + lane) & (kQueue - 1);
-        const uint32_t en = lane < n ? quad_q[at] : 0u;
-        const float4 l4 = logit_q[at];
-        const float l[4] = {l4.x, l4.y, l4.z, l4.w};
-        q_head += n;
-        wave_sync();
-        draw_quads(quad_top | (en >> 4), en & 15u, l, fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3])));
-    };
-    // Fetched groups are worked on one batch late: the logits of a batch are requested when it is
-    // taken from the queue and used when the next batch is taken (or at the end), so that a
-    // wavefront always has a load in flight while it computes.
-    uint32_t m = 0, m_next = 0;                                // allowed bits of this lane's group; 0: none
-    int t = 0, t_next = 0;                                     // its first token
-    uint32_t e[kWords], e_next[kWords];                        // its logits
-    bool own = false, own_next = false;                        // this lane holds a group (WRITE: also when m is 0)
-    auto take_batch = [&](uint32_t n) __attribute__((always_inline)) {   // n <= 64 queued groups: request their logits
-        wave_sync();
-        m_next = 0;
-        own_next = lane < n;
-        if (own_next) {
-            const uint2 en = group_q[(g_head + lane) & (kQueue - 1)];
-            t_next = (int)en.x << 3;
-            m_next = en.y;
-            load_words<DTYPE>(row, t_next, V, e_next);
+        Quad k, next;
+        fetch((uint32_t)lane, n, k);
+        for (uint32_t i = 0; i < n; i += 64) {
+            fetch(i + 64 + (uint32_t)lane, n, next);
+            uint32_t w[4];
+            generate(k.e >> 4, w);
+            look();
+            if (__builtin_amdgcn_ballot_w64(!(quad_bound(k.l, w) < reached)) != 0) settle(k.e >> 4, k.e & 15u, k.l, w);
+            k = next;
         }
-        g_head += n;
         wave_sync();
-    };
-    auto work_batch = [&]() __attribute__((always_inline)) {   // the batch whose logits were requested before
-        if (__builtin_amdgcn_ballot_w64(m != 0) != 0) {
-            const uint32_t rk = __hip_atomic_load(&s_reached, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            reach((uint32_t)__builtin_amdgcn_readfirstlane((int)rk));
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const uint32_t mask = (m >> (4 * h)) & 15u;
-                float l[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int i = 4 * h + j;
-                    uint32_t x;
-                    if constexpr (DTYPE == TDFA_F32) x = e[i];
-                    else x = i & 1 ? e[i >> 1] & 0xFFFF0000u : e[i >> 1] << 16;
-                    const uint32_t ok = (uint32_t)((int32_t)(m << (31 - i)) >> 31);         // all bits: the token is allowed
-                    l[j] = __uint_as_float((x & ok) | (0xFF800000u & ~ok));
-                }
-                // (fma rises with the logit, so the largest one decides)
-                const float most = fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3]));
-                const bool live = mask != 0 && !(__builtin_fmaf(most, sp.inv_t, kNoiseMax) < reached);
-                const unsigned long long bal = __builtin_amdgcn_ballot_w64(live);
-                if (bal == 0) continue;
-                const uint32_t quad = (uint32_t)(t >> 2) + (uint32_t)h, n = (uint32_t)__popcll(bal);
-                if (n >= (uint32_t)kDenseQuads) {
-                    draw_quads(quad, live ? mask : 0u, l, most);
-                } else {
-                    if (live) {
-                        const uint32_t at = (q_tail + below(bal)) & (kQueue - 1);
-                        quad_q[at] = quad << 4 | mask;
-                        logit_q[at] = make_float4(l[0], l[1], l[2], l[3]);
-                    }
-                    q_tail += n;
-                    if (q_tail - q_head >= 64u) draw_waiting(64u);   // fewer than 64 waited, fewer than 64 came
-                }
-            }
-        }
-        if (WRITE && own) {
-            Elem o[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const uint32_t x = DTYPE == TDFA_F32 ? e[j % kWords] : e[j / 2] >> (16 * (j & 1));
-                o[j] = (m >> j) & 1u ? (Elem)x : NEG_INF;
-            }
-            store_group<DTYPE>(orow, t, V, o);
-        }
-    };
-    bool pending_batch = false;                                // uniform: a batch has been taken and not worked on
-    auto fetch_groups = [&](uint32_t n) __attribute__((always_inline)) {
-        take_batch(n);
-        if (pending_batch) work_batch();
-        m = m_next;
-        t = t_next;
-        own = own_next;
-#pragma unroll
-        for (int j = 0; j < kWords; ++j) e[j] = e_next[j];
-        pending_batch = true;
     };
 
-    // Allowed bits, one 32-bit word (four groups) per load and lane, kWordsAhead loads in flight; g_lo
-    // is a multiple of four groups (the launcher sees to that).
-    const uint32_t* words = reinterpret_cast<const uint32_t*>(bits);
-    const int w_lo = g_lo >> 2, w_hi = (g_hi + 3) >> 2;
-    const int NT = (int)blockDim.x;
-    auto load_word = [&](int wi) { return (valid && wi < w_hi) ? words[wi] : 0u; };
-    static_assert(kWordsAhead == 4, "the rotation below is written for four words in flight");
-    int wi = w_lo + (int)threadIdx.x;
-    uint32_t w0 = load_word(wi), w1 = load_word(wi + NT), w2 = load_word(wi + 2 * NT), w3 = load_word(wi + 3 * NT);
-    for (int base = w_lo; base < w_hi; base += NT, wi += NT) {               // trip count uniform in the workgroup
-        const uint32_t w = w0;
-        w0 = w1;
-        w1 = w2;
-        w2 = w3;
-        w3 = load_word(wi + 4 * NT);
-        const int left = g_hi - (wi << 2);                                   // groups of this word inside the part
-        const uint32_t wm = left >= 4 ? w : (left > 0 ? w & ((1u << (8 * left)) - 1u) : 0u);
-        if (!WRITE && __builtin_amdgcn_ballot_w64(wm != 0) == 0) continue;
-        // The 64 words of the wavefront cover 256 consecutive groups.  They are handed over 64
-        // consecutive groups at a time (lane L takes byte L mod 4 of the word of lane 16 i + L / 4), so
-        // that neighbouring lanes fetch neighbouring logits.
+    if (WRITE || (n_allowed != kUnknown && n_allowed >= (uint32_t)V / kDrawDense)) {
+        constexpr int kLoads = DTYPE == TDFA_F32 ? 2 : 1;
+        const __amdgpu_buffer_rsrc_t r_x = __builtin_amdgcn_make_buffer_rsrc(const_cast<Elem*>(row), 0, n_full * 8 * kSize, kRawBuffer);
+        const __amdgpu_buffer_rsrc_t r_o = __builtin_amdgcn_make_buffer_rsrc(orow, 0, WRITE ? n_full * 8 * kSize : 0, kRawBuffer);
+        const __amdgpu_buffer_rsrc_t r_m = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(bits), 0, valid ? n_full : 0, kRawBuffer);
+        struct Chunk {                                         // 64 groups: two quads per lane, and their allowed bits
+            u32x4 x[kLoads];
+            uint32_t m[kLoads];
+        };
+        // bf16: a lane takes a group; fp32: quad `lane` of either half, so that a load covers a whole kilobyte
+        auto load = [&](int g, Chunk& c) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) {
+                c.x[i] = __builtin_amdgcn_raw_buffer_load_b128(r_x, lane * 16 + g * 8 * kSize + i * 1024, 0, kReadOnce);
+                c.m[i] = __builtin_amdgcn_raw_buffer_load_b8(r_m, (DTYPE == TDFA_F32 ? lane >> 1 : lane) + g + i * 32, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);                 // (the loads return in the order they are used in; an offset of its own per
+                                                               // lane: the range check wraps where the scalar offset lies past the end)
+        };
+        auto draw_chunk = [&](int g, const Chunk& c) __attribute__((always_inline)) {
+            float l[2][4];
+            uint32_t w[2][4], quad[2], ok[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if constexpr (DTYPE == TDFA_F32) {
+                    const u32x4 x = c.x[h];
+                    l[h][0] = __uint_as_float(x.x); l[h][1] = __uint_as_float(x.y); l[h][2] = __uint_as_float(x.z); l[h][3] = __uint_as_float(x.w);
+                    quad[h] = 2u * (uint32_t)g + 64u * (uint32_t)h + (uint32_t)lane;
+                    ok[h] = c.m[h] >> (4 * (lane & 1)) & 15u;
+                } else {
+                    const uint32_t x0 = h ? c.x[0].z : c.x[0].x, x1 = h ? c.x[0].w : c.x[0].y;
+                    l[h][0] = __uint_as_float(x0 << 16); l[h][1] = __uint_as_float(x0 & 0xFFFF0000u);
+                    l[h][2] = __uint_as_float(x1 << 16); l[h][3] = __uint_as_float(x1 & 0xFFFF0000u);
+                    quad[h] = 2u * (uint32_t)(g + lane) + (uint32_t)h;
+                    ok[h] = c.m[0] >> (4 * h) & 15u;
+                }
+            }
+            if constexpr (WRITE) {
+                uint32_t o[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const uint32_t x = DTYPE == TDFA_F32 ? __float_as_uint(l[i >> 2][i & 3]) : __float_as_uint(l[i >> 2][i & 3]) >> 16;
+                    o[i] = ok[i >> 2] >> (i & 3) & 1u ? x : NEG_INF;
+                }
+                if constexpr (DTYPE == TDFA_F32) {
+                    __builtin_amdgcn_raw_buffer_store_b128(u32x4{o[0], o[1], o[2], o[3]}, r_o, lane * 16 + g * 32, 0, kReadOnce);
+                    __builtin_amdgcn_raw_buffer_store_b128(u32x4{o[4], o[5], o[6], o[7]}, r_o, lane * 16 + g * 32 + 1024, 0, kReadOnce);
+                } else {
+                    __builtin_amdgcn_raw_buffer_store_b128(u32x4{o[0] | o[1] << 16, o[2] | o[3] << 16, o[4] | o[5] << 16, o[6] | o[7] << 16},
+                                                           r_o, lane * 16 + g * 16, 0, kReadOnce);
+                }
+                if (__builtin_amdgcn_ballot_w64((ok[0] | ok[1]) != 0) == 0) return;
+            }
+            generate(quad[0], w[0]);
+            generate(quad[1], w[1]);
+            look();
+            const float top0 = quad_bound(l[0], w[0]), top1 = quad_bound(l[1], w[1]);
+            if (__builtin_amdgcn_ballot_w64(!(top0 < reached) | !(top1 < reached)) == 0) return;
 #pragma unroll 1
-        for (int i = 0; i < 4; ++i) {
-            const int src = 16 * i + (int)(lane >> 2);
-            const uint32_t ws = (uint32_t)__shfl((int)wm, src, 64);
-            const int g = ((wi - (int)lane + src) << 2) + (int)(lane & 3u);
-            const uint32_t mg = (ws >> (8 * (lane & 3u))) & 0xFFu;
-            const bool has = WRITE ? g < g_hi : mg != 0;                     // the masked row needs every group
-            const unsigned long long bal = __builtin_amdgcn_ballot_w64(has);
-            if (bal == 0) continue;
-            if (has) group_q[(g_tail + below(bal)) & (kQueue - 1)] = make_uint2((uint32_t)g, mg);
-            g_tail += (uint32_t)__popcll(bal);
-            if (g_tail - g_head >= 64u) fetch_groups(64u);
+            for (int h = 0; h < 2; ++h) {
+                if (__builtin_amdgcn_ballot_w64(!((h ? top1 : top0) < reached)) == 0) continue;
+                float lh[4];
+                uint32_t wh[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    lh[j] = h ? l[1][j] : l[0][j];
+                    wh[j] = h ? w[1][j] : w[0][j];
+                }
+                settle(h ? quad[1] : quad[0], h ? ok[1] : ok[0], lh, wh);
+            }
+        };
+        constexpr int step = 64 * kWaves;
+        int g = 64 * wave;
+        constexpr int kDepth = 4 / kLoads;
+        Chunk c[kDepth];
+#pragma unroll
+        for (int d = 0; d < kDepth; ++d) load(g + d * step, c[d]);
+        const int g_2 = n_full >> 2, g_1 = n_full >> 1, g_0 = n_full - g_2;
+        __builtin_amdgcn_s_setprio(3);                         // (so that the wavefronts of a SIMD end together)
+        for (; g < n_full; g += kDepth * step) {               // (a chunk past the end is all zeros: nothing allowed)
+            if (g >= g_0) __builtin_amdgcn_s_setprio(0);
+            else if (g >= g_1) __builtin_amdgcn_s_setprio(1);
+            else if (g >= g_2) __builtin_amdgcn_s_setprio(2);
+#pragma unroll
+            for (int d = 0; d < kDepth; ++d) {
+                if (g + d * step < n_full) draw_chunk(g + d * step, c[d]);
+                load(g + (kDepth + d) * step, c[d]);
+            }
+        }
+        if (n_tok > 8 * n_full && wave == 0) {                 // the row's last, partial group
+            const uint32_t m = valid ? (uint32_t)bits[n_full] & ((1u << (n_tok - 8 * n_full)) - 1u) : 0u;
+            if (lane < 2) list[lane] = (uint32_t)(2 * n_full + lane) << 4 | (m >> (4 * lane) & 15u);
+            Elem x = (Elem)0;
+            const int t = 8 * n_full + lane;
+            if (WRITE && t < n_tok) x = row[t];
+            draw_list(2u);
+            if (WRITE && t < n_tok) orow[t] = m >> lane & 1u ? x : (Elem)NEG_INF;
+        }
+    } else {
+        // The quads with an allowed token, listed by wavefronts of their own: a lane reads the allowed bits of 128 tokens at
+        // a time, kDrawPieces such pieces in flight.
+        if (parts == 1) __builtin_amdgcn_s_setprio(3);
+        // (A part of 4,096 groups or less by words of 32 tokens, so that every lane has some.)
+        const bool by_word = n_part <= 64 * kDrawPieces * kWaves * 4;
+        const int unit = by_word ? 32 : 128, n_units = (n_tok + unit - 1) / unit, per_wave = (n_units + kWaves - 1) / kWaves;
+        const int hi = min(n_units, (wave + 1) * per_wave);
+        const __amdgpu_buffer_rsrc_t r_bits = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint8_t*>(bits), 0, (int)min(a.row_words * 4 - g_lo, (int64_t)n_part + 15 & ~15), kRawBuffer);
+        for (int i0 = wave * per_wave; i0 < hi; i0 += 64 * kDrawPieces) {
+            u32x4 v[kDrawPieces];
+            uint32_t live[kDrawPieces], all = 0;
+#pragma unroll
+            for (int k = 0; k < kDrawPieces; ++k) {
+                const int i = i0 + 64 * k + lane;
+                if (by_word) v[k] = u32x4{__builtin_amdgcn_raw_buffer_load_b32(r_bits, i < hi ? i * 4 : 0x7FFFFFF0, 0, 0), 0, 0, 0};
+                else v[k] = __builtin_amdgcn_raw_buffer_load_b128(r_bits, i < hi ? i * 16 : 0x7FFFFFF0, 0, 0);
+            }
+#pragma unroll
+            for (int k = 0; k < kDrawPieces; ++k) {
+                const int left = n_tok - (i0 + 64 * k + lane) * unit;
+                if (left < 128) {
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        const int rem = left - 32 * d;
+                        if (rem < 32) v[k][d] = rem <= 0 ? 0u : v[k][d] & ((1u << rem) - 1u);
+                    }
+                }
+                live[k] = 0;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    uint32_t x = v[k][d] | v[k][d] >> 1;
+                    x = (x | x >> 2) & 0x11111111u;
+                    live[k] += (uint32_t)__builtin_popcount(x);
+                }
+                all += live[k];
+            }
+            const uint32_t total = wave_sum_u32(all);
+            if (total == 0) continue;
+            // all pieces at once, or one after the other where the list would not hold them
+            const int rounds = total <= (uint32_t)kDrawList ? 1 : kDrawPieces;
+            for (int r = 0; r < rounds; ++r) {
+                uint32_t mine = 0;
+#pragma unroll
+                for (int k = 0; k < kDrawPieces; ++k) mine += rounds == 1 || k == r ? live[k] : 0u;
+                const uint32_t incl = wave_prefix_u32(mine);
+                const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+                uint32_t at = incl - mine;
+#pragma unroll
+                for (int k = 0; k < kDrawPieces; ++k) {
+                    if ((rounds != 1 && k != r) || __builtin_amdgcn_ballot_w64(live[k] != 0) == 0) continue;
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        if (d != 0 && by_word) continue;
+                        uint32_t rest = v[k][d];
+                        while (rest) {
+                            const int s = __builtin_ctz(rest) & 28;
+                            const uint32_t nib = rest >> s & 15u;
+                            list[at++] = (uint32_t)((i0 + 64 * k + lane) * (unit >> 2) + 8 * d + (s >> 2)) << 4 | nib;
+                            rest &= ~(15u << s);
+                        }
+                    }
+                }
+                draw_list(n);
+            }
         }
     }
-    if (g_tail != g_head) fetch_groups(g_tail - g_head);
-    if (pending_batch) work_batch();
-    if (q_tail != q_head) draw_waiting(q_tail - q_head);
+    compete();
     unsigned long long cand = best_key ? ((unsigned long long)best_key << 32) | (0xFFFFFFFFu - best_idx) : 0ull;
     cand = block_max_u64(cand, wave_best);
     if (threadIdx.x != 0) return;
-    if (combine_parts(a, b, parts, cand)) write_result(a, b, q, valid, cand);
+    if (combine_parts(a, b, parts, cand)) { write_result(a, b, q, valid, cand); }
 }
 
 // Runs of speculated tokens (Section 5.3): one lane per sequence follows its k tokens through the
@@ -2294,28 +2493,32 @@ int launch_sample_step(const MaskArgs& a, float inv_t, int32_t top_k, uint64_t s
         TDFA_HIP(hipGetLastError());
         return TDFA_OK;
     }
-    // workgroups of 256 threads, kDrawGroups or more of them (rows in parts of at least 1,024 groups).  With half as many, rows
-    // that all allow little gain (128 rows 11.9 -> 7.9 us, all that allow most 24.7 -> 21.4), but rows anywhere in their texts lose:
-    // 72, 80, 96, 112, 120 and 128 rows 14.7, 15.2, 15.4, 17.1, 18.1 and 19.5 -> 15.9, 16.0, 17.1, 19.8, 18.9 and 19.4 us.
+    // Workgroups of 256 threads, about as many as the chip holds (rows in parts of at least 1,024 groups).
     const int n_groups = (a.n_tokens + 7) >> 3;
-    int parts = (kDrawGroups + a.batch - 1) / a.batch;
-    const int max_parts = (n_groups + 1023) / 1024;
-    if (parts > max_parts) parts = max_parts;
-    if (parts < 1) parts = 1;
-    int gpp = ((n_groups + parts - 1) / parts + 3) / 4 * 4;
-    if (gpp < 4) gpp = 4;
-    if (n_groups > kDrawPartGroups) {                          // parts of a power of two, so that none crosses a line
-        int power = 4;
-        while (power < gpp && power < kDrawPartGroups) power *= 2;
-        gpp = power;
-        parts = (n_groups + gpp - 1) / gpp;
+    const int64_t batch = a.batch;
+    int64_t parts = std::min<int64_t>(kDrawGroups / batch, (n_groups + 1023) / 1024);
+    parts = std::max<int64_t>({parts, ((int64_t)n_groups + kDrawPartGroups - 1) / kDrawPartGroups, 1});
+    const int gpp = (int)(((n_groups + parts - 1) / parts + 63) & ~63);
+    int64_t grid = batch * parts;
+    // Where the states' memory is not written by this very step, which a workgroup that starts late would read for its plan, rows
+    // are taken by what their states allow: shared out by their cost if there is enough of them (one million groups: 64 rows of
+    // 128,256 tokens, 128 of 64,000; below, the plan costs more than it gives), else only the lone ones told apart.
+    int shares = 0;
+    auto apart_from_states = [&](const int32_t* out) { return out + batch <= a.states || a.states + batch <= out; };
+    const bool apart = apart_from_states(a.new_states) && apart_from_states(a.tokens);
+    if (!a.masked_out && (a.row_allowed || a.row_begin) && apart && n_groups <= kDrawPartGroups) {
+        shares = -1;
+        if (batch <= kShareRows && batch * n_groups >= 1000000 && n_groups >= 2 * kShareGroups) {
+            shares = n_groups / kShareGroups;
+            grid = std::min<int64_t>(batch * shares, kShareFull + batch);
+        }
     }
-    if ((int64_t)a.batch * parts > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
-    const dim3 grid((unsigned)(a.batch * parts));
-    if (a.dtype == TDFA_F32 && a.masked_out) draw_step_kernel<TDFA_F32, true><<<grid, kDrawThreads, 0, stream>>>(a, sp, parts, gpp);
-    else if (a.dtype == TDFA_F32) draw_step_kernel<TDFA_F32, false><<<grid, kDrawThreads, 0, stream>>>(a, sp, parts, gpp);
-    else if (a.masked_out) draw_step_kernel<TDFA_BF16, true><<<grid, kDrawThreads, 0, stream>>>(a, sp, parts, gpp);
-    else draw_step_kernel<TDFA_BF16, false><<<grid, kDrawThreads, 0, stream>>>(a, sp, parts, gpp);
+    if (grid > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
+    const dim3 blocks((unsigned)grid);
+    if (a.dtype == TDFA_F32 && a.masked_out) draw_step_kernel<TDFA_F32, true><<<blocks, kDrawThreads, 0, stream>>>(a, sp, (int)parts, gpp, shares);
+    else if (a.dtype == TDFA_F32) draw_step_kernel<TDFA_F32, false><<<blocks, kDrawThreads, 0, stream>>>(a, sp, (int)parts, gpp, shares);
+    else if (a.masked_out) draw_step_kernel<TDFA_BF16, true><<<blocks, kDrawThreads, 0, stream>>>(a, sp, (int)parts, gpp, shares);
+    else draw_step_kernel<TDFA_BF16, false><<<blocks, kDrawThreads, 0, stream>>>(a, sp, (int)parts, gpp, shares);
     TDFA_HIP(hipGetLastError());
     return TDFA_OK;
 }

@@ -316,6 +316,34 @@ def test_draw_beyond_2_30_tokens(T):
 
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("n_tokens,batch", [(9001, 4), (16389, 512), (40003, 257), (128261, 64), (16384, 1024), (8200, 1025)])
+def test_rows_shared_out_by_cost(T, oracle, dtype, n_tokens, batch):
+    """States of every cost, as counted by a packed table: none, one token, either side of the lines between lone, small
+    and large rows and of the line from which every quad is drawn, all tokens.  Large batches are shared out by cost (4
+    rows of 9,001 tokens are not), unless the states are written in place: both against the oracle."""
+    rng = np.random.default_rng(n_tokens)
+    V = n_tokens
+    counts = [0, 1, 2, V // 256 - 1, V // 256 + 1, V // 250, V // 249 + 1, V // 40, V // 10 - 1, V // 10 + 1, V // 2, V]
+    tab = np.full((len(counts), V), DEAD, dtype=np.int32)
+    for q, n in enumerate(counts):
+        where = rng.permutation(V)[:n] if q % 3 else np.arange(V - n, V)           # (clustered at the row's end as well)
+        tab[q, where] = rng.integers(0, len(counts), size=n)
+    table = T.table_pack(_upload_table(T, tab))
+    states = rng.integers(-1, len(counts) + 1, size=batch).astype(np.int32)
+    stride = (V + 7) // 8 * 8
+    x = np.zeros((batch, stride), dtype=np.float32)
+    x[:, :V] = rng.normal(0, 2, size=(batch, V))
+    x[::5, rng.integers(0, V, size=7)] = np.array([np.nan, np.inf, -np.inf, 1e30, -1e30, 0.0, -0.0], dtype=np.float32)
+    lg = x if dtype == F32 else LG.f32_to_bf16_bits(x)
+    got = _sample_strided(T, oracle, table, tab, lg, dtype, states, 0.8, 99, 7, masked=False)
+    st = torch.from_numpy(states).cuda()
+    tok = torch.full((batch,), -9, dtype=torch.int32, device="cuda")
+    T.sample_step(table, _to_dev(lg, dtype), st, 0.8, 99, 7, tok, st)
+    torch.cuda.synchronize()
+    assert np.array_equal(tok.cpu().numpy(), got[0]) and np.array_equal(st.cpu().numpy(), got[1])
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
 def test_special_values(T, oracle, dtype):
     n_tokens = 4096 + 64
     tab = _rand_table(5, n_tokens, 0.3, 1)

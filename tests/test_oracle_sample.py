@@ -219,6 +219,11 @@ def test_noise_bound_from_the_bits_of_the_tail(oracle):
         ub = (b.astype(np.float64) * float(c0) + float(c1)).astype(np.float32)          # one rounding: the fused operation
         g = oracle.gumbel_of_words(x)
         assert (ub.astype(np.float64) >= g.astype(np.float64) + 5e-4).all()             # half the slack is still unused
+        # from u = 0.9 on the noise is less than 0.168 below the bound: a score is not below its bound less 0.2, with
+        # roundings of up to 2^-9 each in the score, the bound and the difference
+        tight = x >= np.uint32(0xE6666800)
+        assert ((x[tight] >> np.uint32(9)).min() + 0.5) * 2.0 ** -23 >= 0.9
+        assert (ub[tight].astype(np.float64) - g[tight].astype(np.float64)).max() < 0.2 - 3 * 2.0 ** -9
         tail = -np.log(v.astype(np.float64) * 2.0 ** -32)
         assert (ub.astype(np.float64) - tail).max() < 0.0861 * np.log(2.0) + 1.1e-3
 
