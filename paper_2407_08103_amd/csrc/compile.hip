@@ -144,11 +144,17 @@ start_bytes_kernel(BatchDesc batch, const uint32_t* __restrict__ vprefix, const 
 //            scalar registers + the lane's entry) under the mask of live lanes; a group with no
 //            live lane issues nothing.  The KT * S/64 chains of a wavefront are independent and
 //            their loads are in flight together; the walk stops as soon as no lane of a token
-//            with bytes left is alive.  Only live results go to the tile.  Tiles without a jump
-//            group and tiles with one run different loops (see there).
+//            with bytes left is alive.  Tiles without a jump group and tiles with one run different
+//            loops (see there).
 //   phase 2  rows are flushed: a lane converts four consecutive entries and writes 16 bytes, the
 //            allowed bits of eight lanes are merged into one word (rows that cannot be written
 //            16 bytes at a time: one entry per lane and a wave ballot)
+//
+// Bound by the instructions of the walk (a compute unit has one scalar unit: with 26 scalar and 20 vector instructions per 64
+// entries it was busy in 70 % of the cycles, the vector units in 53 %) and by the stores behind it.  So what a step wants to
+// know of its token is gathered once per wavefront, a token per lane, instead of three dependent reads of LDS per token, and
+// phase 0 waits for memory once, not after each of its five kinds of load.  5,387 states x 128,256 tokens (50 signatures), the whole
+// compile: 710 -> 594 us; 200 to 300 states x 2,000 tokens 40 -> 37 us.
 constexpr int kTileThreads = 1024;             // largest workgroup of the tile kernel
 constexpr int kLdsWords = 8;    // words of each token kept in LDS (32 bytes)
 constexpr int kXcds = 8;        // accelerator dies of the MI355X
@@ -245,30 +251,53 @@ compile_tile_kernel(BatchDesc batch,
         for (int i = threadIdx.x; i < n16; i += kTileThreads) dst[i] = src[i];
     }
     {
-        uint32_t* w = reinterpret_cast<uint32_t*>(smem);
-        constexpr int n_words = (int)(Shape::tile_bytes / 4);
-        const uint32_t fill = sizeof(ST) == 2 ? (SINK | (SINK << 16)) : SINK;
-        for (int i = threadIdx.x; i < n_words; i += kTileThreads) w[i] = fill;
-        for (int r = threadIdx.x; r < S; r += kTileThreads) s_state[r] = q0 + r < n_order ? order[q0 + r] : -1;
-        if (threadIdx.x < G) s_gc[threadIdx.x] = q0 + (int)threadIdx.x * 64 < n_order ? (int)group_class[q0 / 64 + threadIdx.x] : -1;
+        // Every load is requested before the first one is waited for: one trip to memory, under which the tile is filled.
+        static_assert(S <= kTileThreads && T * G <= kTileThreads && T <= kTileThreads && T * kLdsWords % kTileThreads == 0, "one round of loads");
+        static_assert(kLdsWords == 8, "the vocabulary's prefix array holds 8 words per token");
+        constexpr int kPrefix = T * kLdsWords / kTileThreads;      // words of the tokens' first bytes per thread
+        constexpr int kFirst = kTileThreads - T * G;               // threads from here on fetch start bytes
+        const int tid = (int)threadIdx.x;
+        uint32_t prefix[kPrefix];
+#pragma unroll
+        for (int k = 0; k < kPrefix; ++k) {
+            const int i = k * kTileThreads + tid;
+            prefix[k] = 0u;
+            if (t0 + i / kLdsWords < n_tokens) prefix[k] = vprefix[(size_t)t0 * kLdsWords + i];
+        }
         // what each (token, group) pair starts with (see start_bytes_kernel); without the workspace
         // every group looks up every non-empty token's first byte
-        for (int i = threadIdx.x; i < T * G; i += kTileThreads) {
-            const int g = i / T, tl = i % T, t = t0 + tl;
-            unsigned char sb = 0xFF;
-            if (t < n_tokens && q0 + g * 64 < n_order)
-                sb = start_bytes ? start_bytes[(size_t)(q0 / 64 + g) * n_tokens + t] : (vlen[t] ? 0 : 0xFF);
-            reinterpret_cast<unsigned char*>(s_clean)[tl * (Shape::CW * 4) + g] = sb;
+        const int sb_g = (tid - kFirst) / T, sb_t = (tid - kFirst) % T;
+        uint32_t sb = 0xFFu;
+        if (tid >= kFirst && t0 + sb_t < n_tokens && q0 + sb_g * 64 < n_order) {
+            if (start_bytes) sb = start_bytes[(size_t)(q0 / 64 + sb_g) * n_tokens + (t0 + sb_t)];
+            else sb = vlen[t0 + sb_t] ? 0u : 0xFFu;
         }
-        for (int tl = threadIdx.x; tl < T; tl += kTileThreads) {
-            const int t = t0 + tl;
-            s_sorted[tl] = t < n_tokens ? (uint32_t)vsorted[t] : (uint32_t)(tl & (kSortBlock - 1));
-            s_len[tl] = t < n_tokens ? vlen[t] : 0u;
-            s_off[tl] = t < n_tokens ? voff[t] : 0u;
+        int32_t state = -1, cls = -1;
+        if (tid < S && q0 + tid < n_order) state = order[q0 + tid];
+        if (tid < G && q0 + tid * 64 < n_order) cls = (int32_t)group_class[q0 / 64 + tid];
+        uint32_t sorted = (uint32_t)(tid & (kSortBlock - 1)), len = 0u, off = 0u;
+        if (tid < T && t0 + tid < n_tokens) {
+            sorted = (uint32_t)vsorted[t0 + tid];
+            len = vlen[t0 + tid];
+            off = voff[t0 + tid];
         }
-        static_assert(kLdsWords == 8, "the vocabulary's prefix array holds 8 words per token");
-        for (int i = threadIdx.x; i < T * kLdsWords; i += kTileThreads)
-            s_bytes[i] = t0 + i / kLdsWords < n_tokens ? vprefix[(size_t)t0 * kLdsWords + i] : 0u;
+        const uint32_t fill = sizeof(ST) == 2 ? (SINK | (SINK << 16)) : SINK;
+        static_assert(Shape::tile_bytes % 16 == 0, "filled 16 bytes at a time");
+        constexpr int n_words = (int)(Shape::tile_bytes / 16);
+        const uint4 fill4 = make_uint4(fill, fill, fill, fill);
+#pragma unroll
+        for (int i0 = 0; i0 < n_words; i0 += kTileThreads)
+            if (i0 + kTileThreads <= n_words || i0 + tid < n_words) reinterpret_cast<uint4*>(smem)[i0 + tid] = fill4;
+#pragma unroll
+        for (int k = 0; k < kPrefix; ++k) s_bytes[k * kTileThreads + tid] = prefix[k];
+        if (tid >= kFirst) reinterpret_cast<unsigned char*>(s_clean)[sb_t * (Shape::CW * 4) + sb_g] = (unsigned char)sb;
+        if (tid < S) s_state[tid] = state;
+        if (tid < G) s_gc[tid] = cls;
+        if (tid < T) {
+            s_sorted[tid] = sorted;
+            s_len[tid] = len;
+            s_off[tid] = off;
+        }
     }
     __syncthreads();
     int gc[G];
@@ -297,7 +326,136 @@ compile_tile_kernel(BatchDesc batch,
         return i < (uint32_t)kNear ? (uint32_t)__builtin_amdgcn_readlane(byte_lane, i)
                                    : (__builtin_amdgcn_readfirstlane(vwords[off + (i >> 2)]) >> ((i & 3u) * 8)) & 0xFFu;
     };
-    if (!any_jump) {
+    if constexpr (KT == 1) {
+        // One token at a time.  Lane j holds what the walk wants to know of the wavefront's j-th token in sorted order, so that
+        // a step reads it with a few v_readlane and tokens that no state of the tile survives the first byte of cost nothing.
+        static_assert(G == 4 && Shape::CW == 1 && kRun <= 64, "a token's start bytes are one word, a run's tokens one per lane");
+        const uint32_t stride = (uint32_t)q_stride * (uint32_t)sizeof(ST);                   // bytes of a column
+        const int k = wave * kRun + min(lane, kRun - 1);
+        const int my_tl = (k & ~(kSortBlock - 1)) + (int)s_sorted[k];
+        const uint32_t my_len = s_len[my_tl], my_off = s_off[my_tl], my_clean = s_clean[my_tl];
+        const uint32_t my_b1 = s_bytes[my_tl * kLdsWords] & 0xFFu;
+        unsigned long long todo = __builtin_amdgcn_ballot_w64(lane < kRun && my_clean != 0xFFFFFFFFu);
+        auto of = [](uint32_t x, int j) { return (uint32_t)__builtin_amdgcn_readlane((int)x, j); };
+        // entry at byte `at` of a column (or of a row of jumps) that begins `off` bytes behind `base`
+        auto look = [](const ST* base, uint32_t off, uint32_t at) -> uint32_t {
+            const char* col = reinterpret_cast<const char*>(base) + off;
+            return *reinterpret_cast<const ST*>(col + at);
+        };
+        auto bytes_of = [&](uint32_t tl) -> uint32_t {             // lane i: byte i of the token
+            return (s_bytes[tl * kLdsWords + ((lane & (kNear - 1)) >> 2)] >> ((lane & 3) * 8)) & 0xFFu;
+        };
+        // (a lane that no state is alive in holds the sink, which the tile is filled with)
+        auto put = [&](uint32_t tl, const uint32_t (&v)[G]) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) tile[(g * 64 + lane) * RS + (int)tl] = (ST)v[g];
+        };
+        if (!any_jump) {
+            // Plain tiles.  When a token starts with the same byte as the one before it, the states after that byte are reused.
+            uint32_t prev_b1 = 0xFFFFFFFFu;
+            uint32_t first[G] = {SINK, SINK, SINK, SINK};
+#pragma unroll 1
+            while (todo) {
+                const int j = __builtin_ctzll(todo);
+                todo &= todo - 1;
+                const uint32_t tl = of((uint32_t)my_tl, j), len = of(my_len, j), off = of(my_off, j), b1 = of(my_b1, j);
+                const uint32_t byte_lane = bytes_of(tl);
+                if (b1 != prev_b1) {
+                    const uint32_t clean = of(my_clean, j);
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        first[g] = SINK;
+                        // (nothing to look up for a group that no state of survives this byte)
+                        if (((clean >> (g * 8)) & 0xFFu) != 0xFFu) first[g] = look(tt, b1 * stride, start[g]);
+                    }
+                    prev_b1 = b1;
+                }
+                uint32_t v[G];
+#pragma unroll
+                for (int g = 0; g < G; ++g) v[g] = first[g];
+#pragma unroll 1
+                for (uint32_t i = 1; i < len; ++i) {
+                    uint32_t lowest = SINK;
+#pragma unroll
+                    for (int g = 0; g < G; ++g) lowest = min(lowest, v[g]);
+                    if (__builtin_amdgcn_ballot_w64(lowest < SINK) == 0) break;
+                    const uint32_t col = token_byte(byte_lane, off, i) * stride;
+#pragma unroll
+                    for (int g = 0; g < G; ++g)
+                        if (v[g] != SINK) v[g] = look(tt, col, v[g]);
+                }
+                put(tl, v);
+            }
+        } else if (todo) {
+            // Tiles with groups of a jump class.  Such a group takes the token's clean prefix (m bytes) in one lookup in the
+            // jump table and joins the byte-by-byte walk at byte m; the other groups, and a jump group whose token starts
+            // with a byte that is not clean, start with an ordinary lookup of the first byte.  Lane j has worked out where each
+            // group of its token looks first, how many bytes that takes, and the first byte that a group walks.
+            uint32_t my_at[G], my_taken = my_clean, my_step = 0xFFFFFFFFu;
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const uint32_t m = (my_clean >> (g * 8)) & 0xFFu, p = max(m, 1u);
+                my_at[g] = (m - 1u < 0xFEu ? m - 1u : my_b1) * stride;
+                my_taken += m == 0u ? 1u << (g * 8) : 0u;
+                if (p < my_len) my_step = min(my_step, p);
+            }
+            // first the tokens that all four groups take in one jump, two at a time (the same one twice at the end)
+            unsigned long long whole =
+                todo & __builtin_amdgcn_ballot_w64(my_len <= (uint32_t)kJumpDepth && my_clean == my_len * 0x01010101u);
+            todo &= ~whole;
+#pragma unroll 1
+            while (whole) {
+                const int j0 = __builtin_ctzll(whole);
+                whole &= whole - 1;
+                const int j1 = whole ? __builtin_ctzll(whole) : j0;
+                whole &= whole - 1;
+                const uint32_t at0 = of(my_at[0], j0), at1 = of(my_at[0], j1);
+                uint32_t x0[G], x1[G];
+#pragma unroll
+                for (int g = 0; g < G; ++g) x0[g] = look(jt, at0, start[g]);
+#pragma unroll
+                for (int g = 0; g < G; ++g) x1[g] = look(jt, at1, start[g]);
+                put(of((uint32_t)my_tl, j0), x0);
+                put(of((uint32_t)my_tl, j1), x1);
+            }
+#pragma unroll 1
+            while (todo) {
+                const int j = __builtin_ctzll(todo);
+                todo &= todo - 1;
+                const uint32_t tl = of((uint32_t)my_tl, j), len = of(my_len, j), off = of(my_off, j);
+                const uint32_t clean = of(my_clean, j), taken = of(my_taken, j);
+                const uint32_t byte_lane = bytes_of(tl);
+                uint32_t v[G];
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const uint32_t m = (clean >> (g * 8)) & 0xFFu;
+                    v[g] = SINK;
+                    if (m != 0xFFu) v[g] = look(m != 0u ? jt : tt, of(my_at[g], j), start[g]);
+                }
+#pragma unroll 1
+                for (uint32_t i = of(my_step, j); i < len; ++i) {
+                    const uint32_t col = token_byte(byte_lane, off, i) * stride;
+                    uint32_t lowest = SINK;              // below SINK iff a lane with bytes left is alive
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const uint32_t p = (taken >> (g * 8)) & 0xFFu;
+                        // (0: the group is still ahead of byte i)
+                        const uint32_t walking_below = i >= p ? SINK : 0u;
+                        if (v[g] < walking_below) v[g] = look(tt, col, v[g]);
+                    }
+                    if (i + 1 == len) break;
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const uint32_t p = (taken >> (g * 8)) & 0xFFu;
+                        const uint32_t done_floor = p < len ? 0u : SINK;   // a group that took the whole token is not waiting for bytes
+                        lowest = min(lowest, max(v[g], done_floor));
+                    }
+                    if (__builtin_amdgcn_ballot_w64(lowest < SINK) == 0) break;
+                }
+                put(tl, v);
+            }
+        }
+    } else if (!any_jump) {
         // Plain tiles.  When the next token of a run starts with the same byte as the one before
         // it, the states after that byte are reused.
         uint32_t prev_b1[KT];
@@ -305,12 +463,6 @@ compile_tile_kernel(BatchDesc batch,
 #pragma unroll
         for (int u = 0; u < KT; ++u) prev_b1[u] = 0xFFFFFFFFu;
         for (int step = 0; step < kRun; ++step) {
-            if constexpr (KT == 1 && G == 4) {
-                // no state of the tile survives this token's first byte: nothing to do
-                const int k = wave * kRun + step;
-                const int tl = (k & ~(kSortBlock - 1)) + (int)__builtin_amdgcn_readfirstlane(s_sorted[k]);
-                if (__builtin_amdgcn_readfirstlane(s_clean[tl]) == 0xFFFFFFFFu) continue;
-            }
             uint32_t len[KT], off[KT], byte_lane[KT];
             int tls[KT];
             uint32_t v[KT][G];
@@ -379,28 +531,6 @@ compile_tile_kernel(BatchDesc batch,
         // folded into scalar operands (a base pointer, a threshold), so the G lookups of a step
         // are issued back to back like in a plain tile.
         for (int step = 0; step < kRun; ++step) {
-            if constexpr (KT == 1 && G == 4) {
-                // The two common cases, each decided by one comparison of the four start bytes:
-                // no group has anything to do, or all four take the whole token in one jump.
-                const int k = wave * kRun + step;
-                const int tl = (k & ~(kSortBlock - 1)) + (int)__builtin_amdgcn_readfirstlane(s_sorted[k]);
-                const uint32_t n = __builtin_amdgcn_readfirstlane(s_len[tl]);
-                const uint32_t w = __builtin_amdgcn_readfirstlane(s_clean[tl]);
-                if (w == 0xFFFFFFFFu) continue;
-                if (n <= (uint32_t)kJumpDepth && w == n * 0x01010101u) {
-                    const ST* base = jt + (n - 1) * (uint32_t)q_stride;
-                    uint32_t x[G];
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        x[g] = SINK;
-                        if (start[g] != SINK) x[g] = gather(base, start[g]);
-                    }
-#pragma unroll
-                    for (int g = 0; g < G; ++g)
-                        if (x[g] != SINK) tile[(g * 64 + lane) * RS + tl] = (ST)x[g];
-                    continue;
-                }
-            }
             uint32_t len[KT], off[KT], byte_lane[KT];
             int tls[KT];
             uint32_t v[KT][G];

@@ -334,6 +334,26 @@ def test_counter_classes(T, oracle, pattern, alphabet, n_random):
     _full_check(T, oracle, dfa, vocab, compose_rows=(0, min(dfa.n_states, 40)))
 
 
+@pytest.mark.parametrize("last", [1, 7, 8, 9, 63, 64])
+def test_runs_of_whole_jumps(T, oracle, last):
+    """Blocks of 64 ids with every number of tokens that one jump takes whole (they are walked in pairs, eight sorted tokens to
+    a wavefront), among tokens that start with an ordinary lookup, that leave the class, that are longer than a jump, that
+    no state survives and that are empty; the last block holds `last` tokens."""
+    dfa = compile_regex(r'"[^"\\]{0,90}"(,[0-9]{1,30})*')
+    rng = np.random.default_rng(last)
+    fresh = iter(range(10 ** 6))
+    other = [lambda: b'"' + b"q%d" % next(fresh), lambda: b"z%d" % next(fresh) + b'"', lambda: b"\\%d" % next(fresh),
+             lambda: b"k" * 33 + b"%d" % next(fresh), lambda: b"m" * 31 + b"%d" % next(fresh) + b'",7', lambda: b"", lambda: b",%d" % next(fresh)]
+    toks = []
+    for whole in [*range(18), 32, 63, 64]:
+        n = 64 if len(toks) < 20 * 64 else last
+        block = [b"a%d" % next(fresh) for _ in range(min(whole, n))]
+        block += [other[int(rng.integers(len(other)))]() for _ in range(n - len(block))]
+        rng.shuffle(block)
+        toks += block
+    _full_check(T, oracle, dfa, V.from_tokens(toks), compose_rows=(0, 30))
+
+
 def test_counter_classes_stacked_with_plain(T, oracle):
     """One launch that holds automata with and without jump classes, and a repeated handle."""
     rng = np.random.default_rng(77)
