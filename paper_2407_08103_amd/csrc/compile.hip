@@ -19,6 +19,7 @@
 //   3. compile_tile_kernel: a workgroup owns S states x T consecutive token ids; the tile lives in
 //      LDS.  Its phases are described at the kernel.
 #include <algorithm>
+#include <type_traits>
 
 #include "tdfa_internal.h"
 
@@ -147,8 +148,7 @@ start_bytes_kernel(BatchDesc batch, const uint32_t* __restrict__ vprefix, const 
 //            with bytes left is alive.  Tiles without a jump group and tiles with one run different
 //            loops (see there).
 //   phase 2  rows are flushed: a lane converts four consecutive entries and writes 16 bytes, the
-//            allowed bits of eight lanes are merged into one word (rows that cannot be written
-//            16 bytes at a time: one entry per lane and a wave ballot)
+//            allowed bits of eight lanes are merged into one word
 //
 // Bound by the instructions of the walk (a compute unit has one scalar unit: with 26 scalar and 20 vector instructions per 64
 // entries it was busy in 70 % of the cycles, the vector units in 53 %) and by the stores behind it.  So what a step wants to
@@ -178,13 +178,20 @@ __device__ __forceinline__ uint32_t gather(const ST* col, uint32_t byte_off)
 
 // STAGED: the automaton's whole transposed table ([256][q_stride], at most kStagedTableBytes) is
 // copied into LDS behind the tile before the walk, and every lookup of the walk is an LDS read.
-template <typename ST, int S, int T, int KT, bool HAS_JUMP, int kTileWaves, bool STAGED = false>
+//
+// SHIFT: the tiles of a table whose rows do not all begin at a multiple of 64 bytes.  Memory takes 64 bytes at once, and a part of
+// them only by reading the rest: 5,387 rows of 128,256, 128,248 and 128,254 tokens took 600, 1,145 and 1,112 us.  So tiles overlap by
+// kAlign tokens, and a row's piece goes from its own first such boundary in the tile to the one in the next tile: the same three
+// 600, 760 and 767 us (64 schemas of 128,255 tokens 4,050 -> 2,280; 8 of 64,001 250 -> 186).
+constexpr int kAlign = 16;      // tokens in 64 bytes
+
+template <typename ST, int S, int T, int KT, bool HAS_JUMP, int kTileWaves, bool STAGED, bool SHIFT>
 __global__ void __launch_bounds__(kTileWaves * 64)
 compile_tile_kernel(BatchDesc batch,
                     const uint32_t* __restrict__ vwords, const uint32_t* __restrict__ voff,
                     const uint32_t* __restrict__ vlen, const uint8_t* __restrict__ vsorted,
                     const uint32_t* __restrict__ vprefix, int n_tokens,
-                    int n_tiles_t, int share_columns, int wide_rows, int32_t* __restrict__ delta, uint32_t* __restrict__ allow,
+                    int n_tiles_t, int share_columns, int32_t* __restrict__ delta, uint32_t* __restrict__ allow,
                     int64_t row_words)
 {
     static_assert(S % 64 == 0 && T % kSortBlock == 0 && T % (kTileWaves * KT) == 0, "tile shape");
@@ -239,7 +246,8 @@ compile_tile_kernel(BatchDesc batch,
     const uint8_t* __restrict__ start_bytes = dd.start_bytes;
     const ST* __restrict__ jt = reinterpret_cast<const ST*>(dd.plan + plan_jump_offset(n_order));
     const int64_t out_row = dd.out_row;
-    const int t0 = tile_t * T, q0 = (tile_q - dd.tile_q_begin) * S;
+    constexpr int U = SHIFT ? T - kAlign : T;        // tokens from one tile to the next
+    const int t0 = tile_t * U, q0 = (tile_q - dd.tile_q_begin) * S;
     const uint32_t SINK = (uint32_t)(q_stride - 1) * (uint32_t)sizeof(ST);   // the largest entry there is
 
     // ---- phase 0
@@ -277,7 +285,7 @@ compile_tile_kernel(BatchDesc batch,
         if (tid < G && q0 + tid * 64 < n_order) cls = (int32_t)group_class[q0 / 64 + tid];
         uint32_t sorted = (uint32_t)(tid & (kSortBlock - 1)), len = 0u, off = 0u;
         if (tid < T && t0 + tid < n_tokens) {
-            sorted = (uint32_t)vsorted[t0 + tid];
+            if (!SHIFT) sorted = (uint32_t)vsorted[t0 + tid];          // (the blocks of the order are not the tile's)
             len = vlen[t0 + tid];
             off = voff[t0 + tid];
         }
@@ -329,13 +337,14 @@ compile_tile_kernel(BatchDesc batch,
     if constexpr (KT == 1) {
         // One token at a time.  Lane j holds what the walk wants to know of the wavefront's j-th token in sorted order, so that
         // a step reads it with a few v_readlane and tokens that no state of the tile survives the first byte of cost nothing.
-        static_assert(G == 4 && Shape::CW == 1 && kRun <= 64, "a token's start bytes are one word, a run's tokens one per lane");
+        static_assert((G == 2 || G == 4) && Shape::CW == 1 && kRun <= 64, "a token's start bytes are one word, a run's tokens one per lane");
+        constexpr uint32_t kDeadAll = G == 4 ? 0xFFFFFFFFu : 0xFFFFu, kOnes = 0x01010101u & kDeadAll;
         const uint32_t stride = (uint32_t)q_stride * (uint32_t)sizeof(ST);                   // bytes of a column
         const int k = wave * kRun + min(lane, kRun - 1);
         const int my_tl = (k & ~(kSortBlock - 1)) + (int)s_sorted[k];
-        const uint32_t my_len = s_len[my_tl], my_off = s_off[my_tl], my_clean = s_clean[my_tl];
+        const uint32_t my_len = s_len[my_tl], my_off = s_off[my_tl], my_clean = s_clean[my_tl] & kDeadAll;
         const uint32_t my_b1 = s_bytes[my_tl * kLdsWords] & 0xFFu;
-        unsigned long long todo = __builtin_amdgcn_ballot_w64(lane < kRun && my_clean != 0xFFFFFFFFu);
+        unsigned long long todo = __builtin_amdgcn_ballot_w64(lane < kRun && my_clean != kDeadAll);
         auto of = [](uint32_t x, int j) { return (uint32_t)__builtin_amdgcn_readlane((int)x, j); };
         // entry at byte `at` of a column (or of a row of jumps) that begins `off` bytes behind `base`
         auto look = [](const ST* base, uint32_t off, uint32_t at) -> uint32_t {
@@ -353,7 +362,9 @@ compile_tile_kernel(BatchDesc batch,
         if (!any_jump) {
             // Plain tiles.  When a token starts with the same byte as the one before it, the states after that byte are reused.
             uint32_t prev_b1 = 0xFFFFFFFFu;
-            uint32_t first[G] = {SINK, SINK, SINK, SINK};
+            uint32_t first[G];
+#pragma unroll
+            for (int g = 0; g < G; ++g) first[g] = SINK;
 #pragma unroll 1
             while (todo) {
                 const int j = __builtin_ctzll(todo);
@@ -399,9 +410,9 @@ compile_tile_kernel(BatchDesc batch,
                 my_taken += m == 0u ? 1u << (g * 8) : 0u;
                 if (p < my_len) my_step = min(my_step, p);
             }
-            // first the tokens that all four groups take in one jump, two at a time (the same one twice at the end)
+            // first the tokens that all groups take in one jump, two at a time (the same one twice at the end)
             unsigned long long whole =
-                todo & __builtin_amdgcn_ballot_w64(my_len <= (uint32_t)kJumpDepth && my_clean == my_len * 0x01010101u);
+                todo & __builtin_amdgcn_ballot_w64(my_len <= (uint32_t)kJumpDepth && my_clean == my_len * kOnes);
             todo &= ~whole;
 #pragma unroll 1
             while (whole) {
@@ -598,13 +609,12 @@ compile_tile_kernel(BatchDesc batch,
     __syncthreads();
 
     // ---- phase 2
-    // Rows whose entries can be written 16 bytes at a time (row length a multiple of 4 tokens and
-    // a 16-byte aligned table): a lane converts 4 consecutive entries and stores them at once,
+    // A lane converts 4 consecutive entries and stores them at once,
     // T/4 lanes per row, 256/T rows per wavefront pass; the lane's 4 allowed bits are merged with
     // those of its 7 neighbours into one 32-bit word.  The memory pipeline handles a wavefront's
     // store instruction at a cost that hardly depends on its width, so this takes a quarter of
-    // the store instructions of the entry-per-lane form below.
-    if (wide_rows) {
+    // the store instructions of a form with an entry per lane.
+    if constexpr (!SHIFT) {
         constexpr int LPR = T / 4;                   // lanes per row
         constexpr int RPW = 64 / LPR;                // rows per wavefront pass
         const int sub = lane / LPR, l = lane % LPR;
@@ -653,27 +663,71 @@ compile_tile_kernel(BatchDesc batch,
                 if (row_ok && l < 4 && pad < rw32) allow[(uint64_t)grow * rw32 + pad] = 0u;
             }
         }
-        return;
-    }
-    for (int r = wave; r < S; r += kTileWaves) {
-        const int q = __builtin_amdgcn_readfirstlane(s_state[r]);
-        if (q < 0) continue;                          // idle lane of a padded group, or past the last state
-        int32_t* drow = delta + (size_t)(out_row + q) * n_tokens;
-        uint32_t* arow = allow + (size_t)(out_row + q) * row_words;
+    } else {
+        // The same, but a row's piece begins `sh` tokens into the tile, where 64 bytes begin, and ends U tokens further on; the
+        // U/4 first lanes of a row take it, the others the sh tokens before it in the first tile.  The allowed bits are those
+        // of the whole words in the tile, which may begin in the middle of one.
+        constexpr int LPR = T / 4, RPW = 64 / LPR, kMain = U / 4;
+        static_assert(kAlign == 16 && U % 32 == 16 && (LPR - kMain) * 4 >= kAlign, "every second tile begins in the middle of a word");
+        const int sub = lane / LPR, l = lane % LPR;
+        const uint32_t out_row32 = (uint32_t)out_row, nt32 = (uint32_t)n_tokens, rw32 = (uint32_t)row_words;
+        const uint32_t base = (uint32_t)(reinterpret_cast<uintptr_t>(delta) >> 2);
+        const int half = t0 & 16;
+        const uint32_t word = (uint32_t)((t0 + half) >> 5) + (uint32_t)(l >> 3);
+        const bool has_word = (l & 7) == 0 && (l >> 3) < (half ? T / 32 - 1 : T / 32) && word < rw32;
+        const bool last_tile = tile_t == n_tiles_t - 1, lead = l >= kMain;
+        const int left = n_tokens - t0;
+        for (int r0 = wave * RPW; r0 < S; r0 += kTileWaves * RPW) {
+            const int q = s_state[r0 + sub];
+            const uint32_t grow = out_row32 + (uint32_t)q;
+            const int sh = (int)((0u - (base + grow * nt32)) & (kAlign - 1u));
+            const int at = lead ? 4 * (l - kMain) : sh + 4 * l;                  // first of the lane's four tokens
+            const int end = lead ? (tile_t == 0 ? min(sh, left) : 0) : left;
+            const ST* trow = tile + (r0 + sub) * RS;
+            uint32_t e[4], bits = 0;
+            if (sizeof(ST) == 2) {
+                const uint32_t* tw = reinterpret_cast<const uint32_t*>(trow) + (at >> 1);
+                const uint32_t x0 = tw[0], x1 = tw[1], x2 = tw[2];
+                const uint32_t odd = (uint32_t)(at & 1) * 16u;
+                const uint32_t w0 = __builtin_amdgcn_alignbit(x1, x0, odd), w1 = __builtin_amdgcn_alignbit(x2, x1, odd);
+                e[0] = w0 & 0xFFFFu, e[1] = w0 >> 16, e[2] = w1 & 0xFFFFu, e[3] = w1 >> 16;
+                const uint32_t* bw = reinterpret_cast<const uint32_t*>(trow) + ((half + 4 * l) >> 1);
+                const uint32_t b0 = bw[0] ^ (SINK | SINK << 16), b1 = bw[1] ^ (SINK | SINK << 16);
+                bits = ((b0 & 0xFFFFu) != 0u ? 1u : 0u) | (b0 >> 16 != 0u ? 2u : 0u) | ((b1 & 0xFFFFu) != 0u ? 4u : 0u) | (b1 >> 16 != 0u ? 8u : 0u);
+            } else {
 #pragma unroll
-        for (int k = 0; k < T / 64; ++k) {
-            const int tl = k * 64 + lane;
-            const int t = t0 + tl;
-            const uint32_t e = tile[r * RS + tl];
-            const int v = e == SINK ? TDFA_DEAD : (int)(e / (uint32_t)sizeof(ST)) + state_base;
-            if (t < n_tokens) drow[t] = v;
-            const uint64_t m = __builtin_amdgcn_ballot_w64(v >= 0);
-            const int64_t word = (int64_t)((t0 + k * 64) >> 5) + lane;
-            if (lane < 2 && word < row_words) arow[word] = lane ? (uint32_t)(m >> 32) : (uint32_t)m;
+                for (int j = 0; j < 4; ++j) {
+                    e[j] = trow[at + j];
+                    bits |= (trow[half + 4 * l + j] != SINK ? 1u : 0u) << j;
+                }
+            }
+            int v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = e[j] == SINK ? TDFA_DEAD : (int)(e[j] / (uint32_t)sizeof(ST)) + state_base;
+            const bool row_ok = q >= 0;               // not an idle lane of a padded group, not past the last state
+            int32_t* out = delta + ((uint64_t)grow * nt32 + (uint32_t)(t0 + at));
+            if (row_ok && at < end) {
+                typedef int i32x4 __attribute__((ext_vector_type(4)));
+                const i32x4 pack = {v[0], v[1], v[2], v[3]};
+                if (!lead && at + 4 <= end) {
+                    __builtin_nontemporal_store(pack, reinterpret_cast<i32x4*>(out));
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (at + j < end) out[j] = v[j];
+                }
+            }
+            bits <<= 4 * (l & 7);
+            bits |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)bits, 0xB1, 0xF, 0xF, true);    // quad_perm [1,0,3,2]
+            bits |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)bits, 0x4E, 0xF, 0xF, true);    // quad_perm [2,3,0,1]
+            bits |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)bits, 0x141, 0xF, 0xF, true);   // row_half_mirror
+            if (row_ok && has_word) allow[(uint64_t)grow * rw32 + word] = bits;
+            if (last_tile) {
+                // a row is a multiple of 4 words: what lies past the tile's whole words is padding
+                const uint32_t pad = (uint32_t)((t0 - half + T) >> 5) + (uint32_t)l;
+                if (row_ok && l < 4 && pad < rw32) allow[(uint64_t)grow * rw32 + pad] = 0u;
+            }
         }
-        // a row is a multiple of 4 words: what lies past the last token tile is padding
-        const int64_t pad = (int64_t)((t0 + T) >> 5) + lane;
-        if (tile_t == n_tiles_t - 1 && lane < 4 && pad < row_words) arow[pad] = 0u;
     }
 }
 
@@ -695,7 +749,7 @@ copy_words_kernel(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, 
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) dst[i] = src[i];
 }
 
-template <typename ST, int S, int T, int KT, bool HAS_JUMP, int kTileWaves = 16, bool STAGED = false>
+template <typename ST, int S, int T, int KT, bool HAS_JUMP, int kTileWaves, bool STAGED, bool SHIFT>
 int launch_tiles(const CompileArgs& a, const CompileEntry* e, int n, hipStream_t stream)
 {
     size_t lds = TileShape<ST, S, T>::lds_bytes;
@@ -734,11 +788,11 @@ int launch_tiles(const CompileArgs& a, const CompileEntry* e, int n, hipStream_t
     start_bytes_kernel<<<dim3((a.n_tokens + kThreads - 1) / kThreads, n, (max_groups + kStartChunk - 1) / kStartChunk), kThreads, 0,
                          stream>>>(batch, a.vprefix, a.vlen, a.n_tokens);
     TDFA_HIP(hipGetLastError());
-    const int64_t n_tiles_t = (a.n_tokens + T - 1) / T;
+    constexpr int U = SHIFT ? T - kAlign : T;
+    const int64_t n_tiles_t = (a.n_tokens + U - 1) / U;
     const int64_t n_groups = share_columns ? (n_tiles_t + kXcds - 1) / kXcds * kXcds * n_tiles_q : (n_tiles_t * n_tiles_q + 31) / 32 * 32;
     if (n_groups > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "table too large for one launch");
-    const int wide_rows = a.n_tokens % 4 == 0 && reinterpret_cast<uintptr_t>(a.delta) % 16 == 0;
-    auto kern = compile_tile_kernel<ST, S, T, KT, HAS_JUMP, kTileWaves, STAGED>;
+    auto kern = compile_tile_kernel<ST, S, T, KT, HAS_JUMP, kTileWaves, STAGED, SHIFT>;
     static size_t attr_set = 0;                    // the most LDS this instantiation has been allowed so far
     if (attr_set < lds) {
         TDFA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -746,7 +800,7 @@ int launch_tiles(const CompileArgs& a, const CompileEntry* e, int n, hipStream_t
         attr_set = lds;
     }
     kern<<<dim3((unsigned)n_groups), kTileWaves * 64, lds, stream>>>(batch, a.vwords, a.voff, a.vlen, a.vsorted, a.vprefix, a.n_tokens,
-                                                                  (int)n_tiles_t, share_columns ? 1 : 0, wide_rows, a.delta, a.allow,
+                                                                  (int)n_tiles_t, share_columns ? 1 : 0, a.delta, a.allow,
                                                                   a.row_words);
     TDFA_HIP(hipGetLastError());
     return TDFA_OK;
@@ -799,19 +853,21 @@ int launch_compile(const CompileArgs& a, hipStream_t stream)
         for (int k = 0; k < n; ++k) jump |= e[k].has_jump;
         // Measured: four workgroups of 512 threads per CU with 256 x 64 tiles (38 KB of LDS each)
         // beat two of 1,024 threads with 256 x 128 or 512 x 64 tiles on every workload: the set-up,
-        // walk and flush phases of more independent workgroups overlap better.
-        int rc;
+        // walk and flush phases of more independent workgroups overlap better.  (128 x 128: 600 -> 610 us for 50 signatures,
+        // 1,980 -> 2,100 for 64 schemas; 64 x 256: 810 and 2,630.)  Tiles that overlap are 128 tokens wide, so that the 16 tokens
+        // walked twice are an eighth of them.
         bool staged = e->narrow;
         for (int k = 0; k < n; ++k) staged = staged && e[k].staged;
-        if (!e->narrow)
-            rc = jump ? launch_tiles<uint32_t, 64, 256, 4, true>(a, e, n, stream)
-                      : launch_tiles<uint32_t, 64, 256, 4, false>(a, e, n, stream);
-        else if (staged)
-            rc = jump ? launch_tiles<uint16_t, 256, 64, 1, true, 8, true>(a, e, n, stream)
-                      : launch_tiles<uint16_t, 256, 64, 1, false, 8, true>(a, e, n, stream);
-        else
-            rc = jump ? launch_tiles<uint16_t, 256, 64, 1, true, 8>(a, e, n, stream)
-                      : launch_tiles<uint16_t, 256, 64, 1, false, 8>(a, e, n, stream);
+        const bool shift = a.n_tokens % kAlign != 0 || reinterpret_cast<uintptr_t>(a.delta) % (4 * kAlign) != 0;
+        auto launch = [&](auto has_jump, auto shifted) {
+            constexpr bool kJump = decltype(has_jump)::value, kShift = decltype(shifted)::value;
+            constexpr int S = kShift ? 128 : 256, T = kShift ? 128 : 64;
+            if (!e->narrow) return launch_tiles<uint32_t, 64, 256, 4, kJump, 16, false, kShift>(a, e, n, stream);
+            if (staged) return launch_tiles<uint16_t, S, T, 1, kJump, 8, true, kShift>(a, e, n, stream);
+            return launch_tiles<uint16_t, S, T, 1, kJump, 8, false, kShift>(a, e, n, stream);
+        };
+        const int rc = jump ? (shift ? launch(std::true_type{}, std::true_type{}) : launch(std::true_type{}, std::false_type{}))
+                            : (shift ? launch(std::false_type{}, std::true_type{}) : launch(std::false_type{}, std::false_type{}));
         if (rc != TDFA_OK) return rc;
         i = j;
     }

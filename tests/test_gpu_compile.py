@@ -354,6 +354,25 @@ def test_runs_of_whole_jumps(T, oracle, last):
     _full_check(T, oracle, dfa, V.from_tokens(toks), compose_rows=(0, 30))
 
 
+@pytest.mark.parametrize("n_states,n_tokens", [(150, n) for n in (1, 15, 17, 47, 111, 112, 113, 127, 129, 223, 225, 239, 241, 337, 1000, 1001)] +
+                         [(33000, n) for n in (17, 239, 241, 255, 481)])
+def test_rows_of_any_alignment(T, oracle, n_states, n_tokens):
+    """Rows that begin at every multiple of 4 bytes within 64, with lengths around the tiles of 112 tokens (16-bit states, staged
+    or not) and 240 (more states than that)."""
+    rng = np.random.default_rng(n_states + n_tokens)
+    dfa = random_dfa(n_states, 0.3, 0.2, rng)
+    ls, ps = V.zipf_lengths(1, 9, 1.0)
+    vocab = V.make_vocab(rng, n_tokens, np.zeros(0, np.uint8), ls, ps, np.arange(256, dtype=np.uint8), 1.0, None)
+    walk = oracle.compile_walk(dfa.trans, vocab.data, vocab.offsets, n_threads=8)
+    v = T.Vocab(vocab.data, vocab.offsets)
+    for path in (T.PATH_AUTO, T.PATH_STAGED):
+        d = T.CharDFA(dfa.trans, dfa.accept, dfa.start)
+        d.compile_path(path)
+        table = T.compile_token_dfa(v, d)
+        torch.cuda.synchronize()
+        G.check_rows(table, walk, np.arange(dfa.n_states))
+
+
 def test_counter_classes_stacked_with_plain(T, oracle):
     """One launch that holds automata with and without jump classes, and a repeated handle."""
     rng = np.random.default_rng(77)
