@@ -349,20 +349,29 @@ constexpr int kXS = 256;          // states per tile
 constexpr int kXT = 64;           // tokens per sub-tile
 constexpr int kXSub = 4;
 constexpr int kXBlockT = kXT * kXSub;
-constexpr int kXRS = kXT + 2;     // tile row stride in 16-bit entries: an odd number of 32-bit words
-constexpr size_t kXTileBytes = (size_t)kXS * kXRS * 2;
+constexpr int kXAlign = 16;       // entries of the table in 64 bytes
+// tile row stride in 16-bit entries, an odd number of 32-bit words (shifted: behind the last kXAlign entries of the sub-tile before)
+constexpr int x_row_stride(bool shift) { return kXT + (shift ? kXAlign : 0) + 2; }
+constexpr size_t x_tile_bytes(bool shift) { return (size_t)kXS * x_row_stride(shift) * 2; }
 // tile, allowed bits, per token: list pointer (8), end (4), length class (4)
-constexpr size_t kXLdsBytes = kXTileBytes + (size_t)kXS * 8 * 4 + (size_t)kXBlockT * (8 + 4 + 4);
-static_assert(3 * kXLdsBytes <= 160 * 1024, "three workgroups per compute unit");
+constexpr size_t x_lds_bytes(bool shift) { return x_tile_bytes(shift) + (size_t)kXS * 8 * 4 + (size_t)kXBlockT * (8 + 4 + 4); }
+static_assert(3 * x_lds_bytes(true) <= 160 * 1024, "three workgroups per compute unit");
 
 // Workgroup (block of 256 tokens, run of state tiles).  Per token a cursor into its list (q ascending);
 // per tile of 256 states the pairs below the tile's upper bound are taken off the lists into the LDS
 // tile, 64 tokens at a time with eight lanes per token, and the rows are flushed.
-template <bool WIDE_ROWS, bool BASE0>
+//
+// SHIFT: the rows do not all begin at a multiple of 64 bytes, which memory takes at once (a part of them costs a read of the
+// rest: 20,000 rows of 255,999 tokens took 12.2 ms, of 256,000 6.5).  Blocks overlap by kXAlign tokens there, a row's piece goes from its
+// own first such boundary in the block to the one in the next block, and what a sub-tile leaves of a row's 64 bytes is kept in
+// front of the next one's entries: 8.0 ms (9,000 rows of 50,001 1.14 -> 0.89).
+template <bool SHIFT, bool BASE0>
 __global__ void __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(6, 6)))
 sweep_expand_kernel(SweepDesc d, SweepVocab v, int n_blocks_t, int tiles_per_run, int n_tiles_q, int32_t* __restrict__ delta,
                     uint32_t* __restrict__ allow, int64_t row_words, int allow_vec)
 {
+    constexpr int kXRS = x_row_stride(SHIFT), kKept = SHIFT ? kXAlign : 0;
+    constexpr size_t kXTileBytes = x_tile_bytes(SHIFT);
     extern __shared__ __align__(16) unsigned char smem[];
     uint16_t* tile = reinterpret_cast<uint16_t*>(smem);
     uint32_t* s_bits = reinterpret_cast<uint32_t*>(smem + kXTileBytes);          // [kXS][8]
@@ -374,7 +383,7 @@ sweep_expand_kernel(SweepDesc d, SweepVocab v, int n_blocks_t, int tiles_per_run
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int bt = (int)(blockIdx.x % (unsigned)n_blocks_t), run = (int)(blockIdx.x / (unsigned)n_blocks_t);
     const int qt_lo = run * tiles_per_run, qt_hi = min(n_tiles_q, qt_lo + tiles_per_run);
-    const int n_tokens = v.n_tokens, t_block = bt * kXBlockT;
+    const int n_tokens = v.n_tokens, t_block = bt * (kXBlockT - kKept);
     const uint32_t q_stride = (uint32_t)d.q_stride;
     const uint32_t SINK = (q_stride - 1u) * 2u;
     const int state_base = d.state_base;
@@ -453,7 +462,7 @@ sweep_expand_kernel(SweepDesc d, SweepVocab v, int n_blocks_t, int tiles_per_run
                 uint32_t en = ahead[sub];
                 for (;;) {
                     const bool in_tile = en != kNoPair && (en >> 16) < q_bound;
-                    if (in_tile) tile[((en >> 16) - q_base) * kXRS + tls] = (uint16_t)((en & 0xFFFFu) + 1u);
+                    if (in_tile) tile[((en >> 16) - q_base) * kXRS + kKept + tls] = (uint16_t)((en & 0xFFFFu) + 1u);
                     const unsigned long long bal = __builtin_amdgcn_ballot_w64(in_tile);
                     const uint32_t mine = (uint32_t)(bal >> (lane & ~7)) & 0xFFu;
                     cur[sub] += (uint32_t)__popc(mine);
@@ -483,15 +492,15 @@ sweep_expand_kernel(SweepDesc d, SweepVocab v, int n_blocks_t, int tiles_per_run
                         const uint32_t q = q_base + (uint32_t)(g * 64 + lane);
                         if (q < (uint32_t)d.n_states) {
                             const uint32_t e = col[q];
-                            if (e != SINK) tile[(g * 64 + lane) * kXRS + k] = (uint16_t)((e >> 1) + 1u);
+                            if (e != SINK) tile[(g * 64 + lane) * kXRS + kKept + k] = (uint16_t)((e >> 1) + 1u);
                         }
                     }
                 }
             }
             __syncthreads();
-            if (t0 < n_tokens) {
+            if (t0 - kKept < n_tokens) {
                 // ---- flush the sub-tile's rows and put DEAD back; its allowed bits go to s_bits
-                if (WIDE_ROWS) {
+                if constexpr (!SHIFT) {
                     constexpr int LPR = kXT / 4, RPW = 64 / LPR;     // 16 lanes per row, 4 rows per wavefront pass
                     const int subr = lane / LPR, l = lane % LPR;
                     const int t = t0 + 4 * l;
@@ -524,15 +533,54 @@ sweep_expand_kernel(SweepDesc d, SweepVocab v, int n_blocks_t, int tiles_per_run
                         if ((l & 7) == 0) s_bits[(r0 + subr) * 8 + sub * 2 + (l >> 3)] = bits;
                     }
                 } else {
-                    for (int r = wave; r < kXS; r += kWgWaves) {
-                        const uint32_t q = q_base + (uint32_t)r;
-                        const int t = t0 + lane;
-                        const uint32_t e = tile[r * kXRS + lane];
-                        tile[r * kXRS + lane] = (uint16_t)0;
-                        const int val = e ? (int)e - 1 + state_base : TDFA_DEAD;
-                        if (q < (uint32_t)d.n_states && t < n_tokens) delta[(size_t)(d.out_row + (int)q) * n_tokens + t] = val;
-                        const uint64_t m = __builtin_amdgcn_ballot_w64(val >= 0);
-                        if (lane < 2) s_bits[r * 8 + sub * 2 + lane] = lane ? (uint32_t)(m >> 32) : (uint32_t)m;
+                    // Entry c of a tile row is token t0 - kXAlign + c.  A row's piece is entries sh .. sh + kXT (in the first
+                    // sub-tile of a block from sh + kXAlign on; in the table's first one its kXAlign / 4 idle lanes take what
+                    // lies before that); the last kXAlign entries are kept for the next sub-tile.
+                    constexpr int LPR = kXT / 4, RPW = 64 / LPR;
+                    const int subr = lane / LPR, l = lane % LPR;
+                    const uint32_t base = (uint32_t)(reinterpret_cast<uintptr_t>(delta) >> 2);
+                    const int base1 = state_base - 1;
+                    const bool lead = sub == 0 && l < kXAlign / 4;
+                    for (int r0 = wave * RPW; r0 < kXS; r0 += kWgWaves * RPW) {
+                        const uint32_t q = q_base + (uint32_t)(r0 + subr), grow = out_row32 + q;
+                        const int sh = (int)((0u - (base + grow * nt32)) & (kXAlign - 1u));
+                        uint32_t* trow = reinterpret_cast<uint32_t*>(tile + (r0 + subr) * kXRS);
+                        uint32_t* own = trow + (kXAlign + 4 * l) / 2;              // the tokens t0 + 4 l ..
+                        const uint32_t w0 = own[0], w1 = own[1];
+                        const int at = sh + 4 * l;
+                        const uint32_t x0 = trow[at >> 1], x1 = trow[(at >> 1) + 1], x2 = trow[(at >> 1) + 2];
+                        own[0] = 0u;
+                        own[1] = 0u;
+                        if (l >= LPR - kXAlign / 4) {
+                            trow[2 * (l - (LPR - kXAlign / 4))] = w0;
+                            trow[2 * (l - (LPR - kXAlign / 4)) + 1] = w1;
+                        }
+                        const uint32_t odd = (uint32_t)(at & 1) * 16u;
+                        const uint32_t y0 = lead ? w0 : __builtin_amdgcn_alignbit(x1, x0, odd), y1 = lead ? w1 : __builtin_amdgcn_alignbit(x2, x1, odd);
+                        const uint32_t e[4] = {y0 & 0xFFFFu, y0 >> 16, y1 & 0xFFFFu, y1 >> 16};
+                        int val[4];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) val[j] = BASE0 ? (int)e[j] - 1 : (e[j] ? (int)e[j] + base1 : TDFA_DEAD);
+                        const int t = lead ? t0 + 4 * l : t0 - kXAlign + at;
+                        const int end = lead ? (bt == 0 ? min(sh, n_tokens) : 0) : n_tokens;
+                        if (q < (uint32_t)d.n_states && t < end) {
+                            typedef int i32x4 __attribute__((ext_vector_type(4)));
+                            const i32x4 pack4 = {val[0], val[1], val[2], val[3]};
+                            int32_t* out = delta + ((uint64_t)grow * nt32 + (uint32_t)t);
+                            if (!lead && t + 4 <= end) {
+                                __builtin_nontemporal_store(pack4, reinterpret_cast<i32x4*>(out));
+                            } else {
+#pragma unroll
+                                for (int j = 0; j < 4; ++j)
+                                    if (t + j < end) out[j] = val[j];
+                            }
+                        }
+                        uint32_t bits = min(w0 & 0xFFFFu, 1u) | min(w0 >> 16, 1u) << 1 | min(w1 & 0xFFFFu, 1u) << 2 | min(w1 >> 16, 1u) << 3;
+                        bits <<= 4 * (l & 7);
+                        bits |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)bits, 0xB1, 0xF, 0xF, true);    // quad_perm [1,0,3,2]
+                        bits |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)bits, 0x4E, 0xF, 0xF, true);    // quad_perm [2,3,0,1]
+                        bits |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)bits, 0x141, 0xF, 0xF, true);   // row_half_mirror
+                        if ((l & 7) == 0) s_bits[(r0 + subr) * 8 + sub * 2 + (l >> 3)] = bits;
                     }
                 }
             }
@@ -542,14 +590,31 @@ sweep_expand_kernel(SweepDesc d, SweepVocab v, int n_blocks_t, int tiles_per_run
         {
             const int r = (int)threadIdx.x >> 1, half = (int)threadIdx.x & 1;
             const uint32_t q = q_base + (uint32_t)r;
-            const uint32_t word0 = (uint32_t)bt * 8u + (uint32_t)half * 4u;
             uint32_t* src = s_bits + r * 8 + half * 4;
-            if (q < (uint32_t)d.n_states && word0 < rw32) {       // a row is a multiple of four words
-                uint32_t* dst = allow + ((uint64_t)(out_row32 + q) * rw32 + word0);
-                if (allow_vec) {
-                    *reinterpret_cast<uint4*>(dst) = make_uint4(src[0], src[1], src[2], src[3]);
-                } else {
-                    dst[0] = src[0]; dst[1] = src[1]; dst[2] = src[2]; dst[3] = src[3];
+            if constexpr (!SHIFT) {
+                const uint32_t word0 = (uint32_t)bt * 8u + (uint32_t)half * 4u;
+                if (q < (uint32_t)d.n_states && word0 < rw32) {       // a row is a multiple of four words
+                    uint32_t* dst = allow + ((uint64_t)(out_row32 + q) * rw32 + word0);
+                    if (allow_vec) {
+                        *reinterpret_cast<uint4*>(dst) = make_uint4(src[0], src[1], src[2], src[3]);
+                    } else {
+                        dst[0] = src[0]; dst[1] = src[1]; dst[2] = src[2]; dst[3] = src[3];
+                    }
+                }
+            } else {
+                // the block's whole words, seven of them where it begins in the middle of one; past the last block zeros up to
+                // the end of the row, three words at most
+                const int mid = t_block & 16;
+                const uint32_t word0 = (uint32_t)((t_block + mid) >> 5) + (uint32_t)half * 4u;
+                const uint32_t w[5] = {src[0], src[1], src[2], src[3], half ? 0u : src[4]};
+                const int n_words = bt == n_blocks_t - 1 || half == 0 || mid == 0 ? 4 : 3;
+                if (q < (uint32_t)d.n_states) {
+                    uint32_t* dst = allow + ((uint64_t)(out_row32 + q) * rw32);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (k < n_words && word0 + (uint32_t)k < rw32) dst[word0 + (uint32_t)k] = __builtin_amdgcn_alignbit(w[k + 1], w[k], (uint32_t)mid);
+                    if (bt == n_blocks_t - 1 && half)
+                        for (uint32_t k = word0 + 4u; k < rw32; ++k) dst[k] = 0u;
                 }
             }
             // (sub-tiles past the last token never write their words: they must read as zero for the next tile too)
@@ -614,7 +679,7 @@ int launch_compile_sweep(const CompileArgs& a, const CompileEntry& e, hipStream_
         TDFA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(sweep_token_kernel<4>), hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
         for (auto k : {sweep_expand_kernel<true, true>, sweep_expand_kernel<true, false>, sweep_expand_kernel<false, true>,
                        sweep_expand_kernel<false, false>})
-            TDFA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kXLdsBytes));
+            TDFA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)x_lds_bytes(true)));
         attr_set = true;
     }
     if (!resume) {
@@ -653,7 +718,9 @@ int launch_compile_sweep(const CompileArgs& a, const CompileEntry& e, hipStream_
         TDFA_HIP(hipGetLastError());
     }
     const int n_tiles_q = (e.n_states + kXS - 1) / kXS;
-    const int64_t n_blocks_t = (a.n_tokens + kXBlockT - 1) / kXBlockT;
+    const bool shift = a.n_tokens % kXAlign != 0 || reinterpret_cast<uintptr_t>(a.delta) % (4 * kXAlign) != 0;
+    const int block_step = kXBlockT - (shift ? kXAlign : 0);
+    const int64_t n_blocks_t = (a.n_tokens + block_step - 1) / block_step;
     // enough workgroups to keep every compute unit supplied: runs of state tiles per block of tokens
     int n_runs = (int)std::min<int64_t>(n_tiles_q, (12288 + n_blocks_t - 1) / n_blocks_t);
     if (n_runs < 1) n_runs = 1;
@@ -661,12 +728,11 @@ int launch_compile_sweep(const CompileArgs& a, const CompileEntry& e, hipStream_
     n_runs = (n_tiles_q + tiles_per_run - 1) / tiles_per_run;
     const int64_t grid = n_blocks_t * n_runs;
     if (grid > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "table too large for one launch");
-    const bool wide_rows = a.n_tokens % 4 == 0 && reinterpret_cast<uintptr_t>(a.delta) % 16 == 0;
     const int allow_vec = reinterpret_cast<uintptr_t>(a.allow) % 16 == 0 ? 1 : 0;
     const bool base0 = e.state_base == 0;
-    auto kern = wide_rows ? (base0 ? sweep_expand_kernel<true, true> : sweep_expand_kernel<true, false>)
+    auto kern = shift ? (base0 ? sweep_expand_kernel<true, true> : sweep_expand_kernel<true, false>)
                           : (base0 ? sweep_expand_kernel<false, true> : sweep_expand_kernel<false, false>);
-    kern<<<(unsigned)grid, kWgThreads, kXLdsBytes, stream>>>(d, v, (int)n_blocks_t, tiles_per_run, n_tiles_q, a.delta, a.allow,
+    kern<<<(unsigned)grid, kWgThreads, x_lds_bytes(shift), stream>>>(d, v, (int)n_blocks_t, tiles_per_run, n_tiles_q, a.delta, a.allow,
                                                             a.row_words, allow_vec);
     TDFA_HIP(hipGetLastError());
     return TDFA_OK;

@@ -435,6 +435,27 @@ def test_pairs_random_shapes(T, oracle, n_states, n_tokens, p_live):
     _pairs_check(T, oracle, dfa, vocab)
 
 
+@pytest.mark.parametrize("n_tokens", [1, 15, 47, 49, 63, 65, 79, 111, 113, 175, 177, 191, 193, 207, 239, 241, 255, 257, 271, 479, 481, 497, 500, 719, 1003])
+def test_pairs_rows_of_any_alignment(T, oracle, n_tokens):
+    """Rows that begin at every multiple of 4 bytes within 64, with lengths around sub-tiles of 64 and blocks of 240 tokens; the
+    second automaton of a stacked table, so that its rows' offset is added."""
+    rng = np.random.default_rng(n_tokens)
+    ls, ps = V.zipf_lengths(1, 7, 1.0)
+    vocab = V.make_vocab(rng, n_tokens, np.zeros(0, np.uint8), ls, ps, np.arange(24, dtype=np.uint8), 1.0, None)
+    dfas = [random_dfa(n, 0.8, 0.2, rng) for n in (37, 300)]
+    v = T.Vocab(vocab.data, vocab.offsets)
+    handles = [T.CharDFA(x.trans, x.accept, x.start) for x in dfas]
+    for h in handles:
+        h.compile_path(T.PATH_PAIRS)
+    walks = [oracle.compile_walk(x.trans, vocab.data, vocab.offsets, n_threads=8) for x in dfas]
+    table = T.compile_token_dfa(v, handles[1])
+    stacked, offs = T.compile_stacked(v, handles)
+    torch.cuda.synchronize()
+    G.check_rows(table, walks[1], np.arange(300))
+    ref, _ = oracle.concat_tables(walks)
+    G.check_rows(stacked, ref, np.arange(337))
+
+
 def test_pairs_token_lengths(T, oracle):
     """Empty, one-byte, two-byte, duplicate and long tokens (beyond the 32 bytes kept per token)."""
     rng = np.random.default_rng(12)
