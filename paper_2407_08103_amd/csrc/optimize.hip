@@ -463,7 +463,9 @@ struct Lists {
 // kSearchLaunches launches, with the rows; what is spent between two looks stays near that of twelve plain rounds.
 // 20,000 rows of 1,000 targets that reach no final state, the whole call: 2.0 ms with plain rounds, 14.4 with 192 sweeps for all,
 // 2.3 so; 16,000 rows, 40 % of them traps of
-// 150 targets: 1.2, 3.2 and 1.4 ms; 12,000 rows in a chain of random order: 1,190, 620 and 510 ms.
+// 150 targets: 1.2, 3.2 and 1.4 ms; 12,000 rows in a chain of random order: 1,190, 620 and 510 ms.  With a look only behind both searches
+// and the refinement, whose rounds take two launches and not four (the same calls 1.2, 0.7 and 490 ms), 5,387 rows of 128,256 tokens
+// are minimised in 1.9 ms (2.1 before), 7,300 of 10,001 in 1.25 (1.65) and a few hundred of 2,000 in 0.37 (0.69).
 constexpr int kSweeps = 192;
 constexpr int kSearchRows = 8192, kSearchLaunches = 12;
 
@@ -486,9 +488,11 @@ __device__ __forceinline__ void set_mark(uint8_t* mark, int32_t q)
     __hip_atomic_store(mark + q, (uint8_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// A launch says in *changed whether it marked anything; one whose predecessor did not (*before, NULL for the first) has nothing to do.
 __global__ void __launch_bounds__(kThreads)
-list_reach_kernel(Lists g, int sweeps, uint8_t* mark, uint8_t* done, int32_t* changed)
+list_reach_kernel(Lists g, int sweeps, uint8_t* mark, uint8_t* done, const int32_t* before, int32_t* changed)
 {
+    if (before && *before == 0) return;
     const int32_t q = blockIdx.x * kRowsPerBlock + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (q >= g.n_rows || done[q]) return;
     const int lane = threadIdx.x & 63;
@@ -512,8 +516,9 @@ list_good_start_kernel(int32_t n_rows, const uint8_t* __restrict__ mark, const u
 }
 
 __global__ void __launch_bounds__(kThreads)
-list_reach_final_kernel(Lists g, int sweeps, const uint8_t* mark, uint8_t* good, int32_t* changed)
+list_reach_final_kernel(Lists g, int sweeps, const uint8_t* mark, uint8_t* good, const int32_t* before, int32_t* changed)
 {
+    if (before && *before == 0) return;
     const int32_t q = blockIdx.x * kRowsPerBlock + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (q >= g.n_rows || !mark[q] || good[q]) return;
     const int lane = threadIdx.x & 63;
@@ -534,102 +539,111 @@ list_reach_final_kernel(Lists g, int sweeps, const uint8_t* mark, uint8_t* good,
     }
 }
 
-// An empty hash table for a round of the refinement, and its count of classes.
+// What the searches and the refinement begin with: no row looked at, nothing changed, two empty hash tables.
+struct HashTable {
+    unsigned long long* key;            // 0: free
+    int32_t* min;
+};
 __global__ void __launch_bounds__(kThreads)
-list_clear_kernel(unsigned long long* __restrict__ ht_key, int32_t* __restrict__ ht_min, size_t n, int32_t* __restrict__ n_classes)
+list_init_kernel(int32_t n_rows, uint8_t* __restrict__ done, uint32_t* __restrict__ slot_of, int32_t* __restrict__ flags, int n_flags,
+                 HashTable a, HashTable b, uint32_t ht_size)
 {
     const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n) {
-        ht_key[i] = 0ull;
-        ht_min[i] = 0x7FFFFFFF;
+    if (i < (size_t)n_rows) {
+        done[i] = 0;
+        slot_of[i] = 0;
     }
-    if (i == 0) *n_classes = 0;
+    if (i < (size_t)n_flags) flags[i] = 0;
+    if (i < ht_size) {
+        a.key[i] = b.key[i] = 0ull;
+        a.min[i] = b.min[i] = 0x7FFFFFFF;
+    }
 }
 
-// The first partition: kept rows by their final flag (cls 0 for every kept row, -1 for the rest).
-__global__ void __launch_bounds__(kThreads)
-list_first_keys_kernel(int32_t n_rows, const uint8_t* __restrict__ mark, const uint8_t* __restrict__ good,
-                       const uint8_t* __restrict__ accept, unsigned long long seed, int32_t* __restrict__ cls,
-                       unsigned long long* __restrict__ key)
-{
-    const int32_t q = blockIdx.x * kThreads + threadIdx.x;
-    if (q >= n_rows) return;
-    const bool kept = mark[q] && good[q];
-    cls[q] = kept ? 0 : -1;
-    key[q] = mix64(seed + (accept[q] ? 1 : 2)) | 1ull;
-}
+// A round of the refinement, first half: the key of each kept row, which is its class and the signature of its targets'
+// classes, mixed (never 0; in the first round, which also tells the kept rows, its final flag), and the slot of the table that rows
+// with this key meet in, where they leave their smallest row.  In the early rounds thousands of rows share a key: the rows of
+// a workgroup go to the table as one per key.
+//
+// Nothing is done once a round has split no class (counts[0] is the number of classes of this round, counts[-1] that of the
+// one before; `round` counts from 0): rounds are launched ahead of the host's look.
+constexpr int kKeyThreads = 1024, kKeyRows = kKeyThreads / 64;
 
-// key[q] of a kept row: its class and the signature of its targets' classes, mixed (never 0).
-__global__ void __launch_bounds__(kThreads)
-list_keys_kernel(Lists g, const int32_t* __restrict__ cls, unsigned long long seed, unsigned long long* __restrict__ key)
+__device__ __forceinline__ bool no_class_split(const int32_t* counts, int round) { return round >= 2 && counts[-1] == counts[-2]; }
+
+__global__ void __launch_bounds__(kKeyThreads)
+list_keys_kernel(Lists g, int round, const int32_t* __restrict__ counts, const uint8_t* __restrict__ mark, const uint8_t* __restrict__ good,
+                 const uint8_t* __restrict__ accept, int32_t* __restrict__ cls, unsigned long long seed, HashTable ht, uint32_t ht_mask,
+                 uint32_t* __restrict__ slot_of)
 {
-    const int32_t q = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-    if (q >= g.n_rows || cls[q] < 0) return;
+    __shared__ unsigned long long s_key[kKeyRows];
+    if (no_class_split(counts, round)) return;
     const int lane = threadIdx.x & 63;
-    const unsigned long long b = g.row_begin[q];
-    unsigned long long h = 0;
-    for (int i = lane; i < g.row_n[q]; i += 64) {
-        const int32_t c = cls[g.e_target[b + i]];
-        if (c >= 0) h += mix64(seed ^ (unsigned long long)(unsigned)c) * g.e_weight[b + i];
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int32_t q0 = blockIdx.x * kKeyRows, q = q0 + wave;
+    unsigned long long key = 0;                                    // 0: the row is not kept
+    if (q < g.n_rows) {
+        if (round == 0) {
+            const bool kept = mark[q] && good[q];
+            if (kept) key = mix64(seed + (accept[q] ? 1 : 2)) | 1ull;
+            if (lane == 0) cls[q] = kept ? 0 : -1;
+        } else if (cls[q] >= 0) {
+            const unsigned long long b = g.row_begin[q];
+            unsigned long long h = 0;
+            for (int i = lane; i < g.row_n[q]; i += 64) {
+                const int32_t c = cls[g.e_target[b + i]];
+                if (c >= 0) h += mix64(seed ^ (unsigned long long)(unsigned)c) * g.e_weight[b + i];
+            }
+            for (int off = 32; off > 0; off >>= 1) h += __shfl_xor(h, off, 64);
+            key = mix64(h ^ mix64(seed + 0x632BE59BD9B4E019ull + (unsigned long long)(unsigned)cls[q])) | 1ull;
+        }
     }
-    for (int off = 32; off > 0; off >>= 1) h += __shfl_xor(h, off, 64);
-    if (lane == 0) key[q] = mix64(h ^ mix64(seed + 0x632BE59BD9B4E019ull + (unsigned long long)(unsigned)cls[q])) | 1ull;
-}
-
-// Rows with equal keys meet in one slot of the table (ht_key 0: free; more slots than rows) and
-// leave their smallest row there.  In the early rounds thousands of rows share a key: the lanes that hold the key of the
-// wavefront's first lanes go to the table as one, their first, which has the smallest row.
-__global__ void __launch_bounds__(kThreads)
-list_insert_kernel(int32_t n_rows, const int32_t* __restrict__ cls, const unsigned long long* __restrict__ key,
-                   unsigned long long* ht_key, int32_t* ht_min, uint32_t ht_mask, uint32_t* __restrict__ slot_of)
-{
-    const int32_t q = blockIdx.x * kThreads + threadIdx.x;
-    bool waiting = q < n_rows && cls[q] >= 0;
-    const unsigned long long k = waiting ? key[q] : 0ull;
-    auto insert = [&]() -> uint32_t {
-        uint32_t slot = (uint32_t)(k >> 20) & ht_mask;
+    if (lane == 0) s_key[wave] = key;
+    __syncthreads();
+    if (wave != 0) return;
+    const unsigned long long k = lane < kKeyRows ? s_key[lane] : 0ull;
+    int first = lane;                                              // the first row of the workgroup with this key
+    for (int i = kKeyRows - 1; i >= 0; --i)
+        if (s_key[i] == k && i < lane) first = i;
+    uint32_t slot = 0;
+    if (k != 0ull && first == lane) {
+        slot = (uint32_t)(k >> 20) & ht_mask;
         for (uint32_t probe = 0; probe <= ht_mask; ++probe, slot = (slot + 1) & ht_mask) {
             // (a look first: most rows need not change the slot)
-            unsigned long long was = __hip_atomic_load(&ht_key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (was == 0ull) was = atomicCAS(&ht_key[slot], 0ull, k);
+            unsigned long long was = __hip_atomic_load(&ht.key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (was == 0ull) was = atomicCAS(&ht.key[slot], 0ull, k);
             if (was == 0ull || was == k) {
-                if (__hip_atomic_load(&ht_min[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > q) atomicMin(&ht_min[slot], q);
+                if (__hip_atomic_load(&ht.min[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > q0 + lane) atomicMin(&ht.min[slot], q0 + lane);
                 break;
             }
         }
-        return slot;
-    };
-    constexpr int kShared = 4;
-    for (int pass = 0; pass < kShared; ++pass) {
-        const unsigned long long all = __builtin_amdgcn_ballot_w64(waiting);
-        if (all == 0) return;
-        const int first = __builtin_ctzll(all);
-        const unsigned long long k0 = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(k >> 32), first) << 32) |
-                                      (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)k, first);
-        uint32_t slot = 0;
-        if ((int)(threadIdx.x & 63) == first) slot = insert();
-        slot = (uint32_t)__builtin_amdgcn_readlane((int)slot, first);
-        if (waiting && k == k0) {
-            slot_of[q] = slot;
-            waiting = false;
-        }
     }
-    if (waiting) slot_of[q] = insert();
+    slot = (uint32_t)__shfl((int)slot, first, 64);
+    if (k != 0ull) slot_of[q0 + lane] = slot;
 }
 
+// Second half: a class is named by the smallest row that met there; the table of the round before is emptied for the next.
 __global__ void __launch_bounds__(kThreads)
-list_assign_kernel(int32_t n_rows, const int32_t* __restrict__ cls, const uint32_t* __restrict__ slot_of,
-                   const int32_t* __restrict__ ht_min, int32_t* __restrict__ cls_out, int32_t* n_classes)
+list_assign_kernel(int32_t n_rows, int round, const int32_t* __restrict__ cls, const uint32_t* __restrict__ slot_of, const int32_t* __restrict__ ht_min,
+                   HashTable other, uint32_t ht_size, int32_t* __restrict__ cls_out, int32_t* counts)
 {
-    const int32_t q = blockIdx.x * kThreads + threadIdx.x;
+    const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
+    if (no_class_split(counts, round)) {                           // (the two arrays of classes are the same by now)
+        if (i == 0) counts[0] = counts[-1];
+        return;
+    }
+    if (i < ht_size) {
+        other.key[i] = 0ull;
+        other.min[i] = 0x7FFFFFFF;
+    }
     bool first = false;
-    if (q < n_rows) {
-        const int32_t c = cls[q] < 0 ? -1 : ht_min[slot_of[q]];
-        cls_out[q] = c;
-        first = c == q;
+    if (i < (uint32_t)n_rows) {
+        const int32_t c = cls[i] < 0 ? -1 : ht_min[slot_of[i]];
+        cls_out[i] = c;
+        first = c == (int32_t)i;
     }
     const uint64_t m = __builtin_amdgcn_ballot_w64(first);
-    if ((threadIdx.x & 63) == 0 && m != 0) atomicAdd(n_classes, __builtin_popcountll(m));
+    if ((threadIdx.x & 63) == 0 && m != 0) atomicAdd(&counts[0], __builtin_popcountll(m));
 }
 
 // The comparison of n pairs of rows (allow: the table's bits, or NULL where only the entries count).
@@ -794,49 +808,65 @@ int minimize_lists(const int32_t* delta, const uint32_t* allow, int64_t row_word
                    int32_t n_starts, hipStream_t s, std::vector<int32_t>* first_rows, std::vector<int32_t>* map_out, bool* bits_agree)
 {
     const unsigned long long seed = 0x243F6A8885A308D3ull;
+    const SearchShape search = search_shape(n_rows);
+    // Launches between two looks of the host, which cost as much as half a dozen of them (a copy and a wait, some 25 us); those
+    // behind the last one that changes anything end at once.  The first look comes behind both searches and the refinement,
+    // each with launches enough for most tables; only a search that is not through by then is looked at by itself.
+    const int reaches = search.launches > 1 ? search.launches : 8, finals = search.launches > 1 ? search.launches : 4;
+    const int rounds = search.launches > 1 ? 4 : 8;    // (even: the hash tables take turns)
+    // what the host looks at, side by side: the size of the lists; [0] a row with too many targets, [1] bits that differ, [2] mismatch, then a
+    // flag for each launch of the searches, the number of classes after each round (behind that of the two before), and the classes of the rows
+    const int at_reach = 3, at_final = at_reach + reaches, at_rounds = at_final + finals + 2, n_flags = (at_rounds + rounds + 1) & ~1;
     Arena mem;
-    unsigned long long *counter, *row_begin, *weight, *e_weight = nullptr, *key, *ht_key;
-    int32_t *row_n, *e_target = nullptr, *flags, *cls_a, *cls_b, *ht_min, *rows_dev, *first_dev;
+    unsigned long long *counter, *row_begin, *weight, *e_weight = nullptr, *ht_keys;
+    int32_t *row_n, *e_target = nullptr, *flags, *ht_mins, *pairs_dev, *cls_b;
     uint32_t* slot_of;
-    uint8_t *mark, *aux, *good, *accept_dev;
+    uint8_t *mark, *done, *good, *accept_dev;
     uint32_t ht_size = 1024;
     while (ht_size < 2u * (uint32_t)n_rows && ht_size < 0x80000000u) ht_size <<= 1;
-    TDFA_GET(mem.get(&counter, 1));
+    // (the flags apart from the counter: every row looks at them, and adds to it)
+    constexpr int kApart = 64;                     // in ints: two cache lines
+    TDFA_GET(mem.get(&counter, ((size_t)kApart + (size_t)n_flags + (size_t)n_rows + 1) / 2));
+    flags = reinterpret_cast<int32_t*>(counter) + kApart;
+    int32_t* const cls_a = flags + n_flags;
     TDFA_GET(mem.get(&row_begin, n_rows));
     TDFA_GET(mem.get(&weight, n_tokens));
     TDFA_GET(mem.get(&row_n, n_rows));
-    TDFA_GET(mem.get(&flags, 1 + 3));              // [0] too many targets / changed / mismatch, [1 ..] bits that differ, then classes after each round of a look
-    TDFA_GET(mem.get(&key, n_rows));
-    TDFA_GET(mem.get(&ht_key, ht_size));
-    TDFA_GET(mem.get(&ht_min, ht_size));
+    TDFA_GET(mem.get(&ht_keys, (size_t)2 * ht_size));
+    TDFA_GET(mem.get(&ht_mins, (size_t)2 * ht_size));
     TDFA_GET(mem.get(&slot_of, n_rows));
-    TDFA_GET(mem.get(&cls_a, n_rows));
     TDFA_GET(mem.get(&cls_b, n_rows));
-    TDFA_GET(mem.get(&mark, n_rows));
-    TDFA_GET(mem.get(&aux, n_rows));
+    TDFA_GET(mem.get(&mark, (size_t)2 * n_rows));
+    accept_dev = mark + n_rows;
+    TDFA_GET(mem.get(&done, n_rows));
     TDFA_GET(mem.get(&good, n_rows));
-    TDFA_GET(mem.get(&accept_dev, n_rows));
-    int32_t flag = 0;
+    const HashTable ht[2] = {{ht_keys, ht_mins}, {ht_keys + ht_size, ht_mins + ht_size}};
+    std::vector<uint8_t> mark_h((size_t)2 * n_rows, 0);
+    for (int32_t i = 0; i < n_starts; ++i) mark_h[(size_t)starts[i]] = 1;
+    std::copy(accept, accept + n_rows, mark_h.begin() + n_rows);
+    TDFA_HIP(hipMemcpyAsync(mark, mark_h.data(), mark_h.size(), hipMemcpyHostToDevice, s));
 
     // ---- the lists: one pass over the table (a second one when they need more room than guessed)
     unsigned long long e_cap = std::max<unsigned long long>(1u << 20, std::min<unsigned long long>((unsigned long long)n_rows * 512, 1ull << 26));
     if (n_tokens > 0) token_weights_kernel<<<(unsigned)((n_tokens + kThreads - 1) / kThreads), kThreads, 0, s>>>(seed, n_tokens, weight);
     TDFA_HIP(hipGetLastError());
+    const size_t n_init = std::max<size_t>({(size_t)n_rows, (size_t)(kApart + n_flags), ht_size});
+    std::vector<int32_t> look((size_t)kApart + (size_t)n_flags + (size_t)n_rows);        // the counter, the flags, the classes
+    int32_t* const seen = look.data() + kApart;
     for (int attempt = 0;; ++attempt) {
         TDFA_GET(mem.get(&e_target, e_cap));
         TDFA_GET(mem.get(&e_weight, e_cap));
-        TDFA_HIP(hipMemsetAsync(counter, 0, 8, s));
-        TDFA_HIP(hipMemsetAsync(flags, 0, 8, s));
+        list_init_kernel<<<(unsigned)((n_init + kThreads - 1) / kThreads), kThreads, 0, s>>>(n_rows, done, slot_of, reinterpret_cast<int32_t*>(counter),
+                                                                                             kApart + n_flags, ht[0], ht[1], ht_size);
         row_targets_kernel<<<(unsigned)n_rows, kListThreads, 0, s>>>(delta, allow, n_tokens, row_words, weight, e_cap, counter, row_begin,
                                                                      row_n, e_target, e_weight, flags, flags + 1);
         TDFA_HIP(hipGetLastError());
-        unsigned long long total = 0;
-        int32_t found[2] = {};
-        TDFA_HIP(hipMemcpyAsync(&total, counter, 8, hipMemcpyDeviceToHost, s));
-        TDFA_HIP(hipMemcpyAsync(found, flags, 8, hipMemcpyDeviceToHost, s));
+        TDFA_HIP(hipMemcpyAsync(look.data(), counter, (kApart + 2) * 4, hipMemcpyDeviceToHost, s));
         TDFA_HIP(hipStreamSynchronize(s));
-        if (found[0]) return kNotSparse;
-        *bits_agree = found[1] == 0;
+        unsigned long long total;
+        std::memcpy(&total, look.data(), 8);
+        if (seen[0]) return kNotSparse;
+        *bits_agree = seen[1] == 0;
         if (total <= e_cap) break;
         if (attempt == 1) return fail(TDFA_E_DEVICE, "the lists of targets changed size between two passes");
         e_cap = total;
@@ -844,92 +874,96 @@ int minimize_lists(const int32_t* delta, const uint32_t* allow, int64_t row_word
     const Lists g = {row_begin, row_n, e_target, e_weight, n_rows};
     const unsigned by_wave = (unsigned)(((size_t)n_rows + kRowsPerBlock - 1) / kRowsPerBlock);
     const unsigned by_thread = (unsigned)(((size_t)n_rows + kThreads - 1) / kThreads);
-    // Rounds between two looks of the host: a look costs as much as half a dozen launches (a copy and a wait, some 25 us),
-    // and a round past the last one changes nothing.
-    constexpr int kRefinesPerLook = 3;
+    const unsigned by_key = (unsigned)(((size_t)n_rows + kKeyRows - 1) / kKeyRows);
+    const unsigned by_slot = (unsigned)((std::max<size_t>((size_t)n_rows, ht_size) + kThreads - 1) / kThreads);
+    auto reach = [&](int i) { list_reach_kernel<<<by_wave, kThreads, 0, s>>>(g, search.sweeps, mark, done, i ? flags + at_reach + i - 1 : nullptr, flags + at_reach + i); };
+    auto reach_final = [&](int i) {
+        list_reach_final_kernel<<<by_wave, kThreads, 0, s>>>(g, search.sweeps, mark, good, i ? flags + at_final + i - 1 : nullptr, flags + at_final + i);
+    };
+    // n launches of a search, again and again, until one has changed nothing
+    auto search_on = [&](auto launch, int at, int n) -> int {
+        do {
+            TDFA_HIP(hipMemsetAsync(flags + at, 0, (size_t)n * 4, s));
+            for (int i = 0; i < n; ++i) launch(i);
+            TDFA_HIP(hipGetLastError());
+            TDFA_HIP(hipMemcpyAsync(seen + at, flags + at, (size_t)n * 4, hipMemcpyDeviceToHost, s));
+            TDFA_HIP(hipStreamSynchronize(s));
+        } while (seen[at + n - 1]);
+        return TDFA_OK;
+    };
 
-    // ---- states that a token sequence reaches, then of those the ones that reach a final state
-    std::vector<uint8_t> mark_h((size_t)n_rows, 0);
-    for (int32_t i = 0; i < n_starts; ++i) mark_h[(size_t)starts[i]] = 1;
-    TDFA_HIP(hipMemcpyAsync(mark, mark_h.data(), (size_t)n_rows, hipMemcpyHostToDevice, s));
-    TDFA_HIP(hipMemcpyAsync(accept_dev, accept, (size_t)n_rows, hipMemcpyHostToDevice, s));
-    TDFA_HIP(hipMemsetAsync(aux, 0, (size_t)n_rows, s));
-    TDFA_HIP(hipMemsetAsync(slot_of, 0, (size_t)n_rows * 4, s));
-    const SearchShape search = search_shape(n_rows);
-    for (flag = 1; flag;) {
-        TDFA_HIP(hipMemsetAsync(flags, 0, 4, s));
-        for (int r = 0; r < search.launches; ++r) list_reach_kernel<<<by_wave, kThreads, 0, s>>>(g, search.sweeps, mark, aux, flags);
-        TDFA_HIP(hipGetLastError());
-        TDFA_HIP(hipMemcpyAsync(&flag, flags, 4, hipMemcpyDeviceToHost, s));
-        TDFA_HIP(hipStreamSynchronize(s));
-    }
-    list_good_start_kernel<<<by_thread, kThreads, 0, s>>>(n_rows, mark, accept_dev, good);
-    for (flag = 1; flag;) {
-        TDFA_HIP(hipMemsetAsync(flags, 0, 4, s));
-        for (int r = 0; r < search.launches; ++r) list_reach_final_kernel<<<by_wave, kThreads, 0, s>>>(g, search.sweeps, mark, good, flags);
-        TDFA_HIP(hipGetLastError());
-        TDFA_HIP(hipMemcpyAsync(&flag, flags, 4, hipMemcpyDeviceToHost, s));
-        TDFA_HIP(hipStreamSynchronize(s));
-    }
-
+    // ---- states that a token sequence reaches, and of those the ones that reach a final state
+    auto reach_anew = [&]() { list_good_start_kernel<<<by_thread, kThreads, 0, s>>>(n_rows, mark, accept_dev, good); };
+    for (int i = 0; i < reaches; ++i) reach(i);
+    reach_anew();
+    for (int i = 0; i < finals; ++i) reach_final(i);
     // ---- refinement: classes named by their smallest row
-    int32_t *cls = cls_a, *cls_next = cls_b;
-    list_first_keys_kernel<<<by_thread, kThreads, 0, s>>>(n_rows, mark, good, accept_dev, seed, cls, key);
-    int32_t n_cls[kRefinesPerLook] = {};
-    for (int32_t prev = -1;;) {
-        for (int r = 0; r < kRefinesPerLook; ++r) {
-            list_clear_kernel<<<(ht_size + kThreads - 1) / kThreads, kThreads, 0, s>>>(ht_key, ht_min, ht_size, flags + 1 + r);
-            list_insert_kernel<<<by_thread, kThreads, 0, s>>>(n_rows, cls, key, ht_key, ht_min, ht_size - 1, slot_of);
-            list_assign_kernel<<<by_thread, kThreads, 0, s>>>(n_rows, cls, slot_of, ht_min, cls_next, flags + 1 + r);
-            std::swap(cls, cls_next);
-            list_keys_kernel<<<by_wave, kThreads, 0, s>>>(g, cls, seed, key);   // for the next round
+    int round = 0;
+    auto refine = [&]() {
+        for (int r = 0; r < rounds; ++r, ++round) {
+            int32_t *in = r & 1 ? cls_b : cls_a, *out = r & 1 ? cls_a : cls_b, *counts = flags + at_rounds + r;
+            list_keys_kernel<<<by_key, kKeyThreads, 0, s>>>(g, round, counts, mark, good, accept_dev, in, seed, ht[r & 1], ht_size - 1, slot_of);
+            list_assign_kernel<<<by_slot, kThreads, 0, s>>>(n_rows, round, in, slot_of, ht[r & 1].min, ht[~r & 1], ht_size, out, counts);
         }
+    };
+    refine();
+    for (bool searched = false, stable = false; !stable;) {
         TDFA_HIP(hipGetLastError());
-        TDFA_HIP(hipMemcpyAsync(n_cls, flags + 1, sizeof(n_cls), hipMemcpyDeviceToHost, s));
+        TDFA_HIP(hipMemcpyAsync(seen, flags, ((size_t)n_flags + (size_t)n_rows) * 4, hipMemcpyDeviceToHost, s));
         TDFA_HIP(hipStreamSynchronize(s));
-        // no class split in some round: none did after it either
-        bool stable = false;
-        for (int r = 0; r < kRefinesPerLook; ++r) {
-            stable = stable || n_cls[r] == prev;
-            prev = n_cls[r];
+        if (!searched && (seen[at_reach + reaches - 1] || seen[at_final + finals - 1])) {
+            // a search was not through: it goes on, and the refinement begins anew
+            if (seen[at_reach + reaches - 1]) {
+                TDFA_GET(search_on(reach, at_reach, reaches));
+                reach_anew();
+            }
+            TDFA_GET(search_on(reach_final, at_final, finals));
+            list_init_kernel<<<(unsigned)((n_init + kThreads - 1) / kThreads), kThreads, 0, s>>>(n_rows, done, slot_of, flags, n_flags, ht[0], ht[1], ht_size);
+            searched = true;
+            round = 0;
+            refine();
+            continue;
         }
+        searched = true;
+        // no class split in some round: none did after it either
+        for (int r = round == rounds ? 1 : 0; r < rounds; ++r) stable = stable || seen[at_rounds + r] == seen[at_rounds + r - 1];
         if (stable) break;
+        TDFA_HIP(hipMemcpyAsync(flags + at_rounds - 2, flags + at_rounds + rounds - 2, 8, hipMemcpyDeviceToDevice, s));
+        TDFA_HIP(hipMemsetAsync(flags + at_rounds, 0, rounds * 4, s));
+        refine();
     }
-    std::vector<int32_t> cls_h((size_t)n_rows);
-    TDFA_HIP(hipMemcpyAsync(cls_h.data(), cls, (size_t)n_rows * 4, hipMemcpyDeviceToHost, s));
-    TDFA_HIP(hipStreamSynchronize(s));
+    const int32_t* const cls_h = seen + n_flags;
 
     // ---- every row that joined another one is compared with it
     std::vector<int32_t> joined, with;
     for (int32_t q = 0; q < n_rows; ++q) {
-        const int32_t c = cls_h[(size_t)q];
+        const int32_t c = cls_h[q];
         if (c < 0 || c == q) continue;
-        if (c > q || cls_h[(size_t)c] != c || (accept[q] != 0) != (accept[c] != 0)) return kNotSparse;
+        if (c > q || cls_h[c] != c || (accept[q] != 0) != (accept[c] != 0)) return kNotSparse;
         joined.push_back(q);
         with.push_back(c);
     }
     if (!joined.empty() && n_tokens > 0) {
-        TDFA_GET(mem.get(&rows_dev, joined.size()));
-        TDFA_GET(mem.get(&first_dev, joined.size()));
-        TDFA_HIP(hipMemcpyAsync(rows_dev, joined.data(), joined.size() * 4, hipMemcpyHostToDevice, s));
-        TDFA_HIP(hipMemcpyAsync(first_dev, with.data(), with.size() * 4, hipMemcpyHostToDevice, s));
-        TDFA_HIP(hipMemsetAsync(flags, 0, 4, s));
-        TDFA_GET(launch_verify(delta, *bits_agree ? allow : nullptr, n_tokens, row_words, (int64_t)joined.size(), n_rows, rows_dev, first_dev, cls, flags, s));
-        TDFA_HIP(hipMemcpyAsync(&flag, flags, 4, hipMemcpyDeviceToHost, s));
+        const size_t n = joined.size();
+        TDFA_GET(mem.get(&pairs_dev, 2 * n));
+        joined.insert(joined.end(), with.begin(), with.end());
+        TDFA_HIP(hipMemcpyAsync(pairs_dev, joined.data(), joined.size() * 4, hipMemcpyHostToDevice, s));
+        TDFA_GET(launch_verify(delta, *bits_agree ? allow : nullptr, n_tokens, row_words, (int64_t)n, n_rows, pairs_dev, pairs_dev + n, cls_a, flags + 2, s));
+        TDFA_HIP(hipMemcpyAsync(seen + 2, flags + 2, 4, hipMemcpyDeviceToHost, s));
         TDFA_HIP(hipStreamSynchronize(s));
-        if (flag) return kNotSparse;
+        if (seen[2]) return kNotSparse;
     }
 
     // ---- the classes in the order of their smallest states
     map_out->assign((size_t)n_rows, TDFA_DEAD);
     first_rows->clear();
     for (int32_t q = 0; q < n_rows; ++q)
-        if (cls_h[(size_t)q] == q) {
+        if (cls_h[q] == q) {
             (*map_out)[(size_t)q] = (int32_t)first_rows->size();
             first_rows->push_back(q);
         }
     for (int32_t q = 0; q < n_rows; ++q)
-        if (cls_h[(size_t)q] >= 0) (*map_out)[(size_t)q] = (*map_out)[(size_t)cls_h[(size_t)q]];
+        if (cls_h[q] >= 0) (*map_out)[(size_t)q] = (*map_out)[(size_t)cls_h[q]];
     return TDFA_OK;
 }
 
@@ -954,10 +988,17 @@ int launch_compact_rows(const int32_t* delta, const uint32_t* allow, int32_t n_t
     if (pieces == 0) return TDFA_OK;
     Arena mem;
     int32_t *rows = nullptr, *map_dev = nullptr;
-    TDFA_GET(mem.get(&rows, first_rows.size()));
-    TDFA_GET(mem.get(&map_dev, map.size()));
-    TDFA_HIP(hipMemcpyAsync(rows, first_rows.data(), first_rows.size() * 4, hipMemcpyHostToDevice, s));
-    TDFA_HIP(hipMemcpyAsync(map_dev, map.data(), map.size() * 4, hipMemcpyHostToDevice, s));
+    std::vector<int32_t> both;
+    try {
+        both.reserve(first_rows.size() + map.size());
+    } catch (const std::bad_alloc&) {
+        return fail(TDFA_E_OOM, "host allocation failed");
+    }
+    both.insert(both.end(), first_rows.begin(), first_rows.end());
+    both.insert(both.end(), map.begin(), map.end());
+    TDFA_GET(mem.get(&rows, both.size()));
+    map_dev = rows + first_rows.size();
+    TDFA_HIP(hipMemcpyAsync(rows, both.data(), both.size() * 4, hipMemcpyHostToDevice, s));
     // four workgroups of eight wavefronts per compute unit (two where the map is at its largest)
     const size_t lds = map.size() * 4;
     const unsigned grid = (unsigned)std::min<int64_t>((pieces + kRenameThreads / 64 - 1) / (kRenameThreads / 64), 256 * 4);
