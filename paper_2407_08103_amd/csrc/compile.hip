@@ -302,9 +302,10 @@ compile_tile_kernel(BatchDesc batch,
     }
     {
         // Every load is requested before the first one is waited for: one trip to memory, under which the tile is filled.
-        static_assert(S <= kTileThreads && T * G <= kTileThreads && T <= kTileThreads && T * kLdsWords % kTileThreads == 0, "one round of loads");
+        static_assert(S <= kTileThreads && T * G <= kTileThreads && T <= kTileThreads, "one round of loads");
         static_assert(kLdsWords == 8, "the vocabulary's prefix array holds 8 words per token");
-        constexpr int kPrefix = T * kLdsWords / kTileThreads;      // words of the tokens' first bytes per thread
+        constexpr int kPrefix = (T * kLdsWords + kTileThreads - 1) / kTileThreads;      // words of the tokens' first bytes per thread
+        constexpr bool kAllPrefix = T * kLdsWords % kTileThreads == 0;
         constexpr int kFirst = kTileThreads - T * G;               // threads from here on fetch start bytes
         const int tid = (int)threadIdx.x;
         uint32_t prefix[kPrefix];
@@ -312,7 +313,7 @@ compile_tile_kernel(BatchDesc batch,
         for (int k = 0; k < kPrefix; ++k) {
             const int i = k * kTileThreads + tid;
             prefix[k] = 0u;
-            if (t0 + i / kLdsWords < n_tokens) prefix[k] = vprefix[(size_t)t0 * kLdsWords + i];
+            if ((kAllPrefix || i < T * kLdsWords) && t0 + i / kLdsWords < n_tokens) prefix[k] = vprefix[(size_t)t0 * kLdsWords + i];
         }
         // what each (token, group) pair starts with (see start_bytes_part); without the workspace
         // every group looks up every non-empty token's first byte
@@ -339,7 +340,8 @@ compile_tile_kernel(BatchDesc batch,
         for (int i0 = 0; i0 < n_words; i0 += kTileThreads)
             if (i0 + kTileThreads <= n_words || i0 + tid < n_words) reinterpret_cast<uint4*>(smem)[i0 + tid] = fill4;
 #pragma unroll
-        for (int k = 0; k < kPrefix; ++k) s_bytes[k * kTileThreads + tid] = prefix[k];
+        for (int k = 0; k < kPrefix; ++k)
+            if (kAllPrefix || k * kTileThreads + tid < T * kLdsWords) s_bytes[k * kTileThreads + tid] = prefix[k];
         if (tid >= kFirst) reinterpret_cast<unsigned char*>(s_clean)[sb_t * (Shape::CW * 4) + sb_g] = (unsigned char)sb;
         if (tid < S) s_state[tid] = state;
         if (tid < G) s_gc[tid] = cls;
@@ -873,6 +875,8 @@ int launch_transpose(const CompileEntry* e, int n, hipStream_t stream)
     return TDFA_OK;
 }
 
+constexpr int kFewTiles = 256;         // one to a compute unit
+
 int launch_compile(const CompileArgs& a, hipStream_t stream)
 {
     if (a.n_tokens <= 0) return TDFA_OK;
@@ -906,6 +910,13 @@ int launch_compile(const CompileArgs& a, hipStream_t stream)
             constexpr int S = kShift ? 128 : 256, T = kShift ? 128 : 64;
             if (!e->narrow) return launch_tiles<uint32_t, 64, 256, 4, kJump, 16, false, kShift>(a, e, n, stream);
             if (staged) return launch_tiles<uint16_t, S, T, 1, kJump, 8, true, kShift>(a, e, n, stream);
+            // Few tiles, each with a compute unit to itself: twice as many wavefronts, which walk half as many tokens one after the
+            // other.  240 states x 9,999 tokens (180 tiles) 35.9 -> 32.9 us a compile, a few hundred x 2,000 37 -> 33.7; with up to 512
+            // tiles so 32,000 tokens 43.6 -> 44.4, 400 states x 20,001 tokens with up to 1,024 43.4 -> 45.3.
+            int64_t n_tiles = 0;
+            for (int k = 0; k < n; ++k) n_tiles += (e[k].n_order + S - 1) / S;
+            n_tiles *= (a.n_tokens + T - 1) / T;
+            if (n_tiles <= kFewTiles) return launch_tiles<uint16_t, S, T, 1, kJump, 16, false, kShift>(a, e, n, stream);
             return launch_tiles<uint16_t, S, T, 1, kJump, 8, false, kShift>(a, e, n, stream);
         };
         const int rc = jump ? (shift ? launch(std::true_type{}, std::true_type{}) : launch(std::true_type{}, std::false_type{}))
