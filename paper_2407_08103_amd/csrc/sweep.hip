@@ -549,6 +549,7 @@ sweep_expand_kernel(SweepDesc d, SweepVocab v, int n_blocks_t, int tiles_per_run
                         const uint32_t w0 = own[0], w1 = own[1];
                         const int at = sh + 4 * l;
                         const uint32_t x0 = trow[at >> 1], x1 = trow[(at >> 1) + 1], x2 = trow[(at >> 1) + 2];
+                        wave_lds_sync();                           // (other lanes of the row clear and overwrite what this one has read)
                         own[0] = 0u;
                         own[1] = 0u;
                         if (l >= LPR - kXAlign / 4) {
@@ -607,6 +608,7 @@ sweep_expand_kernel(SweepDesc d, SweepVocab v, int n_blocks_t, int tiles_per_run
                 const int mid = t_block & 16;
                 const uint32_t word0 = (uint32_t)((t_block + mid) >> 5) + (uint32_t)half * 4u;
                 const uint32_t w[5] = {src[0], src[1], src[2], src[3], half ? 0u : src[4]};
+                wave_lds_sync();                                      // (src[4] belongs to the row's other lane, which clears it below)
                 const int n_words = bt == n_blocks_t - 1 || half == 0 || mid == 0 ? 4 : 3;
                 if (q < (uint32_t)d.n_states) {
                     uint32_t* dst = allow + ((uint64_t)(out_row32 + q) * rw32);

@@ -260,4 +260,13 @@ int launch_sample_noise(int32_t batch, int32_t n_tokens, uint64_t seed, uint64_t
 int launch_advance_tokens(const MaskArgs& table, int32_t batch, int32_t k, const int32_t* states, const int32_t* tokens,
                           int32_t* history, int32_t* n_valid, hipStream_t stream);
 
+// Between reads and writes of LDS by different lanes of one wavefront: a wavefront's LDS instructions are carried out in order, so
+// that only the compiler is to be kept from moving one past another.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace tdfa
