@@ -326,7 +326,8 @@ TDFA_API int tdfa_table_pack_info(const tdfa_table *table, int64_t *n_edges, int
  *   masked_out_dev : device, same shape and type as logits, or NULL to skip the write-back; may
  *                    equal logits_dev.
  * Enqueues on `stream`; steps issued on one stream run in order, so states can be chained from
- * step to step without host synchronisation.  Steps meet through a small reduction scratch owned by the
+ * step to step without host synchronisation.  What a step reads must not change while it runs; if it does,
+ * what that step writes is open, and later steps are not affected.  Steps meet through a small reduction scratch owned by the
  * library.  Each of the first 32 streams on a device that steps are issued on has its own, for batches
  * of up to 65,536 sequences; further streams share those, larger batches share a single one, and a
  * recorded graph keeps that of the stream it was captured on: steps that share a scratch must not overlap

@@ -1769,6 +1769,34 @@ __device__ __forceinline__ void share_rows(const MaskArgs& a, int max_parts, uin
     __syncthreads();
 }
 
+// What the workgroups of such a launch found comes together in a launch of its own: each leaves its candidate and its row (from 1;
+// 0: none) in the words of its own number, and this one takes the rows' maxima, writes the results and clears the words.  So nothing
+// is written that a workgroup's plan still reads - the new states may take the states' place -, and nothing is left behind for later
+// steps whatever the plans were (a caller that changes the states under a step spoils that step alone).
+constexpr int kScratchWords = 4096;    // that the scratch holds at least
+static_assert(kShareFull + kShareRows <= kScratchWords, "a word to each workgroup");
+
+__global__ void __launch_bounds__(kShareRows)
+share_results_kernel(MaskArgs a, int n_slots)
+{
+    __shared__ unsigned long long s_best[kShareRows];
+    const int tid = (int)threadIdx.x;
+    const int q = tid < a.batch ? a.states[tid] : TDFA_DEAD;
+    s_best[tid] = 0ull;
+    __syncthreads();
+    for (int i = tid; i < n_slots; i += kShareRows) {
+        const unsigned row = a.scratch_count[i];
+        const unsigned long long cand = a.scratch_best[i];
+        a.scratch_count[i] = 0u;
+        a.scratch_best[i] = 0ull;
+        if (row - 1u < (unsigned)a.batch) atomicMax(&s_best[row - 1u], cand);
+    }
+    __syncthreads();
+    if (tid >= a.batch) return;
+    const bool valid = q >= 0 && (int64_t)q < a.n_rows;
+    write_result(a, tid, q, valid, valid ? s_best[tid] : 0ull);
+}
+
 constexpr int kDrawThreads = 256;      // workgroup of the draw
 constexpr int kDrawGroups = 1024;      // workgroups that a draw of a smaller batch is split into: four to a compute unit, which their LDS lets it hold
 constexpr int kDrawPartGroups = 1 << 24;    // groups of a part at most: its offsets and its quads' numbers have 32 bits
@@ -1779,12 +1807,10 @@ constexpr uint32_t kTightWord = 0xE6666800u;    // generator words from here on 
 constexpr float kBoundSlack = 0.2f, kTightScore = 32768.0f;
 constexpr int kDrawList = 2048;        // quads that a wavefront lists at once
 constexpr int kDrawPieces = 4;         // 16-byte pieces of allowed bits that a lane has in flight
-constexpr uint32_t kDrawLone = 256;    // a state known to allow less than one token in so many is one workgroup's
 constexpr uint32_t kDrawDense = 10;    // a state that allows one token in so many or more has every quad drawn
 
 // The draw from the whole allowed set.  A workgroup takes part of a row: which, it works out from the costs of all rows
-// (max_parts > 0: share_rows), or `parts` workgroups of groups_per_part groups scan each row (max_parts < 0: but a row known to
-// allow few tokens is its first workgroup's).  What a token costs is its generator block, made for four neighbouring tokens
+// (max_parts > 0: share_rows), or `parts` workgroups of groups_per_part groups scan each row.  What a token costs is its generator block, made for four neighbouring tokens
 // (a quad) at a time, one quad per lane.
 //   A state known to allow one token in kDrawDense or more (or a masked row to be written) has every quad drawn, in the
 //     order it lies in: one bound for the quad, from its largest logit, allowed or not, and its largest generator word.
@@ -1839,19 +1865,17 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part, in
         p = blockIdx.x % parts;
         q = a.states[b];
         if (!WRITE && q >= 0 && (int64_t)q < a.n_rows) n_allowed = allowed_count(a, q);
-        if (!WRITE && max_parts < 0 && n_allowed < (uint32_t)V / kDrawLone) {       // (uniform; kUnknown is above)
-            if (p != 0) return;
-            parts = 1;
-            groups_per_part = n_groups;
-        }
         __syncthreads();
     }
     const bool valid = q >= 0 && (int64_t)q < a.n_rows;
+    auto meet = [&](unsigned long long cand) {                 // (thread 0)
+        if (!WRITE && max_parts > 0) {
+            a.scratch_count[blockIdx.x] = (unsigned)b + 1u;
+            a.scratch_best[blockIdx.x] = cand;
+        } else if (combine_parts(a, b, parts, cand)) write_result(a, b, q, valid, cand);
+    };
     if (!WRITE && (!valid || n_allowed == 0u)) {               // no token; (uniform in the workgroup)
-        if (threadIdx.x == 0) {
-            unsigned long long none = 0ull;
-            if (combine_parts(a, b, parts, none)) write_result(a, b, q, valid, none);
-        }
+        if (threadIdx.x == 0) meet(0ull);
         return;
     }
     if (sp.off_dev) {                                          // the same word for every thread
@@ -2151,8 +2175,7 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part, in
     compete();
     unsigned long long cand = best_key ? ((unsigned long long)best_key << 32) | (0xFFFFFFFFu - best_idx) : 0ull;
     cand = block_max_u64(cand, wave_best);
-    if (threadIdx.x != 0) return;
-    if (combine_parts(a, b, parts, cand)) { write_result(a, b, q, valid, cand); }
+    if (threadIdx.x == 0) meet(cand);
 }
 
 // Runs of speculated tokens (Section 5.3): one lane per sequence follows its k tokens through the
@@ -2500,18 +2523,15 @@ int launch_sample_step(const MaskArgs& a, float inv_t, int32_t top_k, uint64_t s
     parts = std::max<int64_t>({parts, ((int64_t)n_groups + kDrawPartGroups - 1) / kDrawPartGroups, 1});
     const int gpp = (int)(((n_groups + parts - 1) / parts + 63) & ~63);
     int64_t grid = batch * parts;
-    // Where the states' memory is not written by this very step, which a workgroup that starts late would read for its plan, rows
-    // are taken by what their states allow: shared out by their cost if there is enough of them (one million groups: 64 rows of
-    // 128,256 tokens, 128 of 64,000; below, the plan costs more than it gives), else only the lone ones told apart.
+    // Rows are shared out by what their states allow if there is enough of them (one million groups: 64 rows of
+    // 128,256 tokens, 128 of 64,000; below, the plan costs more than it gives).
     int shares = 0;
     auto apart_from_states = [&](const int32_t* out) { return out + batch <= a.states || a.states + batch <= out; };
-    const bool apart = apart_from_states(a.new_states) && apart_from_states(a.tokens);
-    if (!a.masked_out && (a.row_allowed || a.row_begin) && apart && n_groups <= kDrawPartGroups) {
-        shares = -1;
-        if (batch <= kShareRows && batch * n_groups >= 1000000 && n_groups >= 2 * kShareGroups) {
-            shares = n_groups / kShareGroups;
-            grid = std::min<int64_t>(batch * shares, kShareFull + batch);
-        }
+    const bool apart = (apart_from_states(a.new_states) || a.new_states == a.states) && apart_from_states(a.tokens);
+    if (!a.masked_out && (a.row_allowed || a.row_begin) && apart && n_groups <= kDrawPartGroups &&
+        batch <= kShareRows && batch * n_groups >= 1000000 && n_groups >= 2 * kShareGroups) {
+        shares = n_groups / kShareGroups;
+        grid = std::min<int64_t>(batch * shares, kShareFull + batch);
     }
     if (grid > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
     const dim3 blocks((unsigned)grid);
@@ -2519,6 +2539,8 @@ int launch_sample_step(const MaskArgs& a, float inv_t, int32_t top_k, uint64_t s
     else if (a.dtype == TDFA_F32) draw_step_kernel<TDFA_F32, false><<<blocks, kDrawThreads, 0, stream>>>(a, sp, (int)parts, gpp, shares);
     else if (a.masked_out) draw_step_kernel<TDFA_BF16, true><<<blocks, kDrawThreads, 0, stream>>>(a, sp, (int)parts, gpp, shares);
     else draw_step_kernel<TDFA_BF16, false><<<blocks, kDrawThreads, 0, stream>>>(a, sp, (int)parts, gpp, shares);
+    TDFA_HIP(hipGetLastError());
+    if (shares) share_results_kernel<<<1, kShareRows, 0, stream>>>(a, (int)grid);
     TDFA_HIP(hipGetLastError());
     return TDFA_OK;
 }

@@ -288,6 +288,50 @@ def test_steps_on_two_streams_at_once(T):
     assert torch.equal(tok[0], want[0])
 
 
+def test_states_changed_under_a_draw(T):
+    """A caller changes the states on another stream while draws run whose rows are shared out by what the states allow: what
+    those draws say is open, but the steps that come after them are right."""
+    rng = np.random.default_rng(31)
+    v, batch, steps = 64008, 256, 60
+    tab = np.full((4, v), DEAD, dtype=np.int32)
+    for q, n in enumerate((1, v // 3, 40, v)):
+        tab[q, rng.permutation(v)[:n]] = q
+    table = T.table_pack(_upload_table(T, tab))
+    lg = torch.from_numpy(rng.normal(0, 2, size=(batch, v)).astype(np.float32)).cuda().bfloat16()
+    sets = [torch.from_numpy(((np.arange(batch) + k) % 4).astype(np.int32)).cuda() for k in range(3)]
+    states = sets[0].clone()
+
+    def draws():
+        out = torch.full((3, 2, batch), -9, dtype=torch.int32, device="cuda")
+        for k in range(3):
+            states.copy_(sets[k])
+            T.sample_step(table, lg, states, 1.0, 5, k, out[k, 0], out[k, 1])
+        torch.cuda.synchronize()
+        return out
+
+    want = draws()
+    assert (want >= 0).all()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    a = torch.ones((8192, 8192), dtype=torch.bfloat16, device="cuda")
+    held = [torch.empty_like(a) for _ in streams]
+    junk = torch.empty((2, batch), dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    for s, out in zip(streams, held):
+        with torch.cuda.stream(s):
+            for _ in range(8):
+                torch.mm(a, a, out=out)
+    for i in range(steps):
+        with torch.cuda.stream(streams[0]):
+            T.sample_step(table, lg, states, 1.0, 5, i, junk[0], junk[1])
+        with torch.cuda.stream(streams[1]):
+            for k in range(8):
+                states.copy_(sets[(i + k) % 3])
+    torch.cuda.synchronize()
+    for s in (*streams, torch.cuda.current_stream()):
+        with torch.cuda.stream(s):
+            assert torch.equal(draws(), want)
+
+
 def test_draw_beyond_2_30_tokens(T):
     """A row of more than 2^30 tokens, few of them allowed: the numbers of the tokens' generator blocks outgrow 28 bits.  At a
     temperature of 1 a score is the logit plus the noise, rounded once, and the noise is what sample_noise gives."""
@@ -320,7 +364,7 @@ def test_draw_beyond_2_30_tokens(T):
 def test_rows_shared_out_by_cost(T, oracle, dtype, n_tokens, batch):
     """States of every cost, as counted by a packed table: none, one token, either side of the lines between lone, small
     and large rows and of the line from which every quad is drawn, all tokens.  Large batches are shared out by cost (4
-    rows of 9,001 tokens are not), unless the states are written in place: both against the oracle."""
+    rows of 9,001 tokens are not), also where the states are written in place: both against the oracle."""
     rng = np.random.default_rng(n_tokens)
     V = n_tokens
     counts = [0, 1, 2, V // 256 - 1, V // 256 + 1, V // 250, V // 249 + 1, V // 40, V // 10 - 1, V // 10 + 1, V // 2, V]
@@ -341,6 +385,12 @@ def test_rows_shared_out_by_cost(T, oracle, dtype, n_tokens, batch):
     T.sample_step(table, _to_dev(lg, dtype), st, 0.8, 99, 7, tok, st)
     torch.cuda.synchronize()
     assert np.array_equal(tok.cpu().numpy(), got[0]) and np.array_equal(st.cpu().numpy(), got[1])
+
+
+@pytest.mark.parametrize("n_tokens,batch", [(128261, 124), (128261, 126), (64001, 251), (63992, 300), (128261, 512), (128261, 513)])
+def test_lines_of_the_rule_that_shares_rows_out(T, oracle, n_tokens, batch):
+    """Batches and rows on either side of the sizes from which, and up to which, rows are shared out; states apart and in place."""
+    test_rows_shared_out_by_cost(T, oracle, BF16, n_tokens, batch)
 
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
