@@ -1690,10 +1690,19 @@ packed_step_kernel(MaskArgs a, int parts, int groups_per_part)
 
 // Rows of a batch shared out over the workgroups of a launch by what they cost, each workgroup working the same plan out
 // for itself from the states and the counts beside the table.  The cost of a row is in 1,024ths of one whose state allows
-// a tenth of the vocabulary or more, which has every quad drawn: a floor for the scan of its bits, and its tokens (measured:
-// a state that allows 7 % costs three quarters).  Rows above kShareSmall come first and take kShareFull workgroups between
-// them, so that every compute unit gets its three or so of about the same cost; the others take one each, behind them.
-constexpr int kShareRows = 1024;       // rows of a batch at most (a multiple of the workgroup's threads)
+// a tenth of the vocabulary or more, which has every quad drawn: a floor for the scan of its bits, which a state that allows
+// nothing takes as well, and its tokens (measured: a state that allows 7 % costs three quarters).  Rows above kShareSmall, those
+// of more than 1 in 250 tokens, come first and take kShareFull workgroups between them, so that every compute unit gets its
+// three or so of about the same cost; the others take one each, behind them.  (640 workgroups: 128 to 512 rows 0.3 us slower; 800: 256 rows
+// 0.3 us faster, 128 rows 1.0 slower.)
+//
+// The plan and the second launch take some 3 us, which few or short rows don't give back: 128,256 tokens, anywhere in their texts /
+// all in states that allow most / all that allow few, against parts of equal length: 64 rows 13.1, 14.6 and 10.9 against 12.6, 13.6 and
+// 8.1 us, 128 rows 15.0, 17.1 and 11.1 against 16.7, 16.5 and 10.0, 256 rows 22.9, 24.2 and 11.5 against 23.6, 21.4 and 10.7, 512 rows 35.4, 41.2 and 13.3 against 38.9,
+// 34.5 and 12.5, 768 rows 43.9, 53.2 and 15.5 against 45.3, 50.1 and 14.7, 1,024 rows 53.6, 68.2 and 21.7 against 54.7, 63.1 and 16.3; 64,000 tokens, 256 rows 16.2, 17.0 and
+// 10.6 against 16.6, 15.8 and 10.2; 32,000 tokens, 512 rows 17.5, 18.5 and 11.2 against 16.6, 16.0 and 8.9.
+constexpr int kShareRows = 512;        // rows of a batch at most (a multiple of the workgroup's threads)
+constexpr int64_t kShareFrom = 2000000, kShareLong = 8000;        // groups of the batch, and of a row, at least: 125 rows of 128,256 tokens, 250 of 64,000
 constexpr int kShareFull = 720;
 constexpr int kShareGroups = 1024;     // groups of a part at least
 constexpr float kShareFloor = 60.0f, kShareTokens = 10000.0f;     // cost of a row; of a token, times the size of the vocabulary
@@ -1737,8 +1746,8 @@ __device__ __forceinline__ void share_rows(const MaskArgs& a, int max_parts, uin
     sum = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) sum += s_sums[0][w];
-    // A large row takes one workgroup and its share, rounded down, of kShareFull less what the rounding leaves over: kShareFull
-    // and as many as there are rows are enough for all.
+    // A large row takes one workgroup and its share, rounded down, of kShareFull less 0.55 for each (a share loses half a workgroup
+    // by the rounding, on average): kShareFull and as many as there are rows are enough for all.
     const float share = fminf(fmaxf((float)kShareFull - 0.55f * (float)(sum >> 21), 0.0f) / (float)max(sum & 0x1FFFFFu, 1u), (float)(max_parts - 1) / 1024.0f);
     uint32_t parts[kMost], mine = 0;                               // workgroups of the large rows, and the small rows << 16
 #pragma unroll
@@ -1797,8 +1806,10 @@ share_results_kernel(MaskArgs a, int n_slots)
     write_result(a, tid, q, valid, valid ? s_best[tid] : 0ull);
 }
 
-constexpr int kDrawThreads = 256;      // workgroup of the draw
+constexpr int kDrawThreads = 256, kDrawWaves = kDrawThreads / 64;      // workgroup of the draw
 constexpr int kDrawGroups = 1024;      // workgroups that a draw of a smaller batch is split into: four to a compute unit, which their LDS lets it hold
+                                       // (2,048: 256 rows 24.4, 21.4 and 10.4 -> 24.2, 26.9 and 12.6 us, 512 rows 39.5, 34.6 and 12.3 -> 37.9, 42.1 and 16.2)
+constexpr int kLineWords = 32;         // words of a cache line
 constexpr int kDrawPartGroups = 1 << 24;    // groups of a part at most: its offsets and its quads' numbers have 32 bits
 // noise_bound is above the noise by at most 0.0861 ln 2 + 0.001 and what -ln(1 - u) exceeds -ln(-ln u) by, which is no more
 // than -ln u: from u = 0.9 on by less than 0.168.  With scores of magnitude kTightScore at most, whose sums are rounded
@@ -1807,14 +1818,25 @@ constexpr uint32_t kTightWord = 0xE6666800u;    // generator words from here on 
 constexpr float kBoundSlack = 0.2f, kTightScore = 32768.0f;
 constexpr int kDrawList = 2048;        // quads that a wavefront lists at once
 constexpr int kDrawPieces = 4;         // 16-byte pieces of allowed bits that a lane has in flight
-constexpr uint32_t kDrawDense = 10;    // a state that allows one token in so many or more has every quad drawn
+constexpr uint32_t kDrawDense = 10;    // a state that allows one token in so many or more has every quad drawn (7: the same within 0.3 us; 14: 256 rows 1.0 us
+                                       // faster, 128 rows 0.7, 512 rows 2.1 and 1,024 rows 6 us slower)
+
+struct DrawShared {
+    unsigned long long wave_best[kDrawWaves];
+    uint4 cands[kDrawWaves][64];                               // tokens that may win: id, logit, generator word, bound of the score
+    uint32_t sums[2][kDrawWaves];
+    RowShare share;
+    uint32_t reached;                                          // order key of the best score any wavefront has reached
+};
 
 // The draw from the whole allowed set.  A workgroup takes part of a row: which, it works out from the costs of all rows
-// (max_parts > 0: share_rows), or `parts` workgroups of groups_per_part groups scan each row.  What a token costs is its generator block, made for four neighbouring tokens
-// (a quad) at a time, one quad per lane.
-//   A state known to allow one token in kDrawDense or more (or a masked row to be written) has every quad drawn, in the
-//     order it lies in: one bound for the quad, from its largest logit, allowed or not, and its largest generator word.
-//   Else the quads with an allowed token are listed from the bits, 64 and more at a time, and drawn from the list.
+// (SHARED: share_rows), or `parts` workgroups of groups_per_part groups scan each row.  What a token costs is its generator block, made
+// for four neighbouring tokens (a quad) at a time, one quad per lane.
+//   A state known to allow one token in kDrawDense or more, a part with an allowed token in half of its quads where
+//     nothing is known of the state, and a masked row to be written have every quad drawn, in the order it lies in:
+//     one bound for the quad, from its largest logit, allowed or not, and its largest generator word.
+//   Else the quads with an allowed token are listed from the bits, 64 and more at a time, and drawn from the list; or the allowed
+//     tokens, where a wavefront has no more of them than lanes: each scored at once.
 // Where a quad's bound reaches the best score so far its tokens are bounded one by one; those that may win are kept, the
 // tightest of them raises the best score by its bound less kBoundSlack, and only what is left at the end (or fills the
 // wavefront's 64 places) gets its two logarithms.  The maximum does not depend on the order: candidates are compared as
@@ -1824,60 +1846,30 @@ constexpr uint32_t kDrawDense = 10;    // a state that allows one token in so ma
 // ns per instruction and SIMD with four wavefronts (a wavefront alone gets half of that), so 256 rows of 128,256
 // tokens all drawn take 15 us of every SIMD; and by some 20 dependent steps, 6 us, where states allow few.  The scheduler
 // serves the oldest wavefront first, so that the last one of a SIMD would run alone: a wavefront lowers its priority as it
-// gets on.  T = 1, 128,256 tokens in bf16, rows anywhere in the texts of 50 signatures / all in states that allow most / all that
-// allow few, replayed, against rows in parts of equal length and two queues per wavefront: 16 rows 10.9, 12.0 and 6.7 -> 9.8,
-// 10.0 and 6.6 us, 64 rows 14.2, 16.5 and 10.5 -> 12.9, 14.2 and 7.5, 256 rows 27.6, 34.0 and 10.5 -> 20.9, 23.7 and 7.6, 1,024 rows 79.4, 94.0 and
-// 15.0 -> 48.3, 66.5 and 12.2; 9,000 tokens, 256 rows 11.9, 11.7 and 6.8 -> 9.2, 8.9 and 7.8; the masked row as well, 256 rows of
-// 128,256 in place 38.7 -> 31.7.  Without the priorities 256 rows 22.1 and 26.2, with equal parts instead of shares 24 and 27.
-template <int DTYPE, bool WRITE>
-__global__ void __launch_bounds__(kDrawThreads)
-draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part, int max_parts)
+// gets on.  (Without: 256 rows 22.1 and 26.2 instead of 20.9 and 23.7 us.)
+//
+// T = 1, bf16, rows anywhere in the texts of 50 signatures / all in states that allow most / all that allow few, replayed, against rows in
+// parts of equal length and two queues per wavefront: 128,256 tokens, 1 row 8.1, 10.3 and 5.5 -> 8.9, 8.8 and 5.8 us, 16 rows 10.5, 11.8 and 7.8 ->
+// 9.1, 9.6 and 6.3, 64 rows 12.9, 16.5 and 9.5 -> 12.6, 13.6 and 8.1, 256 rows 26.8, 34.8 and 11.0 -> 22.9, 24.2 and 11.5, 512 rows 42.4, 53.6 and 13.8 -> 35.4,
+// 41.2 and 13.3, 1,024 rows 75, 99 and 21 -> 55, 64 and 16; 9,000 tokens, 256 rows 11.6, 11.6 and 6.9 -> 9.2, 9.0 and 6.9, 4,096 rows 33.7, 42.4 and 15.5 -> 31.9,
+// 36.2 and 19.7; 2,000 tokens, 1,024 rows 11.2, 11.3 and 5.9 -> 7.9, 7.7 and 7.5, 4,096 rows 22.7, 26.9 and 12.8 -> 20.2, 20.6 and 18.7.  Tables of which no count
+// is known, 128,256 tokens, 256 rows 26.8, 35.4 and 10.9 -> 24.7, 23.0 and 10.9 (every row from the list: 38.8, 43.4 and 10.9); the masked row as well, 256
+// rows 35.3, 40.9 and 29.0 -> 30.0, 29.5 and 30.0.
+template <int DTYPE, bool WRITE, bool SHARED>
+__device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, SampleParams sp, int b, int p, int parts, int groups_per_part, int q,
+                                                        uint32_t n_allowed, uint32_t* s_lists, int list_cap, DrawShared& s)
 {
     using Elem = typename ElemOf<DTYPE>::type;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     constexpr int kSize = (int)sizeof(Elem);
     constexpr uint32_t NEG_INF = DTYPE == TDFA_F32 ? 0xFF800000u : 0xFF80u;
-    constexpr int kWaves = kDrawThreads / 64;
-    __shared__ unsigned long long wave_best[kWaves];
-    __shared__ uint32_t s_list[kWaves][kDrawList];             // a quad's number in the part << 4 | its allowed bits
-    __shared__ uint4 s_cands[kWaves][64];                      // tokens that may win: id, logit, generator word, bound of the score
-    __shared__ uint32_t s_sums[2][kWaves];
-    __shared__ RowShare s_share;
-    __shared__ uint32_t s_reached;                             // order key of the best score any wavefront has reached
+    constexpr int kWaves = kDrawWaves;
     const int V = a.n_tokens, n_groups = (V + 7) >> 3;
     const int lane = (int)threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (threadIdx.x == 0) s_reached = 0;
-    int b, p, q;
-    uint32_t n_allowed = kUnknown;
-    if (!WRITE && max_parts > 0) {
-        share_rows<kDrawThreads>(a, max_parts, s_sums, &s_share);
-        parts = __builtin_amdgcn_readfirstlane(s_share.parts);
-        if (parts == 0) return;                                // (uniform: no row is left for this workgroup)
-        b = __builtin_amdgcn_readfirstlane(s_share.row);
-        p = __builtin_amdgcn_readfirstlane(s_share.part);
-        q = __builtin_amdgcn_readfirstlane(s_share.state);
-        n_allowed = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_share.n_allowed);
-        groups_per_part = ((n_groups + parts - 1) / parts + 255) & ~255;
-    } else {
-        b = blockIdx.x / parts;
-        p = blockIdx.x % parts;
-        q = a.states[b];
-        if (!WRITE && q >= 0 && (int64_t)q < a.n_rows) n_allowed = allowed_count(a, q);
-        __syncthreads();
-    }
     const bool valid = q >= 0 && (int64_t)q < a.n_rows;
-    auto meet = [&](unsigned long long cand) {                 // (thread 0)
-        if (!WRITE && max_parts > 0) {
-            a.scratch_count[blockIdx.x] = (unsigned)b + 1u;
-            a.scratch_best[blockIdx.x] = cand;
-        } else if (combine_parts(a, b, parts, cand)) write_result(a, b, q, valid, cand);
-    };
-    if (!WRITE && (!valid || n_allowed == 0u)) {               // no token; (uniform in the workgroup)
-        if (threadIdx.x == 0) meet(0ull);
-        return;
-    }
+    if (!WRITE && !valid) return 0ull;                         // no token; (uniform in the workgroup)
     if (sp.off_dev) {                                          // the same word for every thread
         const unsigned long long o = *sp.off_dev;
         sp.off_lo = (uint32_t)o;
@@ -1893,6 +1885,89 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part, in
     Elem* orow = WRITE ? static_cast<Elem*>(a.masked_out) + (int64_t)b * a.row_stride + g_lo * 8 : nullptr;
     const uint8_t* bits = reinterpret_cast<const uint8_t*>(a.allow + (valid ? (int64_t)q * a.row_words : 0)) + g_lo;
 
+    // The allowed bits by wavefronts, each a stretch of its own: a lane reads those of 128 tokens at a time, or of 32 in a part of
+    // 4,096 groups or less, so that every lane has some; kDrawPieces such pieces in flight, the first ones requested with the
+    // count of the state and used unless every quad is drawn.
+    const bool by_word = n_part <= 64 * kDrawPieces * kWaves * 4;
+    const int unit = by_word ? 32 : 128, n_units = (n_tok + unit - 1) / unit, per_wave = (n_units + kWaves - 1) / kWaves;
+    const int lo = wave * per_wave, hi = min(n_units, lo + per_wave);
+    const __amdgpu_buffer_rsrc_t r_bits = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t*>(bits), 0, (int)min(a.row_words * 4 - g_lo, (int64_t)((n_part + 15) & ~15)), kRawBuffer);
+    u32x4 v[kDrawPieces];
+    auto load_pieces = [&](int i0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < kDrawPieces; ++k) {
+            if (!SHARED) {
+                v[k] = u32x4{};
+                if (i0 + 64 * k >= hi) continue;               // (uniform: a short part has fewer)
+            }
+            const int i = i0 + 64 * k + lane;
+            if (by_word) v[k] = u32x4{__builtin_amdgcn_raw_buffer_load_b32(r_bits, i < hi ? i * 4 : 0x7FFFFFF0, 0, 0), 0, 0, 0};
+            else v[k] = __builtin_amdgcn_raw_buffer_load_b128(r_bits, i < hi ? i * 16 : 0x7FFFFFF0, 0, 0);
+        }
+    };
+    // What lies behind the row's last token leaves the pieces.
+    auto trim_pieces = [&](int i0) __attribute__((always_inline)) {
+        if (min(i0 + 64 * kDrawPieces, hi) * unit <= n_tok) return;        // (uniform)
+#pragma unroll
+        for (int k = 0; k < kDrawPieces; ++k) {
+            const int left = n_tok - (i0 + 64 * k + lane) * unit;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t rem = (uint32_t)min(max(left - 32 * d, 0), 32);
+                v[k][d] &= (uint32_t)((1ull << rem) - 1ull);
+            }
+        }
+    };
+    uint32_t mine[kDrawPieces];                                // what a lane's pieces hold
+    auto count_tokens = [&]() __attribute__((always_inline)) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int k = 0; k < kDrawPieces; ++k) {
+            mine[k] = (uint32_t)__builtin_popcount(v[k][0]);
+            if (!by_word) mine[k] += (uint32_t)__builtin_popcount(v[k][1]) + (uint32_t)__builtin_popcount(v[k][2]) + (uint32_t)__builtin_popcount(v[k][3]);
+            n += mine[k];
+        }
+        return n;
+    };
+    auto count_quads = [&]() __attribute__((always_inline)) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int k = 0; k < kDrawPieces; ++k) {
+            mine[k] = 0;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                if (d != 0 && by_word) continue;
+                uint32_t x = v[k][d] | v[k][d] >> 1;
+                x = (x | x >> 2) & 0x11111111u;
+                mine[k] += (uint32_t)__builtin_popcount(x);
+            }
+            n += mine[k];
+        }
+        return n;
+    };
+    if constexpr (!SHARED && !WRITE) n_allowed = allowed_count(a, q);
+    const bool counted = !SHARED && !WRITE && n_allowed == kUnknown;
+    uint32_t all = 0, total = 0;                               // of the pieces at hand: quads of the lane, of the wavefront
+    bool dense = WRITE;
+    if (!WRITE && n_allowed == 0u) return 0ull;
+    if (!WRITE && n_allowed != kUnknown) dense = n_allowed >= (uint32_t)V / kDrawDense;
+    if (!dense) load_pieces(lo);
+    // (No count: half of the part's quads, or of the first pieces of a long one.  At 3/4 256 rows anywhere in their texts take 28.4 instead of 25.3 us.)
+    if (counted) {
+        trim_pieces(lo);
+        all = count_quads();
+        total = wave_sum_u32(all);
+        if (lane == 0) s.sums[0][wave] = total;
+        __syncthreads();
+        uint32_t sum = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) sum += s.sums[0][w];
+        dense = sum >= (uint32_t)min(n_tok, kWaves * 64 * kDrawPieces * unit) / 8u;
+    } else if (!SHARED) {
+        __syncthreads();                                       // (s.reached)
+    }
+
     uint32_t best_key = 0, best_idx = 0xFFFFFFFFu;             // key 0: no candidate yet
     float reached = -__builtin_inff();                         // a score that some token of the workgroup has reached
     auto reach = [&](uint32_t key) {                           // (key 0: nothing scored yet)
@@ -1900,32 +1975,28 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part, in
         if (key != 0 && r > reached) reached = r;
     };
     auto look = [&]() {
-        reach((uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(&s_reached, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)));
+        reach((uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(&s.reached, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)));
     };
     // The largest score a token of the quad may have; NaN if one of its logits is.
     auto quad_bound = [&](const float (&l)[4], const uint32_t (&w)[4]) {
         const float most = __builtin_elementwise_maximum(__builtin_elementwise_maximum(l[0], l[1]), __builtin_elementwise_maximum(l[2], l[3]));
         return __builtin_fmaf(most, sp.inv_t, noise_bound(max(max(w[0], w[1]), max(w[2], w[3]))));
     };
-    auto wave_sync = []() {                                    // LDS written by some lanes, read by others
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
     auto publish = [&](uint32_t key) {
-        if (lane == 0) atomicMax(&s_reached, key);               // the other wavefronts prune by it too
+        if (lane == 0) atomicMax(&s.reached, key);               // the other wavefronts prune by it too
         reach(key);
     };
     // The candidates of this wavefront: those that may still win compete.
     uint32_t n_cand = 0;
-    uint4* cands = s_cands[wave];
+    uint4* cands = s.cands[wave];
     auto compete = [&]() __attribute__((always_inline)) {
-        wave_sync();
+        if (n_cand == 0) return;
+        wave_lds_sync();
         look();
         const uint4 c = cands[lane];
         const bool live = (uint32_t)lane < n_cand && !(__uint_as_float(c.w) < reached);
         n_cand = 0;
-        wave_sync();
+        wave_lds_sync();
         if (__builtin_amdgcn_ballot_w64(live) == 0) return;
         if (live) {
             const uint32_t lb = (c.y & 0x7FFFFFFFu) > 0x7F800000u ? 0xFF800000u : c.y;       // NaN counts as -inf
@@ -1965,7 +2036,7 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part, in
     auto generate = [&](uint32_t quad, uint32_t (&w)[4]) {
         philox4x32_10(quad0 + quad, (uint32_t)b, sp.off_lo, sp.off_hi, sp.seed_lo, sp.seed_hi, w);
     };
-    uint32_t* list = s_list[wave];
+    uint32_t* list = s_lists + wave * list_cap;
     const bool ragged = (n_tok & 3) != 0;
     const __amdgpu_buffer_rsrc_t r_quads =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<Elem*>(row), 0, (n_tok & ~3) * kSize, kRawBuffer);
@@ -1992,7 +2063,7 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part, in
         }
     };
     auto draw_list = [&](uint32_t n) __attribute__((always_inline)) {
-        wave_sync();
+        wave_lds_sync();
         Quad k, next;
         fetch((uint32_t)lane, n, k);
         for (uint32_t i = 0; i < n; i += 64) {
@@ -2003,10 +2074,29 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part, in
             if (__builtin_amdgcn_ballot_w64(!(quad_bound(k.l, w) < reached)) != 0) settle(k.e >> 4, k.e & 15u, k.l, w);
             k = next;
         }
-        wave_sync();
+        wave_lds_sync();
     };
 
-    if (WRITE || (n_allowed != kUnknown && n_allowed >= (uint32_t)V / kDrawDense)) {
+    // The n tokens of the wavefront's list, at most 64: each scored at once.
+    auto draw_tokens = [&](uint32_t n) __attribute__((always_inline)) {
+        wave_lds_sync();
+        const bool has = (uint32_t)lane < n;
+        const uint32_t t = has ? list[lane] : 0u;
+        uint32_t x = (uint32_t)row[t], w[4];
+        if constexpr (DTYPE == TDFA_BF16) x <<= 16;
+        generate(t >> 2, w);
+        const uint32_t word = (t & 2u) ? (t & 1u ? w[3] : w[2]) : (t & 1u ? w[1] : w[0]);
+        if ((x & 0x7FFFFFFFu) > 0x7F800000u) x = 0xFF800000u;                                // NaN counts as -inf
+        const uint32_t key = key_f32(__float_as_uint(__builtin_fmaf(__uint_as_float(x), sp.inv_t, gumbel_of(word))));
+        const uint32_t idx = quad0 * 4u + t;
+        if (has && (key > best_key || (key == best_key && idx < best_idx))) {
+            best_key = key;
+            best_idx = idx;
+        }
+        wave_lds_sync();
+    };
+
+    if (dense) {
         constexpr int kLoads = DTYPE == TDFA_F32 ? 2 : 1;
         const __amdgpu_buffer_rsrc_t r_x = __builtin_amdgcn_make_buffer_rsrc(const_cast<Elem*>(row), 0, n_full * 8 * kSize, kRawBuffer);
         const __amdgpu_buffer_rsrc_t r_o = __builtin_amdgcn_make_buffer_rsrc(orow, 0, WRITE ? n_full * 8 * kSize : 0, kRawBuffer);
@@ -2097,85 +2187,101 @@ draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part, in
         }
         if (n_tok > 8 * n_full && wave == 0) {                 // the row's last, partial group
             const uint32_t m = valid ? (uint32_t)bits[n_full] & ((1u << (n_tok - 8 * n_full)) - 1u) : 0u;
-            if (lane < 2) list[lane] = (uint32_t)(2 * n_full + lane) << 4 | (m >> (4 * lane) & 15u);
             Elem x = (Elem)0;
             const int t = 8 * n_full + lane;
             if (WRITE && t < n_tok) x = row[t];
-            draw_list(2u);
+            if (lane < 8 && (m >> lane & 1u)) list[__builtin_popcount(m & ((1u << lane) - 1u))] = (uint32_t)t;
+            draw_tokens((uint32_t)__builtin_popcount(m));
             if (WRITE && t < n_tok) orow[t] = m >> lane & 1u ? x : (Elem)NEG_INF;
         }
     } else {
-        // The quads with an allowed token, listed by wavefronts of their own: a lane reads the allowed bits of 128 tokens at
-        // a time, kDrawPieces such pieces in flight.
+        // What is allowed is listed: single tokens if a wavefront's pieces hold no more of them than it has lanes, else quads.
         if (parts == 1) __builtin_amdgcn_s_setprio(3);
-        // (A part of 4,096 groups or less by words of 32 tokens, so that every lane has some.)
-        const bool by_word = n_part <= 64 * kDrawPieces * kWaves * 4;
-        const int unit = by_word ? 32 : 128, n_units = (n_tok + unit - 1) / unit, per_wave = (n_units + kWaves - 1) / kWaves;
-        const int hi = min(n_units, (wave + 1) * per_wave);
-        const __amdgpu_buffer_rsrc_t r_bits = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint8_t*>(bits), 0, (int)min(a.row_words * 4 - g_lo, (int64_t)n_part + 15 & ~15), kRawBuffer);
-        for (int i0 = wave * per_wave; i0 < hi; i0 += 64 * kDrawPieces) {
-            u32x4 v[kDrawPieces];
-            uint32_t live[kDrawPieces], all = 0;
-#pragma unroll
-            for (int k = 0; k < kDrawPieces; ++k) {
-                const int i = i0 + 64 * k + lane;
-                if (by_word) v[k] = u32x4{__builtin_amdgcn_raw_buffer_load_b32(r_bits, i < hi ? i * 4 : 0x7FFFFFF0, 0, 0), 0, 0, 0};
-                else v[k] = __builtin_amdgcn_raw_buffer_load_b128(r_bits, i < hi ? i * 16 : 0x7FFFFFF0, 0, 0);
+        for (int i0 = lo; i0 < hi; i0 += 64 * kDrawPieces) {
+            if (i0 != lo) load_pieces(i0);
+            if (i0 != lo || !counted) {
+                trim_pieces(i0);
+                all = count_quads();
+                total = wave_sum_u32(all);
             }
-#pragma unroll
-            for (int k = 0; k < kDrawPieces; ++k) {
-                const int left = n_tok - (i0 + 64 * k + lane) * unit;
-                if (left < 128) {
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) {
-                        const int rem = left - 32 * d;
-                        if (rem < 32) v[k][d] = rem <= 0 ? 0u : v[k][d] & ((1u << rem) - 1u);
-                    }
-                }
-                live[k] = 0;
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    uint32_t x = v[k][d] | v[k][d] >> 1;
-                    x = (x | x >> 2) & 0x11111111u;
-                    live[k] += (uint32_t)__builtin_popcount(x);
-                }
-                all += live[k];
-            }
-            const uint32_t total = wave_sum_u32(all);
             if (total == 0) continue;
+            bool single = false;
+            if (total <= 64u) {
+                const uint32_t tokens = count_tokens();
+                single = wave_sum_u32(tokens) <= 64u;
+                if (single) all = tokens;
+                else all = count_quads();
+            }
             // all pieces at once, or one after the other where the list would not hold them
-            const int rounds = total <= (uint32_t)kDrawList ? 1 : kDrawPieces;
+            const int rounds = total <= (uint32_t)list_cap ? 1 : kDrawPieces;
             for (int r = 0; r < rounds; ++r) {
-                uint32_t mine = 0;
-#pragma unroll
-                for (int k = 0; k < kDrawPieces; ++k) mine += rounds == 1 || k == r ? live[k] : 0u;
-                const uint32_t incl = wave_prefix_u32(mine);
+                uint32_t here = all;
+                if (rounds != 1) here = r == 0 ? mine[0] : r == 1 ? mine[1] : r == 2 ? mine[2] : mine[3];
+                const uint32_t incl = wave_prefix_u32(here);
                 const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-                uint32_t at = incl - mine;
+                uint32_t at = incl - here;
 #pragma unroll
                 for (int k = 0; k < kDrawPieces; ++k) {
-                    if ((rounds != 1 && k != r) || __builtin_amdgcn_ballot_w64(live[k] != 0) == 0) continue;
+                    if ((rounds != 1 && k != r) || __builtin_amdgcn_ballot_w64(mine[k] != 0) == 0) continue;
+                    const uint32_t first = (uint32_t)((i0 + 64 * k + lane) * unit);          // token
 #pragma unroll
                     for (int d = 0; d < 4; ++d) {
                         if (d != 0 && by_word) continue;
                         uint32_t rest = v[k][d];
                         while (rest) {
-                            const int s = __builtin_ctz(rest) & 28;
-                            const uint32_t nib = rest >> s & 15u;
-                            list[at++] = (uint32_t)((i0 + 64 * k + lane) * (unit >> 2) + 8 * d + (s >> 2)) << 4 | nib;
-                            rest &= ~(15u << s);
+                            const uint32_t at_bit = (uint32_t)__builtin_ctz(rest), t = first + 32u * (uint32_t)d + at_bit;
+                            if (single) {
+                                list[at++] = t;
+                                rest &= rest - 1u;
+                            } else {
+                                list[at++] = t >> 2 << 4 | (rest >> (at_bit & 28u) & 15u);
+                                rest &= ~(15u << (at_bit & 28u));
+                            }
                         }
                     }
                 }
-                draw_list(n);
+                if (single) draw_tokens(n);
+                else draw_list(n);
             }
         }
     }
     compete();
-    unsigned long long cand = best_key ? ((unsigned long long)best_key << 32) | (0xFFFFFFFFu - best_idx) : 0ull;
-    cand = block_max_u64(cand, wave_best);
-    if (threadIdx.x == 0) meet(cand);
+    const unsigned long long cand = best_key ? ((unsigned long long)best_key << 32) | (0xFFFFFFFFu - best_idx) : 0ull;
+    return block_max_u64(cand, s.wave_best);
+}
+
+template <int DTYPE, bool WRITE, bool SHARED>
+__global__ void __launch_bounds__(kDrawThreads)
+draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part, int list_cap, int spread)
+{
+    extern __shared__ uint32_t s_lists[];                      // [kDrawWaves][list_cap]
+    __shared__ DrawShared s;
+    if (threadIdx.x == 0) s.reached = 0;
+    if constexpr (SHARED) {                                    // (parts: at most as many to a row)
+        share_rows<kDrawThreads>(a, parts, s.sums, &s.share);
+        const int n = __builtin_amdgcn_readfirstlane(s.share.parts);
+        if (n == 0) return;                                    // (no row is left for this workgroup)
+        const int b = __builtin_amdgcn_readfirstlane(s.share.row), q = __builtin_amdgcn_readfirstlane(s.share.state);
+        const int n_groups = (a.n_tokens + 7) >> 3;
+        const unsigned long long cand =
+            draw_part<DTYPE, WRITE, SHARED>(a, sp, b, __builtin_amdgcn_readfirstlane(s.share.part), n, ((n_groups + n - 1) / n + 255) & ~255, q,
+                                            (uint32_t)__builtin_amdgcn_readfirstlane((int)s.share.n_allowed), s_lists, list_cap, s);
+        if (threadIdx.x == 0) {
+            a.scratch_count[blockIdx.x] = (unsigned)b + 1u;
+            a.scratch_best[blockIdx.x] = cand;
+        }
+    } else {
+        const int b = blockIdx.x / parts, q = __builtin_amdgcn_readfirstlane(a.states[b]);
+        unsigned long long cand =
+            draw_part<DTYPE, WRITE, SHARED>(a, sp, b, blockIdx.x % parts, parts, groups_per_part, q, kUnknown, s_lists, list_cap, s);
+        if (threadIdx.x != 0) return;
+        // (read again, the kernel's first argument: kept all along, its pointers spill, and with them the compiler reserves private
+        // memory that every launch next to other kernels pays for, 0.3 to 0.5 us)
+        const __attribute__((address_space(4))) MaskArgs* args = (const __attribute__((address_space(4))) MaskArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(args));
+        const MaskArgs& z = *(const MaskArgs*)args;
+        if (combine_parts(z, b * spread, parts, cand)) write_result(z, b, q, q >= 0 && (int64_t)q < z.n_rows, cand);
+    }
 }
 
 // Runs of speculated tokens (Section 5.3): one lane per sequence follows its k tokens through the
@@ -2523,24 +2629,41 @@ int launch_sample_step(const MaskArgs& a, float inv_t, int32_t top_k, uint64_t s
     parts = std::max<int64_t>({parts, ((int64_t)n_groups + kDrawPartGroups - 1) / kDrawPartGroups, 1});
     const int gpp = (int)(((n_groups + parts - 1) / parts + 63) & ~63);
     int64_t grid = batch * parts;
-    // Rows are shared out by what their states allow if there is enough of them (one million groups: 64 rows of
-    // 128,256 tokens, 128 of 64,000; below, the plan costs more than it gives).
+    // Rows are shared out by what their states allow if there is enough of them (the figures are at kShareRows).  The new states may
+    // take the states' place, as results are written when no plan is read any more.
     int shares = 0;
     auto apart_from_states = [&](const int32_t* out) { return out + batch <= a.states || a.states + batch <= out; };
     const bool apart = (apart_from_states(a.new_states) || a.new_states == a.states) && apart_from_states(a.tokens);
     if (!a.masked_out && (a.row_allowed || a.row_begin) && apart && n_groups <= kDrawPartGroups &&
-        batch <= kShareRows && batch * n_groups >= 1000000 && n_groups >= 2 * kShareGroups) {
+        batch <= kShareRows && batch * n_groups >= kShareFrom && n_groups >= kShareLong) {
         shares = n_groups / kShareGroups;
         grid = std::min<int64_t>(batch * shares, kShareFull + batch);
     }
+    // A wavefront's list: the most quads of one, a quarter of its part, where more workgroups than the chip holds with whole lists can
+    // have use for the room (2,000 tokens, 4,096 rows that allow few 26 -> 18 us; up to 1,024 workgroups more than four to a compute
+    // unit only leave others idle: 256 rows of 128,256 tokens 23.3 -> 24.6 us).
+    int cap = kDrawList;
+    if (!shares && grid > kDrawGroups && gpp <= 64 * kDrawPieces * kDrawWaves * 4)
+        cap = std::min(cap, std::max((gpp / 4 + kDrawWaves) / kDrawWaves * 8, 64));
+    const size_t lds = (size_t)cap * kDrawWaves * 4;
+    // The words that the parts of a row meet through lie as far apart as there is room for, up to a cache line: atomics on one line wait
+    // for each other, some 10 ns each (16 rows that allow few, 16 parts each, 8.2 -> 6.3 us).
+    int spread = 1;
+    while (spread < kLineWords && 2 * spread * batch <= kScratchWords) spread *= 2;
     if (grid > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
     const dim3 blocks((unsigned)grid);
-    if (a.dtype == TDFA_F32 && a.masked_out) draw_step_kernel<TDFA_F32, true><<<blocks, kDrawThreads, 0, stream>>>(a, sp, (int)parts, gpp, shares);
-    else if (a.dtype == TDFA_F32) draw_step_kernel<TDFA_F32, false><<<blocks, kDrawThreads, 0, stream>>>(a, sp, (int)parts, gpp, shares);
-    else if (a.masked_out) draw_step_kernel<TDFA_BF16, true><<<blocks, kDrawThreads, 0, stream>>>(a, sp, (int)parts, gpp, shares);
-    else draw_step_kernel<TDFA_BF16, false><<<blocks, kDrawThreads, 0, stream>>>(a, sp, (int)parts, gpp, shares);
-    TDFA_HIP(hipGetLastError());
-    if (shares) share_results_kernel<<<1, kShareRows, 0, stream>>>(a, (int)grid);
+    auto launch = [&](auto write, auto shared) {
+        constexpr bool kWrite = decltype(write)::value, kShared = decltype(shared)::value;
+        const int n_parts = kShared ? shares : (int)parts;
+        if (a.dtype == TDFA_F32) draw_step_kernel<TDFA_F32, kWrite, kShared><<<blocks, kDrawThreads, lds, stream>>>(a, sp, n_parts, gpp, cap, spread);
+        else draw_step_kernel<TDFA_BF16, kWrite, kShared><<<blocks, kDrawThreads, lds, stream>>>(a, sp, n_parts, gpp, cap, spread);
+    };
+    if (a.masked_out) launch(std::true_type{}, std::false_type{});
+    else if (shares) {
+        launch(std::false_type{}, std::true_type{});
+        share_results_kernel<<<1, kShareRows, 0, stream>>>(a, (int)grid);
+    }
+    else launch(std::false_type{}, std::false_type{});
     TDFA_HIP(hipGetLastError());
     return TDFA_OK;
 }

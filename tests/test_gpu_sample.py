@@ -288,6 +288,42 @@ def test_steps_on_two_streams_at_once(T):
     assert torch.equal(tok[0], want[0])
 
 
+def test_rows_shared_out_in_a_graph(T):
+    """Draws whose rows are shared out, recorded one after the other on states advanced in place: every replay is what the
+    same calls gave before, with other steps on the same stream between the replays."""
+    rng = np.random.default_rng(8)
+    v, batch = 64008, 256
+    tab = np.full((6, v), DEAD, dtype=np.int32)
+    for q, n in enumerate((0, 30, v // 200, v // 9, v // 2, v)):
+        tab[q, rng.permutation(v)[:n]] = rng.integers(0, 6, size=n)
+    table = T.table_pack(_upload_table(T, tab))
+    lg = torch.from_numpy(rng.normal(0, 2, size=(batch, v)).astype(np.float32)).cuda().bfloat16()
+    first = torch.from_numpy(rng.integers(-1, 6, size=batch).astype(np.int32)).cuda()
+    states, tok = first.clone(), torch.empty((3, batch), dtype=torch.int32, device="cuda")
+
+    def steps():
+        states.copy_(first)
+        for i in range(3):
+            T.sample_step(table, lg, states, 1.0, 5, i, tok[i], states)
+
+    steps()
+    torch.cuda.synchronize()
+    want = tok.clone(), states.clone()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        steps()
+    other, new = torch.empty_like(states), torch.empty_like(states)
+    for i in range(4):
+        tok.fill_(-9)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(tok, want[0]) and torch.equal(states, want[1])
+        T.mask_step(table, lg[:16 + i], first[:16 + i], other[:16 + i], new[:16 + i])
+        T.sample_step(table, lg[:40], first[:40], 1.0, 5, 0, other[:40], new[:40])
+        torch.cuda.synchronize()
+        assert torch.equal(other[:40], want[0][0, :40])
+
+
 def test_states_changed_under_a_draw(T):
     """A caller changes the states on another stream while draws run whose rows are shared out by what the states allow: what
     those draws say is open, but the steps that come after them are right."""
@@ -385,6 +421,31 @@ def test_rows_shared_out_by_cost(T, oracle, dtype, n_tokens, batch):
     T.sample_step(table, _to_dev(lg, dtype), st, 0.8, 99, 7, tok, st)
     torch.cuda.synchronize()
     assert np.array_equal(tok.cpu().numpy(), got[0]) and np.array_equal(st.cpu().numpy(), got[1])
+
+
+@pytest.mark.parametrize("n_tokens,batch", [(61, 5), (2003, 1), (2003, 1100), (9001, 40), (33003, 1030), (140003, 3)])
+def test_listed_tokens_and_quads(T, oracle, n_tokens, batch):
+    """States around the numbers that decide how a row is drawn: as many allowed tokens, or quads, to a wavefront as it has lanes,
+    lists that are full, half of the quads; whole lists and those cut to the part (many rows); with and without counts."""
+    rng = np.random.default_rng(n_tokens)
+    V, quads = n_tokens, (n_tokens + 3) // 4
+    rows = []
+    for n in (1, 63, 64, 65, 255, 256, 257, 300):                                  # tokens in a stretch, and anywhere
+        rows += [np.arange(min(n, V)) + (V - min(n, V)) // 3, rng.permutation(V)[:n]]
+    for n in (64, 65, 256, 257, quads // 2 - 1, quads // 2, quads // 2 + 2, quads):       # quads, a token or all of each
+        at = rng.permutation(quads)[:n]
+        rows += [4 * at + rng.integers(0, 4, size=len(at)), (4 * at[:, None] + np.arange(4)).reshape(-1)]
+    tab = np.full((len(rows), V), DEAD, dtype=np.int32)
+    for q, at in enumerate(rows):
+        at = at[at < V]
+        tab[q, at] = rng.integers(0, len(rows), size=len(at))
+    dense = _upload_table(T, tab)
+    states = (np.arange(batch) % len(rows)).astype(np.int32)
+    x = rng.normal(0, 2, size=(batch, (V + 7) // 8 * 8)).astype(np.float32)
+    lg = LG.f32_to_bf16_bits(x)
+    for i, table in enumerate((T.table_pack(dense), dense)):                      # (the second holds caller's arrays: no counts)
+        for first in range(0, len(rows), batch):
+            _sample_strided(T, oracle, table, tab, lg, BF16, (states + first) % len(rows), 0.9, 17, first, masked=False)
 
 
 @pytest.mark.parametrize("n_tokens,batch", [(128261, 124), (128261, 126), (64001, 251), (63992, 300), (128261, 512), (128261, 513)])
