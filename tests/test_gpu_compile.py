@@ -336,22 +336,96 @@ def test_counter_classes(T, oracle, pattern, alphabet, n_random):
 
 @pytest.mark.parametrize("last", [1, 7, 8, 9, 63, 64])
 def test_runs_of_whole_jumps(T, oracle, last):
-    """Blocks of 64 ids with every number of tokens that one jump takes whole (they are walked in pairs, eight sorted tokens to
-    a wavefront), among tokens that start with an ordinary lookup, that leave the class, that are longer than a jump, that
-    no state survives and that are empty; the last block holds `last` tokens."""
+    """Blocks of 64 ids with every number of tokens that one jump takes whole (they are walked in pairs), among tokens that start
+    with an ordinary lookup, that leave the class, that are longer than a jump, that no state survives and that are empty; the
+    last block holds `last` tokens.  Few tiles, so that a wavefront has four tokens of a block, sorted, with 64 in the last one, and
+    eight tokens in the order of their ids else (then rows do not begin at 64 bytes, and tiles advance by 112 ids)."""
     dfa = compile_regex(r'"[^"\\]{0,90}"(,[0-9]{1,30})*')
-    rng = np.random.default_rng(last)
+    toks = _blocks_of_whole_jumps(last, [*range(18), 32, 63, 64], last)
+    _full_check(T, oracle, dfa, V.from_tokens(toks), compose_rows=(0, 30))
+
+
+@pytest.mark.parametrize("last", [64, 16, 63])
+def test_runs_of_whole_jumps_over_many_tiles(T, oracle, last):
+    """The same over more tiles than there are compute units, which fewer wavefronts walk: eight sorted tokens of a block to a
+    wavefront where the row length is a multiple of 16, sixteen of a tile in the order of their ids else."""
+    dfa = compile_regex(r'"[^"\\]{0,90}"(,[0-9]{1,30})*')
+    toks = _blocks_of_whole_jumps(last, [*range(18), 32, 63, 64] * 28, last)
+    _full_check(T, oracle, dfa, V.from_tokens(toks), compose_rows=(0, 30))
+
+
+def _blocks_of_whole_jumps(seed, wholes, last):
+    rng = np.random.default_rng(seed)
     fresh = iter(range(10 ** 6))
     other = [lambda: b'"' + b"q%d" % next(fresh), lambda: b"z%d" % next(fresh) + b'"', lambda: b"\\%d" % next(fresh),
              lambda: b"k" * 33 + b"%d" % next(fresh), lambda: b"m" * 31 + b"%d" % next(fresh) + b'",7', lambda: b"", lambda: b",%d" % next(fresh)]
     toks = []
-    for whole in [*range(18), 32, 63, 64]:
-        n = 64 if len(toks) < 20 * 64 else last
+    for i, whole in enumerate(wholes):
+        n = 64 if i < len(wholes) - 1 else last
         block = [b"a%d" % next(fresh) for _ in range(min(whole, n))]
         block += [other[int(rng.integers(len(other)))]() for _ in range(n - len(block))]
         rng.shuffle(block)
         toks += block
-    _full_check(T, oracle, dfa, V.from_tokens(toks), compose_rows=(0, 30))
+    return toks
+
+
+def _random_vocab(rng, n_tokens):
+    ls, ps = V.zipf_lengths(1, 9, 1.0)
+    return V.make_vocab(rng, n_tokens, np.zeros(0, np.uint8), ls, ps, np.arange(256, dtype=np.uint8), 1.0, None)
+
+
+@pytest.mark.parametrize("n_tokens", [6000, 6001, 6007, 6012])
+def test_rows_of_any_alignment_over_many_tiles(T, oracle, n_tokens):
+    """More tiles than there are compute units, states of 16 bits, the transposed table not staged."""
+    rng = np.random.default_rng(n_tokens)
+    dfa, vocab = random_dfa(1500, 0.3, 0.2, rng), _random_vocab(rng, n_tokens)
+    d = T.CharDFA(dfa.trans, dfa.accept, dfa.start)
+    d.compile_path(T.PATH_WALK)
+    table = T.compile_token_dfa(T.Vocab(vocab.data, vocab.offsets), d)
+    torch.cuda.synchronize()
+    G.check_rows(table, oracle.compile_walk(dfa.trans, vocab.data, vocab.offsets, n_threads=8), np.arange(dfa.n_states))
+
+
+@pytest.mark.parametrize("n_tokens", [15008, 15009, 15015])
+def test_counter_classes_over_many_tiles(T, oracle, n_tokens):
+    """A long counter class over more tiles than there are compute units, alone and stacked with an automaton without a class."""
+    rng = np.random.default_rng(n_tokens)
+    alphabet = b'ab"\\ z01'
+    extra = [b"", b"a" * 40, b'"' + b"b" * 33 + b'"', b"a" * 32, b"z" * 31 + b'"']
+    vocab = _counter_vocab(rng, alphabet, n_tokens - len(extra), extra)
+    v = T.Vocab(vocab.data, vocab.offsets)
+    dfas = [compile_regex(r'"[^"\\]{0,400}"'), random_dfa(90, 0.5, 0.2, rng)]
+    handles = [T.CharDFA(d.trans, d.accept, d.start) for d in dfas]
+    for h in handles:
+        h.compile_path(T.PATH_WALK)
+    walks = [oracle.compile_walk(d.trans, vocab.data, vocab.offsets, n_threads=8) for d in dfas]
+    table = T.compile_token_dfa(v, handles[0])
+    stacked, _ = T.compile_stacked(v, handles)
+    torch.cuda.synchronize()
+    G.check_rows(table, walks[0], np.arange(dfas[0].n_states))
+    ref, _ = oracle.concat_tables(walks)
+    G.check_rows(stacked, ref, np.arange(len(ref)))
+
+
+@pytest.mark.parametrize("first", [1, 5, 15])
+@pytest.mark.parametrize("path,n_states,n_tokens", [("PATH_WALK", 300, n) for n in (17, 1008, 1009)] + [("PATH_WALK", 1500, 6000), ("PATH_WALK", 1500, 6003)] +
+                         [("PATH_WALK", 33000, 272)] + [("PATH_PAIRS", 300, n) for n in (17, 1008, 1009)])
+def test_rows_behind_any_address(T, oracle, path, n_states, n_tokens, first):
+    """A table in the caller's memory that begins `first` entries behind 64 bytes, with rows that are and are not whole multiples of
+    that; what lies before and behind it stays."""
+    rng = np.random.default_rng(n_states + n_tokens)
+    dfa, vocab = random_dfa(n_states, 0.5, 0.2, rng), _random_vocab(rng, n_tokens)
+    around = torch.full((16 + n_states * n_tokens + 16,), -77, dtype=torch.int32, device="cuda")
+    assert around.data_ptr() % 64 == 0
+    allow = torch.full((n_states + 2, T.allow_row_words(n_tokens)), -77, dtype=torch.int32, device="cuda")
+    delta = around[first:first + n_states * n_tokens].view(n_states, n_tokens)
+    d = T.CharDFA(dfa.trans, dfa.accept, dfa.start)
+    d.compile_path(getattr(T, path))
+    table = T.compile_token_dfa(T.Vocab(vocab.data, vocab.offsets), d, out=(delta, allow[1:-1]))
+    torch.cuda.synchronize()
+    G.check_rows(table, oracle.compile_walk(dfa.trans, vocab.data, vocab.offsets, n_threads=8), np.arange(n_states))
+    assert (around[:first] == -77).all() and (around[first + n_states * n_tokens:] == -77).all()
+    assert (allow[0] == -77).all() and (allow[-1] == -77).all()
 
 
 @pytest.mark.parametrize("n_states,n_tokens", [(150, n) for n in (1, 15, 17, 47, 111, 112, 113, 127, 129, 223, 225, 239, 241, 337, 1000, 1001)] +
