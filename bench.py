@@ -317,7 +317,7 @@ def measure(args, workload, steps, warmup, extras):
 
     pairs_path = (union if union is not None else dfas[0]).info()[2] == T.PATH_PAIRS if (n_constraints == 1 or union is not None) else False
     compile_kernel = ("sweep_expand_kernel (+ the sweep's list kernels)" if pairs_path
-                      else "compile_tile_kernel (+ transpose_kernel, start_bytes_kernel)")
+                      else "compile_tile_kernel (+ prepare_kernel)")
     compile_gbs = entries * 4 / (ms_compile * 1e-3) / 1e9
     roof_compile = {"bound": "hbm", "achieved": compile_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": compile_gbs / HBM_PEAK_GBS, "traffic": recorded_traffic(workload, "sweep" if pairs_path else "compile_tile"),

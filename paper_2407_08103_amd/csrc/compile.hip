@@ -88,12 +88,12 @@ __device__ __forceinline__ void transpose_part(const DfaDesc& d, int q0, int b0,
     }
 }
 
-template <typename ST>
+// That alone, for the sweep.
 __global__ void __launch_bounds__(kThreads)
-transpose_kernel(BatchDesc batch)
+transpose_kernel(DfaDesc d)
 {
     __shared__ TransposeTile tile;
-    transpose_part<ST>(batch.d[blockIdx.z], blockIdx.x * 64, blockIdx.y * 64, tile);
+    transpose_part<uint16_t>(d, blockIdx.x * 64, blockIdx.y * 64, tile);
 }
 
 // What every (64-state group, token) pair starts with, one byte each:
@@ -852,25 +852,14 @@ int launch_tiles(const CompileArgs& a, const CompileEntry* e, int n, hipStream_t
 
 }  // namespace
 
-int launch_transpose(const CompileEntry* e, int n, hipStream_t stream)
+int launch_transpose(const CompileEntry& e, hipStream_t stream)
 {
-    if (n <= 0) return TDFA_OK;
-    if (n > kMaxBatch) return fail(TDFA_E_UNSUPPORTED, "too many automata for one launch");
-    BatchDesc batch;
-    batch.n = n;
-    batch.n_tiles_q = 0;
-    int max_q_tiles64 = 0;
-    for (int i = 0; i < n; ++i) {
-        DfaDesc& d = batch.d[i];
-        d = DfaDesc();
-        d.trans = e[i].trans;
-        d.tt = e[i].trans_t;
-        d.n_states = e[i].n_states;
-        d.q_stride = e[i].q_stride;
-        max_q_tiles64 = std::max(max_q_tiles64, (e[i].q_stride + 63) / 64);
-    }
-    if (e[0].narrow) transpose_kernel<uint16_t><<<dim3(max_q_tiles64, 4, n), kThreads, 0, stream>>>(batch);
-    else transpose_kernel<uint32_t><<<dim3(max_q_tiles64, 4, n), kThreads, 0, stream>>>(batch);
+    DfaDesc d = DfaDesc();
+    d.trans = e.trans;
+    d.tt = e.trans_t;
+    d.n_states = e.n_states;
+    d.q_stride = e.q_stride;
+    transpose_kernel<<<dim3((unsigned)(e.q_stride + 63) / 64, 4), kThreads, 0, stream>>>(d);
     TDFA_HIP(hipGetLastError());
     return TDFA_OK;
 }

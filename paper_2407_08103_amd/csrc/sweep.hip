@@ -670,7 +670,7 @@ int launch_compile_sweep(const CompileArgs& a, const CompileEntry& e, hipStream_
     const bool resume = ws.lists_ready && ws.sized && ws.buffers_sized;    // (see SweepWorkspace::lists_ready)
     ws.lists_ready = false;
     if (!resume) {
-        const int rc = launch_transpose(&e, 1, stream);
+        const int rc = launch_transpose(e, stream);
         if (rc != TDFA_OK) return rc;
     }
     const size_t col_bytes = sweep_column_lds_bytes(e.q_stride);

@@ -147,8 +147,8 @@ struct CompileArgs {
     int64_t row_words;
 };
 int launch_compile(const CompileArgs& a, hipStream_t stream);
-// The transposed offset-form tables of n automata of one width (compile.hip).
-int launch_transpose(const CompileEntry* e, int n, hipStream_t stream);
+// The transposed offset-form table of a narrow automaton (compile.hip).
+int launch_transpose(const CompileEntry& e, hipStream_t stream);
 // One narrow automaton by the level-by-level sweep (sweep.hip).  While the workspace is not fully
 // sized (e.sweep->sized / buffers_sized) only the kernels whose results size it are launched.
 int launch_compile_sweep(const CompileArgs& a, const CompileEntry& e, hipStream_t stream);
