@@ -328,7 +328,9 @@ compile_tile_kernel(BatchDesc batch,
         if (tid < G && q0 + tid * 64 < n_order) cls = (int32_t)group_class[q0 / 64 + tid];
         uint32_t sorted = (uint32_t)(tid & (kSortBlock - 1)), len = 0u, off = 0u;
         if (tid < T && t0 + tid < n_tokens) {
-            if (!SHIFT) sorted = (uint32_t)vsorted[t0 + tid];          // (the blocks of the order are not the tile's)
+            // (Under SHIFT the blocks of the order are not the tile's.  It is worth little: with the tokens of all tiles in the order of their
+            // ids 179 states x 2,000 tokens take 31 instead of 29 us, 5,387 x 128,256 586 instead of 599.)
+            if (!SHIFT) sorted = (uint32_t)vsorted[t0 + tid];
             len = vlen[t0 + tid];
             off = voff[t0 + tid];
         }
