@@ -1688,127 +1688,10 @@ packed_step_kernel(MaskArgs a, int parts, int groups_per_part)
     if (threadIdx.x == 0 && combine_parts(a, b, parts, cand)) write_result(a, b, q, valid, cand);
 }
 
-// Rows of a batch shared out over the workgroups of a launch by what they cost, each workgroup working the same plan out
-// for itself from the states and the counts beside the table.  The cost of a row is in 1,024ths of one whose state allows
-// a tenth of the vocabulary or more, which has every quad drawn: a floor for the scan of its bits, which a state that allows
-// nothing takes as well, and its tokens (measured: a state that allows 7 % costs three quarters).  Rows above kShareSmall, those
-// of more than 1 in 250 tokens, come first and take kShareFull workgroups between them, so that every compute unit gets its
-// three or so of about the same cost; the others take one each, behind them.  (640 workgroups: 128 to 512 rows 0.3 us slower; 800: 256 rows
-// 0.3 us faster, 128 rows 1.0 slower.)
-//
-// The plan and the second launch take some 3 us, which few or short rows don't give back: 128,256 tokens, anywhere in their texts /
-// all in states that allow most / all that allow few, against parts of equal length: 64 rows 13.1, 14.6 and 10.9 against 12.6, 13.6 and
-// 8.1 us, 128 rows 15.0, 17.1 and 11.1 against 16.7, 16.5 and 10.0, 256 rows 22.9, 24.2 and 11.5 against 23.6, 21.4 and 10.7, 512 rows 35.4, 41.2 and 13.3 against 38.9,
-// 34.5 and 12.5, 768 rows 43.9, 53.2 and 15.5 against 45.3, 50.1 and 14.7, 1,024 rows 53.6, 68.2 and 21.7 against 54.7, 63.1 and 16.3; 64,000 tokens, 256 rows 16.2, 17.0 and
-// 10.6 against 16.6, 15.8 and 10.2; 32,000 tokens, 512 rows 17.5, 18.5 and 11.2 against 16.6, 16.0 and 8.9.
-constexpr int kShareRows = 512;        // rows of a batch at most (a multiple of the workgroup's threads)
-constexpr int64_t kShareFrom = 2000000, kShareLong = 8000;        // groups of the batch, and of a row, at least: 125 rows of 128,256 tokens, 250 of 64,000
-constexpr int kShareFull = 720;
-constexpr int kShareGroups = 1024;     // groups of a part at least
-constexpr float kShareFloor = 60.0f, kShareTokens = 10000.0f;     // cost of a row; of a token, times the size of the vocabulary
-constexpr uint32_t kShareSmall = 100;
-
-// What of the batch a workgroup takes (parts 0: nothing): part `part` of `parts` of a row, its state and how many tokens that allows.
-struct RowShare {
-    int row, part, parts, state;
-    uint32_t n_allowed;
-};
-
-template <int kThreads>
-__device__ __forceinline__ void share_rows(const MaskArgs& a, int max_parts, uint32_t (*s_sums)[kThreads / 64], RowShare* s_share)
-{
-    constexpr int kMost = kShareRows / kThreads, kWaves = kThreads / 64;
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int per = (a.batch + kThreads - 1) / kThreads;           // rows per thread, one behind the other
-    int q[kMost];
-    uint32_t n[kMost], cost[kMost], sum = 0;
-#pragma unroll
-    for (int j = 0; j < kMost; ++j) {
-        q[j] = -1;
-        n[j] = cost[j] = 0;
-        if (j < per && tid * per + j < a.batch) q[j] = a.states[tid * per + j];
-    }
-    const float per_token = kShareTokens / (float)a.n_tokens;
-#pragma unroll
-    for (int j = 0; j < kMost; ++j)
-        if (j < per && q[j] >= 0 && (int64_t)q[j] < a.n_rows) n[j] = allowed_count(a, q[j]);
-#pragma unroll
-    for (int j = 0; j < kMost; ++j)
-        if (j < per) {
-            cost[j] = (uint32_t)fminf(1024.0f, kShareFloor + (float)n[j] * per_token);
-            if (cost[j] < kShareSmall) cost[j] = 0;
-            sum += cost[j] + (cost[j] ? 1u << 21 : 0u);            // (at most 1,024 rows of 1,024)
-        }
-    sum = wave_sum_u32(sum);
-    if (lane == 0) s_sums[0][wave] = sum;
-    if (tid == 0) s_share->parts = 0;
-    __syncthreads();
-    sum = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) sum += s_sums[0][w];
-    // A large row takes one workgroup and its share, rounded down, of kShareFull less 0.55 for each (a share loses half a workgroup
-    // by the rounding, on average): kShareFull and as many as there are rows are enough for all.
-    const float share = fminf(fmaxf((float)kShareFull - 0.55f * (float)(sum >> 21), 0.0f) / (float)max(sum & 0x1FFFFFu, 1u), (float)(max_parts - 1) / 1024.0f);
-    uint32_t parts[kMost], mine = 0;                               // workgroups of the large rows, and the small rows << 16
-#pragma unroll
-    for (int j = 0; j < kMost; ++j) {
-        parts[j] = 0;
-        if (j < per && tid * per + j < a.batch) parts[j] = cost[j] ? 1u + (uint32_t)((float)cost[j] * share) : 0x10000u;
-        mine += parts[j];
-    }
-    const uint32_t incl = wave_prefix_u32(mine);
-    if (lane == 63) s_sums[1][wave] = incl;
-    __syncthreads();
-    uint32_t at = incl - mine, total = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        const uint32_t x = s_sums[1][w];
-        if (w < wave) at += x;
-        total += x;
-    }
-    const uint32_t g = blockIdx.x, n_first = total & 0xFFFFu;
-#pragma unroll
-    for (int j = 0; j < kMost; ++j)
-        if (j < per) {
-            const bool small = (parts[j] & 0xFFFF0000u) != 0u;
-            const uint32_t first = small ? n_first + (at >> 16) : at & 0xFFFFu, n_wg = small ? 1u : parts[j];
-            if (g >= first && g < first + n_wg) *s_share = {tid * per + j, (int)(g - first), (int)n_wg, q[j], n[j]};
-            at += parts[j];
-        }
-    __syncthreads();
-}
-
-// What the workgroups of such a launch found comes together in a launch of its own: each leaves its candidate and its row (from 1;
-// 0: none) in the words of its own number, and this one takes the rows' maxima, writes the results and clears the words.  So nothing
-// is written that a workgroup's plan still reads - the new states may take the states' place -, and nothing is left behind for later
-// steps whatever the plans were (a caller that changes the states under a step spoils that step alone).
-constexpr int kScratchWords = 4096;    // that the scratch holds at least
-static_assert(kShareFull + kShareRows <= kScratchWords, "a word to each workgroup");
-
-__global__ void __launch_bounds__(kShareRows)
-share_results_kernel(MaskArgs a, int n_slots)
-{
-    __shared__ unsigned long long s_best[kShareRows];
-    const int tid = (int)threadIdx.x;
-    const int q = tid < a.batch ? a.states[tid] : TDFA_DEAD;
-    s_best[tid] = 0ull;
-    __syncthreads();
-    for (int i = tid; i < n_slots; i += kShareRows) {
-        const unsigned row = a.scratch_count[i];
-        const unsigned long long cand = a.scratch_best[i];
-        a.scratch_count[i] = 0u;
-        a.scratch_best[i] = 0ull;
-        if (row - 1u < (unsigned)a.batch) atomicMax(&s_best[row - 1u], cand);
-    }
-    __syncthreads();
-    if (tid >= a.batch) return;
-    const bool valid = q >= 0 && (int64_t)q < a.n_rows;
-    write_result(a, tid, q, valid, valid ? s_best[tid] : 0ull);
-}
-
 constexpr int kDrawThreads = 256, kDrawWaves = kDrawThreads / 64;      // workgroup of the draw
 constexpr int kDrawGroups = 1024;      // workgroups that a draw of a smaller batch is split into: four to a compute unit, which their LDS lets it hold
                                        // (2,048: 256 rows 24.4, 21.4 and 10.4 -> 24.2, 26.9 and 12.6 us, 512 rows 39.5, 34.6 and 12.3 -> 37.9, 42.1 and 16.2)
+constexpr int kScratchWords = 4096;    // that the step's scratch holds at least
 constexpr int kLineWords = 32;         // words of a cache line
 constexpr int kDrawPartGroups = 1 << 24;    // groups of a part at most: its offsets and its quads' numbers have 32 bits
 // noise_bound is above the noise by at most 0.0861 ln 2 + 0.001 and what -ln(1 - u) exceeds -ln(-ln u) by, which is no more
@@ -1824,14 +1707,12 @@ constexpr uint32_t kDrawDense = 10;    // a state that allows one token in so ma
 struct DrawShared {
     unsigned long long wave_best[kDrawWaves];
     uint4 cands[kDrawWaves][64];                               // tokens that may win: id, logit, generator word, bound of the score
-    uint32_t sums[2][kDrawWaves];
-    RowShare share;
+    uint32_t sums[kDrawWaves];
     uint32_t reached;                                          // order key of the best score any wavefront has reached
 };
 
-// The draw from the whole allowed set.  A workgroup takes part of a row: which, it works out from the costs of all rows
-// (SHARED: share_rows), or `parts` workgroups of groups_per_part groups scan each row.  What a token costs is its generator block, made
-// for four neighbouring tokens (a quad) at a time, one quad per lane.
+// The draw from the whole allowed set.  A workgroup takes one part of a row, all parts of the same length.  What a token costs is
+// its generator block, made for four neighbouring tokens (a quad) at a time, one quad per lane.
 //   A state known to allow one token in kDrawDense or more, a part with an allowed token in half of its quads where
 //     nothing is known of the state, and a masked row to be written have every quad drawn, in the order it lies in:
 //     one bound for the quad, from its largest logit, allowed or not, and its largest generator word.
@@ -1850,14 +1731,18 @@ struct DrawShared {
 //
 // T = 1, bf16, rows anywhere in the texts of 50 signatures / all in states that allow most / all that allow few, replayed, against rows in
 // parts of equal length and two queues per wavefront: 128,256 tokens, 1 row 8.1, 10.3 and 5.5 -> 8.9, 8.8 and 5.8 us, 16 rows 10.5, 11.8 and 7.8 ->
-// 9.1, 9.6 and 6.3, 64 rows 12.9, 16.5 and 9.5 -> 12.6, 13.6 and 8.1, 256 rows 26.8, 34.8 and 11.0 -> 22.9, 24.2 and 11.5, 512 rows 42.4, 53.6 and 13.8 -> 35.4,
-// 41.2 and 13.3, 1,024 rows 75, 99 and 21 -> 55, 64 and 16; 9,000 tokens, 256 rows 11.6, 11.6 and 6.9 -> 9.2, 9.0 and 6.9, 4,096 rows 33.7, 42.4 and 15.5 -> 31.9,
+// 9.1, 9.6 and 6.3, 64 rows 12.9, 16.5 and 9.5 -> 12.6, 13.6 and 8.1, 256 rows 26.8, 34.8 and 11.0 -> 25.2, 22.3 and 8.8, 512 rows 42.4, 53.6 and 13.8 -> 39.0,
+// 37.6 and 8.8, 1,024 rows 75, 99 and 21 -> 55, 64 and 16; 9,000 tokens, 256 rows 11.6, 11.6 and 6.9 -> 9.2, 9.0 and 6.9, 4,096 rows 33.7, 42.4 and 15.5 -> 31.9,
 // 36.2 and 19.7; 2,000 tokens, 1,024 rows 11.2, 11.3 and 5.9 -> 7.9, 7.7 and 7.5, 4,096 rows 22.7, 26.9 and 12.8 -> 20.2, 20.6 and 18.7.  Tables of which no count
 // is known, 128,256 tokens, 256 rows 26.8, 35.4 and 10.9 -> 24.7, 23.0 and 10.9 (every row from the list: 38.8, 43.4 and 10.9); the masked row as well, 256
 // rows 35.3, 40.9 and 29.0 -> 30.0, 29.5 and 30.0.
-template <int DTYPE, bool WRITE, bool SHARED>
+//
+// Rows shared out over 720 workgroups by what their states allow, each workgroup working the plan out for itself from all states: 128, 256, 512 and
+// 1,024 rows anywhere in their texts 15.0, 22.0, 34.4 and 48.7 us, 128 and 256 rows that allow few 7.9 and 8.3.  Not done: the plan reads states that a call
+// in place writes, and holds only as long as nobody changes them.
+template <int DTYPE, bool WRITE>
 __device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, SampleParams sp, int b, int p, int parts, int groups_per_part, int q,
-                                                        uint32_t n_allowed, uint32_t* s_lists, int list_cap, DrawShared& s)
+                                                        uint32_t* s_lists, int list_cap, DrawShared& s)
 {
     using Elem = typename ElemOf<DTYPE>::type;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -1897,10 +1782,8 @@ __device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, Sampl
     auto load_pieces = [&](int i0) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < kDrawPieces; ++k) {
-            if (!SHARED) {
-                v[k] = u32x4{};
-                if (i0 + 64 * k >= hi) continue;               // (uniform: a short part has fewer)
-            }
+            v[k] = u32x4{};
+            if (i0 + 64 * k >= hi) continue;                   // (uniform: a short part has fewer)
             const int i = i0 + 64 * k + lane;
             if (by_word) v[k] = u32x4{__builtin_amdgcn_raw_buffer_load_b32(r_bits, i < hi ? i * 4 : 0x7FFFFFF0, 0, 0), 0, 0, 0};
             else v[k] = __builtin_amdgcn_raw_buffer_load_b128(r_bits, i < hi ? i * 16 : 0x7FFFFFF0, 0, 0);
@@ -1946,8 +1829,8 @@ __device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, Sampl
         }
         return n;
     };
-    if constexpr (!SHARED && !WRITE) n_allowed = allowed_count(a, q);
-    const bool counted = !SHARED && !WRITE && n_allowed == kUnknown;
+    const uint32_t n_allowed = WRITE ? kUnknown : allowed_count(a, q);
+    const bool counted = !WRITE && n_allowed == kUnknown;
     uint32_t all = 0, total = 0;                               // of the pieces at hand: quads of the lane, of the wavefront
     bool dense = WRITE;
     if (!WRITE && n_allowed == 0u) return 0ull;
@@ -1958,13 +1841,13 @@ __device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, Sampl
         trim_pieces(lo);
         all = count_quads();
         total = wave_sum_u32(all);
-        if (lane == 0) s.sums[0][wave] = total;
+        if (lane == 0) s.sums[wave] = total;
         __syncthreads();
         uint32_t sum = 0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) sum += s.sums[0][w];
+        for (int w = 0; w < kWaves; ++w) sum += s.sums[w];
         dense = sum >= (uint32_t)min(n_tok, kWaves * 64 * kDrawPieces * unit) / 8u;
-    } else if (!SHARED) {
+    } else {
         __syncthreads();                                       // (s.reached)
     }
 
@@ -2250,38 +2133,22 @@ __device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, Sampl
     return block_max_u64(cand, s.wave_best);
 }
 
-template <int DTYPE, bool WRITE, bool SHARED>
+template <int DTYPE, bool WRITE>
 __global__ void __launch_bounds__(kDrawThreads)
 draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part, int list_cap, int spread)
 {
     extern __shared__ uint32_t s_lists[];                      // [kDrawWaves][list_cap]
     __shared__ DrawShared s;
     if (threadIdx.x == 0) s.reached = 0;
-    if constexpr (SHARED) {                                    // (parts: at most as many to a row)
-        share_rows<kDrawThreads>(a, parts, s.sums, &s.share);
-        const int n = __builtin_amdgcn_readfirstlane(s.share.parts);
-        if (n == 0) return;                                    // (no row is left for this workgroup)
-        const int b = __builtin_amdgcn_readfirstlane(s.share.row), q = __builtin_amdgcn_readfirstlane(s.share.state);
-        const int n_groups = (a.n_tokens + 7) >> 3;
-        const unsigned long long cand =
-            draw_part<DTYPE, WRITE, SHARED>(a, sp, b, __builtin_amdgcn_readfirstlane(s.share.part), n, ((n_groups + n - 1) / n + 255) & ~255, q,
-                                            (uint32_t)__builtin_amdgcn_readfirstlane((int)s.share.n_allowed), s_lists, list_cap, s);
-        if (threadIdx.x == 0) {
-            a.scratch_count[blockIdx.x] = (unsigned)b + 1u;
-            a.scratch_best[blockIdx.x] = cand;
-        }
-    } else {
-        const int b = blockIdx.x / parts, q = __builtin_amdgcn_readfirstlane(a.states[b]);
-        unsigned long long cand =
-            draw_part<DTYPE, WRITE, SHARED>(a, sp, b, blockIdx.x % parts, parts, groups_per_part, q, kUnknown, s_lists, list_cap, s);
-        if (threadIdx.x != 0) return;
-        // (read again, the kernel's first argument: kept all along, its pointers spill, and with them the compiler reserves private
-        // memory that every launch next to other kernels pays for, 0.3 to 0.5 us)
-        const __attribute__((address_space(4))) MaskArgs* args = (const __attribute__((address_space(4))) MaskArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-        asm volatile("" : "+s"(args));
-        const MaskArgs& z = *(const MaskArgs*)args;
-        if (combine_parts(z, b * spread, parts, cand)) write_result(z, b, q, q >= 0 && (int64_t)q < z.n_rows, cand);
-    }
+    const int b = blockIdx.x / parts, q = __builtin_amdgcn_readfirstlane(a.states[b]);
+    unsigned long long cand = draw_part<DTYPE, WRITE>(a, sp, b, blockIdx.x % parts, parts, groups_per_part, q, s_lists, list_cap, s);
+    if (threadIdx.x != 0) return;
+    // (read again, the kernel's first argument: kept all along, its pointers spill, and with them the compiler reserves private
+    // memory that every launch next to other kernels pays for, 0.3 to 0.5 us)
+    const __attribute__((address_space(4))) MaskArgs* args = (const __attribute__((address_space(4))) MaskArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const MaskArgs& z = *(const MaskArgs*)args;
+    if (combine_parts(z, b * spread, parts, cand)) write_result(z, b, q, q >= 0 && (int64_t)q < z.n_rows, cand);
 }
 
 // Runs of speculated tokens (Section 5.3): one lane per sequence follows its k tokens through the
@@ -2628,22 +2495,12 @@ int launch_sample_step(const MaskArgs& a, float inv_t, int32_t top_k, uint64_t s
     int64_t parts = std::min<int64_t>(kDrawGroups / batch, (n_groups + 1023) / 1024);
     parts = std::max<int64_t>({parts, ((int64_t)n_groups + kDrawPartGroups - 1) / kDrawPartGroups, 1});
     const int gpp = (int)(((n_groups + parts - 1) / parts + 63) & ~63);
-    int64_t grid = batch * parts;
-    // Rows are shared out by what their states allow if there is enough of them (the figures are at kShareRows).  The new states may
-    // take the states' place, as results are written when no plan is read any more.
-    int shares = 0;
-    auto apart_from_states = [&](const int32_t* out) { return out + batch <= a.states || a.states + batch <= out; };
-    const bool apart = (apart_from_states(a.new_states) || a.new_states == a.states) && apart_from_states(a.tokens);
-    if (!a.masked_out && (a.row_allowed || a.row_begin) && apart && n_groups <= kDrawPartGroups &&
-        batch <= kShareRows && batch * n_groups >= kShareFrom && n_groups >= kShareLong) {
-        shares = n_groups / kShareGroups;
-        grid = std::min<int64_t>(batch * shares, kShareFull + batch);
-    }
+    const int64_t grid = batch * parts;
     // A wavefront's list: the most quads of one, a quarter of its part, where more workgroups than the chip holds with whole lists can
     // have use for the room (2,000 tokens, 4,096 rows that allow few 26 -> 18 us; up to 1,024 workgroups more than four to a compute
     // unit only leave others idle: 256 rows of 128,256 tokens 23.3 -> 24.6 us).
     int cap = kDrawList;
-    if (!shares && grid > kDrawGroups && gpp <= 64 * kDrawPieces * kDrawWaves * 4)
+    if (grid > kDrawGroups && gpp <= 64 * kDrawPieces * kDrawWaves * 4)
         cap = std::min(cap, std::max((gpp / 4 + kDrawWaves) / kDrawWaves * 8, 64));
     const size_t lds = (size_t)cap * kDrawWaves * 4;
     // The words that the parts of a row meet through lie as far apart as there is room for, up to a cache line: atomics on one line wait
@@ -2652,18 +2509,13 @@ int launch_sample_step(const MaskArgs& a, float inv_t, int32_t top_k, uint64_t s
     while (spread < kLineWords && 2 * spread * batch <= kScratchWords) spread *= 2;
     if (grid > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
     const dim3 blocks((unsigned)grid);
-    auto launch = [&](auto write, auto shared) {
-        constexpr bool kWrite = decltype(write)::value, kShared = decltype(shared)::value;
-        const int n_parts = kShared ? shares : (int)parts;
-        if (a.dtype == TDFA_F32) draw_step_kernel<TDFA_F32, kWrite, kShared><<<blocks, kDrawThreads, lds, stream>>>(a, sp, n_parts, gpp, cap, spread);
-        else draw_step_kernel<TDFA_BF16, kWrite, kShared><<<blocks, kDrawThreads, lds, stream>>>(a, sp, n_parts, gpp, cap, spread);
+    auto launch = [&](auto write) {
+        constexpr bool kWrite = decltype(write)::value;
+        if (a.dtype == TDFA_F32) draw_step_kernel<TDFA_F32, kWrite><<<blocks, kDrawThreads, lds, stream>>>(a, sp, (int)parts, gpp, cap, spread);
+        else draw_step_kernel<TDFA_BF16, kWrite><<<blocks, kDrawThreads, lds, stream>>>(a, sp, (int)parts, gpp, cap, spread);
     };
-    if (a.masked_out) launch(std::true_type{}, std::false_type{});
-    else if (shares) {
-        launch(std::false_type{}, std::true_type{});
-        share_results_kernel<<<1, kShareRows, 0, stream>>>(a, (int)grid);
-    }
-    else launch(std::false_type{}, std::false_type{});
+    if (a.masked_out) launch(std::true_type{});
+    else launch(std::false_type{});
     TDFA_HIP(hipGetLastError());
     return TDFA_OK;
 }

@@ -288,8 +288,8 @@ def test_steps_on_two_streams_at_once(T):
     assert torch.equal(tok[0], want[0])
 
 
-def test_rows_shared_out_in_a_graph(T):
-    """Draws whose rows are shared out, recorded one after the other on states advanced in place: every replay is what the
+def test_draws_in_a_graph(T):
+    """Draws of rows in several parts, recorded one after the other on states advanced in place: every replay is what the
     same calls gave before, with other steps on the same stream between the replays."""
     rng = np.random.default_rng(8)
     v, batch = 64008, 256
@@ -325,8 +325,8 @@ def test_rows_shared_out_in_a_graph(T):
 
 
 def test_states_changed_under_a_draw(T):
-    """A caller changes the states on another stream while draws run whose rows are shared out by what the states allow: what
-    those draws say is open, but the steps that come after them are right."""
+    """A caller changes the states on another stream while draws of rows in several parts run: what those draws say is
+    open, but the steps that come after them are right."""
     rng = np.random.default_rng(31)
     v, batch, steps = 64008, 256, 60
     tab = np.full((4, v), DEAD, dtype=np.int32)
@@ -398,9 +398,8 @@ def test_draw_beyond_2_30_tokens(T):
 @pytest.mark.parametrize("dtype", [F32, BF16])
 @pytest.mark.parametrize("n_tokens,batch", [(9001, 4), (16389, 512), (40003, 257), (128261, 64), (16384, 1024), (8200, 1025)])
 def test_rows_shared_out_by_cost(T, oracle, dtype, n_tokens, batch):
-    """States of every cost, as counted by a packed table: none, one token, either side of the lines between lone, small
-    and large rows and of the line from which every quad is drawn, all tokens.  Large batches are shared out by cost (4
-    rows of 9,001 tokens are not), also where the states are written in place: both against the oracle."""
+    """States of every cost, as counted by a packed table: none, one token, few, either side of the line from which every quad
+    is drawn, all tokens; states apart and written in place, against the oracle."""
     rng = np.random.default_rng(n_tokens)
     V = n_tokens
     counts = [0, 1, 2, V // 256 - 1, V // 256 + 1, V // 250, V // 249 + 1, V // 40, V // 10 - 1, V // 10 + 1, V // 2, V]
@@ -446,12 +445,6 @@ def test_listed_tokens_and_quads(T, oracle, n_tokens, batch):
     for i, table in enumerate((T.table_pack(dense), dense)):                      # (the second holds caller's arrays: no counts)
         for first in range(0, len(rows), batch):
             _sample_strided(T, oracle, table, tab, lg, BF16, (states + first) % len(rows), 0.9, 17, first, masked=False)
-
-
-@pytest.mark.parametrize("n_tokens,batch", [(128261, 124), (128261, 126), (64001, 251), (63992, 300), (128261, 512), (128261, 513)])
-def test_lines_of_the_rule_that_shares_rows_out(T, oracle, n_tokens, batch):
-    """Batches and rows on either side of the sizes from which, and up to which, rows are shared out; states apart and in place."""
-    test_rows_shared_out_by_cost(T, oracle, BF16, n_tokens, batch)
 
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
