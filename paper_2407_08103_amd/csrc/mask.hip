@@ -1689,8 +1689,8 @@ packed_step_kernel(MaskArgs a, int parts, int groups_per_part)
 }
 
 constexpr int kDrawThreads = 256, kDrawWaves = kDrawThreads / 64;      // workgroup of the draw
-constexpr int kDrawGroups = 1024;      // workgroups that a draw of a smaller batch is split into: four to a compute unit, which their LDS lets it hold
-                                       // (2,048: 256 rows 24.4, 21.4 and 10.4 -> 24.2, 26.9 and 12.6 us, 512 rows 39.5, 34.6 and 12.3 -> 37.9, 42.1 and 16.2)
+constexpr int kDrawGroups = 1024;      // workgroups that a draw of a smaller batch is split into: four to a compute unit (1,536: 128 and 256 rows anywhere in
+                                       // their texts 15.5 and 23.1 -> 15.8 and 23.8 us, all wide 16.1 and 22.3 -> 17.4 and 24.0; 2,048: 16.7, 23.4, 19.6 and 27.1)
 constexpr int kScratchWords = 4096;    // that the step's scratch holds at least
 constexpr int kLineWords = 32;         // words of a cache line
 constexpr int kDrawPartGroups = 1 << 24;    // groups of a part at most: its offsets and its quads' numbers have 32 bits
@@ -1701,8 +1701,9 @@ constexpr uint32_t kTightWord = 0xE6666800u;    // generator words from here on 
 constexpr float kBoundSlack = 0.2f, kTightScore = 32768.0f;
 constexpr int kDrawList = 2048;        // quads that a wavefront lists at once
 constexpr int kDrawPieces = 4;         // 16-byte pieces of allowed bits that a lane has in flight
-constexpr uint32_t kDrawDense = 10;    // a state that allows one token in so many or more has every quad drawn (7: the same within 0.3 us; 14: 256 rows 1.0 us
-                                       // faster, 128 rows 0.7, 512 rows 2.1 and 1,024 rows 6 us slower)
+constexpr int kWordGroups = 64 * kDrawPieces * kDrawWaves * 4;     // groups of a part whose allowed bits are read by words of 32 tokens, at most
+constexpr uint32_t kDrawDense = 10;    // a state that allows one token in so many or more has every quad drawn (7: the same within 0.5 us; 14: 256 rows 0.9 us
+                                       // slower, 128 rows 1.4, 512 rows 4.5 and 1,024 rows 4)
 
 struct DrawShared {
     unsigned long long wave_best[kDrawWaves];
@@ -1725,23 +1726,24 @@ struct DrawShared {
 //
 // Bound by the instructions issued where states allow many tokens: 54 per quad, 18 of them 64-bit products, at 1.9 to 2.4
 // ns per instruction and SIMD with four wavefronts (a wavefront alone gets half of that), so 256 rows of 128,256
-// tokens all drawn take 15 us of every SIMD; and by some 20 dependent steps, 6 us, where states allow few.  The scheduler
-// serves the oldest wavefront first, so that the last one of a SIMD would run alone: a wavefront lowers its priority as it
-// gets on.  (Without: 256 rows 22.1 and 26.2 instead of 20.9 and 23.7 us.)
+// tokens all drawn take 15 us of every SIMD; and by some 20 dependent steps, 5 us, where states allow few.  The scheduler
+// serves the oldest wavefront first, so that the last one of a SIMD would run alone: a wavefront that draws every quad lowers its
+// priority as it gets on.  (Without: 256 rows 22.1 and 26.2 instead of 20.9 and 23.7 us.)  One that works from a list mostly waits, for
+// memory and for itself, so it goes first (128, 256 and 512 rows anywhere in their texts 15.5, 23.1 and 34.0 -> 14.2, 21.4 and 32.1 us).
 //
 // T = 1, bf16, rows anywhere in the texts of 50 signatures / all in states that allow most / all that allow few, replayed, against rows in
-// parts of equal length and two queues per wavefront: 128,256 tokens, 1 row 8.1, 10.3 and 5.5 -> 8.9, 8.8 and 5.8 us, 16 rows 10.5, 11.8 and 7.8 ->
-// 9.1, 9.6 and 6.3, 64 rows 12.9, 16.5 and 9.5 -> 12.6, 13.6 and 8.1, 256 rows 26.8, 34.8 and 11.0 -> 25.2, 22.3 and 8.8, 512 rows 42.4, 53.6 and 13.8 -> 39.0,
-// 37.6 and 8.8, 1,024 rows 75, 99 and 21 -> 55, 64 and 16; 9,000 tokens, 256 rows 11.6, 11.6 and 6.9 -> 9.2, 9.0 and 6.9, 4,096 rows 33.7, 42.4 and 15.5 -> 31.9,
-// 36.2 and 19.7; 2,000 tokens, 1,024 rows 11.2, 11.3 and 5.9 -> 7.9, 7.7 and 7.5, 4,096 rows 22.7, 26.9 and 12.8 -> 20.2, 20.6 and 18.7.  Tables of which no count
-// is known, 128,256 tokens, 256 rows 26.8, 35.4 and 10.9 -> 24.7, 23.0 and 10.9 (every row from the list: 38.8, 43.4 and 10.9); the masked row as well, 256
-// rows 35.3, 40.9 and 29.0 -> 30.0, 29.5 and 30.0.
+// parts of equal length and two queues per wavefront: 128,256 tokens, 1 row 10.2, 10.1 and 5.8 -> 8.4, 8.5 and 5.9 us, 16 rows 10.6, 11.6 and 7.1 ->
+// 8.9, 9.3 and 5.4, 64 rows 14.3, 16.1 and 9.1 -> 12.2, 13.1 and 6.9, 128 rows 19.0, 24.2 and 11.2 -> 14.1, 16.1 and 7.0, 256 rows 27.8, 35.1 and 10.8 -> 21.4, 21.6
+// and 7.2, 512 rows 43.0, 54.1 and 12.7 -> 32.5, 40.4 and 9.9, 1,024 rows 77.7, 94.5 and 17.1 -> 56.1, 62.0 and 10.7; 9,000 tokens, 256 rows 11.0, 11.1 and 6.2 ->
+// 9.1, 9.2 and 5.8, 4,096 rows 34.0, 41.8 and 13.9 -> 29.0, 33.8 and 13.9; 2,000 tokens, 1,024 rows 10.8, 11.2 and 5.4 -> 7.4, 7.4 and 6.0, 4,096 rows 22.9, 27.6 and
+// 12.2 -> 17.7, 19.1 and 13.3.  States advanced in place take as long, and tables of which no count is known, 256 rows of 128,256 tokens, 27.4, 34.9
+// and 10.9 -> 21.4, 22.0 and 7.3 (every row from the list: 38.5, 43.6 and 10.5); the masked row as well, 256 rows 35.8, 40.1 and 28.3 -> 29.6, 29.6 and 29.9.
 //
 // Rows shared out over 720 workgroups by what their states allow, each workgroup working the plan out for itself from all states: 128, 256, 512 and
 // 1,024 rows anywhere in their texts 15.0, 22.0, 34.4 and 48.7 us, 128 and 256 rows that allow few 7.9 and 8.3.  Not done: the plan reads states that a call
 // in place writes, and holds only as long as nobody changes them.
-template <int DTYPE, bool WRITE>
-__device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, SampleParams sp, int b, int p, int parts, int groups_per_part, int q,
+template <int DTYPE, bool WRITE, bool WORDS>
+__device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, SampleParams sp, int b, int p, int groups_per_part, int q,
                                                         uint32_t* s_lists, int list_cap, DrawShared& s)
 {
     using Elem = typename ElemOf<DTYPE>::type;
@@ -1773,20 +1775,30 @@ __device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, Sampl
     // The allowed bits by wavefronts, each a stretch of its own: a lane reads those of 128 tokens at a time, or of 32 in a part of
     // 4,096 groups or less, so that every lane has some; kDrawPieces such pieces in flight, the first ones requested with the
     // count of the state and used unless every quad is drawn.
-    const bool by_word = n_part <= 64 * kDrawPieces * kWaves * 4;
+    // (WORDS: no part of the launch is longer; 79 vector registers instead of 114, so that a SIMD holds six wavefronts: 16 rows that allow
+    // few 6.0 -> 5.5 us, 256 rows anywhere in their texts 24.8 -> 23.1, 2,000 tokens, 4,096 rows that allow few 17.7 -> 13.3.)
+    constexpr int kDims = WORDS ? 1 : 4;
+    const bool by_word = WORDS || n_part <= kWordGroups;
     const int unit = by_word ? 32 : 128, n_units = (n_tok + unit - 1) / unit, per_wave = (n_units + kWaves - 1) / kWaves;
     const int lo = wave * per_wave, hi = min(n_units, lo + per_wave);
     const __amdgpu_buffer_rsrc_t r_bits = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t*>(bits), 0, (int)min(a.row_words * 4 - g_lo, (int64_t)((n_part + 15) & ~15)), kRawBuffer);
-    u32x4 v[kDrawPieces];
+    uint32_t v[kDrawPieces][kDims];
     auto load_pieces = [&](int i0) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < kDrawPieces; ++k) {
-            v[k] = u32x4{};
+#pragma unroll
+            for (int d = 0; d < kDims; ++d) v[k][d] = 0u;
             if (i0 + 64 * k >= hi) continue;                   // (uniform: a short part has fewer)
             const int i = i0 + 64 * k + lane;
-            if (by_word) v[k] = u32x4{__builtin_amdgcn_raw_buffer_load_b32(r_bits, i < hi ? i * 4 : 0x7FFFFFF0, 0, 0), 0, 0, 0};
-            else v[k] = __builtin_amdgcn_raw_buffer_load_b128(r_bits, i < hi ? i * 16 : 0x7FFFFFF0, 0, 0);
+            if constexpr (!WORDS) {
+                if (!by_word) {
+                    const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r_bits, i < hi ? i * 16 : 0x7FFFFFF0, 0, 0);
+                    v[k][0] = x.x, v[k][1] = x.y, v[k][2] = x.z, v[k][3] = x.w;
+                    continue;
+                }
+            }
+            v[k][0] = __builtin_amdgcn_raw_buffer_load_b32(r_bits, i < hi ? i * 4 : 0x7FFFFFF0, 0, 0);
         }
     };
     // What lies behind the row's last token leaves the pieces.
@@ -1796,7 +1808,7 @@ __device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, Sampl
         for (int k = 0; k < kDrawPieces; ++k) {
             const int left = n_tok - (i0 + 64 * k + lane) * unit;
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
+            for (int d = 0; d < kDims; ++d) {
                 const uint32_t rem = (uint32_t)min(max(left - 32 * d, 0), 32);
                 v[k][d] &= (uint32_t)((1ull << rem) - 1ull);
             }
@@ -1807,8 +1819,10 @@ __device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, Sampl
         uint32_t n = 0;
 #pragma unroll
         for (int k = 0; k < kDrawPieces; ++k) {
-            mine[k] = (uint32_t)__builtin_popcount(v[k][0]);
-            if (!by_word) mine[k] += (uint32_t)__builtin_popcount(v[k][1]) + (uint32_t)__builtin_popcount(v[k][2]) + (uint32_t)__builtin_popcount(v[k][3]);
+            mine[k] = 0;
+#pragma unroll
+            for (int d = 0; d < kDims; ++d)
+                if (d == 0 || !by_word) mine[k] += (uint32_t)__builtin_popcount(v[k][d]);
             n += mine[k];
         }
         return n;
@@ -1819,7 +1833,7 @@ __device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, Sampl
         for (int k = 0; k < kDrawPieces; ++k) {
             mine[k] = 0;
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
+            for (int d = 0; d < kDims; ++d) {
                 if (d != 0 && by_word) continue;
                 uint32_t x = v[k][d] | v[k][d] >> 1;
                 x = (x | x >> 2) & 0x11111111u;
@@ -2079,7 +2093,7 @@ __device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, Sampl
         }
     } else {
         // What is allowed is listed: single tokens if a wavefront's pieces hold no more of them than it has lanes, else quads.
-        if (parts == 1) __builtin_amdgcn_s_setprio(3);
+        __builtin_amdgcn_s_setprio(3);
         for (int i0 = lo; i0 < hi; i0 += 64 * kDrawPieces) {
             if (i0 != lo) load_pieces(i0);
             if (i0 != lo || !counted) {
@@ -2103,26 +2117,31 @@ __device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, Sampl
                 const uint32_t incl = wave_prefix_u32(here);
                 const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
                 uint32_t at = incl - here;
+                auto list_pieces = [&](auto tokens) __attribute__((always_inline)) {
+                    constexpr bool kTokens = decltype(tokens)::value;
 #pragma unroll
-                for (int k = 0; k < kDrawPieces; ++k) {
-                    if ((rounds != 1 && k != r) || __builtin_amdgcn_ballot_w64(mine[k] != 0) == 0) continue;
-                    const uint32_t first = (uint32_t)((i0 + 64 * k + lane) * unit);          // token
+                    for (int k = 0; k < kDrawPieces; ++k) {
+                        if ((rounds != 1 && k != r) || __builtin_amdgcn_ballot_w64(mine[k] != 0) == 0) continue;
+                        const uint32_t first = (uint32_t)((i0 + 64 * k + lane) * (kTokens ? unit : unit >> 2));
 #pragma unroll
-                    for (int d = 0; d < 4; ++d) {
-                        if (d != 0 && by_word) continue;
-                        uint32_t rest = v[k][d];
-                        while (rest) {
-                            const uint32_t at_bit = (uint32_t)__builtin_ctz(rest), t = first + 32u * (uint32_t)d + at_bit;
-                            if (single) {
-                                list[at++] = t;
-                                rest &= rest - 1u;
-                            } else {
-                                list[at++] = t >> 2 << 4 | (rest >> (at_bit & 28u) & 15u);
-                                rest &= ~(15u << (at_bit & 28u));
+                        for (int d = 0; d < kDims; ++d) {
+                            if (d != 0 && by_word) continue;
+                            uint32_t rest = v[k][d];
+                            while (rest) {
+                                const uint32_t bit = (uint32_t)__builtin_ctz(rest), nib = bit & 28u;
+                                if constexpr (kTokens) {
+                                    list[at++] = first + 32u * (uint32_t)d + bit;
+                                    rest &= rest - 1u;
+                                } else {
+                                    list[at++] = (first + 8u * (uint32_t)d + (nib >> 2)) << 4 | (rest >> nib & 15u);
+                                    rest &= ~(15u << nib);
+                                }
                             }
                         }
                     }
-                }
+                };
+                if (single) list_pieces(std::true_type{});
+                else list_pieces(std::false_type{});
                 if (single) draw_tokens(n);
                 else draw_list(n);
             }
@@ -2133,15 +2152,15 @@ __device__ __forceinline__ unsigned long long draw_part(const MaskArgs& a, Sampl
     return block_max_u64(cand, s.wave_best);
 }
 
-template <int DTYPE, bool WRITE>
-__global__ void __launch_bounds__(kDrawThreads)
+template <int DTYPE, bool WRITE, bool WORDS>
+__global__ void __launch_bounds__(kDrawThreads, WORDS || WRITE ? 6 : 4)
 draw_step_kernel(MaskArgs a, SampleParams sp, int parts, int groups_per_part, int list_cap, int spread)
 {
     extern __shared__ uint32_t s_lists[];                      // [kDrawWaves][list_cap]
     __shared__ DrawShared s;
     if (threadIdx.x == 0) s.reached = 0;
     const int b = blockIdx.x / parts, q = __builtin_amdgcn_readfirstlane(a.states[b]);
-    unsigned long long cand = draw_part<DTYPE, WRITE>(a, sp, b, blockIdx.x % parts, parts, groups_per_part, q, s_lists, list_cap, s);
+    unsigned long long cand = draw_part<DTYPE, WRITE, WORDS>(a, sp, b, blockIdx.x % parts, groups_per_part, q, s_lists, list_cap, s);
     if (threadIdx.x != 0) return;
     // (read again, the kernel's first argument: kept all along, its pointers spill, and with them the compiler reserves private
     // memory that every launch next to other kernels pays for, 0.3 to 0.5 us)
@@ -2489,19 +2508,27 @@ int launch_sample_step(const MaskArgs& a, float inv_t, int32_t top_k, uint64_t s
         TDFA_HIP(hipGetLastError());
         return TDFA_OK;
     }
-    // Workgroups of 256 threads, about as many as the chip holds (rows in parts of at least 1,024 groups).
+    // Workgroups of 256 threads, kDrawGroups of them (rows in parts of at least 1,024 groups), and up to twice as many where parts whose
+    // bits are read by words take that: anywhere in the texts / all wide / all few, 384 rows of 128,256 tokens 31.5, 30.7 and 7.9 -> 25.7,
+    // 30.1 and 8.1 us, 512 rows 38.3, 37.7 and 8.7 -> 32.6, 41.0 and 9.9, 256 of 256,000 37.2, 38.5 and 8.6 -> 34.1, 42.0 and 9.8.  Not for rows
+    // that are not cut otherwise: 768 rows of 128,256 45.8, 53.4 and 9.4 -> 45.1, 56.9 and 12.6, 1,024 rows of 64,000 32.8, 38.1 and 7.9 -> 35.6, 44.1 and 10.2.
     const int n_groups = (a.n_tokens + 7) >> 3;
     const int64_t batch = a.batch;
     int64_t parts = std::min<int64_t>(kDrawGroups / batch, (n_groups + 1023) / 1024);
+    const int64_t by_words = ((int64_t)n_groups + kWordGroups - 1) / kWordGroups;
+    if (parts > 1 && !a.masked_out && batch * by_words <= 2 * kDrawGroups) parts = std::max(parts, by_words);
     parts = std::max<int64_t>({parts, ((int64_t)n_groups + kDrawPartGroups - 1) / kDrawPartGroups, 1});
     const int gpp = (int)(((n_groups + parts - 1) / parts + 63) & ~63);
     const int64_t grid = batch * parts;
-    // A wavefront's list: the most quads of one, a quarter of its part, where more workgroups than the chip holds with whole lists can
-    // have use for the room (2,000 tokens, 4,096 rows that allow few 26 -> 18 us; up to 1,024 workgroups more than four to a compute
-    // unit only leave others idle: 256 rows of 128,256 tokens 23.3 -> 24.6 us).
+    // A wavefront's list holds half of its quads where their bits are read by words (more of them, or of the whole part's where no count is
+    // known, are rarely listed; if so, a piece of 512 at a time), so that a compute unit has room for six workgroups: 2,000 tokens, 4,096 rows
+    // that allow few 26 -> 13 us.
+    const bool words = gpp <= kWordGroups && !a.masked_out;
     int cap = kDrawList;
-    if (grid > kDrawGroups && gpp <= 64 * kDrawPieces * kDrawWaves * 4)
-        cap = std::min(cap, std::max((gpp / 4 + kDrawWaves) / kDrawWaves * 8, 64));
+    if (words) {
+        const int quads = (gpp / 4 + kDrawWaves - 1) / kDrawWaves * 8;
+        cap = std::max(quads <= 512 ? quads : std::max(512, quads / 2), 64);
+    }
     const size_t lds = (size_t)cap * kDrawWaves * 4;
     // The words that the parts of a row meet through lie as far apart as there is room for, up to a cache line: atomics on one line wait
     // for each other, some 10 ns each (16 rows that allow few, 16 parts each, 8.2 -> 6.3 us).
@@ -2509,13 +2536,14 @@ int launch_sample_step(const MaskArgs& a, float inv_t, int32_t top_k, uint64_t s
     while (spread < kLineWords && 2 * spread * batch <= kScratchWords) spread *= 2;
     if (grid > 0x7FFFFFFFll) return fail(TDFA_E_UNSUPPORTED, "batch too large for one launch");
     const dim3 blocks((unsigned)grid);
-    auto launch = [&](auto write) {
-        constexpr bool kWrite = decltype(write)::value;
-        if (a.dtype == TDFA_F32) draw_step_kernel<TDFA_F32, kWrite><<<blocks, kDrawThreads, lds, stream>>>(a, sp, (int)parts, gpp, cap, spread);
-        else draw_step_kernel<TDFA_BF16, kWrite><<<blocks, kDrawThreads, lds, stream>>>(a, sp, (int)parts, gpp, cap, spread);
+    auto launch = [&](auto write, auto by_word) {
+        constexpr bool kWrite = decltype(write)::value, kWords = decltype(by_word)::value;
+        if (a.dtype == TDFA_F32) draw_step_kernel<TDFA_F32, kWrite, kWords><<<blocks, kDrawThreads, lds, stream>>>(a, sp, (int)parts, gpp, cap, spread);
+        else draw_step_kernel<TDFA_BF16, kWrite, kWords><<<blocks, kDrawThreads, lds, stream>>>(a, sp, (int)parts, gpp, cap, spread);
     };
-    if (a.masked_out) launch(std::true_type{});
-    else launch(std::false_type{});
+    if (a.masked_out) launch(std::true_type{}, std::false_type{});
+    else if (words) launch(std::false_type{}, std::true_type{});
+    else launch(std::false_type{}, std::false_type{});
     TDFA_HIP(hipGetLastError());
     return TDFA_OK;
 }

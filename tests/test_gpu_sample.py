@@ -422,10 +422,11 @@ def test_rows_shared_out_by_cost(T, oracle, dtype, n_tokens, batch):
     assert np.array_equal(tok.cpu().numpy(), got[0]) and np.array_equal(st.cpu().numpy(), got[1])
 
 
-@pytest.mark.parametrize("n_tokens,batch", [(61, 5), (2003, 1), (2003, 1100), (9001, 40), (33003, 1030), (140003, 3)])
+@pytest.mark.parametrize("n_tokens,batch", [(61, 5), (2003, 1), (2003, 1100), (9001, 40), (33003, 1030), (140003, 3), (128261, 256)])
 def test_listed_tokens_and_quads(T, oracle, n_tokens, batch):
     """States around the numbers that decide how a row is drawn: as many allowed tokens, or quads, to a wavefront as it has lanes,
-    lists that are full, half of the quads; whole lists and those cut to the part (many rows); with and without counts."""
+    lists that are full, half of the quads; whole lists and those cut to the part, or to half of it, also where a wavefront
+    has all of its quads to list and the others none; with and without counts."""
     rng = np.random.default_rng(n_tokens)
     V, quads = n_tokens, (n_tokens + 3) // 4
     rows = []
@@ -434,6 +435,9 @@ def test_listed_tokens_and_quads(T, oracle, n_tokens, batch):
     for n in (64, 65, 256, 257, quads // 2 - 1, quads // 2, quads // 2 + 2, quads):       # quads, a token or all of each
         at = rng.permutation(quads)[:n]
         rows += [4 * at + rng.integers(0, 4, size=len(at)), (4 * at[:, None] + np.arange(4)).reshape(-1)]
+    for first in (0, quads // 3):                                                # a token of each quad in a stretch
+        at = first + np.arange(quads // 13)
+        rows.append(4 * at + rng.integers(0, 4, size=len(at)))
     tab = np.full((len(rows), V), DEAD, dtype=np.int32)
     for q, at in enumerate(rows):
         at = at[at < V]
@@ -445,6 +449,12 @@ def test_listed_tokens_and_quads(T, oracle, n_tokens, batch):
     for i, table in enumerate((T.table_pack(dense), dense)):                      # (the second holds caller's arrays: no counts)
         for first in range(0, len(rows), batch):
             _sample_strided(T, oracle, table, tab, lg, BF16, (states + first) % len(rows), 0.9, 17, first, masked=False)
+
+
+@pytest.mark.parametrize("n_tokens,batch", [(128261, 256), (128261, 512), (128261, 513), (262145, 227), (262145, 228), (32768, 1025), (32769, 1025)])
+def test_lines_of_the_rule_that_cuts_rows(T, oracle, n_tokens, batch):
+    """Batches and rows on either side of the sizes from which parts are so long that their bits are not read by single words."""
+    test_rows_shared_out_by_cost(T, oracle, BF16, n_tokens, batch)
 
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
