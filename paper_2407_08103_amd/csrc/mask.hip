@@ -1724,8 +1724,8 @@ struct DrawShared {
 // wavefront's 64 places) gets its two logarithms.  The maximum does not depend on the order: candidates are compared as
 // (score, lowest id).
 //
-// Bound by the instructions issued where states allow many tokens: 54 per quad, 18 of them 64-bit products, at 1.9 to 2.4
-// ns per instruction and SIMD with four wavefronts (a wavefront alone gets half of that), so 256 rows of 128,256
+// Bound by the instructions issued where states allow many tokens: 75 vector instructions per quad, 18 of them 64-bit products (counters,
+// 256 rows of 128,256 tokens all in such states: the vector units are busy in 75 % of the cycles), so 256 rows with all
 // tokens all drawn take 15 us of every SIMD; and by some 20 dependent steps, 5 us, where states allow few.  The scheduler
 // serves the oldest wavefront first, so that the last one of a SIMD would run alone: a wavefront that draws every quad lowers its
 // priority as it gets on.  (Without: 256 rows 22.1 and 26.2 instead of 20.9 and 23.7 us.)  One that works from a list mostly waits, for
