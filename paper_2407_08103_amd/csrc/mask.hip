@@ -1725,8 +1725,8 @@ struct DrawShared {
 // (score, lowest id).
 //
 // Bound by the instructions issued where states allow many tokens: 75 vector instructions per quad, 18 of them 64-bit products (counters,
-// 256 rows of 128,256 tokens all in such states: the vector units are busy in 75 % of the cycles), so 256 rows with all
-// tokens all drawn take 15 us of every SIMD; and by some 20 dependent steps, 5 us, where states allow few.  The scheduler
+// 256 rows of 128,256 tokens all in such states: the vector units are busy in 75 % of the cycles), so 256 rows with every
+// quad drawn take 15 us of every SIMD; and by some 20 dependent steps, 5 us, where states allow few.  The scheduler
 // serves the oldest wavefront first, so that the last one of a SIMD would run alone: a wavefront that draws every quad lowers its
 // priority as it gets on.  (Without: 256 rows 22.1 and 26.2 instead of 20.9 and 23.7 us.)  One that works from a list mostly waits, for
 // memory and for itself, so it goes first (128, 256 and 512 rows anywhere in their texts 15.5, 23.1 and 34.0 -> 14.2, 21.4 and 32.1 us).
